@@ -8,6 +8,7 @@
 #include <utility>
 
 #include "lmkan.h"
+#include "lmkan_gather.h"
 #include "lmkan_kernels.h"
 #include "lmkan_sorted.h"
 
@@ -273,6 +274,15 @@ lmkan_status forward_impl(const lmkan_desc *desc, int64_t batch, const float *x_
     hipStream_t hs = static_cast<hipStream_t>(stream);
     drop_stale_error();
     TimedCall timed(kTimeForward);
+    // Small shapes gather the rows they need and locate their inputs themselves: no records, also where
+    // the alignment of this call's pointers sends it to the generic kernel (backward_impl knows).
+    if (forward_gather_shape_ok(s)) {
+        if (gather_table_aligned(coef_dev))
+            launch_forward_gather(s, tab, x_dev, coef_dev, y_dev, hs, conv);
+        else
+            launch_forward_generic(s, tab, x_dev, coef_dev, y_dev, hs, conv);
+        return launch_status();
+    }
     // the records are written whenever the shape has a kernel that reads them, also when the
     // alignment of this call's pointers sends it to the generic kernel: a later call may rely on them
     if (need > 0 && !(desc->flags & LMKAN_FLAG_WORKSPACE_HAS_RECORDS))
@@ -336,8 +346,11 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     const bool head = head_forward_shape_ok(s) && !conv;
     const bool gx_head = grad_x_dev && head;
     const bool gp_head = grad_coef_dev && head;
-    const bool gx_small = grad_x_dev && small && !gx_head;
-    const bool gp_small = grad_coef_dev && small && small_coef_ok(s) && !gp_head;
+    // small shapes: one launch per gradient, no records, no scratch
+    const bool gx_gather = grad_x_dev && !gx_head && backward_input_gather_shape_ok(s) && gather_table_aligned(coef_dev);
+    const bool gp_gather = grad_coef_dev && !gp_head && backward_coef_gather_shape_ok(s);
+    const bool gx_small = grad_x_dev && small && !gx_head && !gx_gather;
+    const bool gp_small = grad_coef_dev && small && small_coef_ok(s) && !gp_head && !gp_gather;
     // Input gradient.  Where a slab kernel applies (G <= 34) it is the faster one for the input
     // gradient alone.  The walk over the cell-sorted samples yields both gradients from one pass
     // over gy: it takes the grids too fine for any slab, and the 16-output slab range when both
@@ -345,15 +358,15 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     // cell on average), except where the table is packed and two 32-output slabs fit LDS: that slab
     // kernel is as quick as its share of the walk, or quicker.  Whatever neither takes goes to the
     // generic kernel.
-    const bool slab_ok = grad_x_dev && !small && slab_backward_input_applicable(s, coef_dev, grad_y_dev, grad_x_dev);
+    const bool slab_ok = grad_x_dev && !small && !gx_gather && slab_backward_input_applicable(s, coef_dev, grad_y_dev, grad_x_dev);
     const bool dense_cells = s.batch >= (int64_t)16 * s.G * s.G;
     const bool fused_pays = !slab_ok || (!slab_tile_is_wide(s) && grad_coef_dev && dense_cells &&
                                          !slab_backward_input_takes_half_tiles(s));
     const bool enough_work = s.batch >= 256 || (int64_t)s.pairs() * s.n_out >= 8192;  // as for the slab kernels
-    const bool gx_fused = grad_x_dev && !small && enough_work && fused_pays &&
+    const bool gx_fused = grad_x_dev && !small && !gx_gather && !gp_gather && enough_work && fused_pays &&
                           fused_backward_applicable(s, coef_dev, grad_y_dev, grad_coef_dev);
     const bool gx_slab = slab_ok && !gx_fused;
-    const bool gp_sorted = grad_coef_dev && !gp_small && !gp_head && coef_sorted_applicable(s, grad_y_dev, grad_coef_dev);
+    const bool gp_sorted = grad_coef_dev && !gp_small && !gp_head && !gp_gather && coef_sorted_applicable(s, grad_y_dev, grad_coef_dev);
     const bool need_records = gp_sorted || gx_fused || gx_slab || gx_small || gp_small;
     const BackwardWorkspace w = backward_workspace(s, grad_x_dev != nullptr, grad_coef_dev != nullptr);
     const size_t need = need_records ? w.total : 0;
@@ -366,7 +379,9 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     float *ws_scratch = reinterpret_cast<float *>(ws + w.scratch);
     char *ws_partial = ws + w.partial;
     TimedCall timed(grad_x_dev ? kTimeGradInput : kTimeGradCoef);
-    if (need_records && !(desc->flags & LMKAN_FLAG_WORKSPACE_HAS_RECORDS)) launch_preamble_records(s, tab, x_dev, ws, hs, conv);
+    // (a forward call that gathers leaves no records behind: the promise is void then)
+    const bool have_records = (desc->flags & LMKAN_FLAG_WORKSPACE_HAS_RECORDS) && !forward_gather_shape_ok(s);
+    if (need_records && !have_records) launch_preamble_records(s, tab, x_dev, ws, hs, conv);
     SortedStream stream_k{};
     GyView gy_k{};
     if (gp_sorted || gx_fused) stream_k = launch_sort(s, ws, ws_sorted, hs);
@@ -375,6 +390,8 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     else gy_k = GyView{grad_y_dev, (int64_t)(LMKAN_PACK_TILE * sizeof(float)), (unsigned)(s.n_out * sizeof(float))};
     if (gp_head) {
         launch_backward_coef_head(s, tab, x_dev, grad_y_dev, grad_coef_dev, !overwrite, hs);
+    } else if (gp_gather) {
+        launch_backward_coef_gather(s, tab, x_dev, grad_y_dev, grad_coef_dev, !overwrite, hs, conv);
     } else if (gp_small) {
         launch_backward_coef_small(s, ws, grad_y_dev, grad_coef_dev, !overwrite, hs);
     } else if (gp_sorted && !gx_fused) {
@@ -386,6 +403,8 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     }
     if (gx_head) {
         launch_backward_input_head(s, tab, x_dev, coef_dev, grad_y_dev, grad_x_dev, hs);
+    } else if (gx_gather) {
+        launch_backward_input_gather(s, tab, x_dev, coef_dev, grad_y_dev, grad_x_dev, hs, conv);
     } else if (gx_fused) {
         // one walk over the cell-sorted samples yields both gradients (the coefficient gradient
         // qualifies whenever the input gradient does)

@@ -59,16 +59,18 @@ inline void finish_split_setup(SlabArgs &a, const LayerShape &s, float *y, float
     if (a.atomic_out) launch_fill_zero(y, (size_t)s.batch * s.n_out, stream);
 }
 
-// four adjacent outputs of a sample leave the registers: one 16-byte store when every row of y
-// starts on a multiple of four outputs, else element by element up to the last column
+// four adjacent outputs of a sample leave the registers: one 16-byte store (rows of a ragged output
+// count start on 4 bytes only, which such a store allows on this hardware), element by element where
+// the row ends before the fourth
 __device__ __forceinline__ void store_outputs(float *dst, const float *v, int n_out, int col, bool atomic)
 {
     if (atomic) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (col + i < n_out) unsafeAtomicAdd(dst + i, v[i]);
-    } else if ((n_out & 3) == 0) {
-        *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+    } else if (col + 4 <= n_out) {
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+        *reinterpret_cast<f4u *>(dst) = f4u{v[0], v[1], v[2], v[3]};
     } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i)

@@ -3,9 +3,9 @@
 //   gP[a][b][k][j] = sum over samples n whose cell for pair k has (a,b) as a corner of
 //                    B_ab(x_n) * gy[n][j]                  (derivative of Alg. 1's sum)
 //
-// Pass 1 (sort_count / sort_layout / sort_scatter kernels): for every pair k the samples are
-// grouped by cell with a counting sort, each cell padded to whole chunks of four samples, and
-// the four B-spline products are stored next to the sample index.
+// Pass 1 (sort_kernel): for every pair k the samples are grouped by cell with a counting sort, each
+// cell padded to whole chunks of four samples, the local coordinates stored next to the sample
+// index.
 // Pass 2 (backward_coef_stream_kernel): one wave owns (pair k, 64 outputs) and walks the
 // sorted chunks, cell after cell.  The four samples of a chunk go to the four 16-lane
 // groups of the wave and a lane covers four adjacent outputs, so gy is read with 16-byte
@@ -32,344 +32,186 @@ constexpr int kDepth = 8;    // chunks of gy values in flight
 constexpr int kPerW = 4;     // chunks whose entries one load instruction brings in
 static_assert(kUnroll % kDepth == 0, "the gy ring must divide the unrolled trip");
 
-// Counting sort of the samples of every pair by cell, in three launches so that long batches
-// are spread over many workgroups.  records_in: [3][K][B] (node, u, v) from the preamble
-// pass.  Per pair k, with S = stream_stride, the samples ordered by (block, cell):
+// Counting sort of the samples of every pair by cell, one launch: a workgroup takes the samples of one
+// (pair, block).  records_in: [3][K][B] (node, u, v) from the preamble pass.  Per pair k, with
+// S = stream_stride and C = stream_block_entries, block b owns the entries [b C, (b + 1) C):
 //   rec [K][S]           (u, v, 1, index) of a sample, 16 bytes; padding entries are
 //                        (0, 0, 0, index of a sample of the same cell)
 //   chunk_cell [K][S/4]  i1 << 8 | i2 of the cell each chunk belongs to, non-decreasing
 //                        inside a block
-//   block_start [K][blocks+1]  first chunk of every block (multiples of kUnroll) and the
-//                        number of chunks to process
-// and as scratch between the launches, with nblk = ceil(B / kSortSeg) batch segments:
-//   seg_count [K][nblk][G*G]  population of a cell inside a segment, then the offset of the
-//                             segment's first sample of that cell within the cell
-//   cell_start [K][blocks][G*G]  first stream position of the (block, cell)
-//   cell_rep [K][G*G]         index of some sample of the cell (any one)
-constexpr int kSortSegThreads = 256;
-constexpr int kMaxCells = LMKAN_MAX_GRID * LMKAN_MAX_GRID;
+//   block_chunks [K][blocks]  chunks of the block to process, a multiple of kUnroll; one trip of
+//                        padding entries follows (the walking kernels prefetch into it)
+// A thread keeps its samples in registers; LDS holds a population per (wave, cell) (16 bits each).
+// A sample's rank is what the counter of its wave and cell held before it, and the wave's samples
+// are a run of consecutive ones, so the order inside a cell follows the indices in steps of 64 and
+// does not depend on which wave happens to run first: sums over a cell repeat in every run.
+// The entries go out through LDS, kSortStage stream positions at a time, so that the stores run along
+// the stream (16-byte stores all over a block's 130 KB are bound by the L2's requests: 175 us at 64
+// pairs x 262144 samples).
+// (Four launches before this one - a histogram per segment of 4096 samples, block sizes, layout,
+// scatter, where a stable order took a pass over each cell's run: 100 us for 512 pairs x 8192
+// samples, 178 us for 64 pairs x 262144.)
+constexpr int kSortWaves = kSortThreads / 64;
+constexpr int kSortPer = 12;  // samples of a thread, at most
+constexpr int kSortStage = 4096;  // stream positions that go through LDS at a time
+static_assert(kBlockSamples + kBlockSamples / 2 <= kSortThreads * kSortPer, "a block must fit a workgroup");
 
-__device__ __forceinline__ int cell_of_node(int node, int G) { return (node / (G + 1)) * G + node % (G + 1); }
-
-// 1: histogram of one batch segment
-__global__ __launch_bounds__(kSortSegThreads) void sort_count_kernel(const int32_t *__restrict__ rec_node,
-                                                                    int32_t *__restrict__ seg_count,
-                                                                    int32_t *__restrict__ cell_rep, int64_t B, int G)
+__host__ __device__ inline size_t sort_lds_bytes(int G)
 {
-    __shared__ int s_count[kMaxCells];
-    __shared__ int s_rep[kMaxCells];
-    const int blk = blockIdx.x, nblk = gridDim.x, k = blockIdx.y;
-    const int cells = G * G;
-    for (int c = threadIdx.x; c < cells; c += blockDim.x) s_count[c] = 0;
-    __syncthreads();
-    const int64_t n0 = (int64_t)blk * kSortSeg;
-    const int64_t n1 = n0 + kSortSeg < B ? n0 + kSortSeg : B;
-    const int32_t *node_k = rec_node + (int64_t)k * B;
-    // all loads of the thread first: these passes are bound by the bytes in flight
-    constexpr int kPer = kSortSeg / kSortSegThreads;
-    int nd[kPer];
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const int64_t n = n0 + threadIdx.x + j * kSortSegThreads;
-        nd[j] = n < n1 ? node_k[n] : -1;
-    }
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        if (nd[j] >= 0) {
-            const int c = cell_of_node(nd[j], G);
-            atomicAdd(&s_count[c], 1);
-            s_rep[c] = (int)(n0 + threadIdx.x + j * kSortSegThreads);  // any writer wins
-        }
-    }
-    __syncthreads();
-    int32_t *out = seg_count + ((int64_t)k * nblk + blk) * cells;
-    for (int c = threadIdx.x; c < cells; c += blockDim.x) {
-        const int cnt = s_count[c];
-        out[c] = cnt;
-        if (cnt > 0) cell_rep[(int64_t)k * cells + c] = s_rep[c];  // any segment wins
-    }
+    const size_t cells = (size_t)G * G, even = (cells + 1) & ~(size_t)1;
+    const size_t counts = ((size_t)kSortWaves * even + even) * sizeof(unsigned short);
+    const size_t stage = (size_t)kSortStage * 3 * sizeof(float);
+    return (cells + 1) * sizeof(int) + (counts > stage ? counts : stage);
 }
 
-// 1b: chunks of every (pair, block): cells padded to whole chunks, the block to whole trips
-__global__ __launch_bounds__(kSortSegThreads) void sort_block_size_kernel(const int32_t *__restrict__ seg_count,
-                                                                         int32_t *__restrict__ block_size, int64_t B,
-                                                                         int G, int nseg)
-{
-    __shared__ int s_sum[kSortSegThreads / 64];
-    const int k = blockIdx.x, blk = blockIdx.y;
-    const int cells = G * G;
-    const int blocks = stream_blocks(B);
-    const int seg_per_block = blocks > 1 ? kSegPerBlock : nseg;
-    const int b0 = blk * seg_per_block, b1 = min(nseg, b0 + seg_per_block);
-    const int32_t *cnt_k = seg_count + (int64_t)k * nseg * cells;
-    int mine = 0;
-    for (int c = threadIdx.x; c < cells; c += blockDim.x) {
-        int run = 0;
-        for (int b = b0; b < b1; ++b) run += cnt_k[(int64_t)b * cells + c];
-        mine += (run + kChunk - 1) / kChunk;
-    }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) mine += __shfl_down(mine, d, 64);
-    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = mine;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int total = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) total += s_sum[w];
-        block_size[(int64_t)k * blocks + blk] = (total + kUnroll - 1) / kUnroll * kUnroll;
-    }
-}
-
-// 2: per (pair, block): positions of the cells (each padded to whole chunks), the
-// cell of every chunk, padding entries, dummy chunks that round the block up to whole trips
-// (they belong to the block's last cell), and after the last block the tail
-__global__ __launch_bounds__(kSortThreads) void sort_layout_kernel(int32_t *__restrict__ seg_count,
-                                                                  int32_t *__restrict__ cell_start,
-                                                                  const int32_t *__restrict__ cell_rep,
-                                                                  f4v *__restrict__ rec,
-                                                                  int32_t *__restrict__ chunk_cell,
-                                                                  int32_t *__restrict__ block_start,
-                                                                  const int32_t *__restrict__ block_size, int64_t B,
-                                                                  int G, int nseg)
-{
-    __shared__ int s_count[kMaxCells];      // population of the cell in this block
-    __shared__ int s_start[kMaxCells + 1];  // first stream position of the cell; [cells] = end
-    __shared__ int s_wave_total[kSortThreads / 64];
-    __shared__ int s_last_cell;
-    const int k = blockIdx.x;
-    const int cells = G * G;
-    const int blocks = stream_blocks(B);
-    const int seg_per_block = blocks > 1 ? kSegPerBlock : nseg;
-    const int64_t S = stream_stride(B, G);
-    f4v *out = rec + (int64_t)k * S;
-    int32_t *out_cell = chunk_cell + (int64_t)k * (S / kChunk);
-    int32_t *cnt_k = seg_count + (int64_t)k * nseg * cells;
-    const int32_t *rep_k = cell_rep + (int64_t)k * cells;
-    int32_t *bs_k = block_start + (int64_t)k * (blocks + 1);
-    auto filler = [](int32_t n) { return f4v{0.f, 0.f, 0.f, __int_as_float(n)}; };
-
-    const int blk = blockIdx.y;
-    // stream position where this block starts (a multiple of kChunk * kUnroll)
-    int base_pos = 0;
-    for (int b = 0; b < blk; ++b) base_pos += block_size[(int64_t)k * blocks + b] * kChunk;
-    {
-        const int b0 = blk * seg_per_block, b1 = min(nseg, b0 + seg_per_block);
-        if (threadIdx.x == 0) s_last_cell = 0;
-        __syncthreads();
-        // populations; the per-segment counts become offsets inside the (block, cell)
-        for (int c = threadIdx.x; c < cells; c += blockDim.x) {
-            int run = 0;
-            for (int b = b0; b < b1; ++b) {
-                const int v = cnt_k[(int64_t)b * cells + c];
-                cnt_k[(int64_t)b * cells + c] = run;
-                run += v;
-            }
-            s_count[c] = run;
-            if (run > 0) atomicMax(&s_last_cell, c);
-        }
-        __syncthreads();
-        // exclusive scan of the padded populations, in pieces of blockDim.x cells
-        int carry = base_pos;
-        for (int base = 0; base < cells; base += blockDim.x) {
-            const int c = base + threadIdx.x;
-            const int cnt = c < cells ? s_count[c] : 0;
-            const int v = (cnt + kChunk - 1) / kChunk * kChunk;
-            int incl = v;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int t = __shfl_up(incl, d, 64);
-                if ((threadIdx.x & 63) >= d) incl += t;
-            }
-            if ((threadIdx.x & 63) == 63) s_wave_total[threadIdx.x >> 6] = incl;
-            __syncthreads();
-            int wave_off = 0;
-            for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) wave_off += s_wave_total[w];
-            int piece_total = 0;
-            for (int w = 0; w < (int)(blockDim.x >> 6); ++w) piece_total += s_wave_total[w];
-            if (c < cells) s_start[c] = carry + wave_off + incl - v;
-            carry += piece_total;
-            __syncthreads();
-        }
-        const int real_end = carry;  // end of the padded samples of this block
-        const int block_chunks = ((real_end - base_pos) / kChunk + kUnroll - 1) / kUnroll * kUnroll;
-        const int block_end = base_pos + block_chunks * kChunk;
-        // the last block is followed by the chunks the pipelines may touch beyond the end
-        const int fill_end = blk + 1 < blocks ? block_end : block_end + kUnroll * kChunk;
-        for (int c = threadIdx.x; c < cells; c += blockDim.x)
-            cell_start[((int64_t)k * blocks + blk) * cells + c] = s_start[c];
-        const int last = s_last_cell;
-        // the cell of every chunk: the highest cell whose start is <= the chunk's first position
-        // (an empty cell shares its start with the next one, so the highest such cell is never
-        // empty); chunks past the real ones belong to the block's last cell
-        for (int q = base_pos / kChunk + threadIdx.x; q < fill_end / kChunk; q += blockDim.x) {
-            int c = last;
-            const int pos = q * kChunk;
-            if (pos < real_end) {
-                int lo = 0, hi = cells - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (s_start[mid] <= pos) lo = mid; else hi = mid - 1;
-                }
-                c = lo;
-            }
-            out_cell[q] = ((c / G) << 8) | (c % G);
-        }
-        // padding entries of every cell, then the dummy chunks: zero products, a sample of that cell
-        for (int c = threadIdx.x; c < cells; c += blockDim.x) {
-            const int cnt = s_count[c];
-            if (cnt == 0) continue;
-            const int first = s_start[c], padded = (cnt + kChunk - 1) / kChunk * kChunk;
-            const f4v fill = filler(rep_k[c]);
-            for (int i = cnt; i < padded; ++i) out[first + i] = fill;
-        }
-        {
-            const f4v fill = filler(rep_k[last]);
-            for (int i = real_end + threadIdx.x; i < fill_end; i += blockDim.x) out[i] = fill;
-        }
-        if (threadIdx.x == 0) {
-            bs_k[blk] = base_pos / kChunk;
-            if (blk + 1 == blocks) bs_k[blocks] = block_end / kChunk;
-        }
-    }
-}
-
-// 3: scatter of one batch segment.  The segment is first ordered by cell inside LDS, so that
-// consecutive threads then write consecutive stream positions (the samples of one cell that
-// lie in this segment form one contiguous run of the stream).
-__host__ __device__ inline size_t scatter_lds_bytes(int G)
-{
-    return (size_t)((G * G * 3 + 3) & ~3) * sizeof(int) + (size_t)kSortSeg * (2 * sizeof(float) + 3 * sizeof(unsigned short));
-}
-
-__global__ __launch_bounds__(kSortSegThreads) void sort_scatter_kernel(const int32_t *__restrict__ rec_node,
-                                                                      const float *__restrict__ rec_u,
-                                                                      const float *__restrict__ rec_v,
-                                                                      const int32_t *__restrict__ seg_count,
-                                                                      const int32_t *__restrict__ cell_start,
-                                                                      f4v *__restrict__ rec, int64_t B, int G,
-                                                                      int stable)
+__global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__restrict__ rec_node,
+                                                           const float *__restrict__ rec_u,
+                                                           const float *__restrict__ rec_v, f4v *__restrict__ rec,
+                                                           int32_t *__restrict__ chunk_cell,
+                                                           int32_t *__restrict__ block_chunks, int64_t B, int G)
 {
     extern __shared__ __align__(16) int s_dyn[];
-    __shared__ int s_wave[kSortSegThreads / 64];
-    const int seg = blockIdx.x, nseg = gridDim.x, k = blockIdx.y;
-    const int cells = G * G;
-    int *s_cnt = s_dyn;              // population of the cell inside this segment
-    int *s_lstart = s_cnt + cells;   // its first position in the segment's own cell order
-    int *s_gbase = s_lstart + cells; // its first position in the stream
-    float *s_u = reinterpret_cast<float *>(s_dyn + ((3 * cells + 3) & ~3));  // 16-byte aligned: s_order is read 16 bytes at a time
-    float *s_v = s_u + kSortSeg;
-    unsigned short *s_cell = reinterpret_cast<unsigned short *>(s_v + kSortSeg);
-    unsigned short *s_rank = s_cell + kSortSeg;
-    unsigned short *s_order = s_rank + kSortSeg;
+    __shared__ int s_wave_total[kSortWaves];
+    __shared__ int s_last_cell;
+    const int cells = G * G, even = (cells + 1) & ~1;
+    int *s_start = s_dyn;                                                             // [cells + 1]
+    unsigned short *s_off = reinterpret_cast<unsigned short *>(s_start + cells + 1);  // [waves][even]
+    unsigned short *s_total = s_off + kSortWaves * even;                              // [even]
+    int *s_count = reinterpret_cast<int *>(s_off);  // the same memory, two counters to a word
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int blk = blockIdx.x, k = blockIdx.y;
     const int blocks = stream_blocks(B);
-    const int blk = blocks > 1 ? seg / kSegPerBlock : 0;
-    const int64_t S = stream_stride(B, G);
-    const int32_t *off = seg_count + ((int64_t)k * nseg + seg) * cells;
-    for (int c = threadIdx.x; c < cells; c += blockDim.x) {
-        s_cnt[c] = 0;
-        s_gbase[c] = cell_start[((int64_t)k * blocks + blk) * cells + c] + off[c];
-    }
-    __syncthreads();
-    const int64_t n0 = (int64_t)seg * kSortSeg;
-    const int count = (int)((n0 + kSortSeg < B ? n0 + kSortSeg : B) - n0);
-    const int32_t *node_k = rec_node + (int64_t)k * B + n0;
-    const float *u_k = rec_u + (int64_t)k * B + n0;
-    const float *v_k = rec_v + (int64_t)k * B + n0;
-    {
-        constexpr int kPer = kSortSeg / kSortSegThreads;
-        int nd[kPer];
-        float uu[kPer], vv[kPer];
+    const int64_t n0 = (int64_t)blk * kBlockSamples;
+    const int count = (int)(blocks > 1 && n0 + kBlockSamples < B ? kBlockSamples : B - n0);
+    const int per = (count + kSortThreads - 1) / kSortThreads;
+    const int64_t o = (int64_t)k * B + n0;
+    const int i0 = wave * per * 64 + lane;  // this thread's samples: i0 + 64 j
+
+    // all loads of the thread first: the pass is bound by the bytes in flight
+    int cell[kSortPer], rank[kSortPer];
+    float u[kSortPer], v[kSortPer];
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int i = threadIdx.x + j * kSortSegThreads;
-            nd[j] = -1;
-            uu[j] = vv[j] = 0.f;
-            if (i < count) {
-                nd[j] = node_k[i];
-                uu[j] = u_k[i];
-                vv[j] = v_k[i];
-            }
+    for (int j = 0; j < kSortPer; ++j) {
+        cell[j] = -1;
+        if (j < per && i0 + 64 * j < count) {
+            cell[j] = rec_node[o + i0 + 64 * j];
+            u[j] = rec_u[o + i0 + 64 * j];
+            v[j] = rec_v[o + i0 + 64 * j];
         }
+    }
+    for (int c = tid; c < kSortWaves * even / 2; c += kSortThreads) s_count[c] = 0;
+    if (tid == 0) s_last_cell = 0;
+    __syncthreads();
+    const unsigned W = G + 1, inv_w = ((1u << 20) + W - 1) / W;  // node / W = node inv_w >> 20 for every node of a table
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int i = threadIdx.x + j * kSortSegThreads;
-            if (nd[j] >= 0) {
-                const int c = cell_of_node(nd[j], G);
-                s_cell[i] = (unsigned short)c;
-                s_rank[i] = (unsigned short)atomicAdd(&s_cnt[c], 1);
-                s_u[i] = uu[j];
-                s_v[i] = vv[j];
-            }
+    for (int j = 0; j < kSortPer; ++j) {
+        if (cell[j] >= 0) {
+            const int c = cell[j] - (int)(((unsigned)cell[j] * inv_w) >> 20);  // i1 (G + 1) + i2 -> i1 G + i2
+            const int shift = (c & 1) * 16;
+            cell[j] = c;
+            rank[j] = (atomicAdd(&s_count[(wave * even + c) >> 1], 1 << shift) >> shift) & 0xffff;
         }
     }
     __syncthreads();
-    // exclusive scan of the populations: a run of consecutive cells per thread
+    // counters -> offsets of a wave's samples inside the cell; padded populations -> first positions
     {
-        const int per = (cells + kSortSegThreads - 1) / kSortSegThreads;
-        const int c0 = threadIdx.x * per, c1 = min(cells, c0 + per);
+        const int run_cells = (cells + kSortThreads - 1) / kSortThreads;
+        const int c0 = min(cells, tid * run_cells), c1 = min(cells, c0 + run_cells);
         int mine = 0;
-        for (int c = c0; c < c1; ++c) mine += s_cnt[c];
+        for (int c = c0; c < c1; ++c) {
+            int run = 0;
+#pragma unroll
+            for (int w = 0; w < kSortWaves; ++w) {
+                const int n = s_off[w * even + c];
+                s_off[w * even + c] = (unsigned short)run;
+                run += n;
+            }
+            s_total[c] = (unsigned short)run;
+            mine += (run + kChunk - 1) / kChunk * kChunk;
+            if (run > 0) atomicMax(&s_last_cell, c);
+        }
         int incl = mine;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int t = __shfl_up(incl, d, 64);
-            if ((threadIdx.x & 63) >= d) incl += t;
+            if (lane >= d) incl += t;
         }
-        if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = incl;
+        if (lane == 63) s_wave_total[wave] = incl;
         __syncthreads();
         int run = incl - mine;
-        for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) run += s_wave[w];
+        for (int w = 0; w < wave; ++w) run += s_wave_total[w];
         for (int c = c0; c < c1; ++c) {
-            s_lstart[c] = run;
-            run += s_cnt[c];
+            s_start[c] = run;
+            run += (s_total[c] + kChunk - 1) / kChunk * kChunk;
         }
+        if (tid == kSortThreads - 1) s_start[cells] = run;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < count; i += blockDim.x) s_order[s_lstart[s_cell[i]] + s_rank[i]] = (unsigned short)i;
-    __syncthreads();
-    // The ranks so far are in the order the atomics happened to be served.  Where the order of
-    // the samples inside a cell reaches the result (a coefficient gradient summed cell by cell by
-    // one wave), replace them by the order of the sample indices (rank = number of samples of the
-    // same cell, in this segment, with a smaller index), so that the stream, and with it the
-    // order of every float32 sum over the samples of a cell, is the same in every run.
-    for (int i = threadIdx.x; stable && i < count; i += blockDim.x) {
-        const int c = s_cell[i];
-        // the run is read eight entries (16 bytes) at a time from an aligned position; entries
-        // outside the run are masked
-        const int first = s_lstart[c], end = first + s_cnt[c];
-        int r = 0;
-        for (int a = first & ~7; a < end; a += 8) {
-            const uint4 w = *reinterpret_cast<const uint4 *>(s_order + a);
-            const unsigned word[4] = {w.x, w.y, w.z, w.w};
+    const int64_t S = stream_stride(B, G), C = stream_block_entries(B, G);
+    f4v *out = rec + (int64_t)k * S + blk * C;
+    int32_t *out_cell = chunk_cell + ((int64_t)k * S + blk * C) / kChunk;
+    const int last = s_last_cell, real_end = s_start[cells];
+    constexpr int kTrip = kUnroll * kChunk;
+    const int block_end = (real_end + kTrip - 1) / kTrip * kTrip, fill_end = block_end + kTrip;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int v = (int)((word[e >> 1] >> (16 * (e & 1))) & 0xffffu);
-                r += (a + e >= first) & (a + e < end) & (v < i);
+    for (int j = 0; j < kSortPer; ++j)
+        if (cell[j] >= 0) rank[j] += s_start[cell[j]] + s_off[wave * even + cell[j]];  // the stream position
+    __syncthreads();
+    // the counters make room for the entries on their way out
+    float *s_u = reinterpret_cast<float *>(s_off), *s_v = s_u + kSortStage;
+    int *s_n = reinterpret_cast<int *>(s_v + kSortStage);
+    int last_sample = 0;  // a sample of the block's last cell, for the padding behind it
+    for (int base = 0; base < fill_end; base += kSortStage) {
+        for (int p = tid; p < kSortStage; p += kSortThreads) s_n[p] = -1;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSortPer; ++j) {
+            const int p = rank[j] - base;
+            if (cell[j] >= 0 && p >= 0 && p < kSortStage) {
+                s_u[p] = u[j];
+                s_v[p] = v[j];
+                s_n[p] = (int32_t)n0 + i0 + 64 * j;
             }
         }
-        s_rank[i] = (unsigned short)r;
+        __syncthreads();
+        if (real_end > base) last_sample = s_n[min(real_end - base, kSortStage) - kChunk];
+        for (int p = tid; p < kSortStage && base + p < fill_end; p += kSortThreads) {
+            // (a chunk's first entry is always a sample, unless the chunk lies past the real ones)
+            const int n = s_n[p], first = s_n[p & ~(kChunk - 1)];
+            f4v e = {0.f, 0.f, 0.f, __int_as_float(first >= 0 ? first : last_sample)};
+            if (n >= 0) e = f4v{s_u[p], s_v[p], 1.0f, __int_as_float(n)};
+            out[base + p] = e;
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    for (int i = threadIdx.x; stable && i < count; i += blockDim.x)
-        s_order[s_lstart[s_cell[i]] + s_rank[i]] = (unsigned short)i;
-    __syncthreads();
-    f4v *out = rec + (int64_t)k * S;
-    for (int lp = threadIdx.x; lp < count; lp += blockDim.x) {
-        const int i = s_order[lp];
-        const int c = s_cell[i];
-        const int pos = s_gbase[c] + lp - s_lstart[c];
-        out[pos] = f4v{s_u[i], s_v[i], 1.0f, __int_as_float((int32_t)(n0 + i))};
+    // the cell of every chunk: the highest cell whose start is <= the chunk's first position (an empty
+    // cell shares its start with the next one, so the highest such cell is never empty); chunks past
+    // the real ones belong to the block's last cell
+    for (int q = tid; q < fill_end / kChunk; q += kSortThreads) {
+        int c = last;
+        if (q * kChunk < real_end) {
+            int lo = 0, hi = cells - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s_start[mid] <= q * kChunk) lo = mid; else hi = mid - 1;
+            }
+            c = lo;
+        }
+        out_cell[q] = ((c / G) << 8) | (c % G);
     }
+    if (tid == 0) block_chunks[(int64_t)k * blocks + blk] = block_end / kChunk;
 }
 
 struct CoefGradArgs {
     const f4v *rec;
     const int32_t *chunk_cell;
-    const int32_t *block_start;  // [K][n_blocks + 1], in chunks
+    const int32_t *block_chunks;  // [K][n_blocks]
     GyView gy;
     float *gP;
     CoefMap gmap;  // layout of Alg. 1
     int64_t B;
     int64_t S;     // stream_stride
+    int block_stride;  // chunks from one block of the stream to the next
     int n_out;
     int K;
     int G;
@@ -406,9 +248,8 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
     // a wave takes a run of whole trips of one block; a run may begin and end anywhere, even
     // inside a cell: every wave then adds what it has into a gradient that starts at zero.
     const bool split = a.n_blocks > 1 || a.n_sub > 1;
-    ScalarIntPtr bs = (ScalarIntPtr)(a.block_start + (int64_t)k * (a.n_blocks + 1));
-    int c_begin = bs[blk];
-    int nch = bs[blk + 1] - c_begin;
+    int c_begin = blk * a.block_stride;
+    int nch = ((ScalarIntPtr)(a.block_chunks + (int64_t)k * a.n_blocks))[blk];
     if (a.n_sub > 1) {
         const int trips = nch / kUnroll;
         const int per = (trips + a.n_sub - 1) / a.n_sub * kUnroll;
@@ -615,20 +456,15 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
 size_t sorted_records_bytes(const LayerShape &s)
 {
     const size_t S = (size_t)stream_stride(s.batch, s.G);
-    const size_t nseg = ((size_t)s.batch + kSortSeg - 1) / kSortSeg;
-    const size_t blocks = (size_t)stream_blocks(s.batch);
-    const size_t cells = (size_t)s.G * s.G;
-    const size_t per_pair = S * sizeof(f4v) + (S / kChunk) * sizeof(int32_t) + (2 * blocks + 1) * sizeof(int32_t) +
-                            (nseg + blocks + 1) * cells * sizeof(int32_t);
+    const size_t per_pair = S * sizeof(f4v) + (S / kChunk + (size_t)stream_blocks(s.batch)) * sizeof(int32_t);
     return ((size_t)s.pairs() * per_pair + 255) & ~(size_t)255;
 }
 
-// The cell-sorted paths index stream positions, and the launch grids batch segments, with 32-bit
-// integers: the longest batch they take.  Longer ones go to the generic kernels.
+// The cell-sorted paths index stream positions with 32-bit integers and launch a workgroup per block:
+// the longest batch they take.  Longer ones go to the generic kernels.
 bool sorted_batch_ok(const LayerShape &s)
 {
-    const int64_t nseg = (s.batch + kSortSeg - 1) / kSortSeg;
-    return nseg <= 65535 && stream_blocks(s.batch) <= 65535 && stream_stride(s.batch, s.G) < ((int64_t)1 << 31);
+    return s.batch <= kMaxSortedBatch && stream_stride(s.batch, s.G) < ((int64_t)1 << 31);
 }
 
 // gy is gathered four columns at a time and the gradient leaves four columns at a time: with a
@@ -643,55 +479,27 @@ bool coef_sorted_applicable(const LayerShape &s, const float *gy, const float *g
     return ((reinterpret_cast<uintptr_t>(gy) | reinterpret_cast<uintptr_t>(gcoef)) & 15) == 0;
 }
 
-SortBuffers sort_buffers(const LayerShape &s, void *sorted)
-{
-    const size_t S = (size_t)stream_stride(s.batch, s.G);
-    const size_t K = (size_t)s.pairs();
-    const size_t nseg = ((size_t)s.batch + kSortSeg - 1) / kSortSeg;
-    const size_t blocks = (size_t)stream_blocks(s.batch);
-    const size_t cells = (size_t)s.G * s.G;
-    SortBuffers b;
-    b.rec = static_cast<f4v *>(sorted);  // 16-byte items first, then the 4-byte ones
-    b.chunk_cell = reinterpret_cast<int32_t *>(b.rec + K * S);
-    b.block_start = b.chunk_cell + K * (S / kChunk);
-    b.block_size = b.block_start + K * (blocks + 1);
-    b.seg_count = b.block_size + K * blocks;
-    b.cell_start = b.seg_count + K * nseg * cells;
-    b.cell_rep = b.cell_start + K * blocks * cells;
-    return b;
-}
-
 SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted, hipStream_t stream)
 {
-    // a fixed order inside the cells matters only where one wave sums a cell from start to end
-    const bool stable = stream_blocks(s.batch) == 1 && stream_run_split(s) == 1;
     const size_t n = (size_t)s.pairs() * (size_t)s.batch;
     const size_t K = (size_t)s.pairs();
     const int32_t *rec_node = static_cast<const int32_t *>(records);
     const float *rec_u = reinterpret_cast<const float *>(rec_node + n);
     const float *rec_v = rec_u + n;
-    const SortBuffers b = sort_buffers(s, sorted);
-    const size_t nseg = ((size_t)s.batch + kSortSeg - 1) / kSortSeg;
-    const size_t blocks = (size_t)stream_blocks(s.batch);
-    const dim3 seg_grid((unsigned)nseg, (unsigned)K);
-    sort_count_kernel<<<seg_grid, kSortSegThreads, 0, stream>>>(rec_node, b.seg_count, b.cell_rep, s.batch, s.G);
-    const dim3 block_grid((unsigned)K, (unsigned)blocks);
-    sort_block_size_kernel<<<block_grid, kSortSegThreads, 0, stream>>>(b.seg_count, b.block_size, s.batch, s.G,
-                                                                       (int)nseg);
-    sort_layout_kernel<<<block_grid, kSortThreads, 0, stream>>>(b.seg_count, b.cell_start, b.cell_rep, b.rec,
-                                                              b.chunk_cell, b.block_start, b.block_size, s.batch, s.G,
-                                                              (int)nseg);
-    const size_t scatter_lds = scatter_lds_bytes(s.G);
-    if (scatter_lds > 64 * 1024) allow_large_lds(reinterpret_cast<const void *>(sort_scatter_kernel), 160 * 1024 - 64);
-    sort_scatter_kernel<<<seg_grid, kSortSegThreads, scatter_lds, stream>>>(rec_node, rec_u, rec_v, b.seg_count,
-                                                                           b.cell_start, b.rec, s.batch,
-                                                                           s.G, stable ? 1 : 0);
     SortedStream st;
-    st.rec = b.rec;
-    st.chunk_cell = b.chunk_cell;
-    st.block_start = b.block_start;
-    st.S = (int64_t)stream_stride(s.batch, s.G);
-    st.n_blocks = (int)blocks;
+    st.S = stream_stride(s.batch, s.G);
+    st.n_blocks = stream_blocks(s.batch);
+    st.block_stride = (int)(stream_block_entries(s.batch, s.G) / kChunk);
+    f4v *rec = static_cast<f4v *>(sorted);  // 16-byte items first, then the 4-byte ones
+    int32_t *chunk_cell = reinterpret_cast<int32_t *>(rec + K * (size_t)st.S);
+    int32_t *block_chunks = chunk_cell + K * (size_t)(st.S / kChunk);
+    const size_t lds = sort_lds_bytes(s.G);
+    if (lds > 60 * 1024) allow_large_lds(reinterpret_cast<const void *>(sort_kernel), 160 * 1024 - 256);
+    sort_kernel<<<dim3((unsigned)st.n_blocks, (unsigned)K), kSortThreads, lds, stream>>>(
+        rec_node, rec_u, rec_v, rec, chunk_cell, block_chunks, s.batch, s.G);
+    st.rec = rec;
+    st.chunk_cell = chunk_cell;
+    st.block_chunks = block_chunks;
     return st;
 }
 
@@ -701,7 +509,8 @@ void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, co
     CoefGradArgs a;
     a.rec = st.rec;
     a.chunk_cell = st.chunk_cell;
-    a.block_start = st.block_start;
+    a.block_chunks = st.block_chunks;
+    a.block_stride = st.block_stride;
     a.gy = gy;
     a.gP = gcoef;
     LayerShape g = s;

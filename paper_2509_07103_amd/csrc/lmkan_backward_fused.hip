@@ -49,7 +49,8 @@ static_assert(kUnroll % kDepth == 0 && kDepth % kGroup == 0 && kUnroll % kCellDe
 struct FusedArgs {
     const f4v *rec;
     const int32_t *chunk_cell;
-    const int32_t *block_start;
+    const int32_t *block_chunks;
+    int block_stride;
     GyView gy;
     const void *P;
     float *gP;        // NULL: input gradient only
@@ -124,9 +125,8 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     const bool col_ok = col < a.n_out;
     typedef __attribute__((address_space(4))) const int32_t *ScalarIntPtr;
     const bool split = a.n_blocks > 1 || a.n_sub > 1;
-    ScalarIntPtr bs = (ScalarIntPtr)(a.block_start + (int64_t)k * (a.n_blocks + 1));
-    int c_begin = bs[blk];
-    int nch = bs[blk + 1] - c_begin;
+    int c_begin = blk * a.block_stride;
+    int nch = ((ScalarIntPtr)(a.block_chunks + (int64_t)k * a.n_blocks))[blk];
     if (a.n_sub > 1) {
         const int trips = nch / kUnroll;
         const int per = (trips + a.n_sub - 1) / a.n_sub * kUnroll;
@@ -434,15 +434,16 @@ constexpr int kCombinePer = 4;  // positions per thread
 
 __global__ __launch_bounds__(256) void gx_combine_kernel(const float2 *__restrict__ partial, const f4v *__restrict__ rec,
                                                         const int32_t *__restrict__ chunk_cell,
-                                                        const int32_t *__restrict__ block_start, GridTab tab,
+                                                        const int32_t *__restrict__ block_chunks, GridTab tab,
                                                         float *__restrict__ gx, int64_t S, int K, int n_tiles,
-                                                        int n_in, int n_blocks, int64_t ld, int vec2)
+                                                        int n_in, int n_blocks, int block_entries, int64_t ld,
+                                                        int vec2)
 {
     __shared__ float s_invh[LMKAN_MAX_GRID];
     for (int i = threadIdx.x; i < tab.G; i += blockDim.x) s_invh[i] = tab.inv_h[i];
     __syncthreads();
     const int k = blockIdx.y;
-    const int used = block_start[(int64_t)k * (n_blocks + 1) + n_blocks] * kChunk;  // entries of this pair's stream
+    const int32_t *used_k = block_chunks + (int64_t)k * n_blocks;
     const f4v *rec_k = rec + (int64_t)k * S;
     const int32_t *cell_k = chunk_cell + (int64_t)k * (S / kChunk);
     const float2 *part_k = partial + (int64_t)k * S;
@@ -451,13 +452,16 @@ __global__ __launch_bounds__(256) void gx_combine_kernel(const float2 *__restric
     f4v e[kCombinePer];
     int cell[kCombinePer];
     float sx[kCombinePer], sy[kCombinePer];
+    bool used[kCombinePer];  // whether the position holds an entry of its block
 #pragma unroll
     for (int i = 0; i < kCombinePer; ++i) {
         const int pos = p0 + i * 256;
         e[i] = f4v{0.f, 0.f, 0.f, 0.f};
         cell[i] = 0;
         sx[i] = sy[i] = 0.f;
-        if (pos < used) {
+        const int blk = pos / block_entries;
+        used[i] = blk < n_blocks && pos - blk * block_entries < used_k[blk] * kChunk;
+        if (used[i]) {
             e[i] = rec_k[pos];
             cell[i] = cell_k[pos / kChunk];
         }
@@ -466,7 +470,7 @@ __global__ __launch_bounds__(256) void gx_combine_kernel(const float2 *__restric
 #pragma unroll
         for (int i = 0; i < kCombinePer; ++i) {
             const int pos = p0 + i * 256;
-            if (pos < used) {
+            if (used[i]) {
                 const float2 p = part_k[t * tile_stride + pos];
                 sx[i] += p.x;
                 sy[i] += p.y;
@@ -515,7 +519,8 @@ void launch_backward_fused(const LayerShape &s, const GridTab &tab, const Sorted
     FusedArgs a;
     a.rec = st.rec;
     a.chunk_cell = st.chunk_cell;
-    a.block_start = st.block_start;
+    a.block_chunks = st.block_chunks;
+    a.block_stride = st.block_stride;
     a.gy = gy;
     a.P = coef;
     a.gP = gcoef;
@@ -559,9 +564,9 @@ void launch_backward_fused(const LayerShape &s, const GridTab &tab, const Sorted
     }
     const bool transposed = gx_transposed != nullptr;
     const dim3 cgrid((unsigned)((st.S + 256 * kCombinePer - 1) / (256 * kCombinePer)), (unsigned)s.pairs());
-    gx_combine_kernel<<<cgrid, 256, 0, stream>>>(a.partial, st.rec, st.chunk_cell, st.block_start, tab,
+    gx_combine_kernel<<<cgrid, 256, 0, stream>>>(a.partial, st.rec, st.chunk_cell, st.block_chunks, tab,
                                                 transposed ? gx_transposed : gx, st.S, s.pairs(), s.out_tiles(),
-                                                s.n_in, st.n_blocks, transposed ? s.batch : 0,
+                                                s.n_in, st.n_blocks, st.block_stride * kChunk, transposed ? s.batch : 0,
                                                 (reinterpret_cast<uintptr_t>(gx) & 7) == 0 ? 1 : 0);
 }
 

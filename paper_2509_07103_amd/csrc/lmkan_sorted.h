@@ -16,30 +16,34 @@ typedef unsigned u2v __attribute__((ext_vector_type(2)));
 
 constexpr int kChunk = 4;    // samples per chunk; a chunk never straddles two cells
 constexpr int kUnroll = 16;  // chunks per trip of the walking kernels' main loops
-constexpr int kSortSeg = 4096;       // samples per workgroup in the count and scatter passes
+constexpr int64_t kMaxSortedBatch = (int64_t)65535 * 4096;
 // A wave reads gy rows in the order of the sorted stream, i.e. all over the batch; as long as
 // the 64-column slice of gy (256 bytes per sample) fits the L2 of an XCD next to the streams,
 // the waves of that XCD share it.  Longer batches are cut into blocks of kBlockSamples samples,
 // the stream of a pair is sorted by (block, cell), and all waves of an XCD work on one block
 // at a time.
 constexpr int kBlockSamples = 8192;  // 2 MiB of gy per block and 64-column tile
-constexpr int kSegPerBlock = kBlockSamples / kSortSeg;
 
 __host__ __device__ inline int stream_blocks(int64_t B)
 {
     return B > kBlockSamples + kBlockSamples / 2 ? (int)((B + kBlockSamples - 1) / kBlockSamples) : 1;
 }
 
-// Entries per pair in the sorted stream: every non-empty (block, cell) is padded to whole
-// chunks, every block to whole trips of kUnroll chunks, and the end is padded so that the
-// walking kernels can prefetch up to three trips beyond the last one without bounds checks
-// (the first trip of that padding holds valid filler entries, the rest is never dereferenced
-// as a sample index).
+// Entries of the sorted stream a block of the batch may take: every non-empty (block, cell) is
+// padded to whole chunks, every block to whole trips of kUnroll chunks, and a trip of padding follows
+// (the walking kernels prefetch sample indices and gy from the trip behind the last one).
+__host__ __device__ inline int64_t stream_block_entries(int64_t B, int G)
+{
+    const int64_t samples = stream_blocks(B) > 1 ? kBlockSamples : B;
+    constexpr int64_t kTrip = kChunk * kUnroll;
+    return (samples + (int64_t)(kChunk - 1) * G * G + kTrip - 1) / kTrip * kTrip + kTrip;
+}
+
+// Entries per pair: the blocks, and two more trips at the end that the walking kernels may load from
+// (never dereferenced as a sample index)
 __host__ __device__ inline int64_t stream_stride(int64_t B, int G)
 {
-    const int64_t blocks = stream_blocks(B);
-    const int64_t body = B + blocks * ((int64_t)(kChunk - 1) * G * G + (int64_t)kChunk * kUnroll);
-    return (body + kChunk - 1) / kChunk * kChunk + (int64_t)kChunk * (3 * kUnroll);
+    return stream_blocks(B) * stream_block_entries(B, G) + (int64_t)kChunk * (2 * kUnroll);
 }
 
 // One entry of the stream, 16 bytes: the local coordinates of Alg. 1's preamble
@@ -51,24 +55,12 @@ struct SortedStream {
     const f4v *rec;              // [K][S]
     const int32_t *chunk_cell;   // [K][S/4]  i1 << 8 | i2 of the cell each chunk belongs to,
                                  //           non-decreasing inside a block
-    const int32_t *block_start;  // [K][blocks + 1]  first chunk of every block (multiples of
-                                 //           kUnroll) and the number of chunks to process
+    const int32_t *block_chunks; // [K][blocks]  chunks of the block to process (a multiple of kUnroll)
     int64_t S;                   // stream_stride
+    int block_stride;            // chunks from the start of a block to that of the next
     int n_blocks;
 };
 
-// Workspace carved up for the sort: the stream above plus the tables the sort passes hand to
-// each other.
-struct SortBuffers {
-    f4v *rec;
-    int32_t *chunk_cell;
-    int32_t *block_start;
-    int32_t *block_size;
-    int32_t *seg_count;
-    int32_t *cell_start;
-    int32_t *cell_rep;
-};
-SortBuffers sort_buffers(const LayerShape &s, void *sorted);
 // records = output of launch_preamble_records; fills the stream in `sorted`
 // (sorted_records_bytes()) and returns its description
 SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted, hipStream_t stream);

@@ -4,6 +4,11 @@ Argument marshalling only: every step of the layer runs in the HIP kernels of
 liblmkan.so.  PyTorch appears here only as the owner of device memory and of
 the current stream.  There is no CPU fallback: if the library is missing or a
 call fails, an exception is raised.
+
+The calls that a program makes per step (forward, backward, pack, the
+convolution) first go to ``_native`` (csrc/lmkan_torch.cpp), which does the same
+marshalling in native code for the ordinary case and returns None for any
+other; the code here then takes over and raises what there is to raise.
 """
 from __future__ import annotations
 
@@ -89,11 +94,12 @@ class LayerDesc:
 
 
 _lib = None
+_native = None   # the extension module, once the library is loaded
 
 
 def lib() -> C.CDLL:
     """Load liblmkan.so (built in-tree by ``build.py``); fail loudly if it is absent."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -140,8 +146,20 @@ def lib() -> C.CDLL:
     L.lmkan_conv2d_backward.restype = C.c_int
     L.lmkan_conv2d_backward.argtypes = [dp, cp, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                         C.c_void_p, C.c_size_t, C.c_void_p]
+    from . import _native as native   # ImportError when it has not been built
+    native.init(*(C.cast(f, C.c_void_p).value for f in (
+        L.lmkan_workspace_bytes, L.lmkan_packed_bytes, L.lmkan_forward, L.lmkan_backward, L.lmkan_conv2d_rows,
+        L.lmkan_conv2d_forward, L.lmkan_conv2d_backward, L.lmkan_pack)))
+    _native = native
     _lib = L
     return L
+
+
+def _fast():
+    """The extension module, loading the library first if need be."""
+    if _native is None:
+        lib()
+    return _native
 
 
 def _check(status: int, where: str) -> None:
@@ -151,7 +169,7 @@ def _check(status: int, where: str) -> None:
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -227,6 +245,10 @@ def _workspace(desc: LayerDesc, batch: int, backward: bool, device, workspace: t
 
 def lmkan_pack(desc: LayerDesc, coef: torch.Tensor, stream=None) -> torch.Tensor:
     """Coefficients [G+1][G+1][K][n_out] -> packed tensor (flat, same dtype)."""
+    if stream is None:
+        out = (_native or _fast()).pack(desc, coef)
+        if out is not None:
+            return out
     dt = _TORCH_DTYPE[desc.coef_dtype]
     src = _dev(coef, dt, desc.coef_shape(), "coef")
     nbytes = lmkan_packed_bytes(desc)
@@ -259,6 +281,10 @@ def lmkan_locate(desc: LayerDesc, x: torch.Tensor, stream=None) -> torch.Tensor:
 
 def lmkan_forward(desc: LayerDesc, x: torch.Tensor, coef: torch.Tensor, y: torch.Tensor | None = None,
                   stream=None, workspace: torch.Tensor | None = None) -> torch.Tensor:
+    if stream is None:
+        out = (_native or _fast()).forward(desc, None, x, coef, y, workspace)
+        if out is not None:
+            return out
     batch = x.shape[0]
     xp = _dev(x, torch.float32, (batch, desc.n_in), "x")
     cp = _coef_ptr(desc, coef)
@@ -290,6 +316,11 @@ def lmkan_backward(desc: LayerDesc, x: torch.Tensor, coef: torch.Tensor | None, 
                    grad_x: torch.Tensor | None = None, grad_coef: torch.Tensor | None = None,
                    stream=None, workspace: torch.Tensor | None = None):
     """Returns (grad_x or None, grad_coef or None); grad_coef is float32 in the layout of Alg. 1."""
+    if stream is None:
+        out = (_native or _fast()).backward(desc, None, x, coef, grad_y, need_grad_x, need_grad_coef, grad_x,
+                                            grad_coef, workspace)
+        if out is not None:
+            return out
     batch = x.shape[0]
     xp = _dev(x, torch.float32, (batch, desc.n_in), "x")
     cp = _coef_ptr(desc, coef)
@@ -348,6 +379,10 @@ def lmkan_conv2d_forward(desc: LayerDesc, conv: Conv2d, x: torch.Tensor, coef: t
                          y: torch.Tensor | None = None, stream=None,
                          workspace: torch.Tensor | None = None) -> torch.Tensor:
     """x[n][h][w][c_in] -> y[n][out_h][out_w][n_out]."""
+    if stream is None:
+        out = (_native or _fast()).forward(desc, conv, x, coef, y, workspace)
+        if out is not None:
+            return out
     rows, oh, ow = lmkan_conv2d_rows(conv)
     xp = _dev(x, torch.float32, conv.image_shape(), "x")
     cp = _coef_ptr(desc, coef)
@@ -367,6 +402,11 @@ def lmkan_conv2d_backward(desc: LayerDesc, conv: Conv2d, x: torch.Tensor, coef: 
                           grad_x: torch.Tensor | None = None, grad_coef: torch.Tensor | None = None, stream=None,
                           workspace: torch.Tensor | None = None):
     """Returns (grad_x in the shape of the image or None, grad_coef in the layout of Alg. 1 or None)."""
+    if stream is None:
+        out = (_native or _fast()).backward(desc, conv, x, coef, grad_y, need_grad_x, need_grad_coef, grad_x,
+                                            grad_coef, workspace)
+        if out is not None:
+            return out
     rows, oh, ow = lmkan_conv2d_rows(conv)
     xp = _dev(x, torch.float32, conv.image_shape(), "x")
     cp = _coef_ptr(desc, coef)

@@ -1,4 +1,5 @@
-"""Build the HIP library (liblmkan.so) for gfx950, in-tree, next to this file."""
+"""Build the HIP library (liblmkan.so) for gfx950, and the extension module that marshals the calls to
+it (_native.so), in-tree, next to this file."""
 from __future__ import annotations
 
 import glob
@@ -6,11 +7,14 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblmkan.so")
+NATIVE_SOURCE = os.path.join(CSRC, "lmkan_torch.cpp")
+NATIVE = os.path.join(HERE, "_native.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -55,15 +59,33 @@ def build(verbose: bool = False, extra: list[str] | None = None) -> str:
     return LIB
 
 
+def build_native() -> str:
+    """Compiles the extension module (host code only) against the headers of the torch in use."""
+    import torch
+    base = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(base, "include"), "-I", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-I", "/opt/rocm/include", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+           "-o", NATIVE, NATIVE_SOURCE,
+           "-L", os.path.join(base, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("g++ failed building _native.so")
+    return NATIVE
+
+
 def up_to_date() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return False
-    t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(ROOT, "include", "lmkan.h")]
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    deps = sources() + [NATIVE_SOURCE] + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(ROOT, "include", "lmkan.h")]
     return all(os.path.getmtime(d) <= t for d in deps)
 
 
 if __name__ == "__main__":
+    print(build_native())
     print(build(verbose=True))
     sys.path.insert(0, ROOT)
     from paper_2509_07103_amd import check_codegen

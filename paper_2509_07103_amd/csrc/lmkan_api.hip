@@ -51,9 +51,9 @@ BackwardWorkspace backward_workspace(const LayerShape &s, bool want_gx, bool wan
 // sigma from Eq. 5 (0.5 e^x on the left half, mirrored on the right), then the two ghost
 // points.  Double precision, each entry rounded once to float32; the spacings are taken
 // from the rounded points.
-lmkan_status build_grid(int G, GridTab *tab)
+GridTab compute_grid(int G)
 {
-    if (G < 3 || G > LMKAN_MAX_GRID) return LMKAN_ERR_SHAPE;
+    GridTab grid, *tab = &grid;
     double e[LMKAN_MAX_GRID + 1];
     for (int k = 1; k <= G - 1; ++k) {
         const int m = (2 * k <= G) ? k : G - k;
@@ -67,6 +67,23 @@ lmkan_status build_grid(int G, GridTab *tab)
     for (int k = 0; k <= G; ++k) tab->node[k] = (float)e[k];
     for (int i = 0; i < G; ++i)
         tab->inv_h[i] = (float)(1.0 / ((double)tab->node[i + 1] - (double)tab->node[i]));
+    return grid;
+}
+
+// every grid once, on the first call (a call for G = 40 spent 1 us on its logarithms)
+struct GridTables {
+    GridTab grid[LMKAN_MAX_GRID + 1];
+    GridTables()
+    {
+        for (int G = 3; G <= LMKAN_MAX_GRID; ++G) grid[G] = compute_grid(G);
+    }
+};
+
+lmkan_status build_grid(int G, GridTab *tab)
+{
+    if (G < 3 || G > LMKAN_MAX_GRID) return LMKAN_ERR_SHAPE;
+    static const GridTables tables;
+    *tab = tables.grid[G];
     return LMKAN_OK;
 }
 

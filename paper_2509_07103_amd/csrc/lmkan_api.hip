@@ -405,6 +405,11 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     // (the slab kernels read gy as it is, except with a ragged output count)
     if (gp_sorted || gx_fused || (gx_slab && ragged_outputs(s))) gy_k = launch_gy_tiles(s, grad_y_dev, ws + w.gy_tiles, hs);
     else gy_k = GyView{grad_y_dev, (int64_t)(LMKAN_PACK_TILE * sizeof(float)), (unsigned)(s.n_out * sizeof(float))};
+    const bool both_gather = gx_gather && gp_gather && backward_gather_shape_ok(s);
+    if (both_gather) {
+        launch_backward_gather(s, tab, x_dev, coef_dev, grad_y_dev, grad_x_dev, grad_coef_dev, !overwrite, hs, conv);
+        return launch_status();
+    }
     if (gp_head) {
         launch_backward_coef_head(s, tab, x_dev, grad_y_dev, grad_coef_dev, !overwrite, hs);
     } else if (gp_gather) {

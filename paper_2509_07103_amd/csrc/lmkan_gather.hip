@@ -300,21 +300,21 @@ __global__ __launch_bounds__(NW * 64) void forward_gather_kernel(GatherArgs a)
 // one pair.  Every (row, pair) belongs to one slot: no atomics, no clearing (except into the
 // overlapping windows of an image, which the caller clears).
 // ---------------------------------------------------------------------------
-template <typename CT, int LPR, int Q>
-__global__ __launch_bounds__(256) void backward_input_gather_kernel(GatherArgs a)
-{
-    constexpr int NS = 64 / LPR, NW = 4;
-    __shared__ float4 s_grid[LMKAN_MAX_GRID];
-    __shared__ float4 s_w[NW][64];   // u, v, 1/h1, 1/h2
-    __shared__ int64_t s_off[NW][64];
-    stage_intervals(a.tab, s_grid);
-    __syncthreads();
+template <int NW>
+struct InputShared {
+    float4 w[NW][64];  // u, v, 1/h1, 1/h2
+    int64_t off[NW][64];
+};
 
+template <typename CT, int LPR, int Q, int NW>
+__device__ __forceinline__ void input_gather(const GatherArgs &a, int block, const float4 *s_grid, InputShared<NW> &sh)
+{
+    constexpr int NS = 64 / LPR;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int slot = lane / LPR, cl = lane % LPR;
     // a wave takes `items` = rows_wave x per_row items
     const int per_row = 1 << a.log_per_row, items = a.items, rows_wave = items >> a.log_per_row;
-    const int64_t id = (int64_t)blockIdx.x * NW + wave;
+    const int64_t id = (int64_t)block * NW + wave;
     const int64_t n0 = id / a.k_chunks * rows_wave;
     const int k0 = (int)(id % a.k_chunks) * per_row;
     if (n0 >= a.B) return;  // whole wave; no block-wide barrier follows
@@ -331,8 +331,8 @@ __global__ __launch_bounds__(256) void backward_input_gather_kernel(GatherArgs a
             wt = make_float4((xv.x - c1.z) * c1.w, (xv.y - c2.z) * c2.w, c1.w, c2.w);
             off = (int64_t)(i1 * a.W + i2) * a.map.s_node + (int64_t)k * a.map.s_pair;
         }
-        s_w[wave][lane] = wt;
-        s_off[wave][lane] = off;
+        sh.w[wave][lane] = wt;
+        sh.off[wave][lane] = off;
     }
     wave_lds_fence();
 
@@ -341,10 +341,10 @@ __global__ __launch_bounds__(256) void backward_input_gather_kernel(GatherArgs a
         const int64_t n = n0 + (e >> a.log_per_row);
         const int k = k0 + (e & (per_row - 1));
         const bool on = n < a.B && k < a.K;
-        const float4 wt = s_w[wave][e];
+        const float4 wt = sh.w[wave][e];
         float d1 = 0.f, d2 = 0.f;
         if (on) {
-            const CT *row = static_cast<const CT *>(a.P) + s_off[wave][e];
+            const CT *row = static_cast<const CT *>(a.P) + sh.off[wave][e];
             const int64_t elems = a.B * a.n_out;
             float da = 0.f, db = 0.f, dc = 0.f, dd = 0.f;  // P10-P00, P11-P01, P01-P00, P11-P10
 #pragma unroll 3 - Q
@@ -408,6 +408,16 @@ __global__ __launch_bounds__(256) void backward_input_gather_kernel(GatherArgs a
     }
 }
 
+template <typename CT, int LPR, int Q>
+__global__ __launch_bounds__(256) void backward_input_gather_kernel(GatherArgs a)
+{
+    __shared__ float4 s_grid[LMKAN_MAX_GRID];
+    __shared__ InputShared<4> sh;
+    stage_intervals(a.tab, s_grid);
+    __syncthreads();
+    input_gather<CT, LPR, Q, 4>(a, blockIdx.x, s_grid, sh);
+}
+
 // ---------------------------------------------------------------------------
 // Coefficient gradient.  A workgroup takes a pair, 4 Q LPR outputs and a share of the table's nodes.  It
 // sorts the samples of the batch by cell in LDS, then every group of LPR lanes takes nodes one
@@ -421,15 +431,12 @@ __global__ __launch_bounds__(256) void backward_input_gather_kernel(GatherArgs a
 // ---------------------------------------------------------------------------
 constexpr int kCoefThreads = 512;
 constexpr int kCoefWaves = kCoefThreads / 64;
-constexpr int kCoefPerMost = 16;  // samples of a thread
+constexpr int kCoefPerFew = 2, kCoefPerMost = 16;  // samples of a thread
 constexpr int kCoefMaxBatch = kCoefThreads * kCoefPerMost;
 
 template <int LPR, int Q, int kCoefPer>
-__global__ __launch_bounds__(kCoefThreads) void backward_coef_gather_kernel(GatherArgs a)
+__device__ __forceinline__ void coef_gather(const GatherArgs &a, int block, float4 *s_grid, int *s_wave, char *gather_smem)
 {
-    extern __shared__ __align__(16) char gather_smem[];
-    __shared__ float4 s_grid[LMKAN_MAX_GRID];
-    __shared__ int s_wave[kCoefWaves];
     const int G = a.W - 1, cells = G * G, B = (int)a.B;
     float2 *s_uv = reinterpret_cast<float2 *>(gather_smem);  // [B], by position
     int *s_row = reinterpret_cast<int *>(s_uv + B);          // [B], by position: the sample
@@ -439,9 +446,7 @@ __global__ __launch_bounds__(kCoefThreads) void backward_coef_gather_kernel(Gath
     int *s_count = reinterpret_cast<int *>(s_off);           // the same memory, two counters to a word
     const int tid = threadIdx.x, wave = tid >> 6;
 
-    const int ct = blockIdx.x % a.n_ct;
-    const int k = (int)(blockIdx.x / a.n_ct) % a.K;
-    const int part = (int)(blockIdx.x / a.n_ct) / a.K;
+    const int ct = block % a.coef_ct, k = block / a.coef_ct % a.K, part = block / a.coef_ct / a.K;
     float2 xv[kCoefPer];
     int64_t first, second;
     pair_offsets(a, k, first, second);
@@ -541,7 +546,7 @@ __global__ __launch_bounds__(kCoefThreads) void backward_coef_gather_kernel(Gath
 #pragma unroll
             for (int i = 0; i < 4 * Q; ++i) acc[i] += __shfl_xor(acc[i], m, 64);
         if (share != 0) continue;
-        float *dst = a.out + ((int64_t)node * a.K + k) * a.n_out;
+        float *dst = a.gcoef + ((int64_t)node * a.K + k) * a.n_out;
 #pragma unroll
         for (int h = 0; h < Q; ++h) {
             const int col = base + cl * 4 + h * 4 * LPR;
@@ -554,6 +559,34 @@ __global__ __launch_bounds__(kCoefThreads) void backward_coef_gather_kernel(Gath
                 store_outputs(dst + col, acc + 4 * h, a.n_out, col, false);
             }
         }
+    }
+}
+
+template <int LPR, int Q, int kCoefPer>
+__global__ __launch_bounds__(kCoefThreads) void backward_coef_gather_kernel(GatherArgs a)
+{
+    extern __shared__ __align__(16) char gather_smem[];
+    __shared__ float4 s_grid[LMKAN_MAX_GRID];
+    __shared__ int s_wave[kCoefWaves];
+    coef_gather<LPR, Q, kCoefPer>(a, blockIdx.x, s_grid, s_wave, gather_smem);
+}
+
+// Both gradients of a small batch in one launch: each waits for its own loads most of the time (5 us for
+// the input gradient, 9 for the coefficient gradient of 256 rows of 16 -> 16), and side by side they
+// take as long as the longer one.
+template <typename CT, int LPRX, int QX, int LPRP, int QP>
+__global__ __launch_bounds__(kCoefThreads) void backward_gather_kernel(GatherArgs a)
+{
+    extern __shared__ __align__(16) char gather_smem[];
+    __shared__ float4 s_grid[LMKAN_MAX_GRID];
+    __shared__ int s_wave[kCoefWaves];
+    __shared__ InputShared<kCoefWaves> sh;
+    if ((int)blockIdx.x < a.coef_blocks) {
+        coef_gather<LPRP, QP, kCoefPerFew>(a, blockIdx.x, s_grid, s_wave, gather_smem);
+    } else {
+        stage_intervals(a.tab, s_grid);
+        __syncthreads();
+        input_gather<CT, LPRX, QX, kCoefWaves>(a, blockIdx.x - a.coef_blocks, s_grid, sh);
     }
 }
 
@@ -570,6 +603,9 @@ int forward_per_lane(const LayerShape &s) { return s.dtype == LMKAN_F32 ? 4 : 8;
 // eight outputs per lane, so that fewer lanes have to meet at the end of an item; float32 rows of up to 4
 // outputs, and of more than 64 (one load per corner and step, two steps in flight): four
 int backward_input_per_lane(const LayerShape &s) { return s.dtype == LMKAN_F32 && (s.n_out <= 4 || s.n_out > 64) ? 4 : 8; }
+
+// wide layers: tiles of 128 outputs (every tile sorts the batch for itself)
+int backward_coef_per_lane(const LayerShape &s) { return s.n_out > 128 ? 8 : 4; }
 
 int log2_of(int power) { return __builtin_ctz((unsigned)power); }
 
@@ -629,6 +665,21 @@ GatherKernel backward_coef_for(int lpr)
     }
 }
 
+// the lanes and quads that the launchers of the single gradients choose for this output count
+template <typename CT>
+GatherKernel backward_for(int n_out)
+{
+    constexpr bool wide = sizeof(CT) == 4;
+    constexpr int q = wide ? 1 : 2;
+    if (n_out <= 4) return backward_gather_kernel<CT, 1, q, 1, 1>;
+    if (n_out <= 8) return backward_gather_kernel<CT, 1, 2, 2, 1>;
+    if (n_out <= 16) return backward_gather_kernel<CT, 2, 2, 4, 1>;
+    if (n_out <= 32) return backward_gather_kernel<CT, 4, 2, 8, 1>;
+    if (n_out <= 64) return backward_gather_kernel<CT, 8, 2, 16, 1>;
+    if (n_out <= 128) return backward_gather_kernel<CT, 16, q, 16, 1>;
+    return backward_gather_kernel<CT, 16, q, 16, 2>;
+}
+
 size_t coef_gather_lds(const LayerShape &s)
 {
     const size_t B = (size_t)s.batch, cells = (size_t)s.G * s.G;
@@ -680,25 +731,19 @@ void launch_forward_gather(const LayerShape &s, const GridTab &tab, const float 
     kernel<<<grid, nw * 64, 0, stream>>>(a);
 }
 
-void launch_backward_input_gather(const LayerShape &s, const GridTab &tab, const float *x, const void *coef,
-                                  const float *gy, float *gx, hipStream_t stream, const ConvGeom *conv)
+// the input gradient's share of the arguments; returns its waves
+static int64_t set_input_args(GatherArgs &a, const LayerShape &s, const float *gy, float *gx, const ConvGeom *conv, int lpr,
+                              hipStream_t stream)
 {
-    GatherArgs a = gather_args(s, tab, x, coef, conv);
     a.gy = gy;
     a.out = gx;
-    const int per_lane = backward_input_per_lane(s);
-    const int lpr = lanes_for(s.n_out, per_lane), ns = 64 / lpr;
     // items per wave: 64, fewer (down to one per slot) until the launch has 2048 waves
     a.items = 64;
-    while (a.items > ns && s.batch * a.K < (int64_t)2048 * a.items) a.items /= 2;
+    while (a.items > 64 / lpr && s.batch * a.K < (int64_t)2048 * a.items) a.items /= 2;
     int per_row = 1;
     while (per_row < a.K && per_row < a.items) per_row *= 2;
     a.log_per_row = log2_of(per_row);
     a.k_chunks = (a.K + per_row - 1) / per_row;
-    const int64_t waves = (s.batch + a.items / per_row - 1) / (a.items / per_row) * a.k_chunks;
-    const GatherKernel kernel = s.dtype == LMKAN_F32 ? (per_lane == 4 ? backward_input_for<float, 1>(lpr) : backward_input_for<float, 2>(lpr))
-                                : s.dtype == LMKAN_F16 ? backward_input_for<_Float16, 2>(lpr)
-                                                       : backward_input_for<bf16_t, 2>(lpr);
     if (conv) {
         // windows that overlap add into the image; elements no window holds are zero
         const ConvGeom &g = *conv;
@@ -706,6 +751,36 @@ void launch_backward_input_gather(const LayerShape &s, const GridTab &tab, const
         const bool covered = g.stride == g.kh && g.stride == g.kw && g.OH * g.kh == g.H && g.OW * g.kw == g.W;
         if (!covered) launch_fill_zero(gx, (size_t)g.N * g.H * g.W * g.C, stream);
     }
+    return (s.batch + a.items / per_row - 1) / (a.items / per_row) * a.k_chunks;
+}
+
+// the coefficient gradient's share; returns its workgroups
+static int64_t set_coef_args(GatherArgs &a, const LayerShape &s, const float *gy, float *gcoef, bool accumulate, int lpr,
+                             int per_lane)
+{
+    a.gy = gy;
+    a.gcoef = gcoef;
+    a.accumulate = accumulate ? 1 : 0;
+    a.coef_ct = (s.n_out + per_lane * lpr - 1) / (per_lane * lpr);
+    // workgroups that share the nodes of a (pair, tile): each sorts the samples for itself
+    const int64_t tiles = (int64_t)a.K * a.coef_ct;
+    a.parts = 1;
+    while (a.parts < 16 && tiles * a.parts < 512 && s.nodes() * lpr > 2 * a.parts * kCoefThreads) a.parts *= 2;
+    // and the lanes of a node's samples, while the nodes leave lanes idle
+    a.spn = 1;
+    while (a.spn < 64 / lpr && (int64_t)s.nodes() * lpr * a.spn < (int64_t)2 * a.parts * kCoefThreads) a.spn *= 2;
+    return tiles * a.parts;
+}
+
+void launch_backward_input_gather(const LayerShape &s, const GridTab &tab, const float *x, const void *coef,
+                                  const float *gy, float *gx, hipStream_t stream, const ConvGeom *conv)
+{
+    GatherArgs a = gather_args(s, tab, x, coef, conv);
+    const int per_lane = backward_input_per_lane(s), lpr = lanes_for(s.n_out, per_lane);
+    const int64_t waves = set_input_args(a, s, gy, gx, conv, lpr, stream);
+    const GatherKernel kernel = s.dtype == LMKAN_F32 ? (per_lane == 4 ? backward_input_for<float, 1>(lpr) : backward_input_for<float, 2>(lpr))
+                                : s.dtype == LMKAN_F16 ? backward_input_for<_Float16, 2>(lpr)
+                                                       : backward_input_for<bf16_t, 2>(lpr);
     KernelTiming timing(stream, kTimeGradInput);
     kernel<<<(unsigned)((waves + 3) / 4), 256, 0, stream>>>(a);
 }
@@ -714,28 +789,40 @@ void launch_backward_coef_gather(const LayerShape &s, const GridTab &tab, const 
                                  bool accumulate, hipStream_t stream, const ConvGeom *conv)
 {
     GatherArgs a = gather_args(s, tab, x, nullptr, conv);
-    a.gy = gy;
-    a.out = gcoef;
-    a.accumulate = accumulate ? 1 : 0;
-    // wide layers: tiles of 128 outputs (every tile sorts the batch for itself)
-    const int per_lane = s.n_out > 128 ? 8 : 4;
-    const int lpr = lanes_for(s.n_out, per_lane);
-    a.n_ct = (s.n_out + per_lane * lpr - 1) / (per_lane * lpr);
-    // workgroups that share the nodes of a (pair, tile): each sorts the samples for itself
-    const int64_t tiles = (int64_t)a.K * a.n_ct;
-    a.parts = 1;
-    while (a.parts < 16 && tiles * a.parts < 512 && s.nodes() * lpr > 2 * a.parts * kCoefThreads) a.parts *= 2;
-    // and the lanes of a node's samples, while the nodes leave lanes idle
-    a.spn = 1;
-    while (a.spn < 64 / lpr && (int64_t)s.nodes() * lpr * a.spn < (int64_t)2 * a.parts * kCoefThreads) a.spn *= 2;
+    const int per_lane = backward_coef_per_lane(s), lpr = lanes_for(s.n_out, per_lane);
+    const int64_t blocks = set_coef_args(a, s, gy, gcoef, accumulate, lpr, per_lane);
     const size_t lds = coef_gather_lds(s);
-    const bool few = s.batch <= 2 * kCoefThreads;
+    const bool few = s.batch <= kCoefPerFew * kCoefThreads;
     const GatherKernel kernel =
-        per_lane == 4 ? (few ? backward_coef_for<1, 2>(lpr) : backward_coef_for<1, kCoefPerMost>(lpr))
-                      : (few ? backward_coef_gather_kernel<16, 2, 2> : backward_coef_gather_kernel<16, 2, kCoefPerMost>);
+        per_lane == 4 ? (few ? backward_coef_for<1, kCoefPerFew>(lpr) : backward_coef_for<1, kCoefPerMost>(lpr))
+                      : (few ? backward_coef_gather_kernel<16, 2, kCoefPerFew> : backward_coef_gather_kernel<16, 2, kCoefPerMost>);
     if (lds > 60 * 1024) allow_large_lds(reinterpret_cast<const void *>(kernel), 155 * 1024);
     KernelTiming timing(stream, kTimeGradCoef);
-    kernel<<<(unsigned)(tiles * a.parts), kCoefThreads, lds, stream>>>(a);
+    kernel<<<(unsigned)blocks, kCoefThreads, lds, stream>>>(a);
+}
+
+// (the LDS of the sort is allocated for the input gradient's workgroups too: only while it leaves room for
+// several of them on a CU)
+bool backward_gather_shape_ok(const LayerShape &s)
+{
+    return backward_input_gather_shape_ok(s) && backward_coef_gather_shape_ok(s) &&
+           s.batch <= kCoefPerFew * kCoefThreads && coef_gather_lds(s) <= 20 * 1024;
+}
+
+void launch_backward_gather(const LayerShape &s, const GridTab &tab, const float *x, const void *coef, const float *gy,
+                            float *gx, float *gcoef, bool accumulate, hipStream_t stream, const ConvGeom *conv)
+{
+    GatherArgs a = gather_args(s, tab, x, coef, conv);
+    const int px = backward_input_per_lane(s), pp = backward_coef_per_lane(s);
+    const int lx = lanes_for(s.n_out, px), lp = lanes_for(s.n_out, pp);
+    const int64_t waves = set_input_args(a, s, gy, gx, conv, lx, stream);
+    a.coef_blocks = (int)set_coef_args(a, s, gy, gcoef, accumulate, lp, pp);
+    const GatherKernel kernel = s.dtype == LMKAN_F32   ? backward_for<float>(s.n_out)
+                                : s.dtype == LMKAN_F16 ? backward_for<_Float16>(s.n_out)
+                                                       : backward_for<bf16_t>(s.n_out);
+    const unsigned grid = (unsigned)(a.coef_blocks + (waves + kCoefWaves - 1) / kCoefWaves);
+    KernelTiming timing(stream, kTimeGradInput);
+    kernel<<<grid, kCoefThreads, coef_gather_lds(s), stream>>>(a);
 }
 
 // rows of the table are read 16 bytes at a time

@@ -26,7 +26,7 @@ bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 // wanted only (pointer alignment, which also steers the choice of kernels, is not known when the
 // caller asks for the size, so every path the shape admits is provided for).
 struct BackwardWorkspace {
-    size_t records, sorted, scratch, partial, gy_tiles;  // offsets
+    size_t records, sorted, scratch, partial, gy_tiles, head;  // offsets
     size_t total;
 };
 BackwardWorkspace backward_workspace(const LayerShape &s, bool want_gx, bool want_gp)
@@ -43,7 +43,8 @@ BackwardWorkspace backward_workspace(const LayerShape &s, bool want_gx, bool wan
     w.scratch = w.sorted + (sorted ? sorted_records_bytes(s) : 0);
     w.partial = w.scratch + (want_gx ? slab_backward_input_scratch_bytes(s) : 0);
     w.gy_tiles = w.partial + (want_gx && !small && sorted ? fused_partial_bytes(s) : 0);
-    w.total = w.gy_tiles + (sorted || (want_gx && !small) ? gy_tiles_bytes(s) : 0);
+    w.head = w.gy_tiles + (sorted || (want_gx && !small) ? gy_tiles_bytes(s) : 0);
+    w.total = w.head + (want_gp && head_forward_shape_ok(s) ? align256(head_partial_bytes(s)) : 0);
     return w;
 }
 
@@ -411,7 +412,10 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
         return launch_status();
     }
     if (gp_head) {
-        launch_backward_coef_head(s, tab, x_dev, grad_y_dev, grad_coef_dev, !overwrite, hs);
+        // (a call may come without a workspace: none is asked for)
+        const bool room = workspace_dev && workspace_bytes >= w.total && aligned(workspace_dev, 256);
+        launch_backward_coef_head(s, tab, x_dev, grad_y_dev, grad_coef_dev, !overwrite,
+                                  room ? reinterpret_cast<float *>(ws + w.head) : nullptr, hs);
     } else if (gp_gather) {
         launch_backward_coef_gather(s, tab, x_dev, grad_y_dev, grad_coef_dev, !overwrite, hs, conv);
     } else if (gp_small) {

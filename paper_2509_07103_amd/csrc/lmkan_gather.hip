@@ -18,33 +18,6 @@ namespace lmkan {
 
 namespace {
 
-// One interval of the grid as locate_cell() wants it: x belongs to interval i when lo <= x < hi
-// (the outer intervals are open ended), u = (x - node) * inv_h.
-__device__ __forceinline__ void stage_intervals(const GridTab &tab, float4 *s_grid)
-{
-    for (int i = threadIdx.x; i < tab.G; i += blockDim.x)
-        s_grid[i] = make_float4(i == 0 ? -INFINITY : tab.node[i], i == tab.G - 1 ? INFINITY : tab.node[i + 1],
-                                tab.node[i], tab.inv_h[i]);
-}
-
-// The interval of x (as locate(): candidate from the exponential, corrected against the table, so
-// the index is exact) and its entry.  One 16-byte LDS read unless the candidate was off.
-__device__ __forceinline__ int locate_cell(const float4 *s_grid, int G, float x, float4 &cell)
-{
-    int i = min(max((int)(sigma(x) * (float)G), 0), G - 1);
-    cell = s_grid[i];
-    while (x < cell.x || x >= cell.y) {
-        i += x < cell.x ? -1 : 1;
-        if (i < 0 || i >= G) {  // x = +inf: the last interval
-            i = G - 1;
-            cell = s_grid[i];
-            break;
-        }
-        cell = s_grid[i];
-    }
-    return i;
-}
-
 // The outputs of a lane among the 4 Q LPR of a tile: quads at first() and, Q = 2, second().  Float32
 // rows arrive in loads that each run along the lanes, 16-bit rows (always Q = 2) in a single one.
 template <typename CT, int LPR, int Q>

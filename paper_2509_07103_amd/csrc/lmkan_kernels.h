@@ -115,8 +115,10 @@ void launch_forward_head(const LayerShape &s, const GridTab &tab, const float *x
 // the layout of Alg. 1
 void launch_backward_input_head(const LayerShape &s, const GridTab &tab, const float *x, const void *coef,
                                 const float *gy, float *gx, hipStream_t stream);
+// (`partial`: head_partial_bytes() of scratch, or NULL: the workgroups then add to gcoef with atomics)
 void launch_backward_coef_head(const LayerShape &s, const GridTab &tab, const float *x, const float *gy,
-                               float *gcoef, bool accumulate, hipStream_t stream);
+                               float *gcoef, bool accumulate, float *partial, hipStream_t stream);
+size_t head_partial_bytes(const LayerShape &s);
 void launch_backward_input_small(const LayerShape &s, const GridTab &tab, const void *coef, const float *gy,
                                  float *gx_scratch, const void *records, hipStream_t stream);
 void launch_backward_coef_small(const LayerShape &s, const void *records, const float *gy, float *gcoef,

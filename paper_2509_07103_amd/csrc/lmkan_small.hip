@@ -13,6 +13,8 @@
 //   coefficient gradient: a workgroup owns a range of pairs whose table slice fits LDS, adds
 //                   its samples into that slice with LDS atomics and then adds the slice into
 //                   the zero-filled gradient (float32 atomics)
+#include <algorithm>
+
 #include "lmkan_kernels.h"
 
 namespace lmkan {
@@ -176,13 +178,10 @@ __global__ __launch_bounds__(kThreads) void backward_coef_small_kernel(SmallArgs
 // write), and locates them itself (Alg. 1 "Preamble"): no records are written or read.
 //   kHeadForward    the products of a sample meet in a sum over its lanes
 //   kHeadGradInput  d/dx1 = gy (1/h1) ((P10 - P00)(1 - v) + (P11 - P01) v), d/dx2 likewise
-//   kHeadGradCoef   gP[corner] += w_corner gy with LDS atomics (the lanes of a sample are different
-//                   pairs: their addresses never coincide), the LDS copy added to the zero-filled
-//                   (or existing) gradient once at the end
 // A wave has kHeadSamples such steps in flight and asks for the inputs of the next ones before it
 // works on those it has.
 // ---------------------------------------------------------------------------
-enum HeadMode { kHeadForward = 0, kHeadGradInput = 1, kHeadGradCoef = 2 };
+enum HeadMode { kHeadForward = 0, kHeadGradInput = 1 };
 
 struct HeadArgs {
     const void *P;
@@ -192,6 +191,7 @@ struct HeadArgs {
     float *y;
     float *gx;             // [B][n_in]
     float *gP;             // float32, layout of Alg. 1
+    float *partial;        // coefficient gradient: [workgroups along the samples][nodes][K], or NULL
     GridTab tab;
     int64_t B;
     int n_in;
@@ -203,9 +203,10 @@ struct HeadArgs {
     int lps;               // lanes per sample
     int samples_per_block;
     int atomic_out;        // forward with several chunks: add into the zero-filled y
+    int copies;            // coefficient gradient: LDS copies of the chunk's gradient, a power of two
 };
 
-constexpr int kHeadSamples = 2;  // steps a wave has in flight (more gain nothing: the two locates of a step bound the kernel)
+constexpr int kHeadSamples = 2;  // steps a wave has in flight
 constexpr int kHeadFill = 12;    // table elements a thread has in flight while LDS is filled
 constexpr int kHeadThreads = 1024;
 
@@ -216,18 +217,14 @@ __device__ __forceinline__ void head_body(const HeadArgs &a)
     const int k0 = blockIdx.y * a.pairs_per_chunk;
     const int kc = min(a.K, k0 + a.pairs_per_chunk) - k0;
     float *s_tab = head_smem;
-    float *s_node = head_smem + (int64_t)a.pairs_per_chunk * a.pitch;
-    float *s_invh = s_node + LMKAN_MAX_GRID + 1;
-    for (int i = threadIdx.x; i <= a.tab.G; i += blockDim.x) s_node[i] = a.tab.node[i];
-    for (int i = threadIdx.x; i < a.tab.G; i += blockDim.x) s_invh[i] = a.tab.inv_h[i];
+    __shared__ float4 s_grid[LMKAN_MAX_GRID];
+    stage_intervals(a.tab, s_grid);
     const int total = kc * a.nodes;
     // element i = node * kc + kl (pairs along the threads: contiguous in the layout of Alg. 1 with
     // one output); a thread's elements lie blockDim.x apart: (node, kl) advance by
     // (step_node, step_kl) with a carry, without a division per element
     const int step_node = (int)blockDim.x / kc, step_kl = (int)blockDim.x - step_node * kc;
-    if constexpr (MODE == kHeadGradCoef) {
-        for (int i = threadIdx.x; i < a.pairs_per_chunk * a.pitch; i += blockDim.x) s_tab[i] = 0.0f;
-    } else {
+    {
         // Every load is unconditional (the node clamped), so that kHeadFill of them are in flight
         // per thread.
         const CT *P = static_cast<const CT *>(a.P);
@@ -293,13 +290,14 @@ __device__ __forceinline__ void head_body(const HeadArgs &a)
             request(more ? n : n + (int64_t)waves * per_round, more ? kk + a.lps : 0, xv_next, g_next);
             const bool on = kk + pl < kc;
             const int kl = min(kk + pl, kc - 1);
-            float *t_pair = s_tab + kl * a.pitch;
+            const float *t_pair = s_tab + kl * a.pitch;
 #pragma unroll
             for (int s = 0; s < kHeadSamples; ++s) {
-                const Preamble pr = preamble(s_node, s_invh, a.tab.G, xv[s].x, xv[s].y);
-                const float u = pr.a_hi, v = pr.b_hi;
+                float4 c1, c2;
+                const int i1 = locate_cell(s_grid, a.tab.G, xv[s].x, c1), i2 = locate_cell(s_grid, a.tab.G, xv[s].y, c2);
+                const float u = (xv[s].x - c1.z) * c1.w, v = (xv[s].y - c2.z) * c2.w;
                 const float a_lo = 1.0f - u, b_lo = 1.0f - v;
-                float *t = t_pair + pr.node;
+                const float *t = t_pair + i1 * a.W + i2;
                 const int64_t mine = n + s * per_step + sub;
                 if constexpr (MODE == kHeadForward) {
                     float val = (a_lo * b_lo) * t[0];
@@ -307,19 +305,12 @@ __device__ __forceinline__ void head_body(const HeadArgs &a)
                     val = fmaf(a_lo * v, t[1], val);
                     val = fmaf(u * v, t[a.W + 1], val);
                     acc[s] += on ? val : 0.0f;
-                } else if constexpr (MODE == kHeadGradInput) {
+                } else {
                     const float s00 = g[s] * t[0], s10 = g[s] * t[a.W], s01 = g[s] * t[1], s11 = g[s] * t[a.W + 1];
-                    const float d1 = pr.rh1 * ((s10 - s00) * b_lo + (s11 - s01) * v);
-                    const float d2 = pr.rh2 * ((s01 - s00) * a_lo + (s11 - s10) * u);
+                    const float d1 = c1.w * ((s10 - s00) * b_lo + (s11 - s01) * v);
+                    const float d2 = c2.w * ((s01 - s00) * a_lo + (s11 - s10) * u);
                     if (on && mine < n_end)
                         *reinterpret_cast<float2 *>(a.gx + mine * a.n_in + 2 * (k0 + kl)) = make_float2(d1, d2);
-                } else {
-                    if (on && mine < n_end) {
-                        atomicAdd(t, (a_lo * b_lo) * g[s]);
-                        atomicAdd(t + a.W, (u * b_lo) * g[s]);
-                        atomicAdd(t + 1, (a_lo * v) * g[s]);
-                        atomicAdd(t + a.W + 1, (u * v) * g[s]);
-                    }
                 }
             }
         }
@@ -339,22 +330,6 @@ __device__ __forceinline__ void head_body(const HeadArgs &a)
         }
         n += (int64_t)waves * per_round;
     }
-
-    if constexpr (MODE == kHeadGradCoef) {
-        // every wave comes here (none leaves early): the block's sums go to the gradient
-        __syncthreads();
-        int node = (int)threadIdx.x / kc, kl = (int)threadIdx.x - node * kc;
-        for (int i = threadIdx.x; i < total; i += blockDim.x) {
-            const float v = s_tab[kl * a.pitch + node];
-            if (v != 0.0f) unsafeAtomicAdd(a.gP + (int64_t)node * a.map.s_node + (int64_t)(k0 + kl) * a.map.s_pair, v);
-            node += step_node;
-            kl += step_kl;
-            if (kl >= kc) {
-                kl -= kc;
-                ++node;
-            }
-        }
-    }
 }
 
 template <typename CT>
@@ -369,9 +344,120 @@ __global__ __launch_bounds__(kHeadThreads) void backward_input_head_kernel(HeadA
     head_body<CT, kHeadGradInput>(a);
 }
 
+// ---------------------------------------------------------------------------
+// The coefficient gradient of one output: gP[corner] += w_corner gy.  The gradient of a chunk of pairs
+// sits in LDS, and every pair's copy of it belongs to four lanes of one wave, one lane per corner.  A wave
+// executes in lockstep and its LDS instructions in order, so the four lanes read, add and write back
+// without atomics: the corners of one sample are four different nodes, and the next sample's reads
+// come after this one's writes.  Each lane locates one of four samples; the samples are then handed
+// round inside the quad.  Where few pairs leave lanes or LDS idle, a pair has several copies, each with
+// samples of its own.  Every workgroup then stores its sums as a partial gradient and
+// head_combine_kernel adds the partials up in a fixed order (adding them to the gradient with atomics, as
+// a call without room for them does, took 38 us for 256 partials of 148 KB, three times as long).
+// (LDS float atomics before this took about 3.5 clocks per lane and CU whatever their addresses: 0.22 ms
+// for 256 -> 1 on 65536 rows.  Bound now by the chain of reads and writes, about 120 clocks per sample,
+// and by the locates.)
+// ---------------------------------------------------------------------------
+template <int S>
+__device__ __forceinline__ float quad_bcast(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), S * 0x55, 0xf, 0xf, true));
+}
+template <int S>
+__device__ __forceinline__ int quad_bcast(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, S * 0x55, 0xf, 0xf, true);
+}
+
 __global__ __launch_bounds__(kHeadThreads) void backward_coef_head_kernel(HeadArgs a)
 {
-    head_body<float, kHeadGradCoef>(a);
+    extern __shared__ __align__(16) float head_smem[];
+    __shared__ float4 s_grid[LMKAN_MAX_GRID];
+    const int k0 = blockIdx.y * a.pairs_per_chunk;
+    const int kc = min(a.K, k0 + a.pairs_per_chunk) - k0;
+    stage_intervals(a.tab, s_grid);
+    for (int i = threadIdx.x; i < a.copies * a.pairs_per_chunk * a.pitch; i += blockDim.x) head_smem[i] = 0.0f;
+    __syncthreads();
+
+    const int quad = threadIdx.x >> 2, corner = threadIdx.x & 3;
+    const int copy = quad / a.pairs_per_chunk, kl = quad - copy * a.pairs_per_chunk;
+    const int64_t n_begin = (int64_t)blockIdx.x * a.samples_per_block;
+    const int64_t n_end = min(a.B, n_begin + a.samples_per_block);
+    if (copy < a.copies && kl < kc) {  // whole quads
+        // this lane's corner: weights (flip_u + sign_u u) (flip_v + sign_v v), its node relative to the cell's
+        const float sign_u = (corner & 1) ? 1.0f : -1.0f, flip_u = (corner & 1) ? 0.0f : 1.0f;
+        const float sign_v = (corner & 2) ? 1.0f : -1.0f, flip_v = (corner & 2) ? 0.0f : 1.0f;
+        float *table = head_smem + quad * a.pitch + (corner & 1) * a.W + (corner >> 1);
+        const float *xp = a.x + 2 * (k0 + kl);
+        const int64_t step = 4 * a.copies;
+        int64_t n = n_begin + 4 * copy + corner;  // the sample this lane locates
+        auto request = [&](int64_t at, float2 &xv, float &g) {
+            const int64_t nn = min(at, n_end - 1);
+            xv = *reinterpret_cast<const float2 *>(xp + nn * a.n_in);
+            g = a.gy[nn];
+        };
+        float2 xv;
+        float g;
+        request(n, xv, g);
+        for (; n - corner < n_end; n += step) {
+            float2 xv_next;
+            float g_next;
+            request(n + step, xv_next, g_next);
+            float4 c1, c2;
+            const int i1 = locate_cell(s_grid, a.tab.G, xv.x, c1), i2 = locate_cell(s_grid, a.tab.G, xv.y, c2);
+            int node = i1 * a.W + i2;
+            float u = (xv.x - c1.z) * c1.w, v = (xv.y - c2.z) * c2.w;
+            if (n >= n_end) node = 0, u = 0.f, v = 0.f, g = 0.f;  // adds zero
+            static_for(std::make_integer_sequence<int, 4>{}, [&](auto sc) {
+                constexpr int S = decltype(sc)::value;
+                const float wu = fmaf(sign_u, quad_bcast<S>(u), flip_u), wv = fmaf(sign_v, quad_bcast<S>(v), flip_v);
+                float *t = table + quad_bcast<S>(node);
+                *t += wu * wv * quad_bcast<S>(g);
+            });
+            xv = xv_next;
+            g = g_next;
+        }
+    }
+    __syncthreads();
+    // element i = node * kc + pair: pairs along the threads, contiguous in the gradient
+    const int total = kc * a.nodes;
+    const int step_node = (int)blockDim.x / kc, step_kl = (int)blockDim.x - step_node * kc;
+    int node = (int)threadIdx.x / kc, kk = (int)threadIdx.x - node * kc;
+    for (int i = threadIdx.x; i < total; i += blockDim.x) {
+        float v = 0.0f;
+        for (int c = 0; c < a.copies; ++c) v += head_smem[(c * a.pairs_per_chunk + kk) * a.pitch + node];
+        if (a.partial)
+            a.partial[((int64_t)blockIdx.x * a.nodes + node) * a.K + k0 + kk] = v;
+        else if (v != 0.0f)
+            unsafeAtomicAdd(a.gP + (int64_t)node * a.map.s_node + (int64_t)(k0 + kk) * a.map.s_pair, v);
+        node += step_node;
+        kk += step_kl;
+        if (kk >= kc) {
+            kk -= kc;
+            ++node;
+        }
+    }
+}
+
+// gP[i] (+)= sum over the partials: 64 elements per workgroup, the partials dealt to its waves, whose
+// sums are added in a fixed order
+constexpr int kCombineWaves = 16;
+__global__ __launch_bounds__(64 * kCombineWaves) void head_combine_kernel(const float *__restrict__ partial,
+                                                                          float *__restrict__ gP, int64_t elems,
+                                                                          int n_part, int accumulate)
+{
+    __shared__ float s_sum[kCombineWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+    float sum = 0.0f;
+    if (i < elems)
+#pragma unroll 8
+        for (int p = wave; p < n_part; p += kCombineWaves) sum += partial[(int64_t)p * elems + i];
+    s_sum[wave][lane] = sum;
+    __syncthreads();
+    if (wave != 0 || i >= elems) return;
+    for (int w = 1; w < kCombineWaves; ++w) sum += s_sum[w][lane];
+    gP[i] = accumulate ? gP[i] + sum : sum;
 }
 
 SmallArgs small_args(const LayerShape &s, const void *coef, const void *records)
@@ -408,10 +494,10 @@ bool small_out_shape_ok(const LayerShape &s)
 
 // LDS floats per pair of the one-output forward kernel, and the pairs one workgroup can hold
 static int head_pitch(const LayerShape &s) { return s.nodes() | 1; }
+static int head_budget() { return (160 * 1024 - LMKAN_MAX_GRID * (int)sizeof(float4)) / (int)sizeof(float); }  // beside the grid
 static int head_chunk(const LayerShape &s)
 {
-    const int budget = (160 * 1024 - 1024) / (int)sizeof(float);  // 1 KB for the grid
-    int kc = budget / head_pitch(s);
+    int kc = head_budget() / head_pitch(s);
     if (kc >= s.pairs()) return s.pairs();
     return kc & ~63;
 }
@@ -441,7 +527,7 @@ static HeadArgs head_args(const LayerShape &s, const GridTab &tab, const float *
     // a sample takes as many lanes as the chunk has pairs, rounded up to a power of two
     a.lps = 1;
     while (a.lps < 64 && a.lps < a.pairs_per_chunk) a.lps *= 2;
-    *lds = ((size_t)a.pairs_per_chunk * a.pitch + 2 * LMKAN_MAX_GRID + 2) * sizeof(float);
+    *lds = (size_t)a.pairs_per_chunk * a.pitch * sizeof(float);
     // every workgroup fills (or clears and later adds out) its LDS copy of the chunk's tables: a
     // workgroup should have at least two rounds of its 16 waves to spread that over
     const int64_t round = (int64_t)(kHeadThreads / 64) * kHeadSamples * (64 / a.lps);
@@ -456,11 +542,11 @@ static HeadArgs head_args(const LayerShape &s, const GridTab &tab, const float *
 typedef void (*HeadKernel)(HeadArgs);
 
 static void launch_head(HeadKernel kernel, const HeadArgs &a, dim3 grid, size_t lds, hipStream_t stream,
-                        TimedKernel kind)
+                        TimedKernel kind, int threads = kHeadThreads)
 {
-    if (lds > 64 * 1024) allow_large_lds(reinterpret_cast<const void *>(kernel), 160 * 1024);
+    if (lds > 60 * 1024) allow_large_lds(reinterpret_cast<const void *>(kernel), 160 * 1024 - LMKAN_MAX_GRID * sizeof(float4));
     KernelTiming timing(stream, kind);
-    kernel<<<grid, kHeadThreads, lds, stream>>>(a);
+    kernel<<<grid, threads, lds, stream>>>(a);
 }
 
 void launch_forward_head(const LayerShape &s, const GridTab &tab, const float *x, const void *coef, float *y,
@@ -494,21 +580,72 @@ void launch_backward_input_head(const LayerShape &s, const GridTab &tab, const f
     launch_head(kernels[s.dtype], a, grid, lds, stream, kTimeGradInput);
 }
 
-void launch_backward_coef_head(const LayerShape &s, const GridTab &tab, const float *x, const float *gy,
-                               float *gcoef, bool accumulate, hipStream_t stream)
-{
-    dim3 grid;
+// how the coefficient gradient is cut up: copies of the pairs in LDS, samples per workgroup
+struct HeadCoefPlan {
+    int pairs_per_chunk, copies, threads, chunks;
+    int64_t samples_per_block, blocks;
     size_t lds;
-    // (bound by the LDS atomics, about 3.5 clocks per lane and CU: every CU has to take part, although
-    // every workgroup ends by adding its whole LDS copy to the gradient)
-    HeadArgs a = head_args(s, tab, x, 256, &grid, &lds);
+};
+static HeadCoefPlan head_coef_plan(const LayerShape &s)
+{
+    HeadCoefPlan p;
+    // four lanes per pair: at most 256 pairs and copies of pairs to a workgroup
+    const int fit = head_budget() / head_pitch(s);
+    p.pairs_per_chunk = std::min(head_chunk(s), 256);
+    p.chunks = (s.pairs() + p.pairs_per_chunk - 1) / p.pairs_per_chunk;
+    p.copies = 1;
+    while (2 * p.copies * p.pairs_per_chunk <= std::min(fit, 256)) p.copies *= 2;
+    p.threads = (p.copies * p.pairs_per_chunk * 4 + 63) & ~63;
+    p.lds = (size_t)p.copies * p.pairs_per_chunk * head_pitch(s) * sizeof(float);
+    // no more workgroups than the chip holds at once, and at least 32 samples to a copy
+    const int64_t resident = 256 * std::max(1, std::min((int)(160 * 1024 / (p.lds + 2048)), 2048 / p.threads));
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(resident / p.chunks, s.batch / (32 * p.copies)));
+    p.samples_per_block = ((s.batch + most - 1) / most + 3) & ~(int64_t)3;
+    p.blocks = (s.batch + p.samples_per_block - 1) / p.samples_per_block;
+    return p;
+}
+
+size_t head_partial_bytes(const LayerShape &s)
+{
+    // (a workgroup whose samples reach few of the nodes adds those few with atomics instead: 4096 rows of
+    // 256 -> 1 take 27 us that way, 30 through partials)
+    const HeadCoefPlan p = head_coef_plan(s);
+    return p.blocks > 1 && 4 * p.samples_per_block >= s.nodes() ? (size_t)p.blocks * s.nodes() * s.pairs() * sizeof(float) : 0;
+}
+
+void launch_backward_coef_head(const LayerShape &s, const GridTab &tab, const float *x, const float *gy,
+                               float *gcoef, bool accumulate, float *partial, hipStream_t stream)
+{
+    const HeadCoefPlan p = head_coef_plan(s);
+    HeadArgs a = {};
+    a.x = x;
+    a.tab = tab;
+    a.B = s.batch;
+    a.n_in = s.n_in;
+    a.K = s.pairs();
+    a.W = s.G + 1;
+    a.nodes = s.nodes();
+    a.pitch = head_pitch(s);
+    a.pairs_per_chunk = p.pairs_per_chunk;
+    a.copies = p.copies;
+    a.samples_per_block = (int)p.samples_per_block;
     LayerShape g = s;
     g.layout = LMKAN_LAYOUT_PAPER;
     a.map = coef_map(g);
     a.gy = gy;
     a.gP = gcoef;
-    if (!accumulate) launch_fill_zero(gcoef, (size_t)s.nodes() * (size_t)s.pairs(), stream);
-    launch_head(backward_coef_head_kernel, a, grid, lds, stream, kTimeGradCoef);
+    const int64_t elems = (int64_t)s.nodes() * s.pairs();
+    // a single workgroup along the samples is its own partial
+    if (p.blocks == 1 && !accumulate)
+        a.partial = gcoef;
+    else
+        a.partial = head_partial_bytes(s) > 0 ? partial : nullptr;
+    if (!a.partial && !accumulate) launch_fill_zero(gcoef, (size_t)elems, stream);
+    launch_head(backward_coef_head_kernel, a, dim3((unsigned)p.blocks, (unsigned)p.chunks), p.lds, stream, kTimeGradCoef,
+                p.threads);
+    if (a.partial && a.partial != gcoef)
+        head_combine_kernel<<<(unsigned)((elems + 63) / 64), 64 * kCombineWaves, 0, stream>>>(a.partial, gcoef, elems,
+                                                                                            (int)p.blocks, accumulate ? 1 : 0);
 }
 
 void launch_forward_small(const LayerShape &s, const void *coef, float *y, const void *records, hipStream_t stream)

@@ -109,3 +109,25 @@ def test_a_forward_call_that_gathers_leaves_the_promise_of_records_harmless(orac
     assert rowwise_rel_err(gx.cpu().numpy(), oracle.backward_input(xh, P.cpu().numpy(), gyh, G)) <= TOL_F32
     for k in range(n_in // 2):
         assert pair_slice_rel_err(gP.cpu().numpy()[:, :, k, :], oracle.backward_coef_pair(xh, gyh, G, k)) <= TOL_F32
+
+
+@pytest.mark.parametrize("room", [True, False])
+@pytest.mark.parametrize("shape", [(9000, 20, 1, 7),     # copies of the pairs, partial gradients
+                                   (2000, 700, 1, 8),    # more pairs than a workgroup has lanes for
+                                   (40, 6, 1, 5),        # one workgroup
+                                   (4096, 130, 1, 16)])  # samples that reach few nodes: atomics
+def test_one_output_coefficient_gradient(oracle, shape, room):
+    """With and without a workspace, into an existing gradient and over a stale one."""
+    dev = torch.device("cuda:0")
+    B, n_in, n_out, G = shape
+    x, P, gy = _inputs(B, n_in, n_out, G, 76, dev)
+    acc = pkg.LayerDesc(n_in, n_out, G, flags=pkg.LMKAN_FLAG_ACCUMULATE_GRAD_COEF)
+    ws = None if room else torch.empty(256, dtype=torch.uint8, device=dev)
+    added = torch.full(acc.coef_shape(), 0.5, device=dev)
+    pkg.lmkan_backward(acc, x, None, gy, need_grad_x=False, grad_coef=added, workspace=ws)
+    over = torch.full(acc.coef_shape(), 9.0, device=dev)
+    pkg.lmkan_backward(pkg.LayerDesc(n_in, n_out, G), x, None, gy, need_grad_x=False, grad_coef=over, workspace=ws)
+    torch.cuda.synchronize()
+    want = oracle.backward_coef(x.cpu().numpy(), gy.cpu().numpy(), G)
+    assert np.abs(over.cpu().numpy() - want).max() <= TOL_F32 * np.abs(want).max()
+    assert np.abs(added.cpu().numpy() - (want + 0.5)).max() <= 2e-5 * max(1.0, np.abs(want).max())

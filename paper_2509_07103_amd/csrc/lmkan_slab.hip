@@ -725,6 +725,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     }
     const int w = W_CT > 0 ? W_CT : a.W;
     float *gx_lane = a.gx + n;   // transposed scratch [n_in][ld], plain layout
+    // The derivatives of a pair are added a pair later, behind the barrier: the wait before it is for
+    // everything this wave has in flight, and atomics issued right before it would be waited for.
+    float d1 = 0.f, d2 = 0.f;
+    auto add_derivatives = [&](int k) {
+        if (valid) {
+            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k) * a.ld, d1);
+            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k + 1) * a.ld, d2);
+        }
+    };
     for (int k = k_begin; k < k_end; ++k) {
         const float *slab = ((k - k_begin) & 1) ? slab1 : slab0;
         float *slab_next = ((k - k_begin) & 1) ? slab0 : slab1;
@@ -738,6 +747,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             fill.template issue<0>(sa, slab_next, k + 1, jt, wave, lane);
             fetch_record(k + 1);
         }
+        if (k > k_begin) add_derivatives(k - 1);
         // piece (j + l15) mod 16 of the row: from `first` for j < 16 - l15, one row back after the wrap
         unsigned first = lds_address(slab) + (unsigned)node * kRowBytes + (unsigned)l15 * 16;
         // The derivative is made of differences between neighbouring corners, and on a smooth table
@@ -792,13 +802,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             }
         });
         if (k + 1 < k_end) fill.template commit<1>(sa, slab_next, wave, lane);
-        const float d1 = rh1 * (dif_a * (1.0f - v) + dif_b * v);
-        const float d2 = rh2 * (dif_c * (1.0f - u) + dif_d * u);
-        if (valid) {
-            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k) * a.ld, d1);
-            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k + 1) * a.ld, d2);
-        }
+        d1 = rh1 * (dif_a * (1.0f - v) + dif_b * v);
+        d2 = rh2 * (dif_c * (1.0f - u) + dif_d * u);
     }
+    if (k_begin < k_end) add_derivatives(k_end - 1);
 }
 
 // ---------------------------------------------------------------------------

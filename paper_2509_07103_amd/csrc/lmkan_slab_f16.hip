@@ -263,6 +263,14 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
         fetch_record(k_begin);
     }
     float *gx_lane = a.gx + n;   // transposed scratch [n_in][ld], plain layout
+    // (added a pair later, behind the barrier, as in backward_input_lane_kernel)
+    float d1 = 0.f, d2 = 0.f;
+    auto add_derivatives = [&](int k) {
+        if (valid) {
+            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k) * a.ld, d1);
+            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k + 1) * a.ld, d2);
+        }
+    };
 
     for (int k = k_begin; k < k_end; ++k) {
         const unsigned cur = ((k - k_begin) & 1) ? base1 : base0;
@@ -277,6 +285,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
             issue_slab_load_h(sa, nxt, k + 1, jt, wave, lane);
             fetch_record(k + 1);
         }
+        if (k > k_begin) add_derivatives(k - 1);
         // piece (j + l15) mod 16 of the row: from `first` for j < 16 - l15, one row back after the wrap
         unsigned first = cur + (unsigned)node * kRowBytesH + (unsigned)l15 * 8;
         // dif_a = sum gy (P10 - P00), dif_b = sum gy (P11 - P01), dif_c = sum gy (P01 - P00),
@@ -307,13 +316,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
             dif_c += p01 - p00;
             dif_d += p11 - p10;
         });
-        const float d1 = rh1 * (dif_a * (1.0f - v) + dif_b * v);
-        const float d2 = rh2 * (dif_c * (1.0f - u) + dif_d * u);
-        if (valid) {
-            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k) * a.ld, d1);
-            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k + 1) * a.ld, d2);
-        }
+        d1 = rh1 * (dif_a * (1.0f - v) + dif_b * v);
+        d2 = rh2 * (dif_c * (1.0f - u) + dif_d * u);
     }
+    if (k_begin < k_end) add_derivatives(k_end - 1);
 }
 
 }  // namespace

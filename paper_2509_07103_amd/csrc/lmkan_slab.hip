@@ -326,9 +326,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     // Workgroup -> (output tile, pair split, sample tile).  Consecutive ids go round-robin
     // over the 8 XCDs, each with its own L2; workgroups that stream the same slabs
     // (same output tile and pair range, different sample tile) are placed on one XCD.
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -509,9 +507,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const int l16 = lane & 15, g = lane >> 4;
     constexpr int kTileB = WAVES * SETS * 64;
     constexpr int TOTAL = SETS * 16;
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -668,9 +664,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l15 = lane & 15;
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -860,9 +854,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l3 = lane & 3;
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -996,9 +988,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l3 = lane & 3;
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -1165,9 +1155,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lp = lane & (PIECES - 1);
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -1320,9 +1308,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lp = lane & (PIECES - 1);
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -1529,9 +1515,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const int sub = lane & 3, grp = lane >> 2;
     constexpr int kTileB = WAVES * SETS * 64;
 
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -1695,9 +1679,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sub = lane & 3, grp = lane >> 2;
     constexpr int kTileB = WAVES * SETS * 64;
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -1919,7 +1901,7 @@ int slab_forward_split(const LayerShape &s)
     const bool half = slab_forward_takes_half_tiles(s);
     const int64_t tile_b = wide ? 1024 : half ? 2048 : 4096;
     const int64_t n_jt = wide ? s.out_tiles() : half ? (s.n_out + 31) / 32 : (s.n_out + 15) / 16;
-    return pair_split_count((int)(((s.batch + tile_b - 1) / tile_b) * n_jt), s.pairs());
+    return pair_split_count(((s.batch + tile_b - 1) / tile_b) * n_jt, s.pairs(), partial_stride(s.batch * s.n_out) * 4);
 }
 
 size_t slab_forward_partial_bytes(const LayerShape &s)
@@ -2040,7 +2022,7 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
     a.n_btiles = (int)((s.batch + kTileB - 1) / kTileB);
     a.n_jt = (s.n_out + kNarrowTile - 1) / kNarrowTile;
     const int tiles = a.n_btiles * a.n_jt;
-    const int split = pair_split_count(tiles, a.K);
+    const int split = slab_forward_split(s);   // what the workspace was sized for
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     finish_split_setup(a, s, y, partials, stream);
@@ -2093,7 +2075,7 @@ void launch_forward_slab(const LayerShape &s, const void *coef, float *y, const 
     a.n_jt = s.out_tiles();
     // split the pairs over several workgroups when the tiles alone cannot fill 256 CUs
     const int tiles = a.n_btiles * a.n_jt;
-    const int split = pair_split_count(tiles, a.K);
+    const int split = slab_forward_split(s);   // what the workspace was sized for
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     finish_split_setup(a, s, y, partials, stream);
@@ -2266,8 +2248,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
         a.n_btiles = (int)((s.batch + 2047) / 2048);
         a.n_jt = (s.n_out + kHalfTile - 1) / kHalfTile;
         const int tiles32 = a.n_btiles * a.n_jt;
-        int split32 = 1;
-        while (tiles32 * split32 < 256 && a.K / (split32 * 2) >= 4) split32 *= 2;
+        const int split32 = pair_split_count(tiles32, a.K, 0);
         a.n_split = split32;
         a.pairs_per_split = (a.K + split32 - 1) / split32;
         a.ld = scratch_row_stride(s.batch, kScratchPlain);
@@ -2319,8 +2300,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
     a.n_btiles = (int)((s.batch + tile_b - 1) / tile_b);
     a.n_jt = narrow ? (s.n_out + kNarrowTile - 1) / kNarrowTile : s.out_tiles();
     const int tiles = a.n_btiles * a.n_jt;
-    int split = 1;
-    while (tiles * split < 256 && a.K / (split * 2) >= 4) split *= 2;
+    const int split = pair_split_count(tiles, a.K, 0);
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     const bool lane_kernel = !narrow && s.dtype == LMKAN_F32;   // its lanes are consecutive samples

@@ -33,17 +33,28 @@ struct SlabArgs {
     int64_t part_elems;
 };
 
-// Pair splits for a launch of `tiles` workgroups over K pairs: double until 256 CUs have work,
-// keeping at least four pairs per split.  A workgroup walks its pairs one after the other, a slab
-// fill and a barrier each (about 3 us), so few workgroups with many pairs each are bound by that
-// latency: with at least 32 pairs per split a 64 -> 64 layer on 4096 rows took 0.10 ms forward and
-// 0.15 ms for grad_x whatever the batch, with four 0.034 and 0.044 ms.
-// (the input-gradient launchers apply the same rule)
-inline int pair_split_count(int tiles, int K)
+// Pair splits for a launch of `tiles` workgroups over K pairs.  A workgroup fills a CU and walks its
+// pairs one after the other, a slab fill and a barrier each (about 3.5 us), so a launch lasts as many
+// such steps as rounds of 256 workgroups times pairs per split.  Few tiles want more splits to have
+// work for every CU, and a count a little above a multiple of 256 wastes most of its last round: the
+// split is the one with the fewest steps, two more per round for the tile's own loads and stores, and
+// at least four pairs in each.  A forward split beyond the first writes a part of its own that is added
+// up later (part_bytes each, moved twice); the input gradient adds atomically and passes 0.
+// (500 -> 333 outputs at G = 20 on 5000 rows, 33 tiles of 250 pairs: 8 splits make 264 workgroups and
+// two rounds of 32 pairs, 7 make 231 in one round of 36: forward 254 -> 157 us, grad_x 261 -> 212 us.)
+inline int pair_split_count(int64_t tiles, int K, int64_t part_bytes)
 {
-    int split = 1;
-    while (tiles * split < 256 && K / (split * 2) >= 4) split *= 2;
-    return split;
+    int best = 1;
+    double best_us = 0.0;
+    for (int split = 1; split == 1 || K / split >= 4; ++split) {
+        const int64_t rounds = (tiles * split + 255) / 256;
+        const int pairs = (K + split - 1) / split;
+        if ((split - 1) * pairs >= K) continue;   // the last split would have none
+        const double us = 3.5 * (double)rounds * (pairs + 2) + (split - 1) * (double)part_bytes * 2 / 4.9e6 +
+                          (split > 1 && part_bytes ? 5.0 : 0.0);
+        if (split == 1 || us < best_us) best = split, best_us = us;
+    }
+    return best;
 }
 
 // floats between the partial outputs of consecutive pair splits: a whole number of 16-byte pieces
@@ -83,6 +94,14 @@ __device__ __forceinline__ float *forward_out_base(const SlabArgs &a, int ks, bo
 {
     atomic = a.atomic_out && !a.y_part;
     return (a.y_part && ks > 0) ? a.y_part + (int64_t)(ks - 1) * a.part_elems : a.y;
+}
+
+// Tile of this workgroup: consecutive workgroups go to the 8 XCDs in turn, so each XCD is given a
+// contiguous run of tiles (those of one slab lie next to each other and share its L2).
+__device__ __forceinline__ int xcd_tile()
+{
+    const int total = gridDim.x, xcd = blockIdx.x & 7, each = total >> 3, over = total & 7;
+    return xcd * each + min(xcd, over) + ((int)blockIdx.x >> 3);
 }
 
 // 16 bytes per lane from global memory straight into LDS at lds_base + lane * 16

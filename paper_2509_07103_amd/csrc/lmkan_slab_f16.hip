@@ -105,9 +105,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
     const int l16 = lane & 15, g = lane >> 4;
     constexpr int kTileB = kWaves * 64;
 
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -208,9 +206,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
     const int l15 = lane & 15;
     const int w = W_CT > 0 ? W_CT : a.W;
     constexpr int kTileB = kWaves * 64;
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     const int ks = rest % a.n_split;
@@ -356,7 +352,7 @@ void launch_forward_slab_f16(const LayerShape &s, const void *coef, float *y, co
     a.n_btiles = (int)((s.batch + kTileB - 1) / kTileB);
     a.n_jt = s.out_tiles();
     const int tiles = a.n_btiles * a.n_jt;
-    const int split = pair_split_count(tiles, a.K);
+    const int split = slab_forward_split(s);   // what the workspace was sized for
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     finish_split_setup(a, s, y, partials, stream);
@@ -398,8 +394,7 @@ void launch_backward_input_slab_f16(const LayerShape &s, const GridTab &tab, con
     a.n_btiles = (int)((s.batch + kTileB - 1) / kTileB);
     a.n_jt = s.out_tiles();
     const int tiles = a.n_btiles * a.n_jt;
-    int split = 1;
-    while (tiles * split < 256 && a.K / (split * 2) >= 4) split *= 2;
+    const int split = pair_split_count(tiles, a.K, 0);
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     const size_t lds = (((size_t)2 * s.nodes() * kRowBytesH + 15) & ~(size_t)15) + LMKAN_MAX_GRID * sizeof(float);

@@ -76,7 +76,7 @@ def test_small_shapes_accumulate(oracle, shape):
 
 
 @pytest.mark.parametrize("storage", ["f32", "f16", "bf16"])
-@pytest.mark.parametrize("shape", [(2600, 512, 193, 16), (5000, 256, 200, 22), (5000, 256, 203, 28),
+@pytest.mark.parametrize("shape", [(2600, 512, 193, 16), (3000, 300, 300, 16), (5000, 256, 200, 22), (5000, 256, 203, 28),
                                    (5000, 256, 200, 40)])
 def test_streamed_tables_match_the_oracle(oracle, shape, storage):
     _check(oracle, shape, storage, 73)

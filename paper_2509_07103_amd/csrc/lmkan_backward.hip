@@ -13,8 +13,8 @@
 // (samples x outputs), and runs on the matrix cores: one 4x4x1 float32 MFMA (16 blocks)
 // multiplies the four products of each group's sample with one gy value per lane, the
 // block-broadcast control handing every block of a group the products of that group's sample.
-// The 16 partial sums (4 corners x 4 outputs) live in the MFMA accumulators.  When the cell
-// ends they are combined across the groups and added into a
+// The 16 partial sums (4 corners x 4 outputs) live in the MFMA accumulators.  When the walk
+// leaves a column of nodes its sums are combined across the groups and added into a
 // two-row window of the table kept in LDS; a table row is written to global memory exactly
 // once, when the walk has passed it.  Rows no sample touches are written as exact zeros, so
 // no separate zero fill is needed.
@@ -35,8 +35,8 @@ static_assert(kUnroll % kDepth == 0, "the gy ring must divide the unrolled trip"
 // Counting sort of the samples of every pair by cell, one launch: a workgroup takes the samples of one
 // (pair, block).  records_in: [3][K][B] (node, u, v) from the preamble pass.  Per pair k, with
 // S = stream_stride and C = stream_block_entries, block b owns the entries [b C, (b + 1) C):
-//   rec [K][S]           (u, v, 1, index) of a sample, 16 bytes; padding entries are
-//                        (0, 0, 0, index of a sample of the same cell)
+//   rec [K][S]           (u, v, 1 or -1 for an even or odd i2, index) of a sample, 16 bytes;
+//                        padding entries are (0, 0, 0, index of a sample of the same cell)
 //   chunk_cell [K][S/4]  i1 << 8 | i2 of the cell each chunk belongs to, non-decreasing
 //                        inside a block
 //   block_chunks [K][blocks]  chunks of the block to process, a multiple of kUnroll; one trip of
@@ -54,6 +54,8 @@ static_assert(kUnroll % kDepth == 0, "the gy ring must divide the unrolled trip"
 constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortPer = 12;  // samples of a thread, at most
 constexpr int kSortStage = 4096;  // stream positions that go through LDS at a time
+constexpr int kOddCell = 1 << 30;  // a flag beside a sample's index: its cell has an odd i2
+static_assert(kMaxSortedBatch < kOddCell, "sample indices leave the bit to the flag");
 static_assert(kBlockSamples + kBlockSamples / 2 <= kSortThreads * kSortPer, "a block must fit a workgroup");
 
 __host__ __device__ inline size_t sort_lds_bytes(int G)
@@ -89,6 +91,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
 
     // all loads of the thread first: the pass is bound by the bytes in flight
     int cell[kSortPer], rank[kSortPer];
+    unsigned odd = 0;  // bit j: sample j's cell has an odd i2
     float u[kSortPer], v[kSortPer];
 #pragma unroll
     for (int j = 0; j < kSortPer; ++j) {
@@ -106,8 +109,10 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
 #pragma unroll
     for (int j = 0; j < kSortPer; ++j) {
         if (cell[j] >= 0) {
-            const int c = cell[j] - (int)(((unsigned)cell[j] * inv_w) >> 20);  // i1 (G + 1) + i2 -> i1 G + i2
+            const int i1 = (int)(((unsigned)cell[j] * inv_w) >> 20);
+            const int c = cell[j] - i1;  // i1 (G + 1) + i2 -> i1 G + i2
             const int shift = (c & 1) * 16;
+            odd |= ((cell[j] ^ (i1 & (int)W)) & 1u) << j;  // i2 = node - i1 W
             cell[j] = c;
             rank[j] = (atomicAdd(&s_count[(wave * even + c) >> 1], 1 << shift) >> shift) & 0xffff;
         }
@@ -162,6 +167,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
     int *s_n = reinterpret_cast<int *>(s_v + kSortStage);
     int last_sample = 0;  // a sample of the block's last cell, for the padding behind it
     for (int base = 0; base < fill_end; base += kSortStage) {
+        // (the flagged indices must not be formed ahead of the loop: 64 registers let two workgroups share a CU)
+        asm volatile("" : "+v"(odd));
         for (int p = tid; p < kSortStage; p += kSortThreads) s_n[p] = -1;
         __syncthreads();
 #pragma unroll
@@ -170,7 +177,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
             if (cell[j] >= 0 && p >= 0 && p < kSortStage) {
                 s_u[p] = u[j];
                 s_v[p] = v[j];
-                s_n[p] = (int32_t)n0 + i0 + 64 * j;
+                s_n[p] = ((int32_t)n0 + i0 + 64 * j) | ((odd >> j & 1u) != 0 ? kOddCell : 0);
             }
         }
         __syncthreads();
@@ -178,8 +185,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
         for (int p = tid; p < kSortStage && base + p < fill_end; p += kSortThreads) {
             // (a chunk's first entry is always a sample, unless the chunk lies past the real ones)
             const int n = s_n[p], first = s_n[p & ~(kChunk - 1)];
-            f4v e = {0.f, 0.f, 0.f, __int_as_float(first >= 0 ? first : last_sample)};
-            if (n >= 0) e = f4v{s_u[p], s_v[p], 1.0f, __int_as_float(n)};
+            f4v e = {0.f, 0.f, 0.f, __int_as_float((first >= 0 ? first : last_sample) & ~kOddCell)};
+            if (n >= 0) e = f4v{s_u[p], s_v[p], (n & kOddCell) != 0 ? -1.0f : 1.0f, __int_as_float(n & ~kOddCell)};
             out[base + p] = e;
         }
         __syncthreads();
@@ -317,27 +324,12 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
 
     for (int i = lane; i < 2 * W * kTile; i += 64) win[i] = 0.0f;
 
-    f4v acc[4];  // [output i of the lane][corner q]
+    f4v acc[4];  // [output i of the lane][2 (column parity) + row], see lmkan_sorted.h
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] = f4v{0.f, 0.f, 0.f, 0.f};
     int cur_cell = -1;  // (i1 << 8 | i2) of the cell the accumulators belong to
     int rows_done = 0;  // table rows [0, rows_done) have been written out
 
-    // add the sums of the finished cell into the two-row window: group 0 holds corner
-    // (i1, i2), group 1 (i1 + 1, i2), group 2 (i1, i2 + 1), group 3 (i1 + 1, i2 + 1)
-    auto flush = [&]() {
-        const int i1 = cur_cell >> 8, i2 = cur_cell & 255;
-        float f[4];
-        combine_groups(acc, f);
-        const int row = (i1 + (g & 1)) & 1, b = i2 + (g >> 1);
-        f4v *p = reinterpret_cast<f4v *>(win + (row * W + b) * kTile) + l16;
-        f4v v = *p;
-        v.x += f[0];
-        v.y += f[1];
-        v.z += f[2];
-        v.w += f[3];
-        *p = v;
-    };
     // table rows below `upto` can receive nothing more: write them and recycle their buffers.
     // Owned columns: four table entries per store instruction, group g takes b = 4 i + g.
     // Shared gradient: one atomic instruction per entry, lanes on consecutive floats (256
@@ -429,13 +421,11 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
                 }
                 landed(gq[P % kDepth], std::integral_constant<int, kDepth - 1 + kDepth / kPerW>{});
                 if (cell_cur != cur_cell) {
-                    if (cur_cell >= 0) flush();
+                    if (cur_cell >= 0) leave_cell(acc, win, W, cur_cell, cell_cur, lane);
                     retire_rows(cell_cur >> 8);
                     cur_cell = cell_cur;
-                    chunk_fma<P % kPerW, true>(acc, wq[P / kPerW], gq[P % kDepth]);
-                } else {
-                    chunk_fma<P % kPerW, false>(acc, wq[P / kPerW], gq[P % kDepth]);
                 }
+                chunk_fma<P % kPerW>(acc, wq[P / kPerW], gq[P % kDepth]);
                 load_gy(gq[P % kDepth], std::integral_constant<int, (P + kDepth) % kUnroll>{},
                         P + kDepth < kUnroll ? n_now : n_nxt);
                 if constexpr (P % kPerW == kPerW - 1) load_e(eq[P / kPerW], c + kUnroll + (P / kPerW) * kPerW);
@@ -447,7 +437,7 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         // nothing may still be on its way to a register once the compiler is free to reuse it
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    if (cur_cell >= 0) flush();
+    if (cur_cell >= 0) leave_cell(acc, win, W, cur_cell, -1, lane);
     retire_rows(split ? min(W, (cur_cell >> 8) + 2) : W);
 }
 

@@ -194,7 +194,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     if constexpr (DO_GP)
         for (int i = lane; i < 2 * W * kTile; i += 64) win[i] = 0.0f;
 
-    f4v acc[4];  // coefficient gradient of the current cell: [output i of the lane][corner]
+    f4v acc[4];  // coefficient gradient: [output i of the lane][2 (column parity) + row], see lmkan_sorted.h
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] = f4v{0.f, 0.f, 0.f, 0.f};
     int cur_cell = -1;  // (i1 << 8 | i2) of the cell being accumulated
@@ -202,19 +202,6 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     int cur_slot = 0;    // LDS slot of the current cell's coefficient rows
     unsigned slots = 0;  // slot of each chunk of the current group, one byte each
 
-    auto flush = [&]() {
-        const int i1 = cur_cell >> 8, i2 = cur_cell & 255;
-        float f[4];
-        combine_groups(acc, f);
-        const int row = (i1 + (g & 1)) & 1, b = i2 + (g >> 1);
-        f4v *p = reinterpret_cast<f4v *>(win + (row * W + b) * kTile) + l16;
-        f4v v = *p;
-        v.x += f[0];
-        v.y += f[1];
-        v.z += f[2];
-        v.w += f[3];
-        *p = v;
-    };
     const int out_col = jt * kTile + lane;
     float *out_lane = DO_GP ? a.gP + (int64_t)k * a.gmap.s_pair + out_col : nullptr;
     auto retire_rows = [&](int upto) {
@@ -335,7 +322,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
             const bool changed = cell_cur != cur_cell;
             if (changed) {
                 if constexpr (DO_GP) {
-                    if (cur_cell >= 0) flush();
+                    if (cur_cell >= 0) leave_cell(acc, win, W, cur_cell, cell_cur, lane);
                     retire_rows(cell_cur >> 8);
                 }
                 cur_cell = cell_cur;
@@ -347,12 +334,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
                 constexpr unsigned kept = SUB == 0 ? 0u : (1u << (8 * SUB)) - 1u;
                 slots = (slots & kept) | (((unsigned)cur_slot * 0x01010101u) & ~kept);
             }
-            if constexpr (DO_GP) {
-                if (changed)
-                    chunk_fma<SUB, true>(acc, prod_now[R], gq[P % kDepth]);
-                else
-                    chunk_fma<SUB, false>(acc, prod_now[R], gq[P % kDepth]);
-            }
+            if constexpr (DO_GP) chunk_fma<SUB>(acc, prod_now[R], gq[P % kDepth]);
             *reinterpret_cast<f4v *>(lds + SUB * 1024 + wr_off) = gq[P % kDepth];
             // refill the ring slots just consumed: gy of chunk c + P + kDepth, rows of the cell that
             // chunk c + P + kCellDepth starts
@@ -418,7 +400,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     part[(int64_t)(nch - kUnroll) * kChunk] = res;
     asm volatile("" ::"v"(touched));
     if constexpr (DO_GP) {
-        if (cur_cell >= 0) flush();
+        if (cur_cell >= 0) leave_cell(acc, win, W, cur_cell, -1, lane);
         retire_rows(split ? min(W, (cur_cell >> 8) + 2) : W);
     }
 }

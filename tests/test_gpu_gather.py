@@ -131,3 +131,31 @@ def test_one_output_coefficient_gradient(oracle, shape, room):
     want = oracle.backward_coef(x.cpu().numpy(), gy.cpu().numpy(), G)
     assert np.abs(over.cpu().numpy() - want).max() <= TOL_F32 * np.abs(want).max()
     assert np.abs(added.cpu().numpy() - (want + 0.5)).max() <= 2e-5 * max(1.0, np.abs(want).max())
+
+
+@pytest.mark.parametrize("G", [15, 16, 40])     # odd and even rows of cells; both gradients from one walk at 40
+@pytest.mark.parametrize("pattern", ["cell", "row", "column", "ends", "gaps"])
+def test_walks_that_skip_cells(oracle, pattern, G):
+    """Coefficient gradients from the cell-sorted samples, where the walk steps from cell to cell, jumps
+    inside a row of cells, from row to row, or sees one cell only."""
+    dev = torch.device("cuda:0")
+    B, n_in, n_out = 3000, 300, 300
+    x, P, gy = _inputs(B, n_in, n_out, G, 77, dev)
+    a, b = x[:, 0::2], x[:, 1::2]
+    if pattern in ("cell", "column"):
+        b.fill_(0.3)
+    if pattern in ("cell", "row"):
+        a.fill_(-0.2)
+    if pattern == "ends":                       # the four corner cells of the grid
+        x.copy_(torch.where(x > 0, 9.0, -9.0))
+    if pattern == "gaps":                       # a few cells, some of them neighbours
+        x.copy_((x * 1.5).round() / 1.5)
+    _, gP = pkg.lmkan_backward(pkg.LayerDesc(n_in, n_out, G), x, P, gy)
+    torch.cuda.synchronize()
+    xh, gyh, gPh = x.cpu().numpy(), gy.cpu().numpy(), gP.cpu().numpy()
+    for k in range(0, n_in // 2, 10):
+        want = oracle.backward_coef_pair(xh, gyh, G, k)
+        # up to 3000 terms meet in a node and may cancel: the scale of a sum's rounding is that of its magnitudes
+        scale = np.abs(oracle.backward_coef_pair(xh, np.abs(gyh), G, k)).max()
+        assert np.abs(gPh[:, :, k, :] - want).max() <= TOL_F32 * scale
+        assert np.all(gPh[:, :, k, :][want == 0.0] == 0.0)

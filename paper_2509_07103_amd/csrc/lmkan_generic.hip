@@ -223,20 +223,53 @@ __global__ __launch_bounds__(kThreads) void locate_kernel(GridTab tab, const flo
     (void)K;
 }
 
-template <typename U>
+// dst[jt][k][node][64] = src[node][k][64 jt ...], zero past n_out.  A pure copy: bound by HBM.  A
+// workgroup takes kPackNodes nodes of a pair with all their outputs, so what it reads are whole rows of
+// src and what it writes are runs of kPackNodes tile rows; a thread moves 16 bytes at a time, kPackBatch
+// loads before the first store.  WIDE: rows of src start on 4 bytes, and so do both tensors (always so
+// for 4-byte types); otherwise the elements of a piece move one by one.
+// (One element per thread, the index of its source divided out in 64 bits: 130 us for 500 -> 333 at
+// G = 20, float32, 316 MB; 56 us now.)
+constexpr int kPackNodes = 16, kPackBatch = 4;
+
+template <typename U, bool WIDE>
 __global__ __launch_bounds__(kThreads) void pack_kernel(const U *__restrict__ src, U *__restrict__ dst,
-                                                       int K, int n_out, int nodes, int64_t total)
+                                                       int K, int n_out, int nodes, int tiles)
 {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; d < total; d += stride) {
-        const int jl = (int)(d % kTile);
-        int64_t r = d / kTile;
-        const int node = (int)(r % nodes);
-        r /= nodes;
-        const int k = (int)(r % K);
-        const int jt = (int)(r / K);
-        const int j = jt * kTile + jl;
-        dst[d] = j < n_out ? src[((int64_t)node * K + k) * n_out + j] : (U)0;
+    constexpr int E = 16 / (int)sizeof(U), kPieces = kTile / E;  // elements of a piece, pieces of a tile row
+    typedef U Piece __attribute__((ext_vector_type(E), aligned(WIDE ? 4 : sizeof(U))));
+    const int k = blockIdx.x, node0 = blockIdx.y * kPackNodes;
+    const int rows = tiles * kPackNodes;
+    for (int first = threadIdx.x; first < rows * kPieces; first += kThreads * kPackBatch) {
+        Piece v[kPackBatch];
+        U *to[kPackBatch];
+#pragma unroll
+        for (int i = 0; i < kPackBatch; ++i) {
+            const int item = first + i * kThreads;
+            const int col = item % kPieces * E, row = item / kPieces;
+            const int node = node0 + row % kPackNodes, jt = row / kPackNodes;
+            const int j = jt * kTile + col;
+            to[i] = nullptr;
+            if (row >= rows || node >= nodes) continue;
+            to[i] = dst + (((int64_t)jt * K + k) * nodes + node) * kTile + col;
+            const U *from = src + ((int64_t)node * K + k) * n_out + j;
+            if (WIDE && j + E <= n_out) {
+                v[i] = *reinterpret_cast<const Piece *>(from);
+            } else {
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[i][e] = j + e < n_out ? from[e] : (U)0;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kPackBatch; ++i) {
+            if (!to[i]) continue;
+            if constexpr (WIDE) {
+                *reinterpret_cast<Piece *>(to[i]) = v[i];
+            } else {
+#pragma unroll
+                for (int e = 0; e < E; ++e) to[i][e] = v[i][e];
+            }
+        }
     }
 }
 
@@ -358,16 +391,18 @@ void launch_locate(const LayerShape &s, const GridTab &tab, const float *x, int3
 
 void launch_pack(const LayerShape &s, const void *src, void *dst, hipStream_t stream)
 {
-    const int64_t total = (int64_t)s.out_tiles() * s.pairs() * s.nodes() * kTile;
-    const int blocks = blocks_for(total, kThreads, 1 << 20);
+    const dim3 grid((unsigned)s.pairs(), (unsigned)((s.nodes() + kPackNodes - 1) / kPackNodes));
+    const bool wide = s.dtype == LMKAN_F32 ||
+                      ((s.n_out & 1) == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 3) == 0);
     if (s.dtype == LMKAN_F32)
-        pack_kernel<uint32_t><<<blocks, kThreads, 0, stream>>>(static_cast<const uint32_t *>(src),
-                                                              static_cast<uint32_t *>(dst), s.pairs(),
-                                                              s.n_out, s.nodes(), total);
+        pack_kernel<uint32_t, true><<<grid, kThreads, 0, stream>>>(static_cast<const uint32_t *>(src), static_cast<uint32_t *>(dst),
+                                                                  s.pairs(), s.n_out, s.nodes(), s.out_tiles());
+    else if (wide)
+        pack_kernel<uint16_t, true><<<grid, kThreads, 0, stream>>>(static_cast<const uint16_t *>(src), static_cast<uint16_t *>(dst),
+                                                                  s.pairs(), s.n_out, s.nodes(), s.out_tiles());
     else
-        pack_kernel<uint16_t><<<blocks, kThreads, 0, stream>>>(static_cast<const uint16_t *>(src),
-                                                              static_cast<uint16_t *>(dst), s.pairs(),
-                                                              s.n_out, s.nodes(), total);
+        pack_kernel<uint16_t, false><<<grid, kThreads, 0, stream>>>(static_cast<const uint16_t *>(src), static_cast<uint16_t *>(dst),
+                                                                   s.pairs(), s.n_out, s.nodes(), s.out_tiles());
 }
 
 void launch_fill_zero(float *p, size_t n, hipStream_t stream)

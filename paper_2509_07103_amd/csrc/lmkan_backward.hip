@@ -15,8 +15,8 @@
 // block-broadcast control handing every block of a group the products of that group's sample.
 // The 16 partial sums (4 corners x 4 outputs) live in the MFMA accumulators.  When the walk
 // leaves a column of nodes its sums are combined across the groups and added into a
-// two-row window of the table kept in LDS; a table row is written to global memory exactly
-// once, when the walk has passed it.  Rows no sample touches are written as exact zeros, so
+// ring of nodes kept in LDS; a node is written to global memory exactly
+// once, when the walk has passed it.  Nodes no sample touches are written as exact zeros, so
 // no separate zero fill is needed.
 #include "lmkan_kernels.h"
 #include "lmkan_sorted.h"
@@ -230,7 +230,7 @@ struct CoefGradArgs {
 template <bool kOffset32>
 __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a)
 {
-    extern __shared__ __align__(16) float win[];  // [2][G+1][64]: table rows r and r+1 of this wave's columns
+    extern __shared__ __align__(16) float win[];  // the NodeRing of this wave's columns
     const int lane = threadIdx.x;
     const int g = lane >> 4, l16 = lane & 15;
     const int G = a.G, W = G + 1;
@@ -266,7 +266,6 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
     }
     if (split && nch == 0) return;
     ScalarIntPtr cc = (ScalarIntPtr)(a.chunk_cell + (int64_t)k * (a.S / kChunk) + c_begin);
-    float *out = a.gP + (int64_t)k * a.gmap.s_pair + col;
 
     // entries: lane (g, 4 j + q) fetches the entry of group g's sample of chunk c + j and will
     // form its product q, so one load brings in four chunks (256 contiguous bytes); sample
@@ -322,51 +321,15 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         }
     };
 
-    for (int i = lane; i < 2 * W * kTile; i += 64) win[i] = 0.0f;
+    const NodeRing ring(win, W);
+    for (int i = lane; i < ring.R * kTile; i += 64) win[i] = 0.0f;
+    const GradOut out{a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0, split};
 
     f4v acc[4];  // [output i of the lane][2 (column parity) + row], see lmkan_sorted.h
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] = f4v{0.f, 0.f, 0.f, 0.f};
     int cur_cell = -1;  // (i1 << 8 | i2) of the cell the accumulators belong to
-    int rows_done = 0;  // table rows [0, rows_done) have been written out
-
-    // table rows below `upto` can receive nothing more: write them and recycle their buffers.
-    // Owned columns: four table entries per store instruction, group g takes b = 4 i + g.
-    // Shared gradient: one atomic instruction per entry, lanes on consecutive floats (256
-    // contiguous bytes), entries this wave never touched left alone.
-    const int out_col = jt * kTile + lane;
-    float *out_lane = a.gP + (int64_t)k * a.gmap.s_pair + out_col;
-    auto retire_rows = [&](int upto) {
-        for (; rows_done < upto; ++rows_done) {
-            if (split) {
-                float *row = win + (rows_done & 1) * W * kTile + lane;
-                for (int b = 0; b < W; ++b) {
-                    const float v = row[b * kTile];
-                    row[b * kTile] = 0.f;
-                    if (v != 0.f && out_col < a.n_out)
-                        unsafeAtomicAdd(out_lane + (int64_t)(rows_done * W + b) * a.gmap.s_node, v);
-                }
-            } else {
-                f4v *row = reinterpret_cast<f4v *>(win + (rows_done & 1) * W * kTile) + l16;
-                for (int b = g; b < W; b += 4) {
-                    if (col_ok) {
-                        float *dst = out + (int64_t)(rows_done * W + b) * a.gmap.s_node;
-                        const f4v v = row[b * (kTile / 4)];
-                        if ((a.n_out & 3) == 0) {
-                            f4v *d4 = reinterpret_cast<f4v *>(dst);
-                            *d4 = a.accumulate ? *d4 + v : v;
-                        } else {
-                            // rows of the gradient do not start on 16 bytes and the last one is short
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (col + e < a.n_out) dst[e] = a.accumulate ? dst[e] + v[e] : v[e];
-                        }
-                    }
-                    row[b * (kTile / 4)] = f4v{0.f, 0.f, 0.f, 0.f};
-                }
-            }
-        }
-    };
+    int done = 0;       // nodes below have been written
 
     if (nch > 0) {
         // Software pipeline, all through in-order vector loads: at step P of a trip the chunk
@@ -399,7 +362,7 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         int cells_now[kUnroll], cells_nxt[kUnroll];
 #pragma unroll
         for (int p = 0; p < kUnroll; ++p) cells_now[p] = cc[p];
-        if (split) rows_done = cells_now[0] >> 8;  // rows before the run's first cell are not this wave's
+        if (split) done = (cells_now[0] >> 8) * W + (cells_now[0] & 255);  // nodes before the run's first cell are not this wave's
         for (int c = 0; c < nch; c += kUnroll) {
 #pragma unroll
             for (int p = 0; p < kUnroll; ++p) cells_nxt[p] = cc[c + kUnroll + p];
@@ -421,8 +384,8 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
                 }
                 landed(gq[P % kDepth], std::integral_constant<int, kDepth - 1 + kDepth / kPerW>{});
                 if (cell_cur != cur_cell) {
-                    if (cur_cell >= 0) leave_cell(acc, win, W, cur_cell, cell_cur, lane);
-                    retire_rows(cell_cur >> 8);
+                    if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, cell_cur, lane);
+                    retire_before(ring, out, done, cell_cur, lane);
                     cur_cell = cell_cur;
                 }
                 chunk_fma<P % kPerW>(acc, wq[P / kPerW], gq[P % kDepth]);
@@ -437,8 +400,8 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         // nothing may still be on its way to a register once the compiler is free to reuse it
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    if (cur_cell >= 0) leave_cell(acc, win, W, cur_cell, -1, lane);
-    retire_rows(split ? min(W, (cur_cell >> 8) + 2) : W);
+    if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, -1, lane);
+    retire_nodes(ring, out, done, split ? ((cur_cell >> 8) + 1) * W + (cur_cell & 255) + 2 : W * W, lane);
 }
 
 }  // namespace
@@ -512,7 +475,7 @@ void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, co
     a.K = s.pairs();
     a.G = s.G;
     a.accumulate = accumulate ? 1 : 0;
-    const unsigned lds = (unsigned)(2 * (s.G + 1) * kTile * sizeof(float));
+    const unsigned lds = node_ring_bytes(s.G);
     const int n_sub = stream_run_split(s);
     a.n_blocks = st.n_blocks;
     a.n_sub = n_sub;

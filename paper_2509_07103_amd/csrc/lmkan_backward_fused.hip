@@ -100,7 +100,7 @@ __device__ __forceinline__ f4v widen_coef4(const typename CoefRow<CT>::raw &v)
 template <typename CT, bool DO_GP, bool kOffset32, bool RAGGED>
 __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
 {
-    // [gy rows of the four chunks of a group][coefficient rows of up to kCellSlots cells][gP window: 2 table rows]
+    // [gy rows of the four chunks of a group][coefficient rows of up to kCellSlots cells][NodeRing of gP]
     extern __shared__ __align__(16) float smem[];
     char *lds = reinterpret_cast<char *>(smem);
     float *win = smem + kFusedLdsFixed / 4;
@@ -190,51 +190,18 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
         gy_rd[t] = lds + q * 1024 + rd_off[t];
     }
 
-    float *out = DO_GP ? a.gP + (int64_t)k * a.gmap.s_pair + col : nullptr;
+    const NodeRing ring(win, W);
+    const GradOut out{DO_GP ? a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile : nullptr, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0, split};
     if constexpr (DO_GP)
-        for (int i = lane; i < 2 * W * kTile; i += 64) win[i] = 0.0f;
+        for (int i = lane; i < ring.R * kTile; i += 64) win[i] = 0.0f;
 
     f4v acc[4];  // coefficient gradient: [output i of the lane][2 (column parity) + row], see lmkan_sorted.h
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] = f4v{0.f, 0.f, 0.f, 0.f};
     int cur_cell = -1;  // (i1 << 8 | i2) of the cell being accumulated
-    int rows_done = 0;  // gP table rows [0, rows_done) have been written out
+    int done = 0;       // nodes of gP below have been written
     int cur_slot = 0;    // LDS slot of the current cell's coefficient rows
     unsigned slots = 0;  // slot of each chunk of the current group, one byte each
-
-    const int out_col = jt * kTile + lane;
-    float *out_lane = DO_GP ? a.gP + (int64_t)k * a.gmap.s_pair + out_col : nullptr;
-    auto retire_rows = [&](int upto) {
-        for (; rows_done < upto; ++rows_done) {
-            if (split) {
-                float *row = win + (rows_done & 1) * W * kTile + lane;
-                for (int b = 0; b < W; ++b) {
-                    const float v = row[b * kTile];
-                    row[b * kTile] = 0.f;
-                    if (v != 0.f && out_col < a.n_out)
-                        unsafeAtomicAdd(out_lane + (int64_t)(rows_done * W + b) * a.gmap.s_node, v);
-                }
-            } else {
-                f4v *row = reinterpret_cast<f4v *>(win + (rows_done & 1) * W * kTile) + l16;
-                for (int b = g; b < W; b += 4) {
-                    if (col_ok) {
-                        float *dst = out + (int64_t)(rows_done * W + b) * a.gmap.s_node;
-                        const f4v v = row[b * (kTile / 4)];
-                        if ((a.n_out & 3) == 0) {
-                            f4v *d4 = reinterpret_cast<f4v *>(dst);
-                            *d4 = a.accumulate ? *d4 + v : v;
-                        } else {
-                            // rows of the gradient do not start on 16 bytes and the last one is short
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (col + e < a.n_out) dst[e] = a.accumulate ? dst[e] + v[e] : v[e];
-                        }
-                    }
-                    row[b * (kTile / 4)] = f4v{0.f, 0.f, 0.f, 0.f};
-                }
-            }
-        }
-    };
 
     // lane (q, og, j) keeps the result of sample j of chunk q of group og of a trip; one store per trip
     float2 *part = a.partial + ((int64_t)jt * a.K + k) * a.S + (int64_t)c_begin * kChunk + ((og * kGroup + q) * kChunk + j);
@@ -284,7 +251,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     int cells_now[kUnroll], cells_nxt[kUnroll];
 #pragma unroll
     for (int p = 0; p < kUnroll; ++p) cells_now[p] = cc[p];
-    if (DO_GP && split) rows_done = cells_now[0] >> 8;  // rows before the run's first cell are not this wave's
+    if (DO_GP && split) done = (cells_now[0] >> 8) * W + (cells_now[0] & 255);  // nodes before the run's first cell are not this wave's
 
     // prologue: entries of trip 0, gy of the first kDepth chunks, coefficient rows of the first kCellDepth
 #pragma unroll
@@ -322,8 +289,8 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
             const bool changed = cell_cur != cur_cell;
             if (changed) {
                 if constexpr (DO_GP) {
-                    if (cur_cell >= 0) leave_cell(acc, win, W, cur_cell, cell_cur, lane);
-                    retire_rows(cell_cur >> 8);
+                    if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, cell_cur, lane);
+                    retire_before(ring, out, done, cell_cur, lane);
                 }
                 cur_cell = cell_cur;
                 cur_slot = cur_slot + 1 == kCellSlots ? 0 : cur_slot + 1;
@@ -400,8 +367,8 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     part[(int64_t)(nch - kUnroll) * kChunk] = res;
     asm volatile("" ::"v"(touched));
     if constexpr (DO_GP) {
-        if (cur_cell >= 0) leave_cell(acc, win, W, cur_cell, -1, lane);
-        retire_rows(split ? min(W, (cur_cell >> 8) + 2) : W);
+        if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, -1, lane);
+        retire_nodes(ring, out, done, split ? ((cur_cell >> 8) + 1) * W + (cur_cell & 255) + 2 : W * W, lane);
     }
 }
 
@@ -523,7 +490,7 @@ void launch_backward_fused(const LayerShape &s, const GridTab &tab, const Sorted
     a.n_sub = n_sub;
     if (gcoef && (st.n_blocks > 1 || n_sub > 1) && !accumulate)
         launch_fill_zero(gcoef, (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out, stream);
-    const unsigned lds = (unsigned)(kFusedLdsFixed + (gcoef ? 2 * (s.G + 1) * kTile * sizeof(float) : 0));
+    const unsigned lds = (unsigned)(kFusedLdsFixed + (gcoef ? node_ring_bytes(s.G) : 0));
     const unsigned grid = (unsigned)((int64_t)s.pairs() * s.out_tiles() * st.n_blocks * n_sub);
     typedef void (*Kernel)(FusedArgs);
 #define LMKAN_FUSED_ROW(CT, GP)                                                                       \

@@ -100,7 +100,7 @@ void launch_backward_fused(const LayerShape &s, const GridTab &tab, const Sorted
 // The coefficient gradient's accumulators of a walk: acc[i][2 h + r] is, for output i of the lane and the
 // samples of the lane's group, the sum for node (i1 + r, b) with b = i2 or i2 + 1, whichever has the
 // parity h.  The next cell of a row of cells shares its column of nodes i2 + 1, so on a step along the
-// row only the column left behind is summed over the groups and added to the window (flush_column)
+// row only the column left behind is summed over the groups and added to the ring (flush_column)
 // while the other one goes on accumulating: half the lane swaps and LDS traffic of a cell's end, no
 // copies of live accumulators.  With four samples per cell the end of a cell is most of the walk: step of
 // 2048 -> 2048 (G = 32, 4096 rows, bfloat16) 12.0 -> 11.0 ms, of 256 -> 256 at G = 40 781 -> 734 us; with
@@ -121,12 +121,32 @@ __device__ __forceinline__ void chunk_fma(f4v (&acc)[4], float w, const f4v &g)
     acc[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(w, g.w, acc[3], 2, SUB, 0);
 }
 
-// Adds the sums of a column of nodes (the one with parity H) to the two-row window [2][W][64] of the
-// table, rows i1 and i1 + 1 in places i1 & 1 and (i1 + 1) & 1, and clears its accumulators.  Two rounds
-// of "swap halves of two registers, add": the first pairs row i1 with row i1 + 1 across the 32-lane
-// halves, the second pairs outputs 0, 1 with 2, 3 across odd and even 16-lane rows.
+// The nodes a walk has touched and not yet written: a ring in LDS, [R][64] floats, node id = i1 W + b in
+// slot id mod R.  At cell c = i1 W + i2 the nodes below c are final and the highest one with a sum is
+// c + W + 1; nodes are written four at a time, so up to three final ones wait: W + 5 slots.
+// The ring's size sets how many waves a CU holds on the fine grids: with two whole rows of the table
+// (2 W slots) 9 at G = 32 and 7 at G = 40, now 16 and 13: step of 2048 -> 2048
+// (G = 32, 4096 rows, bfloat16) 11.0 -> 10.2 ms, of 256 -> 256 at G = 40 734 -> 654 us.
+struct NodeRing {
+    float *win;
+    int W, R;
+    unsigned inv;  // id / R = id inv >> 20 for every node of a table and one row beyond (id R < 2^20)
+    __device__ __forceinline__ NodeRing(float *window, int w)
+        : win(window), W(w), R(w + 5), inv(((1u << 20) + (unsigned)w + 4u) / ((unsigned)w + 5u))
+    {
+    }
+    __device__ __forceinline__ int slot(int id) const { return id - R * (int)(((unsigned)id * inv) >> 20); }
+};
+static_assert((LMKAN_MAX_GRID + 2) * (LMKAN_MAX_GRID + 1) * (LMKAN_MAX_GRID + 6) < (1 << 20), "NodeRing::slot");
+
+inline unsigned node_ring_bytes(int G) { return (unsigned)((G + 1 + 5) * LMKAN_PACK_TILE * sizeof(float)); }
+
+// Adds the sums of a column of nodes (the one with parity H; `id` is its node in row i1) to the ring and
+// clears its accumulators.  Two rounds of "swap halves of two registers, add": the first pairs row i1
+// with row i1 + 1 across the 32-lane halves, the second pairs outputs 0, 1 with 2, 3 across odd and even
+// 16-lane rows.
 template <int H>
-__device__ __forceinline__ void flush_column(f4v (&acc)[4], float *win, int W, int i1, int b, int lane)
+__device__ __forceinline__ void flush_column(f4v (&acc)[4], const NodeRing &ring, int id, int lane)
 {
     float z[4];
 #pragma unroll
@@ -145,8 +165,8 @@ __device__ __forceinline__ void flush_column(f4v (&acc)[4], float *win, int W, i
         f[i] = __uint_as_float(s.x) + __uint_as_float(s.y);  // even rows: output i; odd rows: output i + 2
     }
     typedef float f2v __attribute__((ext_vector_type(2)));
-    const int row = (i1 + (lane >> 5)) & 1;
-    f2v *p = reinterpret_cast<f2v *>(win + (row * W + b) * LMKAN_PACK_TILE) + ((lane & 15) * 2 + ((lane >> 4) & 1));
+    const int slot = lane < 32 ? ring.slot(id) : ring.slot(id + ring.W);
+    f2v *p = reinterpret_cast<f2v *>(ring.win + slot * LMKAN_PACK_TILE) + ((lane & 15) * 2 + ((lane >> 4) & 1));
     f2v v = *p;
     v.x += f[0];
     v.y += f[1];
@@ -154,12 +174,68 @@ __device__ __forceinline__ void flush_column(f4v (&acc)[4], float *win, int W, i
 }
 
 // The walk leaves cell `from` for cell `to` (i1 << 8 | i2; to < 0: it ends).
-__device__ __forceinline__ void leave_cell(f4v (&acc)[4], float *win, int W, int from, int to, int lane)
+__device__ __forceinline__ void leave_cell(f4v (&acc)[4], const NodeRing &ring, int from, int to, int lane)
 {
-    const int i1 = from >> 8, i2 = from & 255;
-    const bool odd = (i2 & 1) != 0, all = to != from + 1;
-    if (all || !odd) flush_column<0>(acc, win, W, i1, odd ? i2 + 1 : i2, lane);
-    if (all || odd) flush_column<1>(acc, win, W, i1, odd ? i2 : i2 + 1, lane);
+    const int c = (from >> 8) * ring.W + (from & 255);
+    const int odd = from & 1;
+    const bool all = to != from + 1;
+    if (all || odd == 0) flush_column<0>(acc, ring, c + odd, lane);
+    if (all || odd != 0) flush_column<1>(acc, ring, c + 1 - odd, lane);
+}
+
+// Where the nodes of a wave's 64 columns go.  Owned columns: four nodes per store instruction, group g
+// takes node 4 i + g.  Shared gradient (`split`): one atomic instruction per node, lanes on consecutive
+// floats (256 contiguous bytes), sums that are zero left out.
+struct GradOut {
+    float *base;  // first column of the tile, node 0
+    int64_t s_node;
+    int tile_col;  // first column of the tile
+    int n_out;
+    bool accumulate, split;
+};
+
+// Nodes [done, upto) can receive nothing more: they are written and their slots cleared.
+__device__ __forceinline__ void retire_nodes(const NodeRing &ring, const GradOut &o, int &done, int upto, int lane)
+{
+    const int g = lane >> 4, l16 = lane & 15;
+    for (; done < upto; done += 4) {
+        if (o.split) {
+            for (int id = done; id < min(done + 4, upto); ++id) {
+                float *p = ring.win + ring.slot(id) * LMKAN_PACK_TILE + lane;
+                const float v = *p;
+                *p = 0.f;
+                if (v != 0.f && o.tile_col + lane < o.n_out) unsafeAtomicAdd(o.base + id * o.s_node + lane, v);
+            }
+        } else {
+            int slot = ring.slot(done) + g;
+            if (slot >= ring.R) slot -= ring.R;
+            f4v *p = reinterpret_cast<f4v *>(ring.win + slot * LMKAN_PACK_TILE) + l16;
+            if (done + g < upto) {
+                const int col = o.tile_col + l16 * 4;
+                if (col < o.n_out) {
+                    float *dst = o.base + (done + g) * o.s_node + l16 * 4;
+                    const f4v v = *p;
+                    if ((o.n_out & 3) == 0) {
+                        f4v *d4 = reinterpret_cast<f4v *>(dst);
+                        *d4 = o.accumulate ? *d4 + v : v;
+                    } else {
+                        // rows of the gradient do not start on 16 bytes and the last one is short
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (col + e < o.n_out) dst[e] = o.accumulate ? dst[e] + v[e] : v[e];
+                    }
+                }
+                *p = f4v{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+    }
+}
+
+// Whole groups of four nodes that are final once the walk stands at cell `cell`.
+__device__ __forceinline__ void retire_before(const NodeRing &ring, const GradOut &o, int &done, int cell, int lane)
+{
+    const int c = (cell >> 8) * ring.W + (cell & 255);
+    retire_nodes(ring, o, done, done + ((c - done) & ~3), lane);
 }
 
 // product q = (lane & 3) of an entry, in the order of the accumulators: ((1-u)(1-v), u(1-v), (1-u)v, uv)[q]

@@ -493,11 +493,19 @@ void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, co
 // 256 CUs x 16 waves.  Several blocks: as many runs as it takes for the pairs of one (tile,
 // block) to occupy an XCD (512 waves), so that the XCD works on one block at a time.  A run
 // keeps at least four trips.
+// Uncut streams own their nodes and save the zero fill and the atomics.  A few waves per CU do nearly
+// the work of sixteen (the walk is bound by vector instructions), so that wins well below a full chip,
+// and the sooner the fewer samples there are per node.  Training steps, uncut against cut: 3072 streams
+// (768 -> 512) at G = 28 with 3 samples per cell 967 / 1336 us, at G = 16 with 32 1099 / 1223; 2048 at
+// G = 9 with 100 677 / 680; 1536 at G = 20 with 12 595 / 611; 1280 at G = 16 with 32
+// 555 / 544; 1024 at G = 28 with 4 499 / 507, at G = 20 with 12 467 / 460; 768 450 / 415.
 int stream_run_split(const LayerShape &s)
 {
     const int64_t streams = (int64_t)s.pairs() * s.out_tiles();
     int n_sub = 1;
     if (stream_blocks(s.batch) == 1) {
+        const int64_t cells = (int64_t)s.G * s.G;
+        if (streams >= (s.batch <= 4 * cells ? 1024 : s.batch <= 16 * cells ? 1536 : 2048)) return 1;
         const int64_t trips = stream_stride(s.batch, s.G) / (kChunk * kUnroll);
         while (streams * n_sub < 4096 && trips / (n_sub * 2) >= 4 && n_sub < 64) n_sub *= 2;
     } else {

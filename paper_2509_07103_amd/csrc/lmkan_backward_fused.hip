@@ -26,6 +26,7 @@
 // partial[tile][k][position in the stream]: consecutive lanes, consecutive addresses.
 // gx_combine_kernel adds the tiles in a fixed order, multiplies by 1/h and writes grad_x.
 // No atomics and no zero fill on this path: grad_x is the same in every run.
+#include <algorithm>
 #include <type_traits>
 
 #include "lmkan_kernels.h"
@@ -461,6 +462,33 @@ size_t fused_partial_bytes(const LayerShape &s)
     return ((size_t)s.out_tiles() * s.pairs() * S * sizeof(float2) + 255) & ~(size_t)255;
 }
 
+// Runs per (pair, tile, block).  Few waves fit a CU (registers: two per SIMD, three for 16-bit tables
+// without the coefficient gradient; LDS: seven per CU at G = 40) and each waits for its own loads, so the walk takes as
+// long as its rounds of resident waves: the count of runs with the fewest trips over all rounds, two
+// trips of start and end per run.  Runs that share nodes pay for the zero fill and the atomics, about three
+// times the gradient's bytes, 1 trip per 6 MB.  A run keeps at least four trips.
+// Powers of two up to 4096 waves before: 128 -> 128 at G = 40 on 8192 rows 222 us for the step (32 runs,
+// 2.3 rounds of waves), 207 with 14 (one round); 256 -> 256 654 -> 586 us; 200 -> 320 at G = 48 724 -> 664;
+// 512 -> 384 at G = 40 on 12000 rows 2048 -> 1905 (uncut).
+static int fused_run_split(const LayerShape &s, unsigned lds, bool want_gp)
+{
+    constexpr unsigned kLdsBytes = 160 * 1024, kLdsGranule = 1280;
+    const int blocks = stream_blocks(s.batch);
+    const int64_t units = (int64_t)s.pairs() * s.out_tiles() * blocks;
+    const int64_t trips = (blocks > 1 ? kBlockSamples : stream_stride(s.batch, s.G)) / (kChunk * kUnroll);
+    const int64_t by_lds = kLdsBytes / ((lds + kLdsGranule - 1) / kLdsGranule * kLdsGranule);
+    const int64_t resident = 256 * std::min<int64_t>(want_gp || s.dtype == LMKAN_F32 ? 8 : 12, by_lds);
+    const int64_t shared = want_gp ? (int64_t)s.nodes() * s.pairs() * s.n_out * 4 / 6000000 : 0;
+    int best = 1;
+    int64_t best_cost = 0;
+    for (int n = 1; n <= 64 && (n == 1 || trips / n >= 4); ++n) {
+        const int64_t rounds = (units * n + resident - 1) / resident;
+        const int64_t cost = rounds * ((trips + n - 1) / n + 2) + (n > 1 || blocks > 1 ? shared : 0);
+        if (n == 1 || cost < best_cost) best = n, best_cost = cost;
+    }
+    return best;
+}
+
 void launch_backward_fused(const LayerShape &s, const GridTab &tab, const SortedStream &st, const void *records,
                            const void *coef, const GyView &gy, float *gx, float *gcoef, bool accumulate,
                            void *partial, float *gx_transposed, hipStream_t stream)
@@ -485,12 +513,12 @@ void launch_backward_fused(const LayerShape &s, const GridTab &tab, const Sorted
     a.G = s.G;
     a.accumulate = accumulate ? 1 : 0;
     a.col_limit = s.layout == LMKAN_LAYOUT_PACKED ? s.out_tiles() * kTile : s.n_out;
-    const int n_sub = stream_run_split(s);
+    const unsigned lds = (unsigned)(kFusedLdsFixed + (gcoef ? node_ring_bytes(s.G) : 0));
+    const int n_sub = fused_run_split(s, lds, gcoef != nullptr);
     a.n_blocks = st.n_blocks;
     a.n_sub = n_sub;
     if (gcoef && (st.n_blocks > 1 || n_sub > 1) && !accumulate)
         launch_fill_zero(gcoef, (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out, stream);
-    const unsigned lds = (unsigned)(kFusedLdsFixed + (gcoef ? node_ring_bytes(s.G) : 0));
     const unsigned grid = (unsigned)((int64_t)s.pairs() * s.out_tiles() * st.n_blocks * n_sub);
     typedef void (*Kernel)(FusedArgs);
 #define LMKAN_FUSED_ROW(CT, GP)                                                                       \

@@ -67,7 +67,7 @@ struct SortedStream {
 SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted, hipStream_t stream);
 // whether the batch is short enough for the 32-bit stream positions and 16-bit grid coordinates
 bool sorted_batch_ok(const LayerShape &s);
-// waves per (pair, output tile, block) of the walking kernels
+// waves per (pair, output tile, block) of the coefficient gradient's walk
 int stream_run_split(const LayerShape &s);
 
 // gy as the walking kernels gather it: the 64 columns of output tile t of row n start at

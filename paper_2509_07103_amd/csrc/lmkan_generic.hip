@@ -226,18 +226,18 @@ __global__ __launch_bounds__(kThreads) void locate_kernel(GridTab tab, const flo
 // dst[jt][k][node][64] = src[node][k][64 jt ...], zero past n_out.  A pure copy: bound by HBM.  A
 // workgroup takes kPackNodes nodes of a pair with all their outputs, so what it reads are whole rows of
 // src and what it writes are runs of kPackNodes tile rows; a thread moves 16 bytes at a time, kPackBatch
-// loads before the first store.  WIDE: rows of src start on 4 bytes, and so do both tensors (always so
-// for 4-byte types); otherwise the elements of a piece move one by one.
+// loads before the first store (16-byte accesses of global memory need the alignment of an element only,
+// so rows of any length take them).
 // (One element per thread, the index of its source divided out in 64 bits: 130 us for 500 -> 333 at
 // G = 20, float32, 316 MB; 56 us now.)
 constexpr int kPackNodes = 16, kPackBatch = 4;
 
-template <typename U, bool WIDE>
+template <typename U>
 __global__ __launch_bounds__(kThreads) void pack_kernel(const U *__restrict__ src, U *__restrict__ dst,
                                                        int K, int n_out, int nodes, int tiles)
 {
     constexpr int E = 16 / (int)sizeof(U), kPieces = kTile / E;  // elements of a piece, pieces of a tile row
-    typedef U Piece __attribute__((ext_vector_type(E), aligned(WIDE ? 4 : sizeof(U))));
+    typedef U Piece __attribute__((ext_vector_type(E), aligned(sizeof(U))));
     const int k = blockIdx.x, node0 = blockIdx.y * kPackNodes;
     const int rows = tiles * kPackNodes;
     for (int first = threadIdx.x; first < rows * kPieces; first += kThreads * kPackBatch) {
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const U *__restrict__ sr
             if (row >= rows || node >= nodes) continue;
             to[i] = dst + (((int64_t)jt * K + k) * nodes + node) * kTile + col;
             const U *from = src + ((int64_t)node * K + k) * n_out + j;
-            if (WIDE && j + E <= n_out) {
+            if (j + E <= n_out) {
                 v[i] = *reinterpret_cast<const Piece *>(from);
             } else {
 #pragma unroll
@@ -262,13 +262,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const U *__restrict__ sr
         }
 #pragma unroll
         for (int i = 0; i < kPackBatch; ++i) {
-            if (!to[i]) continue;
-            if constexpr (WIDE) {
-                *reinterpret_cast<Piece *>(to[i]) = v[i];
-            } else {
-#pragma unroll
-                for (int e = 0; e < E; ++e) to[i][e] = v[i][e];
-            }
+            if (to[i]) *reinterpret_cast<Piece *>(to[i]) = v[i];
         }
     }
 }
@@ -392,17 +386,12 @@ void launch_locate(const LayerShape &s, const GridTab &tab, const float *x, int3
 void launch_pack(const LayerShape &s, const void *src, void *dst, hipStream_t stream)
 {
     const dim3 grid((unsigned)s.pairs(), (unsigned)((s.nodes() + kPackNodes - 1) / kPackNodes));
-    const bool wide = s.dtype == LMKAN_F32 ||
-                      ((s.n_out & 1) == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 3) == 0);
     if (s.dtype == LMKAN_F32)
-        pack_kernel<uint32_t, true><<<grid, kThreads, 0, stream>>>(static_cast<const uint32_t *>(src), static_cast<uint32_t *>(dst),
-                                                                  s.pairs(), s.n_out, s.nodes(), s.out_tiles());
-    else if (wide)
-        pack_kernel<uint16_t, true><<<grid, kThreads, 0, stream>>>(static_cast<const uint16_t *>(src), static_cast<uint16_t *>(dst),
-                                                                  s.pairs(), s.n_out, s.nodes(), s.out_tiles());
+        pack_kernel<uint32_t><<<grid, kThreads, 0, stream>>>(static_cast<const uint32_t *>(src), static_cast<uint32_t *>(dst),
+                                                            s.pairs(), s.n_out, s.nodes(), s.out_tiles());
     else
-        pack_kernel<uint16_t, false><<<grid, kThreads, 0, stream>>>(static_cast<const uint16_t *>(src), static_cast<uint16_t *>(dst),
-                                                                   s.pairs(), s.n_out, s.nodes(), s.out_tiles());
+        pack_kernel<uint16_t><<<grid, kThreads, 0, stream>>>(static_cast<const uint16_t *>(src), static_cast<uint16_t *>(dst),
+                                                            s.pairs(), s.n_out, s.nodes(), s.out_tiles());
 }
 
 void launch_fill_zero(float *p, size_t n, hipStream_t stream)

@@ -232,8 +232,8 @@ lmkan_status lmkan_forward_static(const lmkan_desc *desc, int64_t batch, const f
  * (samples of a cell stay in index order), so a grad_coef written by the
  * cell-sorted kernels repeats bit for bit when every (pair, 64-output tile) is
  * walked by one wave (batch <= 12288 rows and at least 4096 (pair, tile) streams,
- * e.g. 1024 -> 1024); shorter layers and longer batches cut the streams into
- * runs that meet through float32 atomics, and the generic kernels and the
+ * e.g. 1024 -> 1024); shorter layers may and longer batches do cut the streams
+ * into runs that meet through float32 atomics, and the generic kernels and the
  * kernels for very few outputs use atomics throughout: there the last bits can
  * differ.  grad_x repeats bit for bit on the
  * sorted walk (grids finer than 34 intervals) and in the kernels for very few

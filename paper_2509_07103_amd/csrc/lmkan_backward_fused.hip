@@ -475,6 +475,7 @@ static int fused_run_split(const LayerShape &s, unsigned lds, bool want_gp)
     constexpr unsigned kLdsBytes = 160 * 1024, kLdsGranule = 1280;
     const int blocks = stream_blocks(s.batch);
     const int64_t units = (int64_t)s.pairs() * s.out_tiles() * blocks;
+    if (blocks == 1 && units >= 4096) return 1;  // (such layers' gradients repeat bit for bit: whole streams)
     const int64_t trips = (blocks > 1 ? kBlockSamples : stream_stride(s.batch, s.G)) / (kChunk * kUnroll);
     const int64_t by_lds = kLdsBytes / ((lds + kLdsGranule - 1) / kLdsGranule * kLdsGranule);
     const int64_t resident = 256 * std::min<int64_t>(want_gp || s.dtype == LMKAN_F32 ? 8 : 12, by_lds);

@@ -61,6 +61,10 @@ def kernel_names(w, n_out, B, storage, packed):
         fit = ((160 * 1024 - 1024) // 4) // ((w.grid + 1) ** 2 | 1)
         if n_out == 1 and not getattr(w, "kh", 0) and (fit >= w.n_in // 2 or fit >= 64):
             fwd, gx, gp = "forward_head_kernel", "backward_input_head_kernel", "backward_coef_head_kernel"
+    elif B * (w.n_in // 2) * n_out <= 1 << 18:
+        # (the library's rule weighs sizes against each other; this file's workloads lie far to either side)
+        fwd, gx, gp = "forward_gather_kernel", "backward_input_gather_kernel", "backward_coef_gather_kernel"
+        both = "backward_gather_kernel"
     elif ok and w.grid <= 16:
         f16 = storage == "f16" and (packed or n_out % 8 == 0)
         fwd = "forward_slab_f16_kernel" if f16 else "forward_slab_kernel"

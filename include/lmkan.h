@@ -95,7 +95,8 @@ typedef enum {
  * and nothing has written to the first lmkan_workspace_bytes(desc, batch, 0) bytes since
  * (the forward pass's partial outputs lie behind the records and do not matter).  The library
  * cannot check the promise: with stale or foreign contents the records are garbage used as
- * table indices, which is as undefined as a wrong pointer. */
+ * table indices, which is as undefined as a wrong pointer.  Small layers and batches, whose forward
+ * kernels locate their inputs themselves and leave no records, ignore the flag. */
 #define LMKAN_FLAG_WORKSPACE_HAS_RECORDS 2
 
 /* Description of one layer (Alg. 1 "Require"). */

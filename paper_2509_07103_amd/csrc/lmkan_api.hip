@@ -22,6 +22,16 @@ size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
+// Shapes whose calls leave the preamble records in their workspace, every one of them: the forward pass reads
+// them, and a backward call writes them also where its own kernels do without (small gradients are gathered,
+// unaligned buffers go the generic way).  LMKAN_FLAG_WORKSPACE_HAS_RECORDS means nothing for other
+// shapes: the library cannot tell which call filled the workspace.
+bool records_kept(const LayerShape &s)
+{
+    if (forward_gather_shape_ok(s) || head_forward_shape_ok(s)) return false;
+    return small_out_shape_ok(s) || slab_forward_shape_ok(s);
+}
+
 // How a backward workspace is carved up; sizes depend on the shape and on which gradients are
 // wanted only (pointer alignment, which also steers the choice of kernels, is not known when the
 // caller asks for the size, so every path the shape admits is provided for).
@@ -397,9 +407,9 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     float *ws_scratch = reinterpret_cast<float *>(ws + w.scratch);
     char *ws_partial = ws + w.partial;
     TimedCall timed(grad_x_dev ? kTimeGradInput : kTimeGradCoef);
-    // (a forward call that gathers leaves no records behind: the promise is void then)
-    const bool have_records = (desc->flags & LMKAN_FLAG_WORKSPACE_HAS_RECORDS) && !forward_gather_shape_ok(s);
-    if (need_records && !have_records) launch_preamble_records(s, tab, x_dev, ws, hs, conv);
+    const bool kept = records_kept(s), room = workspace_dev && workspace_bytes >= w.total && aligned(workspace_dev, 256);
+    const bool have_records = kept && (desc->flags & LMKAN_FLAG_WORKSPACE_HAS_RECORDS);
+    if (!have_records && (need_records || (kept && room))) launch_preamble_records(s, tab, x_dev, ws, hs, conv);
     SortedStream stream_k{};
     GyView gy_k{};
     if (gp_sorted || gx_fused) stream_k = launch_sort(s, ws, ws_sorted, hs);
@@ -413,7 +423,6 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     }
     if (gp_head) {
         // (a call may come without a workspace: none is asked for)
-        const bool room = workspace_dev && workspace_bytes >= w.total && aligned(workspace_dev, 256);
         launch_backward_coef_head(s, tab, x_dev, grad_y_dev, grad_coef_dev, !overwrite,
                                   room ? reinterpret_cast<float *>(ws + w.head) : nullptr, hs);
     } else if (gp_gather) {

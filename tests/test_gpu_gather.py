@@ -159,3 +159,25 @@ def test_walks_that_skip_cells(oracle, pattern, G):
         scale = np.abs(oracle.backward_coef_pair(xh, np.abs(gyh), G, k)).max()
         assert np.abs(gPh[:, :, k, :] - want).max() <= TOL_F32 * scale
         assert np.all(gPh[:, :, k, :][want == 0.0] == 0.0)
+
+
+def test_a_gradient_that_gathers_leaves_the_records_it_promises(oracle):
+    """The coefficient gradient alone gathers, the forward pass of the same layer streams slabs: flagged
+    calls on the workspace of the first give what calls without the flag give."""
+    dev = torch.device("cuda:0")
+    B, n_in, n_out, G = 591, 264, 800, 15
+    x, P, gy = _inputs(B, n_in, n_out, G, 78, dev)
+    paper = pkg.LayerDesc(n_in, n_out, G, coef_dtype=pkg.LMKAN_BF16)
+    Ps = wl.store(P, "bf16").contiguous()
+    packed = pkg.lmkan_pack(paper, Ps)
+    plain, reuse = (pkg.LayerDesc(n_in, n_out, G, coef_dtype=pkg.LMKAN_BF16, coef_layout=pkg.LMKAN_LAYOUT_PACKED, flags=f)
+                    for f in (0, pkg.LMKAN_FLAG_WORKSPACE_HAS_RECORDS))
+    need = max(pkg.lmkan_workspace_bytes(plain, B, False), pkg.lmkan_workspace_bytes(plain, B, True))
+    ws = torch.zeros((need,), dtype=torch.uint8, device=dev)
+    pkg.lmkan_backward(plain, x, None, gy, need_grad_x=False, workspace=ws)
+    y = pkg.lmkan_forward(reuse, x, packed, workspace=ws)
+    gx, _ = pkg.lmkan_backward(reuse, x, packed, gy, need_grad_coef=False, workspace=ws)
+    torch.cuda.synchronize()
+    xh, gyh, code = x.cpu().numpy(), gy.cpu().numpy(), ORACLE_DTYPE["bf16"]
+    assert output_rel_err(y.cpu().numpy(), oracle.forward(xh, bits(Ps), G, dtype=code, threads=8)) <= TOL_F32
+    assert rowwise_rel_err(gx.cpu().numpy(), oracle.backward_input(xh, bits(Ps), gyh, G, dtype=code, threads=8)) <= TOL_F32

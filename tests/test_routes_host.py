@@ -1,0 +1,82 @@
+"""Which kernels a call takes, on the host: the library's own dispatch with its launches written down
+instead of run (routes.py)."""
+import random
+
+import pytest
+
+import paper_2509_07103_amd as pkg
+from routes import names, recorder, routes
+
+REUSE = pkg.LMKAN_FLAG_WORKSPACE_HAS_RECORDS
+
+# the kernels that read the preamble records
+READERS = {"sort_kernel", "forward_slab_kernel", "forward_slab_f16_kernel", "forward_slab_narrow_kernel",
+           "forward_lane32_kernel", "forward_lane32_f32_kernel", "forward_small_kernel",
+           "backward_input_slab_kernel", "backward_input_lane_kernel", "backward_input_slab_f16_kernel",
+           "backward_input_slab_narrow_kernel", "backward_input_lane32_kernel", "backward_input_lane32_f32_kernel",
+           "backward_input_small_kernel", "backward_coef_small_kernel"}     # (backward_fused_kernel: after the sort)
+WITHOUT = {"forward_generic_kernel", "forward_gather_kernel", "forward_head_kernel", "backward_generic_kernel",
+           "backward_gather_kernel", "backward_input_gather_kernel", "backward_coef_gather_kernel",
+           "backward_input_head_kernel", "backward_coef_head_kernel", "backward_coef_stream_kernel",
+           "backward_fused_kernel", "preamble_records_kernel"}
+AROUND = {"fill_zero_kernel", "gy_tiles_kernel", "transpose_kernel", "sum_partials_kernel", "head_combine_kernel",
+          "gx_combine_kernel", "conv_input_gradient_kernel", "conv_input_gradient_scatter_kernel"}
+
+
+@pytest.fixture(scope="module")
+def rec(tmp_path_factory):
+    return recorder(tmp_path_factory.mktemp("recorder"))
+
+
+def _layer(rng):
+    """A layer and batch anywhere in the range the rules choose from."""
+    def log(low, high):
+        return round(low * (high / low) ** rng.random())
+    return dict(n_in=2 * log(1, 1024), n_out=rng.choice([1, 4, 10, log(1, 1024), log(64, 2048)]),
+                grid=rng.choice([rng.randint(3, 16), rng.randint(17, 64)]), batch=log(1, 60000),
+                dtype=rng.randint(0, 2), layout=rng.choice([0, 1, 1]))
+
+
+def _calls(layer, rng):
+    """Every way a call may fill the workspace: the passes, as rows and as 1 x 1 windows, buffers that only
+    have the alignment of their elements."""
+    passes = [dict(fn="forward"), dict(fn="backward"), dict(fn="backward", grad_coef=0), dict(fn="backward", grad_x=0)]
+    element = 4 if layer["dtype"] == 0 else 2
+    for p in passes:
+        yield dict(layer, **p)
+        yield dict(layer, **p, conv=(layer["batch"], 1, 1, layer["n_in"], 1, 1, 1))
+        yield dict(layer, **p, **{b: 4 for b in ("x", "y", "gy", "gx", "gp") if rng.random() < 0.5},
+                   coef=element * rng.randint(0, 1))
+
+
+def _reads_unwritten_records(first, second):
+    return READERS & set(names(second)) and "preamble_records_kernel" not in names(second) + names(first)
+
+
+def test_a_promise_of_records_is_kept_or_ignored(rec):
+    """LMKAN_FLAG_WORKSPACE_HAS_RECORDS after any call that was given the workspace it asked for: either
+    that call wrote the records or the flagged call does."""
+    rng = random.Random(5)
+    # grad_x gathers while the coefficient gradient is sorted; the coefficient gradient gathers while the
+    # forward pass and grad_x stream slabs; one output, where the kernels for rows write no records
+    layers = [dict(n_in=314, n_out=13, grid=16, batch=50094, dtype=0, layout=1),
+              dict(n_in=264, n_out=800, grid=15, batch=591, dtype=2, layout=1),
+              dict(n_in=64, n_out=1, grid=16, batch=4000, dtype=0, layout=0),
+              dict(n_in=1024, n_out=1024, grid=16, batch=8192, dtype=1, layout=1)]
+    layers += [_layer(rng) for _ in range(250)]
+    calls, pairs = [], []
+    for layer in layers:
+        own = list(_calls(layer, rng))
+        pairs.append((len(calls), len(own)))
+        calls += own + [dict(c, flags=REUSE) for c in own]
+    got = routes(calls, rec)
+    seen = set()
+    for at, n in pairs:
+        for i in range(at, at + n):
+            status, first = got[i]
+            assert status == 0
+            seen |= set(names(first))
+            for j in range(at + n, at + 2 * n):
+                assert not _reads_unwritten_records(first, got[j][1]), (calls[i], calls[j], first, got[j][1])
+    assert seen <= READERS | WITHOUT | AROUND, seen - READERS - WITHOUT
+    assert READERS <= seen, READERS - seen      # the draw reaches all of them

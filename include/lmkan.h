@@ -201,13 +201,15 @@ lmkan_status lmkan_forward(const lmkan_desc *desc, int64_t batch, const float *x
 /*
  * lmkan_forward for callers that cannot bring a workspace because they cannot allocate
  * one: code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  Same arguments, same kernels and same result as lmkan_forward; the
+ * hipMalloc.  Same arguments, same kernels and, while lmkan_workspace_bytes(desc,
+ * batch, 0) fits the buffer, same result as lmkan_forward; the
  * preamble records and partial outputs live in a buffer of LMKAN_STATIC_SCRATCH_BYTES
  * that is part of the library itself (one copy on every GPU the library runs on, kept
  * until the process ends).  The call allocates nothing and frees nothing.
- *   - LMKAN_ERR_STATIC_LIMIT when lmkan_workspace_bytes(desc, batch, 0) exceeds the
- *     buffer (nothing is launched); LMKAN_ERR_HIP when the runtime cannot name the
- *     buffer's address.
+ *   - Where the records fit the buffer and all partial outputs do not, the pairs are
+ *     split over fewer workgroups than lmkan_forward's (the last bits can differ).
+ *   - LMKAN_ERR_STATIC_LIMIT when the records alone exceed the buffer (nothing is
+ *     launched); LMKAN_ERR_HIP when the runtime cannot name the buffer's address.
  *   - All calls on one GPU share the buffer: two of them must not overlap in time
  *     (different streams, or host threads, without ordering between them race).
  *   - The first call on a device looks the buffer's address up

@@ -32,6 +32,34 @@ bool records_kept(const LayerShape &s)
     return small_out_shape_ok(s) || slab_forward_shape_ok(s);
 }
 
+// Which kernels a forward call of this shape takes, and the scratch that they need.  `room` bounds the
+// scratch: as many pair splits as partial outputs fit behind the records (the records themselves are not
+// negotiable, `total` exceeds `room` when they do not fit).
+struct ForwardPlan {
+    bool gather, head, small, slab;
+    int split;       // pair splits of the slab kernels
+    size_t partial;  // offset of their partial outputs; the records lie before them
+    size_t total;    // 0: no workspace
+};
+ForwardPlan forward_plan(const LayerShape &s, size_t room = SIZE_MAX)
+{
+    ForwardPlan p = {};
+    p.gather = forward_gather_shape_ok(s);
+    p.head = head_forward_shape_ok(s);  // locates its inputs itself
+    p.small = !p.head && small_out_shape_ok(s);
+    p.slab = !p.head && !p.small && slab_forward_shape_ok(s);
+    p.split = 1;
+    if (p.small) p.total = records_bytes(s);
+    if (p.slab) {
+        p.partial = p.total = align256(records_bytes(s));
+        if (!p.gather) {
+            p.split = slab_forward_split(s, room > p.partial ? room - p.partial : 0);
+            p.total += slab_forward_partial_bytes(s, p.split);
+        }
+    }
+    return p;
+}
+
 // How a backward workspace is carved up; sizes depend on the shape and on which gradients are
 // wanted only (pointer alignment, which also steers the choice of kernels, is not known when the
 // caller asks for the size, so every path the shape admits is provided for).
@@ -220,11 +248,7 @@ size_t lmkan_workspace_bytes(const lmkan_desc *desc, int64_t batch, int32_t pass
     if (check_desc(desc) != LMKAN_OK || batch <= 0) return 0;
     const LayerShape s = shape_of(desc, batch);
     // forward: preamble records, then the partial outputs of a forward split over the pairs
-    if (pass == 0) {
-        if (head_forward_shape_ok(s)) return 0;  // locates its inputs itself
-        if (small_out_shape_ok(s)) return records_bytes(s);
-        return slab_forward_shape_ok(s) ? align256(records_bytes(s)) + slab_forward_partial_bytes(s) : 0;
-    }
+    if (pass == 0) return forward_plan(s).total;
     // backward (1: both gradients, 2: grad_x only, 3: grad_coef only): preamble records, their
     // cell-sorted copy, the per-tile partial sums of grad_x, and a transposed copy of grad_x for the
     // paths that finish with a transpose (small outputs, unaligned tables, convolutions)
@@ -276,10 +300,11 @@ ConvGeom rows_as_windows(const LayerShape &s)
     return g;
 }
 
-// conv == nullptr: rows x[batch][n_in]; otherwise the rows are the windows of an image
+// conv == nullptr: rows x[batch][n_in]; otherwise the rows are the windows of an image.  `room`: the plan
+// makes do with so much scratch (a caller's workspace holds what the unbounded plan asks for)
 lmkan_status forward_impl(const lmkan_desc *desc, int64_t batch, const float *x_dev, const void *coef_dev,
                           float *y_dev, void *workspace_dev, size_t workspace_bytes, void *stream,
-                          const ConvGeom *conv)
+                          const ConvGeom *conv, size_t room = SIZE_MAX)
 {
     const lmkan_status st = check_desc(desc);
     if (st != LMKAN_OK) return st;
@@ -293,18 +318,19 @@ lmkan_status forward_impl(const lmkan_desc *desc, int64_t batch, const float *x_
         plain = rows_as_windows(shape_of(desc, batch));
         conv = &plain;
     }
-    const size_t need = lmkan_workspace_bytes(desc, batch, 0);
+    const LayerShape s = shape_of(desc, batch);
+    const ForwardPlan plan = forward_plan(s, room);
+    const size_t need = plan.total;
     if (need > 0 && (!workspace_dev || workspace_bytes < need)) return LMKAN_ERR_WORKSPACE;
     if (need > 0 && !aligned(workspace_dev, 256)) return LMKAN_ERR_ALIGN;
     GridTab tab;
     build_grid(desc->grid, &tab);
-    const LayerShape s = shape_of(desc, batch);
     hipStream_t hs = static_cast<hipStream_t>(stream);
     drop_stale_error();
     TimedCall timed(kTimeForward);
     // Small shapes gather the rows they need and locate their inputs themselves: no records, also where
     // the alignment of this call's pointers sends it to the generic kernel (backward_impl knows).
-    if (forward_gather_shape_ok(s)) {
+    if (plan.gather) {
         if (gather_table_aligned(coef_dev))
             launch_forward_gather(s, tab, x_dev, coef_dev, y_dev, hs, conv);
         else
@@ -315,19 +341,17 @@ lmkan_status forward_impl(const lmkan_desc *desc, int64_t batch, const float *x_
     // alignment of this call's pointers sends it to the generic kernel: a later call may rely on them
     if (need > 0 && !(desc->flags & LMKAN_FLAG_WORKSPACE_HAS_RECORDS))
         launch_preamble_records(s, tab, x_dev, workspace_dev, hs, conv);
-    if (head_forward_shape_ok(s)) {
+    if (plan.head) {
         // one output: no records (need == 0); windows and 4-byte aligned rows go the generic way
         if (!conv)
             launch_forward_head(s, tab, x_dev, coef_dev, y_dev, hs);
         else
             launch_forward_generic(s, tab, x_dev, coef_dev, y_dev, hs, conv);
-    } else if (small_out_shape_ok(s)) {
+    } else if (plan.small) {
         launch_forward_small(s, coef_dev, y_dev, workspace_dev, hs);
     } else if (slab_forward_applicable(s, coef_dev, y_dev)) {
-        float *partials = slab_forward_partial_bytes(s) > 0
-                              ? reinterpret_cast<float *>(static_cast<char *>(workspace_dev) + align256(records_bytes(s)))
-                              : nullptr;
-        launch_forward_slab(s, coef_dev, y_dev, workspace_dev, partials, hs);
+        float *partials = reinterpret_cast<float *>(static_cast<char *>(workspace_dev) + plan.partial);
+        launch_forward_slab(s, coef_dev, y_dev, workspace_dev, partials, plan.split, hs);
     } else {
         launch_forward_generic(s, tab, x_dev, coef_dev, y_dev, hs, conv);
     }
@@ -530,7 +554,7 @@ lmkan_status lmkan_forward_static(const lmkan_desc *desc, int64_t batch, const f
     if (st != LMKAN_OK) return st;
     if (batch < 0 || batch > LMKAN_MAX_BATCH) return LMKAN_ERR_SHAPE;
     if (batch == 0) return LMKAN_OK;
-    const size_t need = lmkan_workspace_bytes(desc, batch, 0);
+    const size_t need = forward_plan(shape_of(desc, batch), LMKAN_STATIC_SCRATCH_BYTES).total;
     if (need > LMKAN_STATIC_SCRATCH_BYTES) return LMKAN_ERR_STATIC_LIMIT;
     if (!x_dev || !coef_dev || !y_dev) return LMKAN_ERR_NULL;
     void *ws = nullptr;
@@ -541,7 +565,7 @@ lmkan_status lmkan_forward_static(const lmkan_desc *desc, int64_t batch, const f
     // every byte of the workspace a forward kernel reads was written earlier in the same call
     // (records by the preamble pass, partial outputs by the split workgroups), so what an
     // earlier call left behind needs no clearing
-    return forward_impl(desc, batch, x_dev, coef_dev, y_dev, ws, need, stream, nullptr);
+    return forward_impl(desc, batch, x_dev, coef_dev, y_dev, ws, need, stream, nullptr, LMKAN_STATIC_SCRATCH_BYTES);
 }
 
 lmkan_status lmkan_time_next_kernel(void *start_event, void *stop_event)

@@ -69,14 +69,14 @@ struct KernelTiming {
     bool on;
 };
 
-// Pair splits of the slab forward (1: none) and the bytes of the split - 1 partial outputs
-// [batch][n_out] it then needs; `partials` = NULL makes the splits add into y atomically.
-int slab_forward_split(const LayerShape &s);
-size_t slab_forward_partial_bytes(const LayerShape &s);
+// Pair splits of the slab forward (1: none), no more than leave room for the split - 1 partial outputs
+// [batch][n_out] of a launch in `room` bytes, and what these take.
+int slab_forward_split(const LayerShape &s, size_t room);
+size_t slab_forward_partial_bytes(const LayerShape &s, int split);
 // y[i] += sum over p of part[p][i], i < elems (a multiple of 4)
 void launch_sum_partials(float *y, const float *part, int n_part, int64_t elems, hipStream_t stream);
 void launch_forward_slab(const LayerShape &s, const void *coef, float *y, const void *records, float *partials,
-                         hipStream_t stream);
+                         int split, hipStream_t stream);
 
 bool slab_backward_input_shape_ok(const LayerShape &s);
 bool slab_backward_input_takes_half_tiles(const LayerShape &s);  // 32-output tiles of a packed table kept as stored
@@ -92,7 +92,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
 // launchers above when slab_f16_native_ok().  gx_scratch is the zero-filled transposed scratch.
 bool slab_f16_native_ok(const LayerShape &s);
 void launch_forward_slab_f16(const LayerShape &s, const void *coef, float *y, const void *records, float *partials,
-                             hipStream_t stream);
+                             int split, hipStream_t stream);
 void launch_backward_input_slab_f16(const LayerShape &s, const GridTab &tab, const void *coef, const float *gy,
                                     int64_t gy_tile_stride, int64_t gy_row_stride, float *gx_scratch,
                                     const void *records, hipStream_t stream);

@@ -1894,19 +1894,22 @@ bool slab_forward_takes_half_tiles(const LayerShape &s)
 
 // Samples per forward workgroup: 1024 with 64-output tiles, 4096 with 16-output tiles, 2048 with
 // 32-output tiles.
-int slab_forward_split(const LayerShape &s)
+int slab_forward_split(const LayerShape &s, size_t room)
 {
     if (!slab_forward_shape_ok(s)) return 1;
     const bool wide = slab_wide_fits(s);
     const bool half = slab_forward_takes_half_tiles(s);
     const int64_t tile_b = wide ? 1024 : half ? 2048 : 4096;
     const int64_t n_jt = wide ? s.out_tiles() : half ? (s.n_out + 31) / 32 : (s.n_out + 15) / 16;
-    return pair_split_count(((s.batch + tile_b - 1) / tile_b) * n_jt, s.pairs(), partial_stride(s.batch * s.n_out) * 4);
+    const int64_t part = partial_stride(s.batch * s.n_out) * (int64_t)sizeof(float);
+    // (the parts together are rounded up to 256 bytes: `room` is a multiple of that or unbounded)
+    const size_t most = 1 + room / (size_t)part;
+    return pair_split_count(((s.batch + tile_b - 1) / tile_b) * n_jt, s.pairs(), part, most < (size_t)s.pairs() ? (int)most : s.pairs());
 }
 
-size_t slab_forward_partial_bytes(const LayerShape &s)
+size_t slab_forward_partial_bytes(const LayerShape &s, int split)
 {
-    const size_t parts = (size_t)slab_forward_split(s) - 1;
+    const size_t parts = (size_t)split - 1;
     return (parts * (size_t)partial_stride((int64_t)s.batch * s.n_out) * sizeof(float) + 255) & ~(size_t)255;
 }
 
@@ -1954,7 +1957,7 @@ bool slab_forward_applicable(const LayerShape &s, const void *coef, const float 
 }
 
 static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, float *y, const void *records,
-                                       float *partials, hipStream_t stream)
+                                       float *partials, int split, hipStream_t stream)
 {
     constexpr int WAVES = 8, SETS = 8;
     constexpr int kTileB = WAVES * SETS * 64;
@@ -1982,15 +1985,14 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
         a.n_btiles = (int)((s.batch + 2047) / 2048);
         a.n_jt = (s.n_out + kHalfTile - 1) / kHalfTile;
         const int tiles32 = a.n_btiles * a.n_jt;
-        const int split32 = slab_forward_split(s);   // what the workspace was sized for
-        a.n_split = split32;
-        a.pairs_per_split = (a.K + split32 - 1) / split32;
+        a.n_split = split;
+        a.pairs_per_split = (a.K + split - 1) / split;
         finish_split_setup(a, s, y, partials, stream);
         {
             KernelTiming timing(stream, kTimeForward);
-            k32<<<tiles32 * split32, 1024, ((size_t)2 * s.nodes() * half_tile_row_bytes(s) + 15) & ~(size_t)15, stream>>>(a);
+            k32<<<tiles32 * split, 1024, ((size_t)2 * s.nodes() * half_tile_row_bytes(s) + 15) & ~(size_t)15, stream>>>(a);
         }
-        if (a.y_part) launch_sum_partials(y, a.y_part, split32 - 1, (int64_t)s.batch * s.n_out, stream);
+        if (a.y_part) launch_sum_partials(y, a.y_part, split - 1, (int64_t)s.batch * s.n_out, stream);
         return;
     }
     // a float32 table needs no staging registers: 16 waves of 256 samples instead of 8 of 512
@@ -2022,7 +2024,6 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
     a.n_btiles = (int)((s.batch + kTileB - 1) / kTileB);
     a.n_jt = (s.n_out + kNarrowTile - 1) / kNarrowTile;
     const int tiles = a.n_btiles * a.n_jt;
-    const int split = slab_forward_split(s);   // what the workspace was sized for
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     finish_split_setup(a, s, y, partials, stream);
@@ -2034,14 +2035,14 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
 }
 
 void launch_forward_slab(const LayerShape &s, const void *coef, float *y, const void *records, float *partials,
-                         hipStream_t stream)
+                         int split, hipStream_t stream)
 {
     if (!slab_wide_fits(s)) {
-        launch_forward_slab_narrow(s, coef, y, records, partials, stream);
+        launch_forward_slab_narrow(s, coef, y, records, partials, split, stream);
         return;
     }
     if (slab_f16_native_ok(s)) {
-        launch_forward_slab_f16(s, coef, y, records, partials, stream);
+        launch_forward_slab_f16(s, coef, y, records, partials, split, stream);
         return;
     }
     // 1024 samples per workgroup either way: 16 waves x 64 samples for float32 tables, 8 x 128 for
@@ -2075,7 +2076,6 @@ void launch_forward_slab(const LayerShape &s, const void *coef, float *y, const 
     a.n_jt = s.out_tiles();
     // split the pairs over several workgroups when the tiles alone cannot fill 256 CUs
     const int tiles = a.n_btiles * a.n_jt;
-    const int split = slab_forward_split(s);   // what the workspace was sized for
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     finish_split_setup(a, s, y, partials, stream);
@@ -2248,7 +2248,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
         a.n_btiles = (int)((s.batch + 2047) / 2048);
         a.n_jt = (s.n_out + kHalfTile - 1) / kHalfTile;
         const int tiles32 = a.n_btiles * a.n_jt;
-        const int split32 = pair_split_count(tiles32, a.K, 0);
+        const int split32 = pair_split_count(tiles32, a.K, 0, a.K);
         a.n_split = split32;
         a.pairs_per_split = (a.K + split32 - 1) / split32;
         a.ld = scratch_row_stride(s.batch, kScratchPlain);
@@ -2300,7 +2300,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
     a.n_btiles = (int)((s.batch + tile_b - 1) / tile_b);
     a.n_jt = narrow ? (s.n_out + kNarrowTile - 1) / kNarrowTile : s.out_tiles();
     const int tiles = a.n_btiles * a.n_jt;
-    const int split = pair_split_count(tiles, a.K, 0);
+    const int split = pair_split_count(tiles, a.K, 0, a.K);
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     const bool lane_kernel = !narrow && s.dtype == LMKAN_F32;   // its lanes are consecutive samples

@@ -38,15 +38,15 @@ struct SlabArgs {
 // such steps as rounds of 256 workgroups times pairs per split.  Few tiles want more splits to have
 // work for every CU, and a count a little above a multiple of 256 wastes most of its last round: the
 // split is the one with the fewest steps, two more per round for the tile's own loads and stores, and
-// at least four pairs in each.  A forward split beyond the first writes a part of its own that is added
+// at least four pairs in each, `most` at most.  A forward split beyond the first writes a part of its own that is added
 // up later (part_bytes each, moved twice); the input gradient adds atomically and passes 0.
 // (500 -> 333 outputs at G = 20 on 5000 rows, 33 tiles of 250 pairs: 8 splits make 264 workgroups and
 // two rounds of 32 pairs, 7 make 231 in one round of 36: forward 254 -> 157 us, grad_x 261 -> 212 us.)
-inline int pair_split_count(int64_t tiles, int K, int64_t part_bytes)
+inline int pair_split_count(int64_t tiles, int K, int64_t part_bytes, int most)
 {
     int best = 1;
     double best_us = 0.0;
-    for (int split = 1; split == 1 || K / split >= 4; ++split) {
+    for (int split = 1; split == 1 || (K / split >= 4 && split <= most); ++split) {
         const int64_t rounds = (tiles * split + 255) / 256;
         const int pairs = (K + split - 1) / split;
         if ((split - 1) * pairs >= K) continue;   // the last split would have none

@@ -330,7 +330,7 @@ bool slab_f16_native_ok(const LayerShape &s)
 }
 
 void launch_forward_slab_f16(const LayerShape &s, const void *coef, float *y, const void *records, float *partials,
-                             hipStream_t stream)
+                             int split, hipStream_t stream)
 {
     constexpr int kTileB = kWaves * 64;
     allow_large_lds(reinterpret_cast<const void *>(forward_slab_f16_kernel), 160 * 1024);
@@ -352,7 +352,6 @@ void launch_forward_slab_f16(const LayerShape &s, const void *coef, float *y, co
     a.n_btiles = (int)((s.batch + kTileB - 1) / kTileB);
     a.n_jt = s.out_tiles();
     const int tiles = a.n_btiles * a.n_jt;
-    const int split = slab_forward_split(s);   // what the workspace was sized for
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     finish_split_setup(a, s, y, partials, stream);
@@ -394,7 +393,7 @@ void launch_backward_input_slab_f16(const LayerShape &s, const GridTab &tab, con
     a.n_btiles = (int)((s.batch + kTileB - 1) / kTileB);
     a.n_jt = s.out_tiles();
     const int tiles = a.n_btiles * a.n_jt;
-    const int split = pair_split_count(tiles, a.K, 0);
+    const int split = pair_split_count(tiles, a.K, 0, a.K);
     a.n_split = split;
     a.pairs_per_split = (a.K + split - 1) / split;
     const size_t lds = (((size_t)2 * s.nodes() * kRowBytesH + 15) & ~(size_t)15) + LMKAN_MAX_GRID * sizeof(float);

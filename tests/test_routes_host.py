@@ -80,3 +80,29 @@ def test_a_promise_of_records_is_kept_or_ignored(rec):
                 assert not _reads_unwritten_records(first, got[j][1]), (calls[i], calls[j], first, got[j][1])
     assert seen <= READERS | WITHOUT | AROUND, seen - READERS - WITHOUT
     assert READERS <= seen, READERS - seen      # the draw reaches all of them
+
+
+def test_the_static_scratch_takes_every_batch_whose_records_fit(rec):
+    """lmkan_forward_static splits the pairs as far as partial outputs fit its buffer; where all fit, it
+    launches what lmkan_forward launches."""
+    rng = random.Random(6)
+    limit, mib = pkg.LMKAN_STATIC_SCRATCH_BYTES, 1 << 20
+    # 1.3 MB of records; the quickest split has 59 MB of partial outputs
+    layers = [dict(n_in=48, n_out=3256, grid=30, batch=4698, dtype=2, layout=1),
+              dict(n_in=1024, n_out=1024, grid=16, batch=8192, dtype=0, layout=1)]     # 50 MB of records
+    layers += [_layer(rng) for _ in range(400)]
+    got = routes([dict(layer, fn=fn) for layer in layers for fn in ("workspace", "forward", "forward_static")
+                  for layer in [dict(layer, grad_x=0, grad_coef=0, pass_=0)]], rec)
+    fewer = 0
+    for i, layer in enumerate(layers):
+        (size, _), (status, free), (static_status, static) = got[3 * i:3 * i + 3]
+        assert status == 0
+        records = layer["n_in"] // 2 * layer["batch"] * 12 if size else 0
+        assert static_status == (7 if records > limit else 0), layer
+        if size <= limit:
+            assert static == free
+        elif static_status == 0:
+            assert names(static)[:2] == names(free)[:2]
+            assert static[1][1][0] < free[1][1][0]
+            fewer += 1
+    assert got[2][0] == 0 and got[5][0] == 7 and fewer >= 3, fewer

@@ -50,3 +50,20 @@ def test_static_scratch_forward_refuses_a_batch_beyond_its_buffer():
     with pytest.raises(pkg.LmkanError) as e:
         pkg.lmkan_forward_static(desc, x, P, y)
     assert e.value.status == 7
+
+
+@pytest.mark.parametrize("G", [16, 20])
+def test_static_scratch_forward_with_fewer_splits_than_the_forward_call(oracle, G):
+    """The records fit the buffer, the partial outputs of the quickest pair split do not: as many splits
+    as fit (the sums are grouped differently, so the result is compared with the oracle's)."""
+    dev = torch.device("cuda:0")
+    B, n_in, n_out = 5000, 200, 333
+    paper = pkg.LayerDesc(n_in, n_out, G)
+    desc = pkg.LayerDesc(n_in, n_out, G, coef_layout=pkg.LMKAN_LAYOUT_PACKED)
+    assert pkg.lmkan_workspace_bytes(desc, B, False) > pkg.LMKAN_STATIC_SCRATCH_BYTES > n_in // 2 * B * 12
+    x, P = _inputs(B, n_in, n_out, G, 910, dev)
+    y = torch.full((B, n_out), float("nan"), device=dev)
+    pkg.lmkan_forward_static(desc, x, pkg.lmkan_pack(paper, P), y)
+    torch.cuda.synchronize()
+    want = oracle.forward(x.cpu().numpy(), P.cpu().numpy(), G, threads=8)
+    assert rowwise_rel_err(y.cpu().numpy(), want) <= TOL_F32

@@ -7,6 +7,7 @@
 // status other than LMKAN_OK) makes a function return None without having launched anything that
 // counts, and binding.py goes its own way, which raises the error that describes it.
 #include <Python.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>
@@ -145,14 +146,21 @@ bool read_rows(PyObject *conv, const lmkan_desc &d, const at::Tensor *x, Rows &r
     return r.rows >= 0 && fits(x, at::kFloat, r.in);
 }
 
+// The Python exception of a C++ one, as torch's own functions raise it: running out of memory stays
+// torch.OutOfMemoryError, which callers catch to go on with a smaller batch
+PyObject *raise_in_python(const std::exception_ptr &e)
+{
+    torch::translate_exception_to_python(e);
+    return nullptr;
+}
+
 // every function: arguments by position, None when binding.py has to take over
 #define LMKAN_GUARDED_BEGIN try {
 #define LMKAN_GUARDED_END                                                  \
     }                                                                      \
-    catch (const std::exception &e)                                        \
+    catch (...)                                                            \
     {                                                                      \
-        PyErr_SetString(PyExc_RuntimeError, e.what());                     \
-        return nullptr;                                                    \
+        return raise_in_python(std::current_exception());                  \
     }
 
 // forward(desc, conv, x, coef, y, workspace) -> y

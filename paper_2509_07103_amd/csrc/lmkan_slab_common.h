@@ -3,6 +3,7 @@
 #pragma once
 
 #include "lmkan_kernels.h"
+#include "lmkan_split.h"
 
 namespace lmkan {
 
@@ -32,30 +33,6 @@ struct SlabArgs {
     float *y_part;     // NULL: use atomic_out
     int64_t part_elems;
 };
-
-// Pair splits for a launch of `tiles` workgroups over K pairs.  A workgroup fills a CU and walks its
-// pairs one after the other, a slab fill and a barrier each (about 3.5 us), so a launch lasts as many
-// such steps as rounds of 256 workgroups times pairs per split.  Few tiles want more splits to have
-// work for every CU, and a count a little above a multiple of 256 wastes most of its last round: the
-// split is the one with the fewest steps, two more per round for the tile's own loads and stores, and
-// at least four pairs in each, `most` at most.  A forward split beyond the first writes a part of its own that is added
-// up later (part_bytes each, moved twice); the input gradient adds atomically and passes 0.
-// (500 -> 333 outputs at G = 20 on 5000 rows, 33 tiles of 250 pairs: 8 splits make 264 workgroups and
-// two rounds of 32 pairs, 7 make 231 in one round of 36: forward 254 -> 157 us, grad_x 261 -> 212 us.)
-inline int pair_split_count(int64_t tiles, int K, int64_t part_bytes, int most)
-{
-    int best = 1;
-    double best_us = 0.0;
-    for (int split = 1; split == 1 || (K / split >= 4 && split <= most); ++split) {
-        const int64_t rounds = (tiles * split + 255) / 256;
-        const int pairs = (K + split - 1) / split;
-        if ((split - 1) * pairs >= K) continue;   // the last split would have none
-        const double us = 3.5 * (double)rounds * (pairs + 2) + (split - 1) * (double)part_bytes * 2 / 4.9e6 +
-                          (split > 1 && part_bytes ? 5.0 : 0.0);
-        if (split == 1 || us < best_us) best = split, best_us = us;
-    }
-    return best;
-}
 
 // floats between the partial outputs of consecutive pair splits: a whole number of 16-byte pieces
 inline int64_t partial_stride(int64_t elems) { return (elems + 3) & ~(int64_t)3; }

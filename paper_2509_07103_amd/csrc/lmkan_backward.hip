@@ -43,8 +43,8 @@ static_assert(kUnroll % kDepth == 0, "the gy ring must divide the unrolled trip"
 //                        padding entries follows (the walking kernels prefetch into it)
 // A thread keeps its samples in registers; LDS holds a population per (wave, cell) (16 bits each).
 // A sample's rank is what the counter of its wave and cell held before it, and the wave's samples
-// are a run of consecutive ones, so the order inside a cell follows the indices in steps of 64 and
-// does not depend on which wave happens to run first: sums over a cell repeat in every run.
+// are a run of consecutive ones taken in order, so the order inside a cell is that of the indices:
+// sums over a cell repeat in every run.
 // The entries go out through LDS, kSortStage stream positions at a time, so that the stores run along
 // the stream (16-byte stores all over a block's 130 KB are bound by the L2's requests: 175 us at 64
 // pairs x 262144 samples).
@@ -111,10 +111,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
         if (cell[j] >= 0) {
             const int i1 = (int)(((unsigned)cell[j] * inv_w) >> 20);
             const int c = cell[j] - i1;  // i1 (G + 1) + i2 -> i1 G + i2
-            const int shift = (c & 1) * 16;
             odd |= ((cell[j] ^ (i1 & (int)W)) & 1u) << j;  // i2 = node - i1 W
             cell[j] = c;
-            rank[j] = (atomicAdd(&s_count[(wave * even + c) >> 1], 1 << shift) >> shift) & 0xffff;
+            rank[j] = count_in_order(s_count, wave * even + c, c, cells > 256);
         }
     }
     __syncthreads();

@@ -163,6 +163,35 @@ __device__ __forceinline__ void fmac_row_bcast(float &acc, float w, float c)
         : "v"(w), "v"(c), "n"(S));
 }
 
+// Counts this lane's sample in a counter of its wave (16 bits, two to an LDS word) and returns how many samples
+// the counter held before it: those of earlier calls, and of this call those of lower lanes.  `key` (12 bits,
+// `wide` if it has more than 8) tells the counters of the wave apart.
+// What an atomic returns depends on the order in which it takes the lanes that meet in a counter, which is the
+// hardware's and not documented.  So the lanes with the same key are found by a ballot per bit, the counter is
+// read before any of them adds (a wave's LDS operations take place in the order they are issued, and
+// an address that may be the same keeps the compiler from exchanging them), and nothing waits in between.
+__device__ __forceinline__ int count_in_order(int *words, int counter, int key, bool wide)
+{
+    const uint64_t running = __ballot(true);
+    unsigned lo = (unsigned)running, hi = (unsigned)(running >> 32);
+    const auto meet = [&](int bit) {
+        const unsigned set = (unsigned)__builtin_amdgcn_sbfe(key, bit, 1);  // all ones or zero
+        const uint64_t those = __ballot(set != 0);
+        lo &= ~((unsigned)those ^ set);
+        hi &= ~((unsigned)(those >> 32) ^ set);
+    };
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) meet(bit);
+    if (wide)
+#pragma unroll
+        for (int bit = 8; bit < 12; ++bit) meet(bit);
+    int *word = &words[counter >> 1];
+    const int shift = (counter & 1) * 16;
+    const int held = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    (void)__hip_atomic_fetch_add(word, 1 << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return ((held >> shift) & 0xffff) + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+}
+
 template <int... Ts, class F>
 __device__ __forceinline__ void static_for(std::integer_sequence<int, Ts...>, F &&f)
 {

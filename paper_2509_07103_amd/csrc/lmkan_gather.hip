@@ -399,7 +399,7 @@ __global__ __launch_bounds__(256) void backward_input_gather_kernel(GatherArgs a
 // atomics.  A sample is gathered four times, by the four corners of its cell, and sorted anew for
 // every tile, which is what limits this kernel to small batches.
 // The counting sort keeps a population per (wave, cell): a sample's rank is what the wave's counter
-// held before it, so the order inside a cell follows waves and steps and does not depend on which
+// held before it, so the order inside a cell follows waves, steps and lanes and does not depend on which
 // wave happens to run first: the sums are the same in every run.
 // ---------------------------------------------------------------------------
 constexpr int kCoefThreads = 512;
@@ -440,8 +440,7 @@ __device__ __forceinline__ void coef_gather(const GatherArgs &a, int block, floa
             const int i1 = locate_cell(s_grid, G, xv[j].x, c1), i2 = locate_cell(s_grid, G, xv[j].y, c2);
             uv[j] = make_float2((xv[j].x - c1.z) * c1.w, (xv[j].y - c2.z) * c2.w);
             cell[j] = i1 * G + i2;
-            const int shift = (cell[j] & 1) * 16;
-            rank[j] = (atomicAdd(&s_count[(wave * even + cell[j]) >> 1], 1 << shift) >> shift) & 0xffff;
+            rank[j] = count_in_order(s_count, wave * even + cell[j], cell[j], cells > 256);
         }
     }
     __syncthreads();

@@ -329,8 +329,10 @@ lmkan_status forward_impl(const lmkan_desc *desc, int64_t batch, const float *x_
     drop_stale_error();
     TimedCall timed(kTimeForward);
     // Small shapes gather the rows they need and locate their inputs themselves: no records, also where
-    // the alignment of this call's pointers sends it to the generic kernel (backward_impl knows).
-    if (plan.gather) {
+    // the alignment of this call's pointers sends it to the generic kernel (backward_impl knows).  One
+    // output has another kernel that does the same, for rows.
+    const bool head = plan.head && !conv && !(plan.gather && gather_table_aligned(coef_dev) && forward_gather_beats_head(s));
+    if (plan.gather && !head) {
         if (gather_table_aligned(coef_dev))
             launch_forward_gather(s, tab, x_dev, coef_dev, y_dev, hs, conv);
         else
@@ -341,12 +343,11 @@ lmkan_status forward_impl(const lmkan_desc *desc, int64_t batch, const float *x_
     // alignment of this call's pointers sends it to the generic kernel: a later call may rely on them
     if (need > 0 && !(desc->flags & LMKAN_FLAG_WORKSPACE_HAS_RECORDS))
         launch_preamble_records(s, tab, x_dev, workspace_dev, hs, conv);
-    if (plan.head) {
+    if (head) {
+        launch_forward_head(s, tab, x_dev, coef_dev, y_dev, hs);
+    } else if (plan.head) {
         // one output: no records (need == 0); windows and 4-byte aligned rows go the generic way
-        if (!conv)
-            launch_forward_head(s, tab, x_dev, coef_dev, y_dev, hs);
-        else
-            launch_forward_generic(s, tab, x_dev, coef_dev, y_dev, hs, conv);
+        launch_forward_generic(s, tab, x_dev, coef_dev, y_dev, hs, conv);
     } else if (plan.small) {
         launch_forward_small(s, coef_dev, y_dev, workspace_dev, hs);
     } else if (slab_forward_applicable(s, coef_dev, y_dev)) {

@@ -33,6 +33,8 @@ struct GatherArgs {
 };
 
 bool forward_gather_shape_ok(const LayerShape &s);
+// of a shape that head_forward_shape_ok(), on rows
+bool forward_gather_beats_head(const LayerShape &s);
 bool backward_input_gather_shape_ok(const LayerShape &s);
 bool backward_coef_gather_shape_ok(const LayerShape &s);
 // both gradients from one launch

@@ -848,6 +848,20 @@ bool forward_gather_shape_ok(const LayerShape &s)
     return gather_us(s, tile, 128, 27e6, 0.25) < kPromise * slab_us(s, 26, 3e6, 2.8e6, 1.8e6);
 }
 
+// One output on rows: against the kernel that keeps the pairs' columns of the table in LDS.  A workgroup of it
+// fetches a line per node and pair first, which the gathers save while there are few rows; from then on it
+// does a pair in a third to a fourth of the time.  (Fitted to 250 random layers of 4 ... 512 pairs, 1 ... 130000
+// rows, G of 4 to 30, packed tables, to 30 %.  The choice takes 1.4 % longer than the better of the two,
+// at most 7 % longer than the kernel with the columns in LDS; gathering always takes 9 % longer, up to
+// 4.4 times as long, and never gathering 81 % longer.)
+bool forward_gather_beats_head(const LayerShape &s)
+{
+    const int chunk = head_pairs_per_chunk(s);
+    const double items = (double)s.batch * s.pairs(), lines = (double)chunk * s.nodes();
+    const double head = 6.4 + lines / 1480 + 3.3 * ((s.pairs() + chunk - 1) / chunk - 1) + items / 227e3 + items * lines / 5.9e9;
+    return gather_us(s, forward_per_lane(s), 128, 27e6, 0.25) < kPromise * head;
+}
+
 bool backward_input_gather_shape_ok(const LayerShape &s)
 {
     if (!rows_by_16_bytes(s)) return false;

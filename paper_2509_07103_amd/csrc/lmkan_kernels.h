@@ -109,6 +109,7 @@ void launch_forward_small(const LayerShape &s, const void *coef, float *y, const
 // in LDS and the kernel locates the inputs itself, so the call needs no records and no workspace.
 // Applies when at least 64 pairs' tables (or all of them) fit LDS at once.
 bool head_forward_shape_ok(const LayerShape &s);
+int head_pairs_per_chunk(const LayerShape &s);
 void launch_forward_head(const LayerShape &s, const GridTab &tab, const float *x, const void *coef, float *y,
                          hipStream_t stream);
 // its gradients, the same way: x, gy [batch] and grad_x 8-byte aligned rows; grad_coef float32 in

@@ -495,7 +495,7 @@ bool small_out_shape_ok(const LayerShape &s)
 // LDS floats per pair of the one-output forward kernel, and the pairs one workgroup can hold
 static int head_pitch(const LayerShape &s) { return s.nodes() | 1; }
 static int head_budget() { return (160 * 1024 - LMKAN_MAX_GRID * (int)sizeof(float4)) / (int)sizeof(float); }  // beside the grid
-static int head_chunk(const LayerShape &s)
+int head_pairs_per_chunk(const LayerShape &s)
 {
     int kc = head_budget() / head_pitch(s);
     if (kc >= s.pairs()) return s.pairs();
@@ -505,7 +505,7 @@ static int head_chunk(const LayerShape &s)
 // One output, rows (not windows), and at least a wave of pairs fits LDS at a time (G <= 24, or few pairs)
 bool head_forward_shape_ok(const LayerShape &s)
 {
-    return s.n_out == 1 && head_chunk(s) > 0;
+    return s.n_out == 1 && head_pairs_per_chunk(s) > 0;
 }
 
 // grid, LDS and per-block share of a launch of head_kernel over at most `max_blocks` workgroups
@@ -522,7 +522,7 @@ static HeadArgs head_args(const LayerShape &s, const GridTab &tab, const float *
     a.W = s.G + 1;
     a.nodes = s.nodes();
     a.pitch = head_pitch(s);
-    a.pairs_per_chunk = head_chunk(s);
+    a.pairs_per_chunk = head_pairs_per_chunk(s);
     const int chunks = (a.K + a.pairs_per_chunk - 1) / a.pairs_per_chunk;
     // a sample takes as many lanes as the chunk has pairs, rounded up to a power of two
     a.lps = 1;
@@ -591,7 +591,7 @@ static HeadCoefPlan head_coef_plan(const LayerShape &s)
     HeadCoefPlan p;
     // four lanes per pair: at most 256 pairs and copies of pairs to a workgroup
     const int fit = head_budget() / head_pitch(s);
-    p.pairs_per_chunk = std::min(head_chunk(s), 256);
+    p.pairs_per_chunk = std::min(head_pairs_per_chunk(s), 256);
     p.chunks = (s.pairs() + p.pairs_per_chunk - 1) / p.pairs_per_chunk;
     p.copies = 1;
     while (2 * p.copies * p.pairs_per_chunk <= std::min(fit, 256)) p.copies *= 2;

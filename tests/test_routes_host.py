@@ -106,3 +106,21 @@ def test_the_static_scratch_takes_every_batch_whose_records_fit(rec):
             assert static[1][1][0] < free[1][1][0]
             fewer += 1
     assert got[2][0] == 0 and got[5][0] == 7 and fewer >= 3, fewer
+
+
+def test_one_packed_output_gathers_while_rows_are_few(rec):
+    """Rows of a layer with one output: the kernel that keeps the tables in LDS, unless few rows make its
+    filling the larger part; windows gather or go the generic way; an unaligned table is none for gathers."""
+    def main(batch, n_in=256, grid=16, **more):
+        call = dict(dict(n_in=n_in, n_out=1, grid=grid, batch=batch, layout=1, fn="forward"), **more)
+        (status, launches), = routes([call], rec)
+        assert status == 0
+        return [n for n in names(launches) if n != "fill_zero_kernel"]
+    for batch in (1, 16, 256):
+        assert main(batch) == ["forward_gather_kernel"]
+        assert main(batch, coef=4) == ["forward_head_kernel"]
+    for batch in (30000, 200000):
+        for n_in, grid in ((16, 6), (256, 16), (1000, 8)):
+            assert main(batch, n_in, grid) == ["forward_head_kernel"]
+    assert main(0, conv=(64, 1, 1, 256, 1, 1, 1)) == ["forward_gather_kernel"]
+    assert main(64, layout=0) == ["forward_head_kernel"]

@@ -563,7 +563,7 @@ __global__ __launch_bounds__(kCoefThreads) void backward_gather_kernel(GatherArg
 }
 
 // lanes per row, `per_lane` outputs each: as many as the outputs fill, up to sixteen
-int lanes_for(int n_out, int per_lane)
+constexpr int lanes_for(int n_out, int per_lane)
 {
     int lpr = 1;
     while (lpr < 16 && lpr * per_lane < n_out) lpr *= 2;
@@ -574,10 +574,12 @@ int forward_per_lane(const LayerShape &s) { return s.dtype == LMKAN_F32 ? 4 : 8;
 
 // eight outputs per lane, so that fewer lanes have to meet at the end of an item; float32 rows of up to 4
 // outputs, and of more than 64 (one load per corner and step, two steps in flight): four
-int backward_input_per_lane(const LayerShape &s) { return s.dtype == LMKAN_F32 && (s.n_out <= 4 || s.n_out > 64) ? 4 : 8; }
+constexpr int input_per_lane(bool f32, int n_out) { return f32 && (n_out <= 4 || n_out > 64) ? 4 : 8; }
+int backward_input_per_lane(const LayerShape &s) { return input_per_lane(s.dtype == LMKAN_F32, s.n_out); }
 
 // wide layers: tiles of 128 outputs (every tile sorts the batch for itself)
-int backward_coef_per_lane(const LayerShape &s) { return s.n_out > 128 ? 8 : 4; }
+constexpr int coef_per_lane(int n_out) { return n_out > 128 ? 8 : 4; }
+int backward_coef_per_lane(const LayerShape &s) { return coef_per_lane(s.n_out); }
 
 int log2_of(int power) { return __builtin_ctz((unsigned)power); }
 
@@ -637,19 +639,31 @@ GatherKernel backward_coef_for(int lpr)
     }
 }
 
-// the lanes and quads that the launchers of the single gradients choose for this output count
-template <typename CT>
-GatherKernel backward_for(int n_out)
+// The kernel for both gradients, with the lanes and outputs per lane of the kernels for one: they change at
+// these output counts only.
+struct BothGradients {
+    GatherKernel kernel;
+    int input_lanes, input_per, coef_lanes, coef_per;
+};
+
+template <typename CT, int N_OUT>
+BothGradients backward_at()
 {
-    constexpr bool wide = sizeof(CT) == 4;
-    constexpr int q = wide ? 1 : 2;
-    if (n_out <= 4) return backward_gather_kernel<CT, 1, q, 1, 1>;
-    if (n_out <= 8) return backward_gather_kernel<CT, 1, 2, 2, 1>;
-    if (n_out <= 16) return backward_gather_kernel<CT, 2, 2, 4, 1>;
-    if (n_out <= 32) return backward_gather_kernel<CT, 4, 2, 8, 1>;
-    if (n_out <= 64) return backward_gather_kernel<CT, 8, 2, 16, 1>;
-    if (n_out <= 128) return backward_gather_kernel<CT, 16, q, 16, 1>;
-    return backward_gather_kernel<CT, 16, q, 16, 2>;
+    constexpr int px = input_per_lane(sizeof(CT) == 4, N_OUT), pp = coef_per_lane(N_OUT);
+    constexpr int lx = lanes_for(N_OUT, px), lp = lanes_for(N_OUT, pp);
+    return {backward_gather_kernel<CT, lx, px / 4, lp, pp / 4>, lx, px, lp, pp};
+}
+
+template <typename CT>
+BothGradients backward_for(int n_out)
+{
+    return n_out <= 4    ? backward_at<CT, 4>()
+           : n_out <= 8  ? backward_at<CT, 8>()
+           : n_out <= 16 ? backward_at<CT, 16>()
+           : n_out <= 32 ? backward_at<CT, 32>()
+           : n_out <= 64 ? backward_at<CT, 64>()
+           : n_out <= 128 ? backward_at<CT, 128>()
+                          : backward_at<CT, LMKAN_MAX_N_OUT>();
 }
 
 size_t coef_gather_lds(const LayerShape &s)
@@ -785,16 +799,14 @@ void launch_backward_gather(const LayerShape &s, const GridTab &tab, const float
                             float *gx, float *gcoef, bool accumulate, hipStream_t stream, const ConvGeom *conv)
 {
     GatherArgs a = gather_args(s, tab, x, coef, conv);
-    const int px = backward_input_per_lane(s), pp = backward_coef_per_lane(s);
-    const int lx = lanes_for(s.n_out, px), lp = lanes_for(s.n_out, pp);
-    const int64_t waves = set_input_args(a, s, gy, gx, conv, lx, stream);
-    a.coef_blocks = (int)set_coef_args(a, s, gy, gcoef, accumulate, lp, pp);
-    const GatherKernel kernel = s.dtype == LMKAN_F32   ? backward_for<float>(s.n_out)
-                                : s.dtype == LMKAN_F16 ? backward_for<_Float16>(s.n_out)
-                                                       : backward_for<bf16_t>(s.n_out);
+    const BothGradients both = s.dtype == LMKAN_F32   ? backward_for<float>(s.n_out)
+                               : s.dtype == LMKAN_F16 ? backward_for<_Float16>(s.n_out)
+                                                      : backward_for<bf16_t>(s.n_out);
+    const int64_t waves = set_input_args(a, s, gy, gx, conv, both.input_lanes, stream);
+    a.coef_blocks = (int)set_coef_args(a, s, gy, gcoef, accumulate, both.coef_lanes, both.coef_per);
     const unsigned grid = (unsigned)(a.coef_blocks + (waves + kCoefWaves - 1) / kCoefWaves);
     KernelTiming timing(stream, kTimeGradInput);
-    kernel<<<grid, kCoefThreads, coef_gather_lds(s), stream>>>(a);
+    both.kernel<<<grid, kCoefThreads, coef_gather_lds(s), stream>>>(a);
 }
 
 // rows of the table are read 16 bytes at a time

@@ -416,8 +416,12 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     const bool fused_pays = !slab_ok || (!slab_tile_is_wide(s) && grad_coef_dev && dense_cells &&
                                          !slab_backward_input_takes_half_tiles(s));
     const bool enough_work = s.batch >= 256 || (int64_t)s.pairs() * s.n_out >= 8192;  // as for the slab kernels
-    const bool gx_fused = grad_x_dev && !small && !gx_gather && !gp_gather && enough_work && fused_pays &&
-                          fused_backward_applicable(s, coef_dev, grad_y_dev, grad_coef_dev);
+    // Beside a coefficient gradient that gathers, grad_x alone: by a slab kernel, by the walk, or by the generic
+    // kernel while there is little to do (7 pairs x 156 outputs x 812 rows at G = 37: 10 against 37 us; 100 x 100 x
+    // 400 at G = 36: 111 against 42; 306 x 12 x 1613 at G = 50: 250 against 102).
+    const bool walk_beside = !slab_ok && s.batch * s.pairs() * s.n_out > 1 << 20;
+    const bool gx_fused = grad_x_dev && !small && !gx_gather && (!gp_gather || walk_beside) && enough_work && fused_pays &&
+                          fused_backward_applicable(s, coef_dev, grad_y_dev, gp_gather ? nullptr : grad_coef_dev);
     const bool gx_slab = slab_ok && !gx_fused;
     const bool gp_sorted = grad_coef_dev && !gp_small && !gp_head && !gp_gather && coef_sorted_applicable(s, grad_y_dev, grad_coef_dev);
     const bool need_records = gp_sorted || gx_fused || gx_slab || gx_small || gp_small;
@@ -467,9 +471,9 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
         launch_backward_input_gather(s, tab, x_dev, coef_dev, grad_y_dev, grad_x_dev, hs, conv);
     } else if (gx_fused) {
         // one walk over the cell-sorted samples yields both gradients (the coefficient gradient
-        // qualifies whenever the input gradient does)
-        launch_backward_fused(s, tab, stream_k, ws, coef_dev, gy_k, grad_x_dev, grad_coef_dev, !overwrite, ws_partial,
-                              conv ? ws_scratch : nullptr, hs);
+        // qualifies whenever the input gradient does), unless that one has gathered its own
+        launch_backward_fused(s, tab, stream_k, ws, coef_dev, gy_k, grad_x_dev, gp_gather ? nullptr : grad_coef_dev,
+                              !overwrite, ws_partial, conv ? ws_scratch : nullptr, hs);
         if (conv) launch_input_gradient_out(ws_scratch, grad_x_dev, s, conv, hs);
     } else if (gx_small) {
         launch_backward_input_small(s, tab, coef_dev, grad_y_dev, ws_scratch, ws, hs);

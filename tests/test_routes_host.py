@@ -124,3 +124,19 @@ def test_one_packed_output_gathers_while_rows_are_few(rec):
             assert main(batch, n_in, grid) == ["forward_head_kernel"]
     assert main(0, conv=(64, 1, 1, 256, 1, 1, 1)) == ["forward_gather_kernel"]
     assert main(64, layout=0) == ["forward_head_kernel"]
+
+
+def test_both_gradients_take_no_general_kernel_that_one_alone_does_not(rec):
+    """The choices of a call for both gradients depend on each other; none may leave grad_x or the coefficient
+    gradient to the generic kernel when a call for that gradient alone has a better one (a million
+    multiply-adds and more: below, the generic kernel can be the better one)."""
+    rng = random.Random(7)
+    layers = [dict(n_in=200, n_out=100, grid=36, batch=400, dtype=1, layout=0),
+              dict(n_in=612, n_out=12, grid=50, batch=1613, dtype=2, layout=0)]
+    layers += [dict(_layer(rng), layout=rng.randint(0, 1)) for _ in range(600)]
+    layers = [layer for layer in layers if layer["n_in"] // 2 * layer["n_out"] * layer["batch"] > 1 << 20]
+    calls = [dict(layer, fn="backward", **which) for layer in layers for which in ({}, dict(grad_coef=0), dict(grad_x=0))]
+    got = routes(calls, rec)
+    for i, layer in enumerate(layers):
+        both, alone = names(got[3 * i][1]), names(got[3 * i + 1][1]) + names(got[3 * i + 2][1])
+        assert both.count("backward_generic_kernel") <= alone.count("backward_generic_kernel"), (layer, both, alone)

@@ -48,6 +48,44 @@ def parse():
     return ap.parse_args()
 
 
+def gathers(w, n_out, B, storage, packed):
+    """Which passes (forward, grad_x, grad_coef) of a layer of more than eight outputs take the gathering
+    kernels: the library's rules, which compare fitted times in microseconds (lmkan_gather.hip)."""
+    item, K, G = 4 if storage == "f32" else 2, w.n_in // 2, w.grid
+    nodes, quads = (G + 1) ** 2, (n_out + 3) // 4 * 4
+    rows = float(B) * K
+    table = nodes * K * ((n_out + 63) // 64 * 64) * item
+
+    def tile(per_lane):
+        lanes = 1
+        while lanes < 16 and lanes * per_lane < n_out:
+            lanes *= 2
+        return lanes * per_lane
+
+    def gather_us(per_lane, least_line, rate, falls):
+        t = tile(per_lane)
+        line, loaded = max(quads * item, least_line), (n_out + t - 1) // t * t * item
+        line = (line + loaded) / 2 if loaded > line else line
+        rate = min(rate, max(7e6, rate * (4e6 / table) ** falls)) if table <= 256e6 else 5.5e6
+        return 4 + rows * 4 * line / rate
+
+    def slab_us(least, half, fine):
+        work = (rows * ((n_out + 63) // 64 * 64) / 3e6 if G <= 16 else
+                rows * ((n_out + 31) // 32 * 32) / (half if G <= 34 else fine))
+        return max(least + work, table / 4.8e6)
+
+    by16 = packed or n_out % (4 if storage == "f32" else 8) == 0
+    wide = 4 if storage == "f32" else 8
+    fwd = by16 and (G > 48 or gather_us(wide, 128, 27e6, 0.25) < 0.85 * slab_us(26, 2.8e6, 1.8e6))
+    gx = by16 and gather_us(4 if storage == "f32" and n_out > 64 else 8, 64, 20e6, 0.33) < 0.85 * slab_us(38, 2.8e6, 1.4e6)
+    grad, work = nodes * K * n_out * 4, rows * quads
+    lds = B * 12 + (G * G + 1) * 4 + 8 * ((G * G + 1) & ~1) * 2
+    gp = (B <= 8192 and lds <= 155 * 1024 and
+          6 + B / 150 + 0.2 * B / (G * G) + work / 1.4e6 + grad / 5e6 <
+          0.85 * (25 + min(grad / 1e6, 40 + grad / 5e6) + work / 5e6))
+    return fwd, gx, gp, gx and gp and B <= 1024 and lds <= 20 * 1024
+
+
 def kernel_names(w, n_out, B, storage, packed):
     """Main kernel of a forward call, of a grad_x-only call and of a grad_coef-only call, and of a call
     for both gradients when one kernel forms both: mirrors the library's dispatch (lmkan_api.hip)."""
@@ -61,10 +99,6 @@ def kernel_names(w, n_out, B, storage, packed):
         fit = ((160 * 1024 - 1024) // 4) // ((w.grid + 1) ** 2 | 1)
         if n_out == 1 and not getattr(w, "kh", 0) and (fit >= w.n_in // 2 or fit >= 64):
             fwd, gx, gp = "forward_head_kernel", "backward_input_head_kernel", "backward_coef_head_kernel"
-    elif B * (w.n_in // 2) * n_out <= 1 << 18:
-        # (the library's rule weighs sizes against each other; this file's workloads lie far to either side)
-        fwd, gx, gp = "forward_gather_kernel", "backward_input_gather_kernel", "backward_coef_gather_kernel"
-        both = "backward_gather_kernel"
     elif ok and w.grid <= 16:
         f16 = storage == "f16" and (packed or n_out % 8 == 0)
         fwd = "forward_slab_f16_kernel" if f16 else "forward_slab_kernel"
@@ -88,6 +122,12 @@ def kernel_names(w, n_out, B, storage, packed):
     else:
         fwd, gx = "forward_generic_kernel", "backward_generic_kernel(grad_x)"
         gp = "backward_coef_stream_kernel"
+    if n_out > 8:
+        fwd_gathers, gx_gathers, gp_gathers, both_gather = gathers(w, n_out, B, storage, packed)
+        fwd = "forward_gather_kernel" if fwd_gathers else fwd
+        gx = "backward_input_gather_kernel" if gx_gathers else gx
+        gp = "backward_coef_gather_kernel" if gp_gathers else gp
+        both = "backward_gather_kernel" if both_gather else None if gx_gathers or gp_gathers else both
     return fwd, gx, gp, both
 
 

@@ -1,5 +1,6 @@
 """Host-side checks of bench.py and the workload recipes that need no GPU."""
 import os
+import random
 import subprocess
 import sys
 
@@ -90,3 +91,27 @@ def test_missing_library_is_a_loud_error(tmp_path, monkeypatch):
     monkeypatch.setattr(binding, "LIB_PATH", str(tmp_path / "liblmkan.so"))
     with pytest.raises(ImportError):
         binding.lib()
+
+
+def test_bench_names_the_kernels_that_run(tmp_path):
+    """bench.py names the main kernels of its workloads by rules of its own; the library's launches decide."""
+    import bench
+    from paper_2509_07103_amd import workloads as wl
+    from routes import names, recorder, routes
+    cases, calls = [], []
+    rng = random.Random(9)
+    drawn = [wl.Workload(f"drawn {i}", 2 * round(256 ** rng.random()) + 2, 64 * rng.randint(1, 8) + rng.choice([0, 0, 3]),
+                         rng.randint(4, 48), round(256 * 200 ** rng.random()), 0.1, 0) for i in range(150)]
+    for w in list(wl.BY_NAME.values()) + list(wl.CONV_BY_NAME.values()) + drawn:
+        conv = (w.n, w.h, w.w, w.c_in, w.kh, w.kw, w.stride) if hasattr(w, "kh") else None
+        for dtype, storage in enumerate(("f32", "f16", "bf16")):
+            packed = w.n_out != 1
+            layer = dict(n_in=w.n_in, n_out=w.n_out, grid=w.grid, batch=w.batch, dtype=dtype, layout=int(packed), conv=conv)
+            cases.append((w.name, storage, bench.kernel_names(w, w.n_out, w.batch, storage, packed)))
+            calls += [dict(layer, fn="forward"), dict(layer, fn="backward", grad_coef=0),
+                      dict(layer, fn="backward", grad_x=0), dict(layer, fn="backward")]
+    got = routes(calls, recorder(tmp_path))
+    for i, (name, storage, want) in enumerate(cases):
+        fwd, gx, gp, both = (names(launches) for _, launches in got[4 * i:4 * i + 4])
+        assert want[0] in fwd and want[1] in gx and want[2] in gp, (name, storage, want, fwd, gx, gp)
+        assert want[3] in both if want[3] else want[1] in both and want[2] in both, (name, storage, want, both)

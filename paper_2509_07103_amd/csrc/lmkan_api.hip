@@ -328,12 +328,14 @@ lmkan_status forward_impl(const lmkan_desc *desc, int64_t batch, const float *x_
     hipStream_t hs = static_cast<hipStream_t>(stream);
     drop_stale_error();
     TimedCall timed(kTimeForward);
-    // Small shapes gather the rows they need and locate their inputs themselves: no records, also where
-    // the alignment of this call's pointers sends it to the generic kernel (backward_impl knows).  One
-    // output has another kernel that does the same, for rows.
-    const bool head = plan.head && !conv && !(plan.gather && gather_table_aligned(coef_dev) && forward_gather_beats_head(s));
-    if (plan.gather && !head) {
-        if (gather_table_aligned(coef_dev))
+    // Small shapes gather the rows they need and locate their inputs themselves: no records.  One output has
+    // another kernel that does the same, for rows.  Tables that are not 16-byte aligned cannot be gathered:
+    // few outputs have the kernel that adds them up from the records (which are then nobody else's: the
+    // flag means nothing for these shapes), others go the generic way.
+    const bool table_ok = gather_table_aligned(coef_dev);
+    const bool head = plan.head && !conv && !(plan.gather && table_ok && forward_gather_beats_head(s));
+    if (plan.gather && !head && (table_ok || !plan.small)) {
+        if (table_ok)
             launch_forward_gather(s, tab, x_dev, coef_dev, y_dev, hs, conv);
         else
             launch_forward_generic(s, tab, x_dev, coef_dev, y_dev, hs, conv);
@@ -341,8 +343,8 @@ lmkan_status forward_impl(const lmkan_desc *desc, int64_t batch, const float *x_
     }
     // the records are written whenever the shape has a kernel that reads them, also when the
     // alignment of this call's pointers sends it to the generic kernel: a later call may rely on them
-    if (need > 0 && !(desc->flags & LMKAN_FLAG_WORKSPACE_HAS_RECORDS))
-        launch_preamble_records(s, tab, x_dev, workspace_dev, hs, conv);
+    const bool have_records = !plan.gather && (desc->flags & LMKAN_FLAG_WORKSPACE_HAS_RECORDS);
+    if (need > 0 && !have_records) launch_preamble_records(s, tab, x_dev, workspace_dev, hs, conv);
     if (head) {
         launch_forward_head(s, tab, x_dev, coef_dev, y_dev, hs);
     } else if (plan.head) {

@@ -140,3 +140,14 @@ def test_both_gradients_take_no_general_kernel_that_one_alone_does_not(rec):
     for i, layer in enumerate(layers):
         both, alone = names(got[3 * i][1]), names(got[3 * i + 1][1]) + names(got[3 * i + 2][1])
         assert both.count("backward_generic_kernel") <= alone.count("backward_generic_kernel"), (layer, both, alone)
+
+
+def test_few_outputs_keep_their_kernel_when_the_table_is_not_aligned(rec):
+    """A table that starts on its element size only cannot be gathered 16 bytes at a time; up to eight outputs
+    where no slab kernel applies then take the kernel that works from the records, as without the gathers."""
+    for n_out, layout in ((3, 1), (8, 1), (4, 0), (8, 0)):
+        layer = dict(n_in=40, n_out=n_out, grid=40, batch=2000, layout=layout, coef=4)
+        calls = [dict(layer, fn="forward"), dict(layer, fn="forward", flags=REUSE), dict(layer, fn="forward", coef=0)]
+        a, reuse, aligned = (names(launches) for _, launches in routes(calls, rec))
+        assert a[0] == "preamble_records_kernel" and a[-1] == "forward_small_kernel" and reuse == a
+        assert aligned == ["forward_gather_kernel"]

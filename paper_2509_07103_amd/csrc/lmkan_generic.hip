@@ -224,22 +224,24 @@ __global__ __launch_bounds__(kThreads) void locate_kernel(GridTab tab, const flo
 }
 
 // dst[jt][k][node][64] = src[node][k][64 jt ...], zero past n_out.  A pure copy: bound by HBM.  A
-// workgroup takes kPackNodes nodes of a pair with all their outputs, so what it reads are whole rows of
+// workgroup takes kPackNodes nodes of a pair with all or a part of their outputs, so what it reads are whole rows of
 // src and what it writes are runs of kPackNodes tile rows; a thread moves 16 bytes at a time, kPackBatch
 // loads before the first store (16-byte accesses of global memory need the alignment of an element only,
 // so rows of any length take them).
+// (One pair with 65536 outputs at G = 16, where pairs and nodes make 19 workgroups: 243 us, 24 us with
+// the outputs in 108 parts.)
 // (One element per thread, the index of its source divided out in 64 bits: 130 us for 500 -> 333 at
 // G = 20, float32, 316 MB; 56 us now.)
 constexpr int kPackNodes = 16, kPackBatch = 4;
 
 template <typename U>
 __global__ __launch_bounds__(kThreads) void pack_kernel(const U *__restrict__ src, U *__restrict__ dst,
-                                                       int K, int n_out, int nodes, int tiles)
+                                                       int K, int n_out, int nodes, int all_tiles, int part_tiles)
 {
     constexpr int E = 16 / (int)sizeof(U), kPieces = kTile / E;  // elements of a piece, pieces of a tile row
     typedef U Piece __attribute__((ext_vector_type(E), aligned(sizeof(U))));
-    const int k = blockIdx.x, node0 = blockIdx.y * kPackNodes;
-    const int rows = tiles * kPackNodes;
+    const int k = blockIdx.x, node0 = blockIdx.y * kPackNodes, tile0 = blockIdx.z * part_tiles;
+    const int rows = min(part_tiles, all_tiles - tile0) * kPackNodes;
     for (int first = threadIdx.x; first < rows * kPieces; first += kThreads * kPackBatch) {
         Piece v[kPackBatch];
         U *to[kPackBatch];
@@ -247,7 +249,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const U *__restrict__ sr
         for (int i = 0; i < kPackBatch; ++i) {
             const int item = first + i * kThreads;
             const int col = item % kPieces * E, row = item / kPieces;
-            const int node = node0 + row % kPackNodes, jt = row / kPackNodes;
+            const int node = node0 + row % kPackNodes, jt = tile0 + row / kPackNodes;
             const int j = jt * kTile + col;
             to[i] = nullptr;
             if (row >= rows || node >= nodes) continue;
@@ -385,13 +387,18 @@ void launch_locate(const LayerShape &s, const GridTab &tab, const float *x, int3
 
 void launch_pack(const LayerShape &s, const void *src, void *dst, hipStream_t stream)
 {
-    const dim3 grid((unsigned)s.pairs(), (unsigned)((s.nodes() + kPackNodes - 1) / kPackNodes));
+    // A workgroup takes all outputs, unless pairs and nodes alone make fewer than 2048 workgroups: the
+    // outputs are then cut into as many parts as that takes.
+    const int node_blocks = (s.nodes() + kPackNodes - 1) / kPackNodes, tiles = s.out_tiles();
+    const int parts = (2048 + s.pairs() * node_blocks - 1) / (s.pairs() * node_blocks);
+    const int part_tiles = (tiles + parts - 1) / parts;
+    const dim3 grid((unsigned)s.pairs(), (unsigned)node_blocks, (unsigned)((tiles + part_tiles - 1) / part_tiles));
     if (s.dtype == LMKAN_F32)
         pack_kernel<uint32_t><<<grid, kThreads, 0, stream>>>(static_cast<const uint32_t *>(src), static_cast<uint32_t *>(dst),
-                                                            s.pairs(), s.n_out, s.nodes(), s.out_tiles());
+                                                            s.pairs(), s.n_out, s.nodes(), tiles, part_tiles);
     else
         pack_kernel<uint16_t><<<grid, kThreads, 0, stream>>>(static_cast<const uint16_t *>(src), static_cast<uint16_t *>(dst),
-                                                            s.pairs(), s.n_out, s.nodes(), s.out_tiles());
+                                                            s.pairs(), s.n_out, s.nodes(), tiles, part_tiles);
 }
 
 void launch_fill_zero(float *p, size_t n, hipStream_t stream)

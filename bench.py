@@ -49,7 +49,7 @@ def parse():
 
 
 def gathers(w, n_out, B, storage, packed):
-    """Which passes (forward, grad_x, grad_coef) of a layer of more than eight outputs take the gathering
+    """Which passes (forward, grad_x, grad_coef, both gradients) of a layer of more than eight outputs take the gathering
     kernels: the library's rules, which compare fitted times in microseconds (lmkan_gather.hip)."""
     item, K, G = 4 if storage == "f32" else 2, w.n_in // 2, w.grid
     nodes, quads = (G + 1) ** 2, (n_out + 3) // 4 * 4

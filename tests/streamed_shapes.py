@@ -1,0 +1,75 @@
+"""Layers that the kernels for larger work take (tables streamed through LDS, samples sorted by cell), small
+enough for the oracle, with the kernels that their calls reach.  test_gpu_streamed.py runs them;
+test_routes_host.py checks, without a GPU, that they reach what they are listed for: the rules that choose a
+kernel follow measured times and move."""
+
+SLAB, SLAB16, LANE = "forward_slab_kernel", "forward_slab_f16_kernel", "backward_input_lane_kernel"
+LANE32, LANE32F = "forward_lane32_kernel", "forward_lane32_f32_kernel"
+NARROW, GATHER = "forward_slab_narrow_kernel", "forward_gather_kernel"
+IN_SLAB, IN_SLAB16, IN_NARROW = "backward_input_slab_kernel", "backward_input_slab_f16_kernel", "backward_input_slab_narrow_kernel"
+IN_LANE32, IN_LANE32F = "backward_input_lane32_kernel", "backward_input_lane32_f32_kernel"
+WALK, STREAM, COEF_GATHER = "backward_fused_kernel", "backward_coef_stream_kernel", "backward_coef_gather_kernel"
+
+PAPER, PACKED = 0, 1
+
+# B, n_in, n_out, G, storage, layout, kernel of the forward pass, kernels of both gradients
+SHAPES = [
+    # 64-output tiles: fewer rows than a tile's, ragged last tiles, every table type and layout
+    (119, 428, 662, 13, "f32", PACKED, SLAB, (LANE, COEF_GATHER)),
+    (130, 600, 818, 16, "f32", PACKED, SLAB, (LANE, COEF_GATHER)),
+    (1300, 364, 132, 16, "f32", PAPER, SLAB, (LANE, COEF_GATHER)),
+    (1025, 500, 260, 3, "f32", PAPER, SLAB, (LANE, STREAM)),
+    (20000, 480, 9, 16, "f32", PACKED, SLAB, ("backward_input_gather_kernel", STREAM)),
+    (228, 502, 1033, 10, "f16", PACKED, SLAB16, (IN_SLAB16, COEF_GATHER)),
+    (169, 408, 1180, 16, "f16", PACKED, SLAB16, (IN_SLAB16, COEF_GATHER)),
+    (228, 502, 1033, 10, "bf16", PACKED, SLAB, (IN_SLAB, COEF_GATHER)),
+    (169, 408, 1180, 16, "bf16", PACKED, SLAB, (IN_SLAB, COEF_GATHER)),
+    # tables that cannot be gathered (16-bit rows of 8 bytes, Alg. 1's layout): down to a single row
+    (1, 128, 132, 16, "f16", PAPER, SLAB, (IN_SLAB, COEF_GATHER)),
+    (300, 10, 220, 6, "f16", PAPER, SLAB, (IN_SLAB, COEF_GATHER)),
+    (3, 64, 260, 8, "bf16", PAPER, SLAB, (IN_SLAB, COEF_GATHER)),
+    (1, 234, 100, 30, "bf16", PAPER, NARROW, (IN_NARROW, COEF_GATHER)),
+    (2, 300, 76, 34, "f16", PAPER, NARROW, (IN_NARROW, COEF_GATHER)),
+    (1, 108, 180, 44, "bf16", PAPER, NARROW, ("backward_generic_kernel", COEF_GATHER)),
+    (110, 160, 132, 40, "f16", PAPER, NARROW, (WALK, COEF_GATHER)),
+    # 32-output tiles (packed, two slabs fit as stored) at both ends of their grids, tiles of 2048 rows
+    (2049, 300, 100, 17, "f32", PACKED, LANE32F, (IN_LANE32F, STREAM)),
+    (4100, 480, 37, 24, "f32", PACKED, LANE32F, (IN_LANE32F, STREAM)),
+    (2047, 450, 200, 17, "bf16", PACKED, LANE32, (IN_LANE32, STREAM)),
+    (3000, 460, 67, 34, "f16", PACKED, LANE32, (IN_LANE32, COEF_GATHER)),
+    # 16-output tiles: the grids left to them, and the one slab at a time from 35 to 48
+    (4097, 392, 21, 25, "f32", PACKED, NARROW, (IN_NARROW, STREAM)),
+    (4100, 392, 20, 34, "f32", PAPER, NARROW, (IN_NARROW, STREAM)),
+    (2000, 600, 72, 20, "f32", PAPER, NARROW, (IN_NARROW, COEF_GATHER)),
+    (3400, 386, 36, 35, "f32", PACKED, NARROW, (WALK, COEF_GATHER)),
+    (4300, 300, 40, 48, "f32", PAPER, NARROW, (WALK, COEF_GATHER)),
+    (4300, 300, 140, 48, "bf16", PACKED, NARROW, (WALK,)),
+    # both gradients from one walk: the 16-output range with dense cells, no slab at all, several blocks
+    # of the batch (even and ragged outputs, one tile and several)
+    (7000, 240, 72, 20, "f32", PAPER, NARROW, (WALK,)),
+    (8914, 190, 18, 54, "f32", PACKED, GATHER, (WALK,)),
+    (2330, 40, 12, 36, "f16", PAPER, NARROW, (WALK,)),
+    (4619, 20, 12, 55, "bf16", PAPER, "forward_generic_kernel", (WALK,)),
+    (1336, 98, 600, 63, "f16", PACKED, GATHER, (WALK, COEF_GATHER)),
+    (958, 478, 135, 39, "bf16", PACKED, GATHER, (WALK, COEF_GATHER)),
+    (1100, 160, 132, 41, "bf16", PAPER, NARROW, (WALK, COEF_GATHER)),
+    (16384, 128, 128, 40, "f32", PACKED, NARROW, (WALK,)),
+    (13000, 160, 67, 36, "f32", PACKED, NARROW, (WALK,)),
+    (12289, 160, 132, 36, "f16", PACKED, NARROW, (WALK,)),
+    # the sorted stream: one block at its longest and the first of two, wide rows of gy copied tile by tile
+    (12288, 96, 132, 6, "f32", PACKED, SLAB, (LANE, STREAM)),
+    (12289, 96, 132, 6, "f32", PACKED, SLAB, (LANE, STREAM)),
+    (1500, 40, 2116, 9, "f32", PACKED, SLAB, (LANE, STREAM)),
+]
+
+# walks that are not cut into runs: a gradient that one wave writes repeats bit for bit
+WHOLE_STREAMS = (2000, 512, 1024, 8)
+# grad_x of the walk over the sorted samples repeats bit for bit, with the coefficient gradient and without
+WALKS = [(16384, 128, 128, 40), (3400, 386, 36, 35)]
+
+# as SHAPES, for a convolution: images, H, W, C, window, stride, n_out, G, storage, layout, kernels: the walk over
+# the sorted samples writes the transposed gradient of a layer on windows
+CONV = [
+    (9, 23, 24, 30, 2, 1, 130, 40, "f32", PACKED, NARROW, (WALK, "conv_input_gradient_kernel")),
+    (300, 9, 9, 15, 2, 2, 260, 37, "f32", PAPER, NARROW, (WALK, "conv_input_gradient_scatter_kernel")),
+]

@@ -44,6 +44,10 @@ def _stored(P, storage, desc, layout):
     return Ps, Ps
 
 
+# Tile edges, thresholds and odd sizes of every family of kernels.  The kernels named below are the ones that read
+# tables whose rows cannot be gathered 16 bytes at a time (Alg. 1's layout with an output count that is not a
+# multiple of four in float32, of eight in 16 bits); with other tables layers this small are gathered, and
+# streamed_shapes.py has the ones that reach each of these kernels with any table.
 SHAPES = [
     # B, n_in, n_out, G
     (1, 2, 1, 3),
@@ -206,11 +210,9 @@ def test_backward_matches_oracle(dev, oracle, shape, storage, layout):
         assert np.all(np.abs(gx.cpu().numpy().astype(np.float64) - master) <= bound + 1e-30)
 
 
-# one shape per way the coefficient gradient can be formed: float32 atomics in the generic
-# kernel (n_out not a multiple of 4), the cell-sorted stream written row by row, the same
-# stream cut into runs that meet through atomics (long batch, few pairs), the LDS-privatised
-# kernel of narrow layers
-# and the walk that forms both gradients at once (a grid too fine for the slab kernels)
+# layers whose gradients are gathered, with grad_x by the generic kernel (rows of 70 floats), by the kernel for few
+# outputs (3), by the gathers, and a batch whose coefficient gradient a workgroup sorts alone
+# (the sorted stream and the walk that forms both gradients: test_gpu_streamed.py)
 @pytest.mark.parametrize("shape", [(90, 12, 70, 8), (90, 12, 72, 8), (2100, 12, 72, 8), (90, 12, 3, 8),
                                    (2100, 10, 132, 40)])
 def test_backward_pieces_and_accumulate_flag(dev, oracle, shape):
@@ -250,7 +252,8 @@ def test_backward_pieces_and_accumulate_flag(dev, oracle, shape):
 @pytest.mark.parametrize("shape", [(1100, 140, 132, 16), (1024, 66, 4, 16), (4200, 6, 40, 32), (2100, 10, 132, 40)])
 def test_calls_can_reuse_the_records_in_the_workspace(dev, oracle, shape):
     """LMKAN_FLAG_WORKSPACE_HAS_RECORDS: a backward (or forward) call on the workspace an earlier call
-    on the same x left behind skips the preamble pass and gives what the full call gives."""
+    on the same x left behind gives what the full call gives.  (These layers are gathered and keep no records;
+    test_gpu_streamed.py has the ones whose calls skip the preamble pass.)"""
     B, n_in, n_out, G = shape
     x, P, gy = _inputs(B, n_in, n_out, G, 55, dev)
     desc = _desc(n_in, n_out, G)
@@ -261,7 +264,7 @@ def test_calls_can_reuse_the_records_in_the_workspace(dev, oracle, shape):
     want_y = pkg.lmkan_forward(desc, x, P)
     want_gx, want_gp = pkg.lmkan_backward(desc, x, P, gy)
     ws.fill_(0xFF)                                   # nothing usable in the workspace yet
-    y = pkg.lmkan_forward(desc, x, P, workspace=ws)  # writes the records
+    y = pkg.lmkan_forward(desc, x, P, workspace=ws)
     gx, gp = pkg.lmkan_backward(reuse, x, P, gy, workspace=ws)
     y2 = pkg.lmkan_forward(reuse, x, P, workspace=ws)
     gx2, gp2 = pkg.lmkan_backward(reuse, x, P, gy, workspace=ws)
@@ -279,16 +282,17 @@ def test_sorted_paths_repeat_bit_for_bit(dev):
     """What the header promises about run-to-run variation: the counting sort leaves the samples of
     a cell in the order of their indices, so a coefficient gradient that one wave writes row by
     row (stream not cut into runs) is the same float32 sum in every run, and so is the input
-    gradient of the walk over the sorted samples (its tiles are added in a fixed order).  Paths
-    that meet through float32 atomics are only held to the tolerance (other tests)."""
-    # a short stream: one run per (pair, tile)
+    gradient of the walk over the sorted samples (its tiles are added in a fixed order; layers that
+    take the walk: test_gpu_streamed.py).  Paths that meet through float32 atomics are only held to
+    the tolerance (other tests)."""
+    # a coefficient gradient that is gathered, from samples a workgroup sorts for itself
     B, n_in, n_out, G = 30, 12, 72, 4
     x, P, gy = _inputs(B, n_in, n_out, G, 51, dev)
     desc = _desc(n_in, n_out, G)
     runs = [pkg.lmkan_backward(desc, x, None, gy, need_grad_x=False)[1] for _ in range(3)]
     torch.cuda.synchronize()
     assert torch.equal(runs[0], runs[1]) and torch.equal(runs[0], runs[2])
-    # both gradients from the sorted walk: grad_x repeats exactly
+    # an input gradient that is gathered, by one wave per item
     B, n_in, n_out, G = 2100, 10, 132, 40
     x, P, gy = _inputs(B, n_in, n_out, G, 52, dev)
     desc = _desc(n_in, n_out, G)

@@ -151,3 +151,40 @@ def test_few_outputs_keep_their_kernel_when_the_table_is_not_aligned(rec):
         a, reuse, aligned = (names(launches) for _, launches in routes(calls, rec))
         assert a[0] == "preamble_records_kernel" and a[-1] == "forward_small_kernel" and reuse == a
         assert aligned == ["forward_gather_kernel"]
+
+
+DTYPE = {"f32": 0, "f16": 1, "bf16": 2}
+
+
+def test_streamed_shapes_reach_the_kernels_they_are_listed_for(rec):
+    from streamed_shapes import CONV, PACKED, SHAPES, STREAM, WALK, WALKS, WHOLE_STREAMS
+    layers = [(dict(n_in=n_in, n_out=n_out, grid=G, batch=B, dtype=DTYPE[storage], layout=layout), fwd, both)
+              for B, n_in, n_out, G, storage, layout, fwd, both in SHAPES]
+    layers += [(dict(n_in=k * k * c, n_out=n_out, grid=G, dtype=DTYPE[storage], layout=layout, conv=(n, h, w, c, k, k, s)), fwd, both)
+               for n, h, w, c, k, s, n_out, G, storage, layout, fwd, both in CONV]
+    got = routes([dict(layer, fn=fn) for layer, _, _ in layers for fn in ("forward", "backward")], rec)
+    seen = set()
+    for i, (layer, fwd, both) in enumerate(layers):
+        forward, backward = names(got[2 * i][1]), names(got[2 * i + 1][1])
+        assert fwd in forward, (layer, forward)
+        assert set(both) <= set(backward), (layer, backward)
+        seen |= {launch[0] for launch in got[2 * i][1] + got[2 * i + 1][1]}
+    # every form of these kernels, except those for tensors of 4 GB and more
+    forms = {f"forward_slab_kernel<{t}, {w}>" for t in ("float, 16, 1, 1", "half, 8, 2, 2", "bf16_t, 8, 2, 2") for w in (0, 17)}
+    forms |= {f"forward_slab_narrow_kernel<{t}, {s}>" for t in ("float, 16, 4", "half, 8, 8", "bf16_t, 8, 8") for s in ("true", "false")}
+    forms |= {f"backward_input_slab_kernel<{t}, 8, 2, 2, {w}>" for t in ("half", "bf16_t") for w in (0, 17)}
+    forms |= {f"backward_input_slab_narrow_kernel<{t}>" for t in ("float, 16, 4", "half, 8, 8", "bf16_t, 8, 8")}
+    forms |= {f"backward_fused_kernel<{t}, {gp}, true, {r}>" for t in ("float", "half", "bf16_t") for gp in ("true", "false") for r in ("true", "false")}
+    forms |= {"forward_slab_f16_kernel", "forward_lane32_f32_kernel", "forward_lane32_kernel<half>", "forward_lane32_kernel<bf16_t>",
+              "backward_input_lane32_f32_kernel", "backward_input_lane32_kernel<half>", "backward_input_lane32_kernel<bf16_t>",
+              "backward_input_lane_kernel<float, 0>", "backward_input_lane_kernel<float, 17>",
+              "backward_input_slab_f16_kernel<0>", "backward_input_slab_f16_kernel<17>", "backward_coef_stream_kernel<true>",
+              "gx_combine_kernel", "gy_tiles_kernel", "sum_partials_kernel", "sort_kernel"}
+    assert forms <= seen, forms - seen
+    # one wave per (pair, tile): the launch is no larger than that
+    B, n_in, n_out, G = WHOLE_STREAMS
+    (_, launches), = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, fn="backward", grad_x=0)], rec)
+    assert [launch[1][0] for launch in launches if launch[0].startswith(STREAM)] == [n_in // 2 * (n_out // 64)]
+    for B, n_in, n_out, G in WALKS:
+        (_, launches), = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, layout=PACKED, fn="backward")], rec)
+        assert WALK in names(launches)

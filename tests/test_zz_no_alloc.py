@@ -22,8 +22,8 @@ def test_static_scratch_forward_twice_second_call_smaller(oracle):
     assert torch.cuda.is_available(), "GPU tests need a GPU"
     pkg.lib()
     dev = torch.device("cuda:0")
-    # first: slab kernels with a pair split (records and partial outputs in the scratch, 5.6 MB);
-    # second: fewer rows, fewer pairs, another grid (records only) -- both well under the limit
+    # two layers that are gathered: a workspace is asked for and not used (partial outputs and records
+    # in the buffer: the test with fewer splits below)
     for i, (B, n_in, n_out, G) in enumerate([(1100, 140, 132, 16), (300, 10, 260, 3)]):
         desc = pkg.LayerDesc(n_in, n_out, G)
         need = pkg.lmkan_workspace_bytes(desc, B, False)

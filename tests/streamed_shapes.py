@@ -2,6 +2,7 @@
 enough for the oracle, with the kernels that their calls reach.  test_gpu_streamed.py runs them;
 test_routes_host.py checks, without a GPU, that they reach what they are listed for: the rules that choose a
 kernel follow measured times and move."""
+import random
 
 SLAB, SLAB16, LANE = "forward_slab_kernel", "forward_slab_f16_kernel", "backward_input_lane_kernel"
 LANE32, LANE32F = "forward_lane32_kernel", "forward_lane32_f32_kernel"
@@ -72,4 +73,52 @@ WALKS = [(16384, 128, 128, 40), (3400, 386, 36, 35)]
 CONV = [
     (9, 23, 24, 30, 2, 1, 130, 40, "f32", PACKED, NARROW, (WALK, "conv_input_gradient_kernel")),
     (300, 9, 9, 15, 2, 2, 260, 37, "f32", PAPER, NARROW, (WALK, "conv_input_gradient_scatter_kernel")),
+    # 64-output tiles: windows side by side, over odd channel counts (pairs straddle pixels), overlapping, with
+    # pixels that no window holds, single pixels
+    (20, 32, 32, 60, 2, 2, 126, 8, "f32", PACKED, SLAB, (LANE, STREAM)),
+    (40, 22, 23, 51, 2, 2, 128, 12, "f32", PAPER, SLAB, (LANE, STREAM)),
+    (8, 24, 24, 20, 3, 1, 100, 16, "f32", PACKED, SLAB, (LANE, STREAM)),
+    (60, 28, 29, 40, 3, 3, 184, 16, "f16", PACKED, SLAB16, (IN_SLAB16, STREAM)),
+    (24, 16, 16, 200, 1, 1, 128, 10, "f32", PACKED, SLAB, (LANE, STREAM)),
+    (7, 20, 20, 24, 3, 1, 140, 12, "f16", PAPER, SLAB, (IN_SLAB, STREAM)),
+    # 32-output and 16-output tiles
+    (20, 18, 18, 40, 3, 1, 62, 20, "f32", PACKED, LANE32F, (IN_LANE32F, STREAM)),
+    (20, 18, 18, 40, 3, 1, 94, 28, "bf16", PACKED, LANE32, (IN_LANE32, STREAM)),
+    (20, 18, 19, 40, 3, 1, 62, 26, "f32", PACKED, NARROW, (IN_NARROW, STREAM)),
 ]
+
+
+# Forward pass and both gradients at every grid that some slab fits: a layer per grid, storage type, layout and
+# output count rotating with G
+def every_grid(G):
+    storage, layout = ("f32", "f16", "bf16")[G % 3], (PACKED, PAPER)[(G // 3) % 2]
+    B, n_in, n_out = (1300, 600, 124) if G <= 16 else (2100, 400, 100) if G <= 34 else (3400, 386, 60)
+    if storage != "f32":
+        n_out += 64 if G <= 16 else 100
+        layout = PAPER if G <= 12 else layout     # (smaller 16-bit tables are gathered; 188 outputs cannot be)
+    return B, n_in, n_out + ((0, 1, 2, 3)[G % 4] if layout == PACKED else 0), G, storage, layout
+
+
+# Layers drawn at random from those that are more work than the gathers take: batch, sizes, grid, storage, layout, which
+# gradients ("both", "x", "coef"), whether the coefficient gradient is added to one that is there
+def drawn(n, seed):
+    rng, out = random.Random(seed), []
+    while len(out) < n:
+        B, n_in = round(100 * 150 ** rng.random()), 2 * rng.randint(60, 300)
+        n_out, G = rng.choice([rng.randint(9, 64), rng.randint(100, 128), rng.randint(30, 700)]), rng.choice([rng.randint(3, 16), rng.randint(17, 34), rng.randint(35, 48)])
+        storage, layout = rng.choice(["f32", "f32", "f16", "bf16"]), rng.choice([PAPER, PACKED, PACKED])
+        if layout == PAPER:
+            n_out = (n_out + 3) // 4 * 4
+        if not 2e7 < B * n_in // 2 * n_out < 8e7 or (G + 1) ** 2 * n_in // 2 * n_out > 4e7:
+            continue
+        grads = rng.choice(["both", "both", "x", "coef"])
+        out.append((B, n_in, n_out, G, storage, layout, grads, grads != "x" and rng.random() < 0.5))
+    return out
+
+
+DRAWN = drawn(60, 20260101)
+
+# layers recorded into a graph: partial outputs, tiles of every kind, runs that meet through atomics, blocks
+REPLAYED = [(1025, 500, 260, 3, "f32", PAPER), (169, 408, 1180, 16, "f16", PACKED), (2049, 300, 100, 17, "f32", PACKED),
+            (4097, 392, 21, 25, "f32", PACKED), (3400, 386, 36, 35, "f32", PACKED), (13000, 160, 67, 36, "f32", PACKED),
+            (12289, 96, 132, 6, "f32", PACKED)]

@@ -2,7 +2,8 @@
 every window) against the oracle, which gathers the windows into rows and calls its fully
 connected functions.  The library never writes the rows out, so these tests are what checks
 its window map: forward, the input gradient (summed over overlapping windows, zero outside
-every window) and the coefficient gradient, on every kernel family the dispatch can pick."""
+every window) and the coefficient gradient.  (Convolutions that are work enough for the slab kernels, the
+sorted stream and the walk: test_gpu_streamed.py.)"""
 import os
 
 import numpy as np
@@ -25,6 +26,8 @@ def dev():
     return torch.device("cuda:0")
 
 
+# (The kernels are those the sizes were chosen for.  Layers this small are gathered now, except where the
+# generic kernels or those for few outputs take them: streamed_shapes.py has convolutions that reach the others.)
 CASES = [
     # N, H, W, C, kh, kw, stride, n_out, G          rows  kernels
     (4, 32, 32, 6, 2, 2, 2, 16, 8),     # 1024  slab; the 2x2 stride-2 stage of the CIFAR-like backbone
@@ -175,7 +178,7 @@ def test_conv2d_accumulates_coefficient_gradient(dev, oracle):
 
 def _random_geometries(n, seed):
     """Seeded draws of image, window, stride, output count, grid, storage and layout.  A third of
-    the draws have enough windows (256 and more) for the slab kernels."""
+    the draws have 256 windows and more."""
     rng = np.random.RandomState(seed)
     out = []
     while len(out) < n:

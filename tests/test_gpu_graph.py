@@ -2,7 +2,7 @@
 with fill kernels only, so forward + backward can be recorded once and replayed (what a
 launch-bound small layer or a serving loop wants).  Every replay is checked against the eager
 result for the same inputs, with the program's own eager work and synchronisations between the
-replays."""
+replays.  (Steps of layers that stream their table: test_gpu_streamed.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -25,9 +25,9 @@ def _rand(shape, seed, dev, scale=1.0):
 
 
 @pytest.mark.parametrize("shape", [(256, 16, 16, 8),        # cfg1: launch-bound
-                                   (1100, 140, 132, 16),    # pair splits, partial outputs, ragged tiles
-                                   (300, 8, 20, 34),        # 16-output slabs
-                                   (513, 10, 5, 6)])        # small-output kernels
+                                   (1100, 140, 132, 16),    # gathers of a middling layer
+                                   (300, 8, 20, 34),        # and on a fine grid
+                                   (513, 10, 5, 6)])        # few outputs
 def test_forward_backward_replay_matches_eager(dev, shape):
     B, n_in, n_out, G = shape
     desc = pkg.LayerDesc(n_in, n_out, G)

@@ -2,9 +2,9 @@
 storage type, a table layout, which gradients are asked for and whether the coefficient gradient
 is added to an existing one, so that combinations nobody listed by hand meet the dispatch
 (which kernel, which workspace layout) and the oracle.  Sizes are small enough for the oracle;
-a quarter of the draws are wide enough (pairs x outputs >= 8192) for the slab kernels to take
-short batches, a quarter are middling layers (16 to 158 inputs, 1 to 260 outputs) on either side
-of the batch and work thresholds.
+a quarter of the draws are wide (pairs x outputs >= 8192) with short batches, a quarter are middling
+layers (16 to 158 inputs, 1 to 260 outputs) on either side of the batch and work thresholds.  Most are
+gathered; draws of layers that stream their table are in streamed_shapes.py.
 
 LMKAN_TEST_DRAWS and LMKAN_TEST_SEED in the environment replace the number of draws and the seed
 (the committed run uses 144 draws of seed 20240917)."""
@@ -28,7 +28,7 @@ def _draws(n, seed):
     out = []
     for i in range(n):
         G = int(rng.choice([3, 4, 5, 8, 12, 16, 17, 20, 24, 32, 34, 35, 40, 48, 49, 64]))
-        if i % 4 == 0:       # wide enough for the slab kernels whatever the batch
+        if i % 4 == 0:       # wide, with any batch
             n_in = 2 * int(rng.randint(33, 70))
             n_out = int(rng.randint(8192 // (n_in // 2) + 1, 8192 // (n_in // 2) + 40))
             B = int(rng.choice([1, 2, 17, 64, 200, 300]))

@@ -7,7 +7,7 @@ import torch
 import paper_2509_07103_amd as pkg
 from paper_2509_07103_amd import workloads as wl
 from parity_util import ORACLE_DTYPE, TOL_F32, bits, output_rel_err, pair_slice_rel_err, rowwise_rel_err
-from streamed_shapes import CONV, SHAPES, WALKS, WHOLE_STREAMS
+from streamed_shapes import CONV, DRAWN, REPLAYED, SHAPES, WALKS, WHOLE_STREAMS, every_grid
 
 pytestmark = pytest.mark.gpu
 
@@ -22,35 +22,41 @@ def _inputs(B, n_in, n_out, G, seed, dev):
     return x.to(dev), P.to(dev), gy.to(dev)
 
 
-def _table(P, n_in, n_out, G, storage, layout):
+def _table(P, n_in, n_out, G, storage, layout, flags=0):
     paper = pkg.LayerDesc(n_in, n_out, G, coef_dtype=DT_CODE[storage])
     stored = wl.store(P, storage).contiguous()
-    desc = pkg.LayerDesc(n_in, n_out, G, coef_dtype=DT_CODE[storage], coef_layout=layout)
+    desc = pkg.LayerDesc(n_in, n_out, G, coef_dtype=DT_CODE[storage], coef_layout=layout, flags=flags)
     return desc, stored, pkg.lmkan_pack(paper, stored) if layout == pkg.LMKAN_LAYOUT_PACKED else stored
 
 
-def _coef_matches(oracle, gP, xh, gyh, G, pairs):
+def _coef_matches(oracle, gP, xh, gyh, G, pairs, base=0.0):
     """Element by element on a sample of pairs.  Up to 20000 terms meet in a node and may cancel: the scale of a
-    sum's rounding is that of its magnitudes."""
+    sum's rounding is that of its magnitudes; added to `base`, it is rounded at base's magnitude, once for every
+    run of the stream that adds (eight half units cover the cases here)."""
     for k in range(0, pairs, max(1, pairs // 8)):
         want = oracle.backward_coef_pair(xh, gyh, G, k)
         scale = np.abs(oracle.backward_coef_pair(xh, np.abs(gyh), G, k)).max()
-        assert np.abs(gP[:, :, k, :] - want).max() <= TOL_F32 * scale
-        assert np.all(gP[:, :, k, :][want == 0.0] == 0.0)
+        assert np.abs(gP[:, :, k, :] - (want + base)).max() <= TOL_F32 * scale + 8 * 2.0 ** -24 * abs(base)
+        assert np.all(gP[:, :, k, :][want == 0.0] == base)
 
 
-@pytest.mark.parametrize("B,n_in,n_out,G,storage,layout", [s[:6] for s in SHAPES])
-def test_layers_match_the_oracle(oracle, B, n_in, n_out, G, storage, layout):
+@pytest.mark.parametrize("B,n_in,n_out,G,storage,layout,grads,accumulate",
+                         [(*s[:6], "both", False) for s in SHAPES] + [(*every_grid(G), "both", False) for G in range(3, 49)] + DRAWN)
+def test_layers_match_the_oracle(oracle, B, n_in, n_out, G, storage, layout, grads, accumulate):
     dev = torch.device("cuda:0")
     x, P, gy = _inputs(B, n_in, n_out, G, 91, dev)
-    desc, stored, table = _table(P, n_in, n_out, G, storage, layout)
+    flags = pkg.LMKAN_FLAG_ACCUMULATE_GRAD_COEF if accumulate else 0
+    desc, stored, table = _table(P, n_in, n_out, G, storage, layout, flags)
+    base = torch.full(desc.coef_shape(), 0.5, device=dev) if accumulate else None
     y = pkg.lmkan_forward(desc, x, table)
-    gx, gP = pkg.lmkan_backward(desc, x, table, gy)
+    gx, gP = pkg.lmkan_backward(desc, x, table, gy, need_grad_x=grads != "coef", need_grad_coef=grads != "x", grad_coef=base)
     torch.cuda.synchronize()
     xh, gyh, code = x.cpu().numpy(), gy.cpu().numpy(), ORACLE_DTYPE[storage]
     assert output_rel_err(y.cpu().numpy(), oracle.forward(xh, bits(stored), G, dtype=code, threads=8)) <= TOL_F32
-    assert rowwise_rel_err(gx.cpu().numpy(), oracle.backward_input(xh, bits(stored), gyh, G, dtype=code, threads=8)) <= TOL_F32
-    _coef_matches(oracle, gP.cpu().numpy(), xh, gyh, G, n_in // 2)
+    if grads != "coef":
+        assert rowwise_rel_err(gx.cpu().numpy(), oracle.backward_input(xh, bits(stored), gyh, G, dtype=code, threads=8)) <= TOL_F32
+    if grads != "x":
+        _coef_matches(oracle, gP.cpu().numpy(), xh, gyh, G, n_in // 2, 0.5 if accumulate else 0.0)
 
 
 @pytest.mark.parametrize("n,h,w,c,window,stride,n_out,G,storage,layout", [s[:10] for s in CONV])
@@ -120,3 +126,40 @@ def test_input_gradients_of_the_walk_repeat_bit_for_bit(B, n_in, n_out, G):
     runs = [pkg.lmkan_backward(desc, x, table, gy)[0] for _ in range(3)]
     torch.cuda.synchronize()
     assert torch.equal(runs[0], runs[1]) and torch.equal(runs[0], runs[2])
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,storage,layout", REPLAYED)
+def test_replays_of_a_captured_step_match_eager_calls(B, n_in, n_out, G, storage, layout):
+    """Records, sort, partial outputs, runs that meet in a cleared gradient: recorded once and replayed on other
+    inputs, with eager work and synchronisations between the replays."""
+    dev = torch.device("cuda:0")
+    x, P, gy = _inputs(B, n_in, n_out, G, 97, dev)
+    desc, _, table = _table(P, n_in, n_out, G, storage, layout)
+    reuse = pkg.LayerDesc(n_in, n_out, G, coef_dtype=desc.coef_dtype, coef_layout=layout, flags=pkg.LMKAN_FLAG_WORKSPACE_HAS_RECORDS)
+    need = max(pkg.lmkan_workspace_bytes(desc, B, False), pkg.lmkan_workspace_bytes(desc, B, True))
+    ws = torch.zeros(need, dtype=torch.uint8, device=dev)
+    y, gx, gP = torch.empty_like(gy), torch.empty_like(x), torch.empty(desc.coef_shape(), device=dev)
+
+    def step():
+        pkg.lmkan_forward(desc, x, table, y=y, workspace=ws)
+        pkg.lmkan_backward(reuse, x, table, gy, grad_x=gx, grad_coef=gP, workspace=ws)
+
+    step()                      # kernel attributes are set outside the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for rep in range(3):
+        xs, _, gys = _inputs(B, n_in, n_out, G, 100 + rep, dev)
+        y_e = pkg.lmkan_forward(desc, xs, table)
+        gx_e, gP_e = pkg.lmkan_backward(desc, xs, table, gys)
+        torch.cuda.synchronize()
+        x.copy_(xs)
+        gy.copy_(gys)
+        for t in (y, gx, gP):
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, y_e), rep             # the forward sums in a fixed order
+        assert float((gx - gx_e).abs().max()) <= TOL_F32 * float(gx_e.abs().max())
+        assert float((gP - gP_e).abs().max()) <= TOL_F32 * float(gP_e.abs().max())

@@ -157,7 +157,7 @@ DTYPE = {"f32": 0, "f16": 1, "bf16": 2}
 
 
 def test_streamed_shapes_reach_the_kernels_they_are_listed_for(rec):
-    from streamed_shapes import CONV, PACKED, SHAPES, STREAM, WALK, WALKS, WHOLE_STREAMS
+    from streamed_shapes import CONV, PACKED, REPLAYED, SHAPES, STREAM, WALK, WALKS, WHOLE_STREAMS, every_grid
     layers = [(dict(n_in=n_in, n_out=n_out, grid=G, batch=B, dtype=DTYPE[storage], layout=layout), fwd, both)
               for B, n_in, n_out, G, storage, layout, fwd, both in SHAPES]
     layers += [(dict(n_in=k * k * c, n_out=n_out, grid=G, dtype=DTYPE[storage], layout=layout, conv=(n, h, w, c, k, k, s)), fwd, both)
@@ -188,3 +188,9 @@ def test_streamed_shapes_reach_the_kernels_they_are_listed_for(rec):
     for B, n_in, n_out, G in WALKS:
         (_, launches), = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, layout=PACKED, fn="backward")], rec)
         assert WALK in names(launches)
+    # forward pass at every grid, and what is recorded into graphs: a kernel that streams the table
+    layers = [every_grid(G) for G in range(3, 49)] + REPLAYED
+    got = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, dtype=DTYPE[storage], layout=layout, fn="forward")
+                  for B, n_in, n_out, G, storage, layout in layers], rec)
+    gathered = [layer for layer, (_, launches) in zip(layers, got) if "forward_gather_kernel" in names(launches)]
+    assert len(gathered) <= 2, gathered

@@ -343,7 +343,7 @@ class Bench:
         if not detailed:
             return summary
         out = {
-            # the benchmark's metric; `value` is the samples/sec of a forward + backward step
+            # `value` is the samples/sec of a forward + backward step
             "metric": f"lmKAN layer samples/sec + achieved gather GB/s vs HBM peak ({w.n_in}->{n_out}, 1 GPU)",
             "value": round(B / (ms_per_step * 1e-3), 1),
             "unit": "samples/s",
@@ -528,7 +528,7 @@ def main():
     out["roofline"]["measured"] = b.machine()
     headline = args.workload == HEADLINE and not args.grid
     if headline and not args.no_configs:
-        # the other four configurations of the benchmark spec, short runs (5 warm-up + 15 timed steps each;
+        # the other four configurations, short runs (5 warm-up + 15 timed steps each;
         # the 46 ms steps of cfg5: 2 + 5)
         wl = b.wl
         configs = {}

@@ -170,8 +170,10 @@ lmkan_status lmkan_pack(const lmkan_desc *desc, const void *coef_paper_dev, void
  *             pair) plus per-pair tables) when a kernel that walks it can serve the
  *             shape; for grad_x a transposed float32 copy of it and, for grids too
  *             fine for the slab kernels, its per-output-tile partial sums (8 bytes
- *             per (sample, pair) and 64 outputs).  The size for pass = 1 covers the
- *             other two.
+ *             per (sample, pair) and 64 outputs); for the coefficient gradient of one
+ *             output over long batches, the partial gradients of its workgroups (a
+ *             call without that workspace is taken too: they then add atomically).
+ *             The size for pass = 1 covers the other two.
  * The contents are scratch: nothing is kept between calls, and two calls that share a
  * workspace must not overlap in time.  Any other pass gives 0.
  */
@@ -235,11 +237,14 @@ lmkan_status lmkan_forward_static(const lmkan_desc *desc, int64_t batch, const f
  * (samples of a cell stay in index order), so a grad_coef written by the
  * cell-sorted kernels repeats bit for bit when every (pair, 64-output tile) is
  * walked by one wave (batch <= 12288 rows and at least 4096 (pair, tile) streams,
- * e.g. 1024 -> 1024); shorter layers may and longer batches do cut the streams
+ * e.g. 1024 -> 1024), and so does one that small layers and batches gather, and
+ * the one of a single output over long batches (many samples per table node),
+ * whose partial gradients are added in a fixed order; shorter layers may and longer batches do cut the streams
  * into runs that meet through float32 atomics, and the generic kernels and the
- * kernels for very few outputs use atomics throughout: there the last bits can
- * differ.  grad_x repeats bit for bit on the
- * sorted walk (grids finer than 34 intervals) and in the kernels for very few
+ * other kernels for very few outputs use atomics throughout: there the last bits
+ * can differ.  grad_x repeats bit for bit on the
+ * sorted walk (grids finer than 34 intervals), where it is gathered (windows that
+ * overlap aside) and in the kernels for very few
  * outputs (one output, or up to eight where no slab kernel applies); the slab
  * kernels (grids up to 34) add their output tiles with float32 atomics.
  */

@@ -12,7 +12,7 @@
 // batch through L2) feeds eight 4x4x1 float32 MFMAs, four for each gradient.
 //
 // Coefficient gradient: as in lmkan_backward.hip (the four samples of a chunk in the four
-// 16-lane groups, block-broadcast products, two-row window of the table in LDS).
+// 16-lane groups, block-broadcast products, a ring of table nodes in LDS).
 //
 // Input gradient: the MFMA wants the four samples of a chunk in the four lanes of a block,
 // which is not how a coalesced load leaves them, so the rows of four chunks go through LDS

@@ -815,11 +815,12 @@ static bool rows_by_16_bytes(const LayerShape &s)
     return s.layout == LMKAN_LAYOUT_PACKED || s.n_out % (s.dtype == LMKAN_F32 ? 4 : 8) == 0;
 }
 
-// Where the gathers win.  All three rules compare a fitted time of the gathering kernel with one of the
-// kernels it would replace (microseconds; fitted to 1900 random layers of 4 ... 1024 inputs and outputs,
-// 1 ... 200000 rows, grids of 4 to 40, all table types).  The fits are good to a third, so a gather has
-// to promise 15 % less: the choice then costs 1 to 2 % over the better of the two, never gathering
-// 3.5 times as much, and gathering where it is the slower one 0.1 %.
+// Where the gathers win.  The rules compare a fitted time of the gathering kernel with one of the
+// kernels it would replace (microseconds).  The fits are good to a third, so a gather has to promise 15 %
+// less.  Over 500 random layers (4 ... 1024 inputs, 2 ... 1024 outputs, 1 ... 200000 rows, grids of 4 to 40, all
+// table types) the choice takes 0.6 % longer than the better of the two for the forward pass, 0.8 % for
+// grad_x, 8 % for grad_coef (it sorts sparse cells that a gather takes a fourth of the time for); gathering
+// always 7, 7 and 8 %, never three times as long.
 constexpr double kPromise = 0.85;
 
 static double table_bytes(const LayerShape &s)

@@ -26,7 +26,7 @@ class Workload:
     storage: tuple = ("f32",)     # coefficient storage variants measured for this config
 
 
-# benchmark configs; cfg2 is a stack, listed layer by layer.
+# The configurations; cfg2 is a stack, listed layer by layer.
 CFG1 = Workload("cfg1_16x16_G8", 16, 16, 8, 256, 0.1, 1)
 CFG2_LAYERS = (
     Workload("cfg2_l0_64x256_G16", 64, 256, 16, 65536, 0.1, 20, x_kind="correlated"),

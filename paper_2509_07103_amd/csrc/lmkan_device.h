@@ -177,8 +177,8 @@ __device__ __forceinline__ int count_in_order(int *words, int counter, int key, 
     const auto meet = [&](int bit) {
         const unsigned set = (unsigned)__builtin_amdgcn_sbfe(key, bit, 1);  // all ones or zero
         const uint64_t those = __ballot(set != 0);
-        lo &= ~((unsigned)those ^ set);
-        hi &= ~((unsigned)(those >> 32) ^ set);
+        lo = __builtin_amdgcn_bitop3_b32(lo, (unsigned)those, set, 0x90);  // lo & ~(those ^ set)
+        hi = __builtin_amdgcn_bitop3_b32(hi, (unsigned)(those >> 32), set, 0x90);
     };
 #pragma unroll
     for (int bit = 0; bit < 8; ++bit) meet(bit);

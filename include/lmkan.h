@@ -239,14 +239,14 @@ lmkan_status lmkan_forward_static(const lmkan_desc *desc, int64_t batch, const f
  * walked by one wave (batch <= 12288 rows and at least 4096 (pair, tile) streams,
  * e.g. 1024 -> 1024), and so does one that small layers and batches gather, and
  * the one of a single output over long batches (many samples per table node),
- * whose partial gradients are added in a fixed order; shorter layers may and longer batches do cut the streams
- * into runs that meet through float32 atomics, and the generic kernels and the
- * other kernels for very few outputs use atomics throughout: there the last bits
- * can differ.  grad_x repeats bit for bit on the
- * sorted walk (grids finer than 34 intervals), where it is gathered (windows that
- * overlap aside) and in the kernels for very few
- * outputs (one output, or up to eight where no slab kernel applies); the slab
- * kernels (grids up to 34) add their output tiles with float32 atomics.
+ * whose partial gradients are added in a fixed order; shorter layers may and longer
+ * batches do cut the streams into runs that meet through float32 atomics, and the
+ * generic kernels and the other kernels for very few outputs use atomics throughout:
+ * there the last bits can differ.  grad_x repeats bit for bit on the sorted walk
+ * (grids finer than 34 intervals), where it is gathered (windows that overlap aside)
+ * and in the kernels for very few outputs (one output, or up to eight where no slab
+ * kernel applies); the slab kernels (grids up to 34) add their output tiles with
+ * float32 atomics.
  */
 lmkan_status lmkan_backward(const lmkan_desc *desc, int64_t batch, const float *x_dev,
                             const void *coef_dev, const float *grad_y_dev, float *grad_x_dev,

@@ -168,8 +168,8 @@ __device__ __forceinline__ void fmac_row_bcast(float &acc, float w, float c)
 // `wide` if it has more than 8) tells the counters of the wave apart.
 // What an atomic returns depends on the order in which it takes the lanes that meet in a counter, which is the
 // hardware's and not documented.  So the lanes with the same key are found by a ballot per bit, the counter is
-// read before any of them adds (a wave's LDS operations take place in the order they are issued, and
-// an address that may be the same keeps the compiler from exchanging them), and nothing waits in between.
+// read before any of them adds (a wave's LDS operations take place in the order they are issued; the empty
+// instructions keep the compiler from exchanging or joining them), and nothing waits in between.
 // (Five vector instructions per bit.  One lane adding for all that meet, and handing out what the atomic
 // returned, waits for LDS twice per sample: 11 us of a step with 512 pairs x 8192 samples instead of 4.)
 __device__ __forceinline__ int count_in_order(int *words, int counter, int key, bool wide)
@@ -190,7 +190,9 @@ __device__ __forceinline__ int count_in_order(int *words, int counter, int key, 
     int *word = &words[counter >> 1];
     const int shift = (counter & 1) * 16;
     const int held = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("" : : : "memory");
     (void)__hip_atomic_fetch_add(word, 1 << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("" : : : "memory");
     return ((held >> shift) & 0xffff) + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
 }
 

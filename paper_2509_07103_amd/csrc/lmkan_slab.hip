@@ -15,6 +15,7 @@
 // the weights directly from that lane's registers through the DPP row broadcast
 // of v_fmac_f32, so the four multiply-adds of Alg. 1 cost exactly four VALU
 // instructions per output quadruple.
+#include <type_traits>
 #include <utility>
 
 #include "lmkan_kernels.h"
@@ -23,6 +24,9 @@
 namespace lmkan {
 
 namespace {
+
+template <int N>
+using Int = std::integral_constant<int, N>;
 
 constexpr int kTile = LMKAN_PACK_TILE;  // 64 outputs per workgroup tile
 constexpr int kRowBytes = kTile * 4;    // one table row of a float32 slab in LDS
@@ -126,52 +130,14 @@ __global__ __launch_bounds__(256) void preamble_records_kernel(GridTab tab, cons
     }
 }
 
-// Stream the slab of (pair k, output tile jt) into LDS.  A wave instruction moves
-// 4 table rows (one per 16-lane group, 16 bytes per lane); the 1 KiB it writes is
-// contiguous in LDS.  Chunks are dealt round-robin to the waves.
-// LPS = lanes per table row: 16 for 64-output tiles, 4 for 16-output tiles (a 1 KiB chunk is
-// then 16 rows).
-template <int WAVES, int LPS = 16>
-__device__ __forceinline__ void issue_slab_load(const SlabArgs &a, float *slab, int k, int jt, int wave,
-                                                int lane)
-{
-    constexpr int NG = 64 / LPS;  // rows per chunk
-    const int g = lane / LPS, l16 = lane % LPS;
-    const unsigned base = __builtin_amdgcn_readfirstlane(lds_address(slab));
-    if (LPS == 16 && a.packed) {
-        // the slab is one contiguous run of nodes x 256 bytes: chunk c sits at byte c * 1024
-        const char *src = reinterpret_cast<const char *>(static_cast<const float *>(a.P) + (int64_t)k * a.map.s_pair +
-                                                         (int64_t)jt * a.map.s_tile);
-        const int full = a.nodes >> 2;  // chunks made of four rows
-        const unsigned lane_off = (unsigned)lane * 16u;
-        for (int c = wave; c < full; c += WAVES)
-            lds_dma16_uniform(src + (size_t)c * (4 * kRowBytes), lane_off, base + c * (4 * kRowBytes));
-        const int rest = a.nodes & 3;  // rows of the last, partial chunk
-        if (rest != 0 && full % WAVES == wave && g < rest)
-            lds_dma16_uniform(src + (size_t)full * (4 * kRowBytes), lane_off, base + full * (4 * kRowBytes));
-        return;
-    }
-    const int col = jt * (LPS * 4) + l16 * 4;
-    const float *src = static_cast<const float *>(a.P) + (int64_t)k * a.map.s_pair +
-                       (int64_t)(col >> 6) * a.map.s_tile + (col & 63);
-    const int chunks = (a.nodes + NG - 1) / NG;
-    const bool col_ok = col < a.col_limit;  // never read past a table row
-    for (int c = wave; c < chunks; c += WAVES) {
-        const int node = c * NG + g;
-        if (node < a.nodes && col_ok)
-            lds_dma16(src + (int64_t)node * a.map.s_node,
-                      __builtin_amdgcn_readfirstlane(base + c * (4 * kRowBytes)));
-    }
-}
+constexpr int kMaxSlabBytes = 80 * 1024;  // one of the two slab buffers
 
 // Filling a slab from 16-bit storage: the values travel through registers, are widened to
 // float32 and written with ds_write_b128, so the slab in LDS and everything that reads it
 // are those of the float32 path while the table costs half the bytes in HBM and L2.
 // issue() requests the wave's chunks (8 bytes per lane: the lane's four outputs of one
 // row), commit() converts and stores them; between the two the wave computes on the other
-// buffer.  For float32 storage issue() is the LDS-direct load above and commit() is empty.
-constexpr int kMaxSlabBytes = 80 * 1024;  // one of the two slab buffers
-
+// buffer.  (float32 storage: SlabFeed.)
 // A slab that has LDS to itself (up to 160 KiB) is filled in four phases of the same size.
 template <typename CT, int WAVES, int LPS = 16, int PHASES = 2>
 struct SlabFill {
@@ -222,19 +188,6 @@ struct SlabFill {
                 *reinterpret_cast<float4 *>(slab + c * (4 * kTile) + lane * 4) = f;
             }
         }
-    }
-};
-
-template <int WAVES, int LPS, int PHASES>
-struct SlabFill<float, WAVES, LPS, PHASES> {
-    template <int PHASE>
-    __device__ __forceinline__ void issue(const SlabArgs &a, float *slab, int k, int jt, int wave, int lane)
-    {
-        if constexpr (PHASE == 0) issue_slab_load<WAVES, LPS>(a, slab, k, jt, wave, lane);
-    }
-    template <int PHASE>
-    __device__ __forceinline__ void commit(const SlabArgs &, float *, int, int)
-    {
     }
 };
 
@@ -291,17 +244,22 @@ __device__ __forceinline__ void fma_corners(float *acc, const Corners &c, float 
 // Software pipeline over the SETS * 16 steps of one pair: the rows of step T + AHEAD are
 // requested from LDS before the multiply-adds of step T are issued.
 
-template <int T, int END, int TOTAL, int AHEAD, int W_CT>
+template <typename PACE, int T, int END, int TOTAL, int AHEAD, int W_CT>
 __device__ __forceinline__ void slab_pipeline(float *acc, Corners (&ring)[AHEAD + 1], int lane_base,
                                               const int *off, const float *w00, const float *w10,
                                               const float *w01, const float *w11, int W)
 {
     if constexpr (T < END) {
+        PACE::template step_priority<T, TOTAL>();
+        // (the empty statement ties the address to the step before: it keeps the reads of a step between the
+        // multiply-adds of the steps before it, where the compiler would request several steps and spill them)
+        if constexpr (T > 0)
+            asm volatile("" : "+v"(lane_base), "+v"(acc[4 * T - 4]), "+v"(acc[4 * T - 3]), "+v"(acc[4 * T - 2]), "+v"(acc[4 * T - 1]));
         if constexpr (T + AHEAD < TOTAL)
             load_corners<(T + AHEAD) % 16, W_CT>(ring[(T + AHEAD) % (AHEAD + 1)], lane_base, off[(T + AHEAD) / 16], W);
         fma_corners<T % 16>(acc + 4 * T, ring[T % (AHEAD + 1)], w00[T / 16], w10[T / 16], w01[T / 16],
                             w11[T / 16]);
-        slab_pipeline<T + 1, END, TOTAL, AHEAD, W_CT>(acc, ring, lane_base, off, w00, w10, w01, w11, W);
+        slab_pipeline<PACE, T + 1, END, TOTAL, AHEAD, W_CT>(acc, ring, lane_base, off, w00, w10, w01, w11, W);
     }
 }
 
@@ -350,26 +308,39 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     auto fetch_records = [&](int k) {
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            const int64_t n = n_wave + s * 64 + lane;
-            nx_node[s] = 0;
-            nx_u[s] = 0.f;
-            nx_v[s] = 0.f;
-            if (n < a.B) {
-                const int64_t o = (int64_t)k * a.B + n;
-                nx_node[s] = a.rec_node[o];
-                nx_u[s] = a.rec_u[o];
-                nx_v[s] = a.rec_v[o];
-            }
+            const RecordBase rb(n_wave + s * 64, a.B);
+            const int64_t o = (int64_t)k * a.B + rb.n;
+            const unsigned l = rb.lane_index(lane);
+            nx_node[s] = (a.rec_node + o)[l];
+            nx_u[s] = (a.rec_u + o)[l];
+            nx_v[s] = (a.rec_v + o)[l];
         }
     };
 
+    // A float32 slab comes by LDS-direct loads and the waves hand the buffers over by the gate.  A 16-bit slab is
+    // staged through registers until the last steps of a pair, which leaves a gate nothing to relax (measured:
+    // bfloat16, 1024 -> 1024, G = 16: the same time), and keeps a barrier per pair.
+    constexpr bool kDirect = sizeof(CT) == 4;
+    typedef std::conditional_t<kDirect, PaceEarly, PaceLate> PACE;
+    SlabGate gate;
+    SlabFeed<kRowBytes, WAVES> feed;
     SlabFill<CT, WAVES> fill;
+    if constexpr (kDirect) {
+        gate.init(__builtin_amdgcn_readfirstlane(lds_address(smem)) + 8 * (unsigned)slab_floats);
+        feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kTile, wave, lane);
+    }
     if (k_begin < k_end) {
-        fill.template issue<0>(a, slab0, k_begin, jt, wave, lane);
-        fill.template commit<0>(a, slab0, wave, lane);
-        fill.template issue<1>(a, slab0, k_begin, jt, wave, lane);
-        fill.template commit<1>(a, slab0, wave, lane);
         fetch_records(k_begin);
+        if constexpr (kDirect) {
+            feed.issue(__builtin_amdgcn_readfirstlane(lds_address(slab0)), k_begin);
+            __syncthreads();  // the counters are in place
+            gate.slab_landed();
+        } else {
+            fill.template issue<0>(a, slab0, k_begin, jt, wave, lane);
+            fill.template commit<0>(a, slab0, wave, lane);
+            fill.template issue<1>(a, slab0, k_begin, jt, wave, lane);
+            fill.template commit<1>(a, slab0, wave, lane);
+        }
     }
     const int lane_bytes = l16 * 16;
     for (int k = k_begin; k < k_end; ++k) {
@@ -388,13 +359,15 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             w01[s] = a_lo * v;
             w11[s] = u * v;
         }
-        // this wave's slab loads for pair k have landed; after the barrier everybody's have,
-        // and everybody has finished reading the other buffer (pair k-1)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (k + 1 < k_end) {
-            fill.template issue<0>(a, slab_next, k + 1, jt, wave, lane);
-            fetch_records(k + 1);
+        const int step = k - k_begin;
+        const bool more = k + 1 < k_end;
+        const int k_next = more ? k + 1 : k;  // (records are read again for nobody rather than not read)
+        if constexpr (kDirect) {
+            gate.wait_landed<WAVES>(step);
+        } else {
+            __syncthreads();  // the slab of pair k is complete, nobody reads the other buffer any more
+            if (more) fill.template issue<0>(a, slab_next, k_next, jt, wave, lane);
+            fetch_records(k_next);
         }
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
@@ -405,15 +378,31 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         const int lane_base = (int)lds_address(slab) + lane_bytes;
         load_corners<0, W_CT>(ring[0], lane_base, off[0], a.W);
         if constexpr (AHEAD > 1) load_corners<1, W_CT>(ring[1], lane_base, off[0], a.W);
-        // the steps of the pair in two halves; a 16-bit table is staged half a slab at a time
-        constexpr int kHalf = SETS * 8;
-        slab_pipeline<0, kHalf, SETS * 16, AHEAD, W_CT>(acc, ring, lane_base, off, w00, w10, w01, w11, a.W);
-        if (k + 1 < k_end) {
-            fill.template commit<0>(a, slab_next, wave, lane);
-            fill.template issue<1>(a, slab_next, k + 1, jt, wave, lane);
+        constexpr int T = SETS * 16;
+        auto steps = [&](auto from, auto to) {
+            slab_pipeline<PACE, decltype(from)::value, decltype(to)::value, T, AHEAD, W_CT>(acc, ring, lane_base, off, w00, w10, w01,
+                                                                                     w11, a.W);
+        };
+        if constexpr (kDirect) {
+            constexpr int kFill = T * PACE::kFill / 16, kLanded = T * PACE::kLanded / 16;
+            steps(Int<0>{}, Int<kFill>{});
+            gate.wait_read<WAVES>(step);
+            feed.issue(__builtin_amdgcn_readfirstlane(lds_address(slab_next)), k_next, more);
+            fetch_records(k_next);
+            steps(Int<kFill>{}, Int<kLanded>{});
+            gate.slab_landed();
+            steps(Int<kLanded>{}, Int<T>{});
+            gate.slab_read();
+        } else {
+            // staged half a slab at a time
+            steps(Int<0>{}, Int<T / 2>{});
+            if (more) {
+                fill.template commit<0>(a, slab_next, wave, lane);
+                fill.template issue<1>(a, slab_next, k_next, jt, wave, lane);
+            }
+            steps(Int<T / 2>{}, Int<T>{});
+            if (more) fill.template commit<1>(a, slab_next, wave, lane);
         }
-        slab_pipeline<kHalf, SETS * 16, SETS * 16, AHEAD, W_CT>(acc, ring, lane_base, off, w00, w10, w01, w11, a.W);
-        if (k + 1 < k_end) fill.template commit<1>(a, slab_next, wave, lane);
     }
 
     // lane (g, l16) holds outputs jt*64 + 4*l16 .. +3 of samples n_wave + set*64 + 16*g + step
@@ -677,16 +666,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     float *slab1 = smem + slab_floats;
     float *s_invh = smem + 2 * slab_floats;
     for (int i = threadIdx.x; i < a.tab.G; i += blockDim.x) s_invh[i] = a.tab.inv_h[i];
-    SlabArgs sa;  // only the fields issue_slab_load reads
-    sa.P = a.P;
-    sa.map = a.map;
-    sa.nodes = a.nodes;
-    sa.col_limit = a.col_limit;
-    sa.packed = a.packed;
-
-    const int64_t n = (int64_t)btile * (WAVES * 64) + wave * 64 + lane;
+    const int64_t n_wave = (int64_t)btile * (WAVES * 64) + wave * 64, n = n_wave + lane;
     const bool valid = n < a.B;
-    const int64_t n_rd = valid ? n : a.B - 1;
 
     // register j: gy of outputs jt*64 + 4 p .. + 3 with p = (j + l15) mod 16
     float4 gyr[16];
@@ -700,48 +681,37 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 
     // columns past the end of a ragged output tile are never loaded: make them read as zero
     for (int i = threadIdx.x; i < 2 * slab_floats; i += blockDim.x) smem[i] = 0.0f;
-    __syncthreads();  // zeros and s_invh in place before any slab load lands
-    SlabFill<CT, WAVES> fill;
+    typedef PaceLate PACE;
+    SlabGate gate;
+    gate.init(__builtin_amdgcn_readfirstlane(lds_address(smem)) + 8 * (unsigned)slab_floats + LMKAN_MAX_GRID * 4);
+    __syncthreads();  // zeros, s_invh and the counters in place before any slab load lands
+    SlabFeed<kRowBytes, WAVES> feed;
+    feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kTile, wave, lane);
     int nx_node = 0;
     float nx_u = 0.f, nx_v = 0.f;
     auto fetch_record = [&](int k) {
-        const int64_t o = (int64_t)k * a.B + n_rd;
-        nx_node = a.rec_node[o];
-        nx_u = a.rec_u[o];
-        nx_v = a.rec_v[o];
+        const RecordBase rb(n_wave, a.B);
+        const int64_t o = (int64_t)k * a.B + rb.n;
+        const unsigned l = rb.lane_index(lane);
+        nx_node = (a.rec_node + o)[l];
+        nx_u = (a.rec_u + o)[l];
+        nx_v = (a.rec_v + o)[l];
     };
     if (k_begin < k_end) {
-        fill.template issue<0>(sa, slab0, k_begin, jt, wave, lane);
-        fill.template commit<0>(sa, slab0, wave, lane);
-        fill.template issue<1>(sa, slab0, k_begin, jt, wave, lane);
-        fill.template commit<1>(sa, slab0, wave, lane);
+        feed.issue(__builtin_amdgcn_readfirstlane(lds_address(slab0)), k_begin);
         fetch_record(k_begin);
+        gate.slab_landed();
     }
     const int w = W_CT > 0 ? W_CT : a.W;
-    float *gx_lane = a.gx + n;   // transposed scratch [n_in][ld], plain layout
-    // The derivatives of a pair are added a pair later, behind the barrier: the wait before it is for
-    // everything this wave has in flight, and atomics issued right before it would be waited for.
-    float d1 = 0.f, d2 = 0.f;
-    auto add_derivatives = [&](int k) {
-        if (valid) {
-            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k) * a.ld, d1);
-            unsafeAtomicAdd(gx_lane + (int64_t)(2 * k + 1) * a.ld, d2);
-        }
-    };
+    float *gx_wave = a.gx + n_wave;   // transposed scratch [n_in][ld], plain layout
     for (int k = k_begin; k < k_end; ++k) {
         const float *slab = ((k - k_begin) & 1) ? slab1 : slab0;
         float *slab_next = ((k - k_begin) & 1) ? slab0 : slab1;
         const int node = nx_node;
         const float u = nx_u, v = nx_v;
-        const int i1 = node / w;
-        const float rh1 = s_invh[i1], rh2 = s_invh[node - i1 * w];
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (k + 1 < k_end) {
-            fill.template issue<0>(sa, slab_next, k + 1, jt, wave, lane);
-            fetch_record(k + 1);
-        }
-        if (k > k_begin) add_derivatives(k - 1);
+        const int step = k - k_begin;
+        const bool more = k + 1 < k_end;
+        gate.wait_landed<WAVES>(step);
         // piece (j + l15) mod 16 of the row: from `first` for j < 16 - l15, one row back after the wrap
         unsigned first = lds_address(slab) + (unsigned)node * kRowBytes + (unsigned)l15 * 16;
         // The derivative is made of differences between neighbouring corners, and on a smooth table
@@ -768,6 +738,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         request(ring[0], 0);
         static_for(std::make_integer_sequence<int, 16>{}, [&](auto jc) {
             constexpr int j = decltype(jc)::value;
+            PACE::step_priority<j, 16>();
             if constexpr (j + 1 < 16) request(ring[(j + 1) & 1], j + 1);
             const Corners &c = ring[j & 1];
             const float4 g = gyr[j];
@@ -788,18 +759,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             dif_b += p11 - p01;
             dif_c += p01 - p00;
             dif_d += p11 - p10;
-            if constexpr (j == 7) {
-                if (k + 1 < k_end) {
-                    fill.template commit<0>(sa, slab_next, wave, lane);
-                    fill.template issue<1>(sa, slab_next, k + 1, jt, wave, lane);
-                }
+            if constexpr (PACE::fill_after<j, 16>) {
+                gate.wait_read<WAVES>(step);
+                feed.issue(__builtin_amdgcn_readfirstlane(lds_address(slab_next)), k + 1, more);
+                fetch_record(more ? k + 1 : k);
             }
+            if constexpr (PACE::landed_after<j, 16>) gate.slab_landed();
         });
-        if (k + 1 < k_end) fill.template commit<1>(sa, slab_next, wave, lane);
-        d1 = rh1 * (dif_a * (1.0f - v) + dif_b * v);
-        d2 = rh2 * (dif_c * (1.0f - u) + dif_d * u);
+        gate.slab_read();
+        if (valid) {
+            const int i1 = node / w;
+            const float rh1 = s_invh[i1], rh2 = s_invh[node - i1 * w];
+            const float d1 = rh1 * (dif_a * (1.0f - v) + dif_b * v);
+            const float d2 = rh2 * (dif_c * (1.0f - u) + dif_d * u);
+            float *dst = gx_wave + (int64_t)(2 * k) * a.ld;
+            unsafeAtomicAdd(dst + (unsigned)lane, d1);
+            unsafeAtomicAdd(dst + a.ld + (unsigned)lane, d2);
+        }
     }
-    if (k_begin < k_end) add_derivatives(k_end - 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -866,17 +843,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     const unsigned base0 = __builtin_amdgcn_readfirstlane(lds_address(smem32));
     const unsigned base1 = base0 + slab_bytes;
 
-    // packed table: the rows of (pair, 64-output tile jt / 2) lie 128 bytes apart, this tile is
-    // their half jt & 1; a wave instruction moves 16 rows (four lanes x 16 bytes each)
-    const CT *half = static_cast<const CT *>(a.P) + (int64_t)(jt >> 1) * a.map.s_tile + (jt & 1) * kHalfTile + (lane & 3) * 8;
-    const int chunks = (a.nodes + 15) >> 4;
-    auto issue_fill = [&](unsigned lds_base, int k) {
-        const CT *src = half + (int64_t)k * a.map.s_pair;
-        for (int c = wave; c < chunks; c += WAVES) {
-            const int node = c * 16 + (lane >> 2);
-            if (node < a.nodes) lds_dma16(src + (int64_t)node * a.map.s_node, __builtin_amdgcn_readfirstlane(lds_base + c * 1024));
-        }
-    };
+    SlabFeed<kHalfRowBytes, WAVES> feed;
+    feed.template init<2>(a.P, a.map, a.nodes, a.col_limit, jt * kHalfTile, wave, lane);
+    typedef PaceEarly PACE;
+    SlabGate gate;
+    gate.init(base0 + ((2 * slab_bytes + 15) & ~15u));
 
     const int64_t n0 = (int64_t)btile * (WAVES * SETS * 64) + wave * (SETS * 64) + lane;
     // register block j of a sample: outputs jt*32 + 8 p .. + 7 with p = (j + l3) mod 4
@@ -888,26 +859,25 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[s][j][i] = 0.0f;
 
-    // (a sample past the end of the batch reads the records of the last one; the records of a pair
-    // start at a wave-uniform address, the sample is a 32-bit index into them)
-    unsigned n_rec[SETS];
-#pragma unroll
-    for (int s = 0; s < SETS; ++s) n_rec[s] = (unsigned)min(n0 + s * 64, a.B - 1);
+    const int64_t n_wave = (int64_t)btile * (WAVES * SETS * 64) + wave * (SETS * 64);
     int nx_node[SETS];
     float nx_u[SETS], nx_v[SETS];
     auto fetch_records = [&](int k) {
-        const int32_t *r_node = a.rec_node + (int64_t)k * a.B;
-        const float *r_u = a.rec_u + (int64_t)k * a.B, *r_v = a.rec_v + (int64_t)k * a.B;
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            nx_node[s] = r_node[n_rec[s]];
-            nx_u[s] = r_u[n_rec[s]];
-            nx_v[s] = r_v[n_rec[s]];
+            const RecordBase rb(n_wave + s * 64, a.B);
+            const int64_t o = (int64_t)k * a.B + rb.n;
+            const unsigned l = rb.lane_index(lane);
+            nx_node[s] = (a.rec_node + o)[l];
+            nx_u[s] = (a.rec_u + o)[l];
+            nx_v[s] = (a.rec_v + o)[l];
         }
     };
     if (k_begin < k_end) {
-        issue_fill(base0, k_begin);
+        feed.issue(base0, k_begin);
         fetch_records(k_begin);
+        __syncthreads();  // the counters are in place
+        gate.slab_landed();
     }
 
     for (int k = k_begin; k < k_end; ++k) {
@@ -923,30 +893,28 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             // piece (j + l3) mod 4 of the row: from `first` for j < 4 - l3, one row back after the wrap
             first[s] = cur + (unsigned)nx_node[s] * kHalfRowBytes + (unsigned)l3 * 16;
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (k + 1 < k_end) {
-            issue_fill(nxt, k + 1);
-            fetch_records(k + 1);
-        }
+        const int step = k - k_begin;
+        const bool more = k + 1 < k_end;
+        gate.wait_landed<WAVES>(step);
         CornersRaw ring[2];
-        auto request = [&](CornersRaw &c, int t, float &tie) {
-            // (the empty statement ties the addresses to a sum of the piece before last: it keeps the
+        auto request = [&](CornersRaw &c, int t, float *before) {
+            // (the empty statement ties the address to the sums of the piece before last: it keeps the
             // reads of a piece between the multiply-adds of the pieces before it)
             const int s = t >> 2, j = t & 3;
-            asm volatile("" : "+v"(first[s]), "+v"(tie));
+            asm volatile("" : "+v"(first[s]), "+v"(before[0]), "+v"(before[1]), "+v"(before[2]), "+v"(before[3]), "+v"(before[4]), "+v"(before[5]), "+v"(before[6]), "+v"(before[7]));
             const unsigned addr = (l3 + j >= 4 ? first[s] - kHalfRowBytes : first[s]) + j * 16;
             c.c00 = lds_load_u4(addr);
             c.c01 = lds_load_u4(addr + kHalfRowBytes);
             c.c10 = lds_load_u4(addr + a.W * kHalfRowBytes);
             c.c11 = lds_load_u4(addr + a.W * kHalfRowBytes + kHalfRowBytes);
         };
-        request(ring[0], 0, acc[SETS - 1][3][7]);
+        request(ring[0], 0, acc[SETS - 1][3]);
         static_for(std::make_integer_sequence<int, SETS * 4>{}, [&](auto tc) {
             constexpr int t = decltype(tc)::value;
             constexpr int s = t >> 2, j = t & 3;
             constexpr int tp = t > 0 ? t - 1 : SETS * 4 - 1;   // the piece before this one
-            if constexpr (t + 1 < SETS * 4) request(ring[(t + 1) & 1], t + 1, acc[tp >> 2][tp & 3][7]);
+            PACE::step_priority<t, SETS * 4>();
+            if constexpr (t + 1 < SETS * 4) request(ring[(t + 1) & 1], t + 1, acc[tp >> 2][tp & 3]);
             const CornersRaw &c = ring[t & 1];
             float f[8];
             widen8<CT>(c.c00, f);
@@ -961,7 +929,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             widen8<CT>(c.c11, f);
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[s][j][i] = fmaf(w11[s], f[i], acc[s][j][i]);
+            if constexpr (PACE::fill_after<t, SETS * 4>) {
+                gate.wait_read<WAVES>(step);
+                feed.issue(nxt, k + 1, more);
+                fetch_records(more ? k + 1 : k);
+            }
+            if constexpr (PACE::landed_after<t, SETS * 4>) gate.slab_landed();
         });
+        gate.slab_read();
     }
 
     bool atomic;
@@ -1169,17 +1144,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     float *s_invh = reinterpret_cast<float *>(smem32 + ((2 * slab_bytes + 15) & ~15u));
     for (int i = threadIdx.x; i < a.tab.G; i += blockDim.x) s_invh[i] = a.tab.inv_h[i];
 
-    // packed table: the rows of (pair, 64-output tile jt / 2) lie 64 elements apart, this tile is
-    // their half jt & 1; a wave instruction moves 1024 bytes (PIECES lanes x 16 bytes per row)
-    const float *half = static_cast<const float *>(a.P) + (int64_t)(jt >> 1) * a.map.s_tile + (jt & 1) * kHalfTile + lp * PER;
-    const int chunks = (a.nodes + Row::kRowsPerFill - 1) >> Row::kFillShift;
-    auto issue_fill = [&](unsigned lds_base, int k) {
-        const float *src = half + (int64_t)k * a.map.s_pair;
-        for (int c = wave; c < chunks; c += WAVES) {
-            const int node = c * Row::kRowsPerFill + (lane >> Row::kPieceShift);
-            if (node < a.nodes) lds_dma16(src + (int64_t)node * a.map.s_node, __builtin_amdgcn_readfirstlane(lds_base + c * 1024));
-        }
-    };
+    SlabFeed<Row::kBytes, WAVES> feed;
+    feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kHalfTile, wave, lane);
+    typedef PaceLate PACE;
+    SlabGate gate;
+    gate.init(base0 + ((2 * slab_bytes + 15) & ~15u) + LMKAN_MAX_GRID * 4);
 
     const int64_t n0 = (int64_t)btile * (WAVES * SETS * 64) + wave * (SETS * 64) + lane;
     // register block j of a sample: gy of outputs jt*32 + PER p .. + PER - 1 with p = (j + lp) mod PIECES
@@ -1198,27 +1167,25 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         }
     }
 
+    const int64_t n_wave = (int64_t)btile * (WAVES * SETS * 64) + wave * (SETS * 64);
     int nx_node[SETS];
     float nx_u[SETS], nx_v[SETS];
-    // (a sample past the end of the batch reads the records of the last one; the records of a pair
-    // start at a wave-uniform address, the sample is a 32-bit index into them)
-    unsigned n_rec[SETS];
-#pragma unroll
-    for (int s = 0; s < SETS; ++s) n_rec[s] = (unsigned)min(n0 + s * 64, a.B - 1);
     auto fetch_records = [&](int k) {
-        const int32_t *r_node = a.rec_node + (int64_t)k * a.B;
-        const float *r_u = a.rec_u + (int64_t)k * a.B, *r_v = a.rec_v + (int64_t)k * a.B;
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            nx_node[s] = r_node[n_rec[s]];
-            nx_u[s] = r_u[n_rec[s]];
-            nx_v[s] = r_v[n_rec[s]];
+            const RecordBase rb(n_wave + s * 64, a.B);
+            const int64_t o = (int64_t)k * a.B + rb.n;
+            const unsigned l = rb.lane_index(lane);
+            nx_node[s] = (a.rec_node + o)[l];
+            nx_u[s] = (a.rec_u + o)[l];
+            nx_v[s] = (a.rec_v + o)[l];
         }
     };
-    __syncthreads();  // s_invh in place
+    __syncthreads();  // s_invh and the counters in place
     if (k_begin < k_end) {
-        issue_fill(base0, k_begin);
+        feed.issue(base0, k_begin);
         fetch_records(k_begin);
+        gate.slab_landed();
     }
 
     for (int k = k_begin; k < k_end; ++k) {
@@ -1228,12 +1195,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         float u[SETS], v[SETS];
 #pragma unroll
         for (int s = 0; s < SETS; ++s) node[s] = nx_node[s], u[s] = nx_u[s], v[s] = nx_v[s];
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (k + 1 < k_end) {
-            issue_fill(nxt, k + 1);
-            fetch_records(k + 1);
-        }
+        const int step = k - k_begin;
+        const bool more = k + 1 < k_end;
+        gate.wait_landed<WAVES>(step);
         // piece (j + lp) mod PIECES of the row: from `first` for j < PIECES - lp, one row back after
         // the wrap
         unsigned first[SETS];
@@ -1256,6 +1220,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         static_for(std::make_integer_sequence<int, STEPS>{}, [&](auto tc) {
             constexpr int t = decltype(tc)::value;
             constexpr int s = t / PIECES, j = t % PIECES;
+            PACE::step_priority<t, STEPS>();
             if constexpr (t + 1 < STEPS) request(ring[(t + 1) & 1], t + 1);
             const CornersRaw &c = ring[t & 1];
             float f[PER];
@@ -1288,7 +1253,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 }
                 dif_a = dif_b = dif_c = dif_d = 0.f;
             }
+            if constexpr (PACE::fill_after<t, STEPS>) {
+                gate.wait_read<WAVES>(step);
+                feed.issue(nxt, k + 1, more);
+                fetch_records(more ? k + 1 : k);
+            }
+            if constexpr (PACE::landed_after<t, STEPS>) gate.slab_landed();
         });
+        gate.slab_read();
     }
 }
 
@@ -1320,17 +1292,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     const unsigned base0 = __builtin_amdgcn_readfirstlane(lds_address(smem32));
     const unsigned base1 = base0 + slab_bytes;
 
-    // packed table: the rows of (pair, 64-output tile jt / 2) lie 64 elements apart, this tile is
-    // their half jt & 1; a wave instruction moves 1024 bytes (PIECES lanes x 16 bytes per row)
-    const float *half = static_cast<const float *>(a.P) + (int64_t)(jt >> 1) * a.map.s_tile + (jt & 1) * kHalfTile + lp * PER;
-    const int chunks = (a.nodes + Row::kRowsPerFill - 1) >> Row::kFillShift;
-    auto issue_fill = [&](unsigned lds_base, int k) {
-        const float *src = half + (int64_t)k * a.map.s_pair;
-        for (int c = wave; c < chunks; c += WAVES) {
-            const int node = c * Row::kRowsPerFill + (lane >> Row::kPieceShift);
-            if (node < a.nodes) lds_dma16(src + (int64_t)node * a.map.s_node, __builtin_amdgcn_readfirstlane(lds_base + c * 1024));
-        }
-    };
+    SlabFeed<Row::kBytes, WAVES> feed;
+    feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kHalfTile, wave, lane);
+    typedef PaceLate PACE;
+    SlabGate gate;
+    gate.init(base0 + ((2 * slab_bytes + 15) & ~15u));
 
     const int64_t n0 = (int64_t)btile * (WAVES * SETS * 64) + wave * (SETS * 64) + lane;
     // register block j of a sample: outputs jt*32 + PER p .. + PER - 1 with p = (j + lp) mod PIECES
@@ -1342,26 +1308,25 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 #pragma unroll
             for (int i = 0; i < PER; ++i) acc[s][j][i] = 0.0f;
 
-    // (a sample past the end of the batch reads the records of the last one; the records of a pair
-    // start at a wave-uniform address, the sample is a 32-bit index into them)
-    unsigned n_rec[SETS];
-#pragma unroll
-    for (int s = 0; s < SETS; ++s) n_rec[s] = (unsigned)min(n0 + s * 64, a.B - 1);
+    const int64_t n_wave = (int64_t)btile * (WAVES * SETS * 64) + wave * (SETS * 64);
     int nx_node[SETS];
     float nx_u[SETS], nx_v[SETS];
     auto fetch_records = [&](int k) {
-        const int32_t *r_node = a.rec_node + (int64_t)k * a.B;
-        const float *r_u = a.rec_u + (int64_t)k * a.B, *r_v = a.rec_v + (int64_t)k * a.B;
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            nx_node[s] = r_node[n_rec[s]];
-            nx_u[s] = r_u[n_rec[s]];
-            nx_v[s] = r_v[n_rec[s]];
+            const RecordBase rb(n_wave + s * 64, a.B);
+            const int64_t o = (int64_t)k * a.B + rb.n;
+            const unsigned l = rb.lane_index(lane);
+            nx_node[s] = (a.rec_node + o)[l];
+            nx_u[s] = (a.rec_u + o)[l];
+            nx_v[s] = (a.rec_v + o)[l];
         }
     };
     if (k_begin < k_end) {
-        issue_fill(base0, k_begin);
+        feed.issue(base0, k_begin);
         fetch_records(k_begin);
+        __syncthreads();  // the counters are in place
+        gate.slab_landed();
     }
 
     for (int k = k_begin; k < k_end; ++k) {
@@ -1383,20 +1348,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             // piece (j + lp) mod PIECES of the row: from `first` for j < PIECES - lp, one row back
             // after the wrap
             first[s] = cur + ((unsigned)nx_node[s] + sw) * Row::kBytes + (unsigned)lp * 16;
-            to_other[s] = sw ? -Row::kBytes : Row::kBytes;
+            to_other[s] = Row::kBytes - (int)(sw * 2 * Row::kBytes);
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (k + 1 < k_end) {
-            issue_fill(nxt, k + 1);
-            fetch_records(k + 1);
-        }
+        const int step = k - k_begin;
+        const bool more = k + 1 < k_end;
+        gate.wait_landed<WAVES>(step);
         CornersRaw ring[2];
-        auto request = [&](CornersRaw &c, int t, float &tie) {
-            // (the empty statement ties the addresses to a sum of the piece before last: it keeps the
+        auto request = [&](CornersRaw &c, int t, float *before) {
+            // (the empty statement ties the address to the sums of the piece before last: it keeps the
             // reads of a piece between the multiply-adds of the pieces before it)
             const int s = t / PIECES, j = t % PIECES;
-            asm volatile("" : "+v"(first[s]), "+v"(tie));
+            if (t > 0) asm volatile("" : "+v"(first[s]), "+v"(before[0]), "+v"(before[1]), "+v"(before[2]), "+v"(before[3]));
             const unsigned addr = (lp + j >= PIECES ? first[s] - Row::kBytes : first[s]) + j * 16;
             const unsigned other = addr + to_other[s];
             c.c00 = lds_load_u4(addr);
@@ -1404,12 +1366,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             c.c10 = lds_load_u4(addr + a.W * Row::kBytes);
             c.c11 = lds_load_u4(other + a.W * Row::kBytes);
         };
-        request(ring[0], 0, acc[SETS - 1][PIECES - 1][PER - 1]);
+        request(ring[0], 0, acc[SETS - 1][PIECES - 1]);
         static_for(std::make_integer_sequence<int, STEPS>{}, [&](auto tc) {
             constexpr int t = decltype(tc)::value;
             constexpr int s = t / PIECES, j = t % PIECES;
             constexpr int tp = t > 0 ? t - 1 : STEPS - 1;   // the piece before this one
-            if constexpr (t + 1 < STEPS) request(ring[(t + 1) & 1], t + 1, acc[tp / PIECES][tp % PIECES][PER - 1]);
+            PACE::step_priority<t, STEPS>();
+            if constexpr (t + 1 < STEPS) request(ring[(t + 1) & 1], t + 1, acc[tp / PIECES][tp % PIECES]);
             const CornersRaw &c = ring[t & 1];
             float f[PER];
             piece_as_floats(c.c00, f);
@@ -1424,7 +1387,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             piece_as_floats(c.c11, f);
 #pragma unroll
             for (int i = 0; i < PER; ++i) acc[s][j][i] = fmaf(w_d[s], f[i], acc[s][j][i]);
+            if constexpr (PACE::fill_after<t, STEPS>) {
+                gate.wait_read<WAVES>(step);
+                feed.issue(nxt, k + 1, more);
+                fetch_records(more ? k + 1 : k);
+            }
+            if constexpr (PACE::landed_after<t, STEPS>) gate.slab_landed();
         });
+        gate.slab_read();
     }
 
     bool atomic;
@@ -1544,15 +1514,28 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     // older ones into waits for everything): a sample past the batch reads the last sample's
     // record (its results are not stored), the step past the last pair reads the last pair again.
     auto fetch_record = [&](int slot, int k) {
-        const int64_t n = min(n_wave + slot * 64 + lane, a.B - 1);
-        const int64_t o = (int64_t)min(k, k_end - 1) * a.B + n;
-        r_node[slot] = a.rec_node[o];
-        r_u[slot] = a.rec_u[o];
-        r_v[slot] = a.rec_v[o];
+        const RecordBase rb(n_wave + slot * 64, a.B);
+        const int64_t o = (int64_t)min(k, k_end - 1) * a.B + rb.n;
+        const unsigned l = rb.lane_index(lane);
+        r_node[slot] = (a.rec_node + o)[l];
+        r_u[slot] = (a.rec_u + o)[l];
+        r_v[slot] = (a.rec_v + o)[l];
     };
 
+    constexpr bool kDirect = sizeof(CT) == 4;    // the slab comes by LDS-direct loads
+    constexpr bool kGated = kDirect && !SINGLE;  // and the waves hand two of them over by the gate
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
+    typedef PaceLate PACE;
+    SlabGate gate;
+    if constexpr (kGated) gate.init(lds0 + 8 * (unsigned)slab_floats);
+    SlabFeed<kNarrowRowBytes, WAVES, SINGLE ? 160 : 80> feed;
+    if constexpr (kDirect) feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kNarrowTile, wave, lane);
     SlabFill<CT, WAVES, LPS, SINGLE ? 4 : 2> fill;
     auto fill_whole = [&](int k) {  // every phase, one after the other
+        if constexpr (kDirect) {
+            feed.issue(lds0, k);
+            return;
+        }
         static_for(std::make_integer_sequence<int, SINGLE ? 4 : 2>{}, [&](auto pc) {
             fill.template issue<decltype(pc)::value>(a, slab0, k, jt, wave, lane);
             fill.template commit<decltype(pc)::value>(a, slab0, wave, lane);
@@ -1562,8 +1545,12 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
 #pragma unroll
         for (int s = 0; s < SETS; ++s) fetch_record(s, k_begin);
         fill_whole(k_begin);
+        if constexpr (kGated) {
+            __syncthreads();  // the counters are in place
+            gate.slab_landed();
+        }
     }
-    const int lane_bytes = sub * 16;
+    int lane_bytes = sub * 16;
     for (int k = k_begin; k < k_end; ++k) {
         const float *slab = ((k - k_begin) & 1) ? slab1 : slab0;
         float *slab_next = ((k - k_begin) & 1) ? slab0 : slab1;
@@ -1573,14 +1560,16 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
                 fill_whole(k);
             }
         }
-        // a float32 table arrives by LDS-direct loads, which nothing but this wait tracks
-        if constexpr (sizeof(CT) == 4) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();  // the slab of pair k is complete, nobody reads the other buffer any more
-        // (16-bit tables: the last pair fetches its own slab once more, for nobody; the LDS-direct
-        // loads of a float32 table are not tracked by the compiler's waits and are simply left out)
-        const int k_next = min(k + 1, k_end - 1);
-        if constexpr (!SINGLE)
-            if (sizeof(CT) != 4 || k + 1 < k_end) fill.template issue<0>(a, slab_next, k_next, jt, wave, lane);
+        const int step = k - k_begin;
+        const bool more = k + 1 < k_end;
+        const int k_next = more ? k + 1 : k;   // (a staged slab is fetched once more for nobody)
+        if constexpr (kGated) {
+            gate.wait_landed<WAVES>(step);
+        } else {
+            if constexpr (kDirect) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();  // the slab of pair k is complete, nobody reads the other buffer any more
+            if constexpr (!SINGLE) fill.template issue<0>(a, slab_next, k_next, jt, wave, lane);
+        }
 
         constexpr int kNear = 1;  // LDS reads run one step ahead (registers are short here)
         Corners ring[kNear + 1];
@@ -1590,8 +1579,9 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         static_for(std::make_integer_sequence<int, STEPS>{}, [&](auto fc) {
             constexpr int F = decltype(fc)::value;
             constexpr int set = F / LPS, t = F % LPS;
+            if constexpr (kGated) PACE::step_priority<F, STEPS>();
             if constexpr (t == 0) {
-                if constexpr (set == SETS / 2 && !SINGLE) {
+                if constexpr (set == SETS / 2 && !SINGLE && !kDirect) {
                     fill.template commit<0>(a, slab_next, wave, lane);
                     fill.template issue<1>(a, slab_next, k_next, jt, wave, lane);
                 }
@@ -1610,12 +1600,21 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             }
             if constexpr (F + kNear < STEPS) {
                 constexpr int F2 = F + kNear;
+                // (ties the address to the step before, as in slab_pipeline)
+                if constexpr (kGated && F > 0)
+                    asm volatile("" : "+v"(lane_bytes), "+v"(acc[4 * F - 4]), "+v"(acc[4 * F - 3]), "+v"(acc[4 * F - 2]), "+v"(acc[4 * F - 1]));
                 load_corners_quad<F2 % LPS>(ring[F2 % (kNear + 1)], slab, (F2 / LPS == set) ? off_cur : off_nxt,
                                             lane_bytes, a.W);
             }
             fma_corners_quad<t>(acc + 4 * F, ring[F % (kNear + 1)], w00, w10, w01, w11);
+            if constexpr (kGated && PACE::fill_after<F, STEPS>) {
+                gate.wait_read<WAVES>(step);
+                feed.issue((step & 1) ? lds0 : lds0 + 4 * (unsigned)slab_floats, k_next, more);
+            }
+            if constexpr (kGated && PACE::landed_after<F, STEPS>) gate.slab_landed();
         });
-        if constexpr (!SINGLE) fill.template commit<1>(a, slab_next, wave, lane);
+        if constexpr (kGated) gate.slab_read();
+        if constexpr (!SINGLE && !kDirect) fill.template commit<1>(a, slab_next, wave, lane);
     }
 
     // lane (grp, sub) holds outputs jt*16 + 4*sub .. +3 of samples n_wave + set*64 + 4*grp + t
@@ -1719,18 +1718,26 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     // (never skipped, like every load of the main loop: see forward_slab_narrow_kernel; a sample
     // past the batch has gy = 0 and adds nothing)
     auto fetch_record = [&](int slot, int k) {
-        const int64_t n = min(n_wave + slot * 64 + lane, a.B - 1);
-        const int64_t o = (int64_t)k * a.B + n;
-        r_node[slot] = a.rec_node[o];
-        r_u[slot] = a.rec_u[o];
-        r_v[slot] = a.rec_v[o];
+        const RecordBase rb(n_wave + slot * 64, a.B);
+        const int64_t o = (int64_t)k * a.B + rb.n;
+        const unsigned l = rb.lane_index(lane);
+        r_node[slot] = (a.rec_node + o)[l];
+        r_u[slot] = (a.rec_u + o)[l];
+        r_v[slot] = (a.rec_v + o)[l];
     };
 
     // columns past the end of a ragged output tile are never loaded: the staged fill writes
     // zeros there, the LDS-direct loads of a float32 table leave them as they are, so they are
     // cleared first; s_invh must be in place before the first set
-    if constexpr (sizeof(CT) == 4) {
+    constexpr bool kDirect = sizeof(CT) == 4;
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
+    typedef PaceLate PACE;
+    SlabGate gate;
+    SlabFeed<kNarrowRowBytes, WAVES> feed;
+    if constexpr (kDirect) {
         for (int i = threadIdx.x; i < 2 * slab_floats; i += blockDim.x) smem[i] = 0.0f;
+        gate.init(lds0 + 8 * (unsigned)slab_floats + LMKAN_MAX_GRID * 4);
+        feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kNarrowTile, wave, lane);
         __syncthreads();
     }
     // Workgroups that differ only in their output tile add into the same entries of the
@@ -1747,10 +1754,15 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         const int k0 = pair_at(0);
 #pragma unroll
         for (int s = 0; s < SETS; ++s) fetch_record(s, k0);
-        fill.template issue<0>(sa, slab0, k0, jt, wave, lane);
-        fill.template commit<0>(sa, slab0, wave, lane);
-        fill.template issue<1>(sa, slab0, k0, jt, wave, lane);
-        fill.template commit<1>(sa, slab0, wave, lane);
+        if constexpr (kDirect) {
+            feed.issue(lds0, k0);
+            gate.slab_landed();
+        } else {
+            fill.template issue<0>(sa, slab0, k0, jt, wave, lane);
+            fill.template commit<0>(sa, slab0, wave, lane);
+            fill.template issue<1>(sa, slab0, k0, jt, wave, lane);
+            fill.template commit<1>(sa, slab0, wave, lane);
+        }
     }
     const int lane_bytes = sub * 16;
     // where this lane's two results of a set go: samples 4 grp + (sub & 1) and + 2 more, input
@@ -1763,9 +1775,12 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         const int k = pair_at(step), k_next = pair_at(step + 1);
         const float *slab = (step & 1) ? slab1 : slab0;
         float *slab_next = (step & 1) ? slab0 : slab1;
-        if constexpr (sizeof(CT) == 4) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (sizeof(CT) != 4 || step + 1 < n_k) fill.template issue<0>(sa, slab_next, k_next, jt, wave, lane);
+        if constexpr (kDirect) {
+            gate.wait_landed<WAVES>(step);
+        } else {
+            __syncthreads();
+            fill.template issue<0>(sa, slab_next, k_next, jt, wave, lane);
+        }
 
         constexpr int kNear = 1;
         Corners ring[kNear + 1];
@@ -1776,8 +1791,9 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         static_for(std::make_integer_sequence<int, STEPS>{}, [&](auto fc) {
             constexpr int F = decltype(fc)::value;
             constexpr int set = F / LPS, t = F % LPS;
+            if constexpr (kDirect) PACE::step_priority<F, STEPS>();
             if constexpr (t == 0) {
-                if constexpr (set == SETS / 2) {
+                if constexpr (set == SETS / 2 && !kDirect) {
                     fill.template commit<0>(sa, slab_next, wave, lane);
                     fill.template issue<1>(sa, slab_next, k_next, jt, wave, lane);
                 }
@@ -1809,8 +1825,14 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
                 if (n < a.B) unsafeAtomicAdd(dst, stash_a);
                 if (n + 2 < a.B) unsafeAtomicAdd(dst + 32, stash_b);
             }
+            if constexpr (kDirect && PACE::fill_after<F, STEPS>) {
+                gate.wait_read<WAVES>(step);
+                feed.issue((step & 1) ? lds0 : lds0 + 4 * (unsigned)slab_floats, k_next, step + 1 < n_k);
+            }
+            if constexpr (kDirect && PACE::landed_after<F, STEPS>) gate.slab_landed();
         });
-        fill.template commit<1>(sa, slab_next, wave, lane);
+        if constexpr (kDirect) gate.slab_read();
+        else fill.template commit<1>(sa, slab_next, wave, lane);
     }
 }
 
@@ -1857,20 +1879,21 @@ static bool slab_batch_ok(const LayerShape &s, bool forward)
 // which tile a shape takes when it takes a slab kernel at all
 static bool slab_wide_fits(const LayerShape &s)
 {
-    return outputs_by_four_ok(s) && slab_forward_lds_bytes(s) <= 160 * 1024;
+    return outputs_by_four_ok(s) && slab_forward_lds_bytes(s) <= 160 * 1024 && slab_feed_reaches(s, 4, 4);
 }
 
 // 16-output tiles for larger grids (G <= 34)
 static bool slab_narrow_fits(const LayerShape &s)
 {
-    return outputs_by_four_ok(s) && !slab_wide_fits(s) && (size_t)2 * s.nodes() * kNarrowRowBytes <= 160 * 1024;
+    return outputs_by_four_ok(s) && !slab_wide_fits(s) && (size_t)2 * s.nodes() * kNarrowRowBytes <= 160 * 1024 &&
+           slab_feed_reaches(s, 16, 4);
 }
 
 // forward only: one 16-output slab at a time (35 <= G <= 48)
 static bool slab_narrow_single_fits(const LayerShape &s)
 {
     return outputs_by_four_ok(s) && !slab_wide_fits(s) && !slab_narrow_fits(s) &&
-           (size_t)s.nodes() * kNarrowRowBytes <= 160 * 1024 - 512;
+           (size_t)s.nodes() * kNarrowRowBytes <= 160 * 1024 - 512 && slab_feed_reaches(s, 16, 4);
 }
 
 bool slab_forward_shape_ok(const LayerShape &s)
@@ -1885,7 +1908,7 @@ static size_t half_tile_row_bytes(const LayerShape &s) { return (size_t)kHalfTil
 static bool slab_half_tiles_fit(const LayerShape &s)
 {
     return slab_narrow_fits(s) && s.layout == LMKAN_LAYOUT_PACKED &&
-           (size_t)2 * s.nodes() * half_tile_row_bytes(s) + LMKAN_MAX_GRID * sizeof(float) <= 160 * 1024;
+           (size_t)2 * s.nodes() * half_tile_row_bytes(s) + LMKAN_MAX_GRID * sizeof(float) + 2 * kGateBytes <= 160 * 1024;
 }
 bool slab_forward_takes_half_tiles(const LayerShape &s)
 {
@@ -1990,7 +2013,7 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
         finish_split_setup(a, s, y, partials, stream);
         {
             KernelTiming timing(stream, kTimeForward);
-            k32<<<tiles32 * split, 1024, ((size_t)2 * s.nodes() * half_tile_row_bytes(s) + 15) & ~(size_t)15, stream>>>(a);
+            k32<<<tiles32 * split, 1024, (((size_t)2 * s.nodes() * half_tile_row_bytes(s) + 15) & ~(size_t)15) + kGateBytes, stream>>>(a);
         }
         if (a.y_part) launch_sum_partials(y, a.y_part, split - 1, (int64_t)s.batch * s.n_out, stream);
         return;
@@ -2029,7 +2052,7 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
     finish_split_setup(a, s, y, partials, stream);
     {
         KernelTiming timing(stream, kTimeForward);
-        kernel<<<tiles * split, waves * 64, (size_t)(single ? 1 : 2) * s.nodes() * kNarrowRowBytes, stream>>>(a);
+        kernel<<<tiles * split, waves * 64, (size_t)(single ? 1 : 2) * s.nodes() * kNarrowRowBytes + kGateBytes, stream>>>(a);
     }
     if (a.y_part) launch_sum_partials(y, a.y_part, split - 1, (int64_t)s.batch * s.n_out, stream);
 }
@@ -2081,7 +2104,7 @@ void launch_forward_slab(const LayerShape &s, const void *coef, float *y, const 
     finish_split_setup(a, s, y, partials, stream);
     {
         KernelTiming timing(stream, kTimeForward);
-        kernel<<<tiles * split, waves * 64, slab_forward_lds_bytes(s), stream>>>(a);
+        kernel<<<tiles * split, waves * 64, slab_forward_lds_bytes(s) + kGateBytes, stream>>>(a);
     }
     if (a.y_part) launch_sum_partials(y, a.y_part, split - 1, (int64_t)s.batch * s.n_out, stream);
 }
@@ -2253,7 +2276,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
         a.pairs_per_split = (a.K + split32 - 1) / split32;
         a.ld = scratch_row_stride(s.batch, kScratchPlain);
         launch_fill_zero(a.gx, (size_t)a.ld * s.n_in, stream);
-        const size_t lds = (((size_t)2 * s.nodes() * half_tile_row_bytes(s) + 15) & ~(size_t)15) + LMKAN_MAX_GRID * sizeof(float);
+        const size_t lds = (((size_t)2 * s.nodes() * half_tile_row_bytes(s) + 15) & ~(size_t)15) + LMKAN_MAX_GRID * sizeof(float) + kGateBytes;
         {
             KernelTiming timing(stream, kTimeGradInput);
             k32<<<tiles32 * split32, 1024, lds, stream>>>(a);
@@ -2311,7 +2334,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
     const int waves = s.dtype == LMKAN_F32 ? (narrow ? 2 * WAVES : kWavesF32) : WAVES;
     {
         KernelTiming timing(stream, kTimeGradInput);
-        kernel<<<tiles * split, waves * 64, slabs + LMKAN_MAX_GRID * sizeof(float), stream>>>(a);
+        kernel<<<tiles * split, waves * 64, slabs + LMKAN_MAX_GRID * sizeof(float) + kGateBytes, stream>>>(a);
     }
     launch_input_gradient_out(a.gx, gx, s, conv, stream, layout);
 }

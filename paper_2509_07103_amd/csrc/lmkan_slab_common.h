@@ -111,6 +111,181 @@ __device__ __forceinline__ void lds_dma16_uniform(const void *gbase, unsigned la
                  : "memory");
 }
 
+// Same for a piece of a fill that may be partial or absent: only the lanes of `lanes` load, and none of
+// them is a case too.  One statement without a branch the compiler could see, so that a fill may stand in
+// the middle of a main loop without cutting it into blocks (each of which would be scheduled by itself).
+// To be used where all lanes of the wave are active.
+__device__ __forceinline__ void lds_dma16_lanes(const void *gbase, unsigned lane_off, unsigned lds_base, uint64_t lanes)
+{
+    asm volatile("s_cmp_eq_u64 %3, 0\n\ts_cbranch_scc1 .Labsent%=\n\ts_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\t"
+                 "global_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1\n.Labsent%=:"
+                 :
+                 : "v"(lane_off), "s"(gbase), "s"(lds_base), "s"(lanes)
+                 : "memory", "scc");
+}
+
+// the first n of 64 lanes (n may be zero, negative or more than 64)
+__device__ __forceinline__ uint64_t first_lanes(int n)
+{
+    return n <= 0 ? 0 : n >= 64 ? ~(uint64_t)0 : ((uint64_t)1 << n) - 1;
+}
+
+// Slabs of one output tile in the form they are stored in: ROW_BYTES per node, filled by LDS-direct loads of
+// 1 KiB (64 lanes x 16 bytes, whole rows), dealt round-robin to the waves.  One code for both layouts: the
+// rows of a chunk lie node_bytes apart, columns that do not exist are lanes that never load.
+template <int ROW_BYTES, int WAVES, int MOST_KIB = 80>
+struct SlabFeed {
+    static constexpr int kLanes = ROW_BYTES / 16;   // lanes per row
+    static constexpr int kRows = 64 / kLanes;       // rows per chunk
+    static constexpr int kMostChunks = (MOST_KIB + WAVES - 1) / WAVES;   // per wave; two slabs share 160 KiB
+    const char *tile;
+    int64_t pair_bytes, chunk_bytes;
+    uint64_t columns;
+    unsigned lane_off;
+    int nodes, wave;
+
+    template <int ELEMENT>
+    __device__ __forceinline__ void init(const void *P, const CoefMap &map, int n_nodes, int col_limit, int first_col, int wave_id,
+                                         int lane)
+    {
+        const int col = first_col + (lane % kLanes) * (16 / ELEMENT);
+        tile = static_cast<const char *>(P) + ((int64_t)(first_col >> 6) * map.s_tile + (first_col & 63)) * ELEMENT;
+        pair_bytes = map.s_pair * ELEMENT;
+        chunk_bytes = map.s_node * (kRows * ELEMENT);
+        lane_off = (unsigned)(lane / kLanes) * (unsigned)(map.s_node * ELEMENT) + (unsigned)(lane % kLanes) * 16u;
+        columns = __ballot(col < col_limit);
+        nodes = n_nodes;
+        wave = wave_id;
+    }
+    __device__ __forceinline__ void issue(unsigned lds_base, int k, bool wanted = true) const
+    {
+        const char *src = tile + (int64_t)k * pair_bytes;
+#pragma unroll
+        for (int i = 0; i < kMostChunks; ++i) {
+            const int c = wave + i * WAVES;
+            lds_dma16_lanes(src + c * chunk_bytes, lane_off, lds_base + c * 1024,
+                            wanted ? first_lanes((nodes - c * kRows) * kLanes) & columns : 0);
+        }
+    }
+};
+
+// (layout of Alg. 1: the rows of a chunk lie pairs x outputs elements apart, and a lane's offset has 32 bits)
+inline bool slab_feed_reaches(const LayerShape &s, int rows_per_chunk, int element)
+{
+    return s.layout == LMKAN_LAYOUT_PACKED ||
+           (int64_t)s.pairs() * s.n_out * element * (rows_per_chunk - 1) < ((int64_t)1 << 32) - 1024;
+}
+
+// How the waves of a workgroup that walks over pairs hand its two slab buffers over.  A barrier per pair
+// lets the waves of a SIMD start every pair together, with nothing in their pipelines, and makes all wait
+// for the last one; what has to hold is less: a pair is walked when every wave's part of its slab has
+// landed, and a buffer is filled when every wave has read it.  Two counters in LDS say so, and a wave may
+// then run ahead of another by part of a pair (Pace):
+//   wait_landed(i); first steps of pair i; wait_read(i), request the slab of pair i + 1; more steps;
+//   slab_landed(); last steps; slab_read().
+// Every wave of the workgroup goes through the same number of pairs, and none waits for something that it
+// has not itself done before: wait_landed(i) asks for what every wave does within pair i - 1 (the first
+// slab: before the walk), wait_read(i) for the end of pair i - 1.  So the last wave never waits for long.
+// LDS instructions of a wave execute in order, so a counter moves after the reads before it.
+// Kernel times with a barrier per pair -> with gate and priorities, 1024 -> 1024, 8192 rows unless stated:
+// forward float32 G = 16 945 -> 830 us, G = 20 915 -> 785, G = 28 1293 -> 1130, float16 G = 16 837 -> 750,
+// G = 24 910 -> 766, bfloat16 4096 -> 4096 at G = 32, 4096 rows 9100 -> 8130; input gradient float32 G = 16
+// 1045 -> 906, G = 20 1377 -> 1167, G = 28 2110 -> 1764; 262144 rows of 128 -> 128, G = 12: 448 -> 425 and
+// 570 -> 520.  The gate without the priorities is no gain (994 us instead of 830): the waves that happen to be
+// ahead then keep the SIMD until the gate stops them, and the others run alone.
+constexpr int kGateBytes = 16;
+
+// When a wave does what, in sixteenths of a pair: FILL: the next slab is requested, LANDED: its arrival is waited
+// for.  A wave that lags behind gets the SIMD first: its priority falls from quarter to quarter of a pair, and
+// steps back up at the start of a pair or (FROM_FILL) at its second quarter, where wait_read has made sure
+// that no wave is still in the pair before.
+template <int FILL, int LANDED, bool FROM_FILL>
+struct Pace {
+    static constexpr int kFill = FILL, kLanded = LANDED;
+    template <int QUARTER>
+    static __device__ __forceinline__ void priority()
+    {
+        __builtin_amdgcn_s_setprio(FROM_FILL ? (4 - QUARTER) % 4 : 3 - QUARTER);
+    }
+    // for step T of TOTAL
+    template <int T, int TOTAL>
+    static __device__ __forceinline__ void step_priority()
+    {
+        if constexpr (T % (TOTAL / 4) == 0) priority<T / (TOTAL / 4)>();
+    }
+    template <int T, int TOTAL>
+    static constexpr bool fill_after = T + 1 == TOTAL * FILL / 16;
+    template <int T, int TOTAL>
+    static constexpr bool landed_after = T + 1 == TOTAL * LANDED / 16;
+};
+typedef Pace<4, 12, true> PaceEarly;
+typedef Pace<8, 14, false> PaceLate;
+
+struct SlabGate {
+    unsigned landed, read;  // LDS addresses of the counters
+
+    // (a barrier has to follow before the first use)
+    __device__ __forceinline__ void init(unsigned lds_addr)
+    {
+        landed = lds_addr;
+        read = lds_addr + 4;
+        if (threadIdx.x < 2) *reinterpret_cast<__attribute__((address_space(3))) int *>(lds_addr + threadIdx.x * 4) = 0;
+    }
+    static __device__ __forceinline__ void arrive(unsigned counter)
+    {
+        uint64_t exec_before;
+        unsigned address, one;   // (set here: nothing of this stays in vector registers over the walk)
+        asm volatile("v_mov_b32 %1, %3\n\tv_mov_b32 %2, 1\n\ts_mov_b64 %0, exec\n\ts_mov_b64 exec, 1\n\t"
+                     "ds_add_u32 %1, %2\n\ts_mov_b64 exec, %0"
+                     : "=&s"(exec_before), "=&v"(address), "=&v"(one)
+                     : "s"(counter)
+                     : "memory");
+    }
+    static __device__ __forceinline__ void wait(unsigned counter, int target)
+    {
+        int v, s;
+        asm volatile(".Lpoll%=:\n\tv_mov_b32 %0, %2\n\tds_read_b32 %0, %0\n\ts_waitcnt lgkmcnt(0)\n\t"
+                     "v_readfirstlane_b32 %1, %0\n\ts_cmp_ge_i32 %1, %3\n\ts_cbranch_scc1 .Lpassed%=\n\t"
+                     "s_sleep 1\n\ts_branch .Lpoll%=\n.Lpassed%=:"
+                     : "=&v"(v), "=&s"(s)
+                     : "s"(counter), "s"(target)
+                     : "memory", "scc");
+    }
+    // waits until this wave's part of the slab requested last is in LDS, and says so
+    __device__ __forceinline__ void slab_landed() const
+    {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        arrive(landed);
+    }
+    __device__ __forceinline__ void slab_read() const { arrive(read); }
+    // step = pairs this workgroup has walked before this one
+    template <int WAVES>
+    __device__ __forceinline__ void wait_landed(int step) const
+    {
+        wait(landed, WAVES * (step + 1));
+    }
+    template <int WAVES>
+    __device__ __forceinline__ void wait_read(int step) const
+    {
+        wait(read, WAVES * step);
+    }
+};
+
+// Records of 64 consecutive samples of a pair, from sample n on: scalar base, 32-bit lane offset.  Samples past
+// the end of the batch read the record of the last one.  (The limit is kept from the compiler: the offset is
+// one instruction, which it would rather keep in a register over the whole walk.)
+struct RecordBase {
+    int64_t n;
+    unsigned last;
+    __device__ __forceinline__ RecordBase(int64_t first, int64_t B) : n(min(first, B - 1)), last((unsigned)min((int64_t)63, B - 1 - n)) {}
+    __device__ __forceinline__ unsigned lane_index(int lane) const
+    {
+        unsigned limit = __builtin_amdgcn_readfirstlane(last);
+        asm volatile("" : "+s"(limit));
+        return min((unsigned)lane, limit);
+    }
+};
+
 struct GradInArgs {
     const void *P;     // float32, or 16-bit storage converted while the slab is filled
     const float *gy;   // column c of row n at gy[(c >> 6) * gy_tile_stride + n * gy_row_stride + (c & 63)]

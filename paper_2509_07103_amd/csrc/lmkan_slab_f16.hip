@@ -126,21 +126,24 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
     int nx_node = 0;
     float nx_u = 0.f, nx_v = 0.f;
     auto fetch_record = [&](int k) {
-        const int64_t n = n_wave + lane;
-        nx_node = 0;
-        nx_u = 0.f;
-        nx_v = 0.f;
-        if (n < a.B) {
-            const int64_t o = (int64_t)k * a.B + n;
-            nx_node = a.rec_node[o];
-            nx_u = a.rec_u[o];
-            nx_v = a.rec_v[o];
-        }
+        const RecordBase rb(n_wave, a.B);
+        const int64_t o = (int64_t)k * a.B + rb.n;
+        const unsigned l = rb.lane_index(lane);
+        nx_node = (a.rec_node + o)[l];
+        nx_u = (a.rec_u + o)[l];
+        nx_v = (a.rec_v + o)[l];
     };
 
+    SlabFeed<kRowBytesH, kWaves> feed;
+    feed.template init<2>(a.P, a.map, a.nodes, a.col_limit, jt * kTile, wave, lane);
+    typedef PaceLate PACE;
+    SlabGate gate;
+    gate.init(base0 + ((2 * slab_bytes + 15) & ~15u));
     if (k_begin < k_end) {
-        issue_slab_load_h(a, base0, k_begin, jt, wave, lane);
+        feed.issue(base0, k_begin);
         fetch_record(k_begin);
+        __syncthreads();  // the counters are in place
+        gate.slab_landed();
     }
     const int lane_bytes = l16 * 8;
     for (int k = k_begin; k < k_end; ++k) {
@@ -150,24 +153,30 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
         const float a_lo = 1.0f - u, b_lo = 1.0f - v;
         const int off = nx_node * kRowBytesH;
         const float w00 = a_lo * b_lo, w10 = u * b_lo, w01 = a_lo * v, w11 = u * v;
-        // this wave's slab loads for pair k have landed; after the barrier everybody's have,
-        // and everybody has finished reading the other buffer (pair k-1)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (k + 1 < k_end) {
-            issue_slab_load_h(a, nxt, k + 1, jt, wave, lane);
-            fetch_record(k + 1);
-        }
+        const int step = k - k_begin;
+        const bool more = k + 1 < k_end;
+        gate.wait_landed<kWaves>(step);
         CornersH ring[kAheadH + 1];
-        const int lane_base = (int)cur + lane_bytes;
+        int lane_base = (int)cur + lane_bytes;
         load_corners_h<0>(ring[0], lane_base, off, a.W);
         load_corners_h<1>(ring[1], lane_base, off, a.W);
         static_for(std::make_integer_sequence<int, 16>{}, [&](auto tc) {
             constexpr int T = decltype(tc)::value;
+            PACE::step_priority<T, 16>();
+            // (ties the address to the step before, as in slab_pipeline of the float32 kernels)
+            if constexpr (T > 0)
+                asm volatile("" : "+v"(lane_base), "+v"(acc[4 * T - 4]), "+v"(acc[4 * T - 3]), "+v"(acc[4 * T - 2]), "+v"(acc[4 * T - 1]));
             if constexpr (T + kAheadH < 16)
                 load_corners_h<T + kAheadH>(ring[(T + kAheadH) % (kAheadH + 1)], lane_base, off, a.W);
             fma_corners_h<T>(acc + 4 * T, ring[T % (kAheadH + 1)], w00, w10, w01, w11);
+            if constexpr (PACE::fill_after<T, 16>) {
+                gate.wait_read<kWaves>(step);
+                feed.issue(nxt, k + 1, more);
+                fetch_record(more ? k + 1 : k);
+            }
+            if constexpr (PACE::landed_after<T, 16>) gate.slab_landed();
         });
+        gate.slab_read();
     }
 
     // lane (g, l16) holds outputs jt*64 + 4*l16 .. +3 of samples n_wave + 16*g + step
@@ -326,7 +335,7 @@ bool slab_f16_native_ok(const LayerShape &s)
 {
     if (s.dtype != LMKAN_F16) return false;
     if (s.layout != LMKAN_LAYOUT_PACKED && s.n_out % 8 != 0) return false;
-    return true;
+    return slab_feed_reaches(s, 8, 2);
 }
 
 void launch_forward_slab_f16(const LayerShape &s, const void *coef, float *y, const void *records, float *partials,
@@ -357,7 +366,7 @@ void launch_forward_slab_f16(const LayerShape &s, const void *coef, float *y, co
     finish_split_setup(a, s, y, partials, stream);
     {
         KernelTiming timing(stream, kTimeForward);
-        forward_slab_f16_kernel<<<tiles * split, kWaves * 64, (size_t)2 * s.nodes() * kRowBytesH, stream>>>(a);
+        forward_slab_f16_kernel<<<tiles * split, kWaves * 64, (((size_t)2 * s.nodes() * kRowBytesH + 15) & ~(size_t)15) + kGateBytes, stream>>>(a);
     }
     if (a.y_part) launch_sum_partials(y, a.y_part, split - 1, (int64_t)s.batch * s.n_out, stream);
 }

@@ -194,3 +194,18 @@ def test_streamed_shapes_reach_the_kernels_they_are_listed_for(rec):
                   for B, n_in, n_out, G, storage, layout in layers], rec)
     gathered = [layer for layer, (_, launches) in zip(layers, got) if "forward_gather_kernel" in names(launches)]
     assert len(gathered) <= 2, gathered
+
+
+@pytest.mark.parametrize("grid,n_in,n_out,layout,streams", [
+    (3, 16384, 16384, 0, True),     # rows of a table node 0.5 GB apart: three of them within a lane's 32 bits
+    (3, 32768, 32768, 0, False),    # 2.1 GB apart
+    (3, 32768, 32768, 1, True),     # packed: 256 bytes apart
+    (17, 8192, 8192, 0, True),      # sixteen rows per load
+    (17, 16384, 16384, 0, False),
+    (40, 16384, 16384, 0, False)])
+def test_rows_too_far_apart_for_a_lane_offset_are_not_streamed(rec, grid, n_in, n_out, layout, streams):
+    call = dict(n_in=n_in, n_out=n_out, grid=grid, batch=512, dtype=0, layout=layout)
+    for fn in (dict(fn="forward"), dict(fn="backward", grad_coef=0)):
+        (status, launches), = routes([dict(call, **fn)], rec)
+        assert status == 0
+        assert streams == any("slab" in n or "lane" in n for n in names(launches)), names(launches)

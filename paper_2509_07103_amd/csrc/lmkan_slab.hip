@@ -20,6 +20,7 @@
 
 #include "lmkan_kernels.h"
 #include "lmkan_slab_common.h"
+#include "lmkan_slab_split.h"
 
 namespace lmkan {
 
@@ -253,7 +254,7 @@ __device__ __forceinline__ void slab_pipeline(float *acc, Corners (&ring)[AHEAD 
         PACE::template step_priority<T, TOTAL>();
         // (the empty statement ties the address to the step before: it keeps the reads of a step between the
         // multiply-adds of the steps before it, where the compiler would request several steps and spill them)
-        if constexpr (T > 0)
+        if constexpr (T > 0 && AHEAD == 1)
             asm volatile("" : "+v"(lane_base), "+v"(acc[4 * T - 4]), "+v"(acc[4 * T - 3]), "+v"(acc[4 * T - 2]), "+v"(acc[4 * T - 1]));
         if constexpr (T + AHEAD < TOTAL)
             load_corners<(T + AHEAD) % 16, W_CT>(ring[(T + AHEAD) % (AHEAD + 1)], lane_base, off[(T + AHEAD) / 16], W);
@@ -305,22 +306,35 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     // record of (sample n_wave + set*64 + lane, pair k), fetched one pair ahead
     int nx_node[SETS];
     float nx_u[SETS], nx_v[SETS];
+    constexpr bool kDirect = sizeof(CT) == 4;
     auto fetch_records = [&](int k) {
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            const RecordBase rb(n_wave + s * 64, a.B);
-            const int64_t o = (int64_t)k * a.B + rb.n;
-            const unsigned l = rb.lane_index(lane);
-            nx_node[s] = (a.rec_node + o)[l];
-            nx_u[s] = (a.rec_u + o)[l];
-            nx_v[s] = (a.rec_v + o)[l];
+            if constexpr (kDirect) {
+                const RecordBase rb(n_wave + s * 64, a.B);
+                const int64_t o = (int64_t)k * a.B + rb.n;
+                const unsigned l = rb.lane_index(lane);
+                nx_node[s] = (a.rec_node + o)[l];
+                nx_u[s] = (a.rec_u + o)[l];
+                nx_v[s] = (a.rec_v + o)[l];
+            } else {
+                const int64_t n = n_wave + s * 64 + lane;
+                nx_node[s] = 0;
+                nx_u[s] = 0.f;
+                nx_v[s] = 0.f;
+                if (n < a.B) {
+                    const int64_t o = (int64_t)k * a.B + n;
+                    nx_node[s] = a.rec_node[o];
+                    nx_u[s] = a.rec_u[o];
+                    nx_v[s] = a.rec_v[o];
+                }
+            }
         }
     };
 
     // A float32 slab comes by LDS-direct loads and the waves hand the buffers over by the gate.  A 16-bit slab is
-    // staged through registers until the last steps of a pair, which leaves a gate nothing to relax (measured:
-    // bfloat16, 1024 -> 1024, G = 16: the same time), and keeps a barrier per pair.
-    constexpr bool kDirect = sizeof(CT) == 4;
+    // staged through registers until the last steps of a pair, which leaves a gate nothing to relax (bfloat16, 1024 ->
+    // 1024, G = 16: the same time with it, and with priorities), and keeps a barrier per pair.
     typedef std::conditional_t<kDirect, PaceEarly, PaceLate> PACE;
     SlabGate gate;
     SlabFeed<kRowBytes, WAVES> feed;
@@ -330,9 +344,9 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kTile, wave, lane);
     }
     if (k_begin < k_end) {
-        fetch_records(k_begin);
         if constexpr (kDirect) {
             feed.issue(__builtin_amdgcn_readfirstlane(lds_address(slab0)), k_begin);
+            fetch_records(k_begin);
             __syncthreads();  // the counters are in place
             gate.slab_landed();
         } else {
@@ -340,6 +354,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             fill.template commit<0>(a, slab0, wave, lane);
             fill.template issue<1>(a, slab0, k_begin, jt, wave, lane);
             fill.template commit<1>(a, slab0, wave, lane);
+            fetch_records(k_begin);
         }
     }
     const int lane_bytes = l16 * 16;
@@ -365,9 +380,13 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         if constexpr (kDirect) {
             gate.wait_landed<WAVES>(step);
         } else {
-            __syncthreads();  // the slab of pair k is complete, nobody reads the other buffer any more
-            if (more) fill.template issue<0>(a, slab_next, k_next, jt, wave, lane);
-            fetch_records(k_next);
+            // the slab of pair k is complete, nobody reads the other buffer any more
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (more) {
+                fill.template issue<0>(a, slab_next, k_next, jt, wave, lane);
+                fetch_records(k_next);
+            }
         }
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
@@ -384,7 +403,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
                                                                                      w11, a.W);
         };
         if constexpr (kDirect) {
-            constexpr int kFill = T * PACE::kFill / 16, kLanded = T * PACE::kLanded / 16;
+            constexpr int kFill = T * PaceEarly::kFill / 16, kLanded = T * PaceEarly::kLanded / 16;
             steps(Int<0>{}, Int<kFill>{});
             gate.wait_read<WAVES>(step);
             feed.issue(__builtin_amdgcn_readfirstlane(lds_address(slab_next)), k_next, more);
@@ -669,6 +688,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     const int64_t n_wave = (int64_t)btile * (WAVES * 64) + wave * 64, n = n_wave + lane;
     const bool valid = n < a.B;
 
+    // columns past the end of a ragged output tile are never loaded: make them read as zero (a packed table has them)
+    if (!a.packed)
+        for (int i = threadIdx.x; i < 2 * slab_floats; i += blockDim.x) smem[i] = 0.0f;
+    typedef PaceLate PACE;
+    SlabGate gate;
+    gate.init(__builtin_amdgcn_readfirstlane(lds_address(smem)) + 8 * (unsigned)slab_floats + LMKAN_MAX_GRID * 4);
+    __syncthreads();  // zeros, s_invh and the counters in place before any slab load lands
+    SlabFeed<kRowBytes, WAVES> feed;
+    feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kTile, wave, lane);
+    if (k_begin < k_end) feed.issue(__builtin_amdgcn_readfirstlane(lds_address(slab0)), k_begin);
+
     // register j: gy of outputs jt*64 + 4 p .. + 3 with p = (j + l15) mod 16
     float4 gyr[16];
 #pragma unroll
@@ -679,14 +709,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             gyr[j] = *reinterpret_cast<const float4 *>(a.gy + (col >> 6) * a.gy_tile_stride + n * a.gy_row_stride + (col & 63));
     }
 
-    // columns past the end of a ragged output tile are never loaded: make them read as zero
-    for (int i = threadIdx.x; i < 2 * slab_floats; i += blockDim.x) smem[i] = 0.0f;
-    typedef PaceLate PACE;
-    SlabGate gate;
-    gate.init(__builtin_amdgcn_readfirstlane(lds_address(smem)) + 8 * (unsigned)slab_floats + LMKAN_MAX_GRID * 4);
-    __syncthreads();  // zeros, s_invh and the counters in place before any slab load lands
-    SlabFeed<kRowBytes, WAVES> feed;
-    feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kTile, wave, lane);
     int nx_node = 0;
     float nx_u = 0.f, nx_v = 0.f;
     auto fetch_record = [&](int k) {
@@ -698,7 +720,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         nx_v = (a.rec_v + o)[l];
     };
     if (k_begin < k_end) {
-        feed.issue(__builtin_amdgcn_readfirstlane(lds_address(slab0)), k_begin);
         fetch_record(k_begin);
         gate.slab_landed();
     }
@@ -780,13 +801,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 }
 
 // ---------------------------------------------------------------------------
-// Input gradient for 16-bit packed tables on grids too fine for 64-output slabs (17 <= G <= 34):
-// 32-output tiles whose slab stays in LDS as it is stored (64 bytes per row, LDS-direct fill, two
-// buffers), a lane per sample as in backward_input_lane_kernel, two samples per lane (2048 per
-// workgroup, so that a slab serves twice as many).  A row is four pieces of eight outputs; lane l
-// reads piece (j + l) mod 4 at step j and holds its gy in that order.  The stored values are
-// widened in registers (a shift or a mask for bfloat16), the differences of neighbouring corners
-// are taken per piece.
+// Kernels for 16-bit packed tables on grids too fine for 64-output slabs (17 <= G <= 34): 32-output
+// tiles whose slab stays in LDS as it is stored (64 bytes per row, LDS-direct fill, two buffers), a
+// lane per sample as in backward_input_lane_kernel, two samples per lane (2048 per workgroup, so that
+// a slab serves twice as many; the input gradient of bfloat16 tables has a form of its own, below).
+// A row is four pieces of eight outputs; lane l reads piece (j + l) mod 4 at step j and holds its
+// outputs or gy in that order.  The stored values are widened in registers (a shift or a mask for
+// bfloat16); the input gradient takes the differences of neighbouring corners per piece.
 // ---------------------------------------------------------------------------
 constexpr int kHalfTile = 32;
 constexpr int kHalfRowBytes = kHalfTile * 2;
@@ -955,10 +976,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     }
 }
 
+// float16: a lane per sample, two samples per lane
 template <typename CT>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) void backward_input_lane32_kernel(GradInArgs a)
+__device__ __forceinline__ void backward_input_lane32(const GradInArgs &a, char *smem32)
 {
-    extern __shared__ __align__(16) char smem32[];  // two slab buffers, then 1/h of the grid
+    // LDS: two slab buffers, 1/h of the grid, the gate
+    typedef PaceLate PACE;
     constexpr int WAVES = 16, SETS = 2;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -977,17 +1000,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     float *s_invh = reinterpret_cast<float *>(smem32 + ((2 * slab_bytes + 15) & ~15u));
     for (int i = threadIdx.x; i < a.tab.G; i += blockDim.x) s_invh[i] = a.tab.inv_h[i];
 
-    // packed table: the rows of (pair, 64-output tile jt / 2) lie 128 bytes apart, this tile is
-    // their half jt & 1; a wave instruction moves 16 rows (four lanes x 16 bytes each)
-    const CT *half = static_cast<const CT *>(a.P) + (int64_t)(jt >> 1) * a.map.s_tile + (jt & 1) * kHalfTile + (lane & 3) * 8;
-    const int chunks = (a.nodes + 15) >> 4;
-    auto issue_fill = [&](unsigned lds_base, int k) {
-        const CT *src = half + (int64_t)k * a.map.s_pair;
-        for (int c = wave; c < chunks; c += WAVES) {
-            const int node = c * 16 + (lane >> 2);
-            if (node < a.nodes) lds_dma16(src + (int64_t)node * a.map.s_node, __builtin_amdgcn_readfirstlane(lds_base + c * 1024));
-        }
-    };
+    SlabFeed<kHalfRowBytes, WAVES> feed;
+    feed.template init<2>(a.P, a.map, a.nodes, a.col_limit, jt * kHalfTile, wave, lane);
+    SlabGate gate;
+    gate.init(base0 + ((2 * slab_bytes + 15) & ~15u) + LMKAN_MAX_GRID * 4);
+
+    __syncthreads();  // s_invh and the counters in place
+    if (k_begin < k_end) feed.issue(base0, k_begin);
 
     const int64_t n0 = (int64_t)btile * (WAVES * SETS * 64) + wave * (SETS * 64) + lane;
     // register block j of a sample: gy of outputs jt*32 + 8 p .. + 7 with p = (j + l3) mod 4
@@ -1008,27 +1027,23 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         }
     }
 
+    const int64_t n_wave = (int64_t)btile * (WAVES * SETS * 64) + wave * (SETS * 64);
     int nx_node[SETS];
     float nx_u[SETS], nx_v[SETS];
-    // (a sample past the end of the batch reads the records of the last one; the records of a pair
-    // start at a wave-uniform address, the sample is a 32-bit index into them)
-    unsigned n_rec[SETS];
-#pragma unroll
-    for (int s = 0; s < SETS; ++s) n_rec[s] = (unsigned)min(n0 + s * 64, a.B - 1);
     auto fetch_records = [&](int k) {
-        const int32_t *r_node = a.rec_node + (int64_t)k * a.B;
-        const float *r_u = a.rec_u + (int64_t)k * a.B, *r_v = a.rec_v + (int64_t)k * a.B;
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            nx_node[s] = r_node[n_rec[s]];
-            nx_u[s] = r_u[n_rec[s]];
-            nx_v[s] = r_v[n_rec[s]];
+            const RecordBase rb(n_wave + s * 64, a.B);
+            const int64_t o = (int64_t)k * a.B + rb.n;
+            const unsigned l = rb.lane_index(lane);
+            nx_node[s] = (a.rec_node + o)[l];
+            nx_u[s] = (a.rec_u + o)[l];
+            nx_v[s] = (a.rec_v + o)[l];
         }
     };
-    __syncthreads();  // s_invh in place
     if (k_begin < k_end) {
-        issue_fill(base0, k_begin);
         fetch_records(k_begin);
+        gate.slab_landed();
     }
 
     for (int k = k_begin; k < k_end; ++k) {
@@ -1038,12 +1053,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         float u[SETS], v[SETS];
 #pragma unroll
         for (int s = 0; s < SETS; ++s) node[s] = nx_node[s], u[s] = nx_u[s], v[s] = nx_v[s];
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (k + 1 < k_end) {
-            issue_fill(nxt, k + 1);
-            fetch_records(k + 1);
-        }
+        const int step = k - k_begin;
+        const bool more = k + 1 < k_end;
+        gate.wait_landed<WAVES>(step);
         // piece (j + l3) mod 4 of the row: from `first` for j < 4 - l3, one row back after the wrap
         unsigned first[SETS];
 #pragma unroll
@@ -1065,6 +1077,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         static_for(std::make_integer_sequence<int, SETS * 4>{}, [&](auto tc) {
             constexpr int t = decltype(tc)::value;
             constexpr int s = t >> 2, j = t & 3;
+            PACE::step_priority<t, SETS * 4>();
             if constexpr (t + 1 < SETS * 4) request(ring[(t + 1) & 1], t + 1);
             const CornersRaw &c = ring[t & 1];
             float f[8];
@@ -1097,8 +1110,32 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 }
                 dif_a = dif_b = dif_c = dif_d = 0.f;
             }
+            if constexpr (PACE::fill_after<t, SETS * 4>) {
+                gate.wait_read<WAVES>(step);
+                feed.issue(nxt, k + 1, more);
+                fetch_records(more ? k + 1 : k);
+            }
+            if constexpr (PACE::landed_after<t, SETS * 4>) gate.slab_landed();
         });
+        gate.slab_read();
     }
+}
+
+// bfloat16: on the matrix cores (lmkan_slab_split.h), 1024 samples per workgroup.  A conversion beside every
+// multiply-add is gone: 2048 -> 2048 at G = 32, 4096 rows 3740 -> 2500 us, 300 -> 200 at G = 18, 3000 rows
+// 64 -> 35.  A float16 table needs no conversion (mixed multiply-adds); the matrix cores win 8192 rows of 1024 ->
+// 1024 at G = 24 (1260 us lane per sample and barrier, 1025 matrix cores) but lose where a slab serves few rows,
+// which costs them twice the fill (512 -> 512 at G = 32, 1500 rows: 108 against 131), and are not taken.
+constexpr int kLane32Rows = 2048, kLane32RowsBf16 = 1024;   // per workgroup
+
+template <typename CT>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) void backward_input_lane32_kernel(GradInArgs a)
+{
+    extern __shared__ __align__(16) char smem32[];
+    if constexpr (is_bf16<CT>::value)
+        backward_input_split<CT, kHalfTile, 16, 80, false, true, 0>(a, smem32);
+    else
+        backward_input_lane32<CT>(a, smem32);
 }
 
 // ---------------------------------------------------------------------------
@@ -1150,6 +1187,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     SlabGate gate;
     gate.init(base0 + ((2 * slab_bytes + 15) & ~15u) + LMKAN_MAX_GRID * 4);
 
+    __syncthreads();  // s_invh and the counters in place
+    if (k_begin < k_end) feed.issue(base0, k_begin);
+
     const int64_t n0 = (int64_t)btile * (WAVES * SETS * 64) + wave * (SETS * 64) + lane;
     // register block j of a sample: gy of outputs jt*32 + PER p .. + PER - 1 with p = (j + lp) mod PIECES
     float gyr[SETS][PIECES][PER];
@@ -1181,9 +1221,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             nx_v[s] = (a.rec_v + o)[l];
         }
     };
-    __syncthreads();  // s_invh and the counters in place
     if (k_begin < k_end) {
-        feed.issue(base0, k_begin);
         fetch_records(k_begin);
         gate.slab_landed();
     }
@@ -2229,7 +2267,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
                                 int64_t gy_tile_stride, int64_t gy_row_stride, float *gx, const void *records,
                                 void *scratch, hipStream_t stream, const ConvGeom *conv)
 {
-    if (slab_wide_fits(s) && slab_f16_native_ok(s)) {
+    if (slab_wide_fits(s) && slab_f16_split_ok(s)) {
         launch_fill_zero(static_cast<float *>(scratch), (size_t)scratch_row_stride(s.batch, kScratchPlain) * s.n_in,
                          stream);
         launch_backward_input_slab_f16(s, tab, coef, gy, gy_tile_stride, gy_row_stride, static_cast<float *>(scratch),
@@ -2241,8 +2279,12 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
     constexpr int kTileB = WAVES * SETS * 64;
     typedef void (*Kernel)(GradInArgs);
     const bool narrow = !slab_wide_fits(s);
-    // packed tables on the grids of the 16-output tiles: 32-output tiles kept as stored where two fit
-    const bool lane32 = slab_backward_input_takes_half_tiles(s);
+    // packed tables on the grids of the 16-output tiles: 32-output tiles kept as stored where two fit.  bfloat16 also
+    // where 64-output tiles would fit (they widen the table on its way to LDS), but for a few rows: 8192 rows of 1024 ->
+    // 1024 at G = 16 1290 us with 64-output tiles, 940 here, 1500 rows of 512 -> 512 at G = 12 88 and 67, 500 rows
+    // of 1024 -> 1024 175 and 153; below 256 rows tiles are mostly empty and the difference comes down to the fill.
+    const bool lane32 = slab_backward_input_takes_half_tiles(s) ||
+                        (slab_wide_fits(s) && s.dtype == LMKAN_BF16 && s.layout == LMKAN_LAYOUT_PACKED && s.batch >= 256);
     if (lane32) {
         const Kernel k32 = s.dtype == LMKAN_F32   ? backward_input_lane32_f32_kernel
                            : s.dtype == LMKAN_F16 ? backward_input_lane32_kernel<_Float16>
@@ -2268,7 +2310,9 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
         a.nodes = s.nodes();
         a.col_limit = s.out_tiles() * kTile;
         a.packed = 1;
-        a.n_btiles = (int)((s.batch + 2047) / 2048);
+        const bool on_matrix_cores = s.dtype == LMKAN_BF16;
+        const int tile_b = on_matrix_cores ? kLane32RowsBf16 : kLane32Rows;
+        a.n_btiles = (int)((s.batch + tile_b - 1) / tile_b);
         a.n_jt = (s.n_out + kHalfTile - 1) / kHalfTile;
         const int tiles32 = a.n_btiles * a.n_jt;
         const int split32 = pair_split_count(tiles32, a.K, 0, a.K);
@@ -2276,7 +2320,12 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
         a.pairs_per_split = (a.K + split32 - 1) / split32;
         a.ld = scratch_row_stride(s.batch, kScratchPlain);
         launch_fill_zero(a.gx, (size_t)a.ld * s.n_in, stream);
-        const size_t lds = (((size_t)2 * s.nodes() * half_tile_row_bytes(s) + 15) & ~(size_t)15) + LMKAN_MAX_GRID * sizeof(float) + kGateBytes;
+        size_t slabs = ((size_t)2 * s.nodes() * half_tile_row_bytes(s) + 15) & ~(size_t)15;
+        const size_t around = LMKAN_MAX_GRID * sizeof(float) + kGateBytes + kNowhereBytes;
+        a.slab_pitch = a.W * kHalfRowBytes;
+        if (on_matrix_cores && (size_t)2 * a.W * split_pitch(a.W, kHalfRowBytes) + around <= 160 * 1024)   // (all but G = 34)
+            a.slab_pitch = split_pitch(a.W, kHalfRowBytes), slabs = (size_t)2 * a.W * a.slab_pitch;
+        const size_t lds = slabs + around;
         {
             KernelTiming timing(stream, kTimeGradInput);
             k32<<<tiles32 * split32, 1024, lds, stream>>>(a);

@@ -7,6 +7,8 @@
 
 namespace lmkan {
 
+typedef float f4v __attribute__((ext_vector_type(4)));
+
 constexpr int kSlabTile = LMKAN_PACK_TILE;  // 64 outputs per workgroup tile
 
 struct SlabArgs {
@@ -81,44 +83,34 @@ __device__ __forceinline__ int xcd_tile()
     return xcd * each + min(xcd, over) + ((int)blockIdx.x >> 3);
 }
 
-// 16 bytes per lane from global memory straight into LDS at lds_base + lane * 16
-// (lds_base wave-uniform).  Written as inline assembly on purpose: the compiler does not
-// track it, so it cannot make every later LDS read wait for loads that fill the *other*
-// buffer; completion is awaited explicitly with s_waitcnt vmcnt(0) before the barrier.
-// m0 is overwritten without being listed as clobbered: it is a reserved register to this
-// compiler, which rejects it in a clobber list and never keeps a value in it across
-// statements (it sets m0 itself right before any instruction of its own that reads it).
-__device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_base)
-{
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :
-                 : "v"(gptr), "s"(lds_base)
-                 : "memory");
-}
-
 __device__ __forceinline__ unsigned lds_address(const void *p)
 {
     return (unsigned)(size_t)(__attribute__((address_space(3))) const void *)p;
 }
 
-// Same, with the global address given as a wave-uniform base (scalar registers) plus a 32-bit
-// per-lane byte offset: stepping through a contiguous slab then costs scalar instructions only.
-__device__ __forceinline__ void lds_dma16_uniform(const void *gbase, unsigned lane_off, unsigned lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(lane_off), "s"(gbase), "s"(lds_base)
-                 : "memory");
-}
-
-// Same for a piece of a fill that may be partial or absent: only the lanes of `lanes` load, and none of
-// them is a case too.  One statement without a branch the compiler could see, so that a fill may stand in
-// the middle of a main loop without cutting it into blocks (each of which would be scheduled by itself).
-// To be used where all lanes of the wave are active.
+// 16 bytes per lane from global memory (a wave-uniform base and 32 bits of offset per lane) straight into LDS at
+// lds_base + lane * 16, for the lanes of `lanes`; none of them is a case too.  Inline assembly on purpose: the
+// compiler does not track it, so it cannot make every later LDS read wait for loads that fill the *other* buffer;
+// completion is awaited explicitly with s_waitcnt vmcnt(0).  And one statement without a branch the compiler could
+// see, so that a fill may stand in the middle of a main loop without cutting it into blocks (each of which would
+// be scheduled by itself).  To be used where all lanes of the wave are active.
+// m0 is overwritten without being listed as clobbered: it is a reserved register to this
+// compiler, which rejects it in a clobber list and never keeps a value in it across
+// statements (it sets m0 itself right before any instruction of its own that reads it).
 __device__ __forceinline__ void lds_dma16_lanes(const void *gbase, unsigned lane_off, unsigned lds_base, uint64_t lanes)
 {
     asm volatile("s_cmp_eq_u64 %3, 0\n\ts_cbranch_scc1 .Labsent%=\n\ts_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\t"
                  "global_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1\n.Labsent%=:"
+                 :
+                 : "v"(lane_off), "s"(gbase), "s"(lds_base), "s"(lanes)
+                 : "memory", "scc");
+}
+
+// Four bytes per lane of `lanes` to lds_base + 4 lane: to bring a line into the L2 without a register to receive it
+__device__ __forceinline__ void lds_dma4_lanes(const void *gbase, unsigned lane_off, unsigned lds_base, uint64_t lanes)
+{
+    asm volatile("s_cmp_eq_u64 %3, 0\n\ts_cbranch_scc1 .Labsent%=\n\ts_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\t"
+                 "global_load_lds_dword %0, %1\n\ts_mov_b64 exec, -1\n.Labsent%=:"
                  :
                  : "v"(lane_off), "s"(gbase), "s"(lds_base), "s"(lanes)
                  : "memory", "scc");
@@ -194,6 +186,7 @@ inline bool slab_feed_reaches(const LayerShape &s, int rows_per_chunk, int eleme
 // 570 -> 520.  The gate without the priorities is no gain (994 us instead of 830): the waves that happen to be
 // ahead then keep the SIMD until the gate stops them, and the others run alone.
 constexpr int kGateBytes = 16;
+constexpr int kNowhereBytes = 256;   // what loads for the L2's sake write into
 
 // When a wave does what, in sixteenths of a pair: FILL: the next slab is requested, LANDED: its arrival is waited
 // for.  A wave that lags behind gets the SIMD first: its priority falls from quarter to quarter of a pair, and
@@ -310,6 +303,7 @@ struct GradInArgs {
     int n_split;
     int col_limit;
     int packed;
+    int slab_pitch;    // kernels on the matrix cores: bytes between two grid lines of a slab in LDS
 };
 
 // Layouts of a row of the transposed scratch gradient.  The slab kernels leave a set of 64

@@ -357,6 +357,25 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             fetch_records(k_begin);
         }
     }
+    // a wave without samples only fetches
+    if (n_wave >= a.B) {
+        if constexpr (kDirect) {
+            const unsigned base0 = __builtin_amdgcn_readfirstlane(lds_address(smem)), base1 = base0 + 4 * (unsigned)slab_floats;
+            gate.feed_only<WAVES>(k_end - k_begin, [&](int i, bool wanted) { feed.issue(i & 1 ? base1 : base0, k_begin + i, wanted); });
+        } else {
+            for (int k = k_begin; k < k_end; ++k) {
+                float *slab_next = ((k - k_begin) & 1) ? slab0 : slab1;
+                __syncthreads();
+                if (k + 1 < k_end) {
+                    fill.template issue<0>(a, slab_next, k + 1, jt, wave, lane);
+                    fill.template commit<0>(a, slab_next, wave, lane);
+                    fill.template issue<1>(a, slab_next, k + 1, jt, wave, lane);
+                    fill.template commit<1>(a, slab_next, wave, lane);
+                }
+            }
+        }
+        return;
+    }
     const int lane_bytes = l16 * 16;
     for (int k = k_begin; k < k_end; ++k) {
         const float *slab = ((k - k_begin) & 1) ? slab1 : slab0;
@@ -723,6 +742,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         fetch_record(k_begin);
         gate.slab_landed();
     }
+    if (n_wave >= a.B) {
+        const unsigned base0 = __builtin_amdgcn_readfirstlane(lds_address(smem)), base1 = base0 + 4 * (unsigned)slab_floats;
+        gate.feed_only<WAVES>(k_end - k_begin, [&](int i, bool wanted) { feed.issue(i & 1 ? base1 : base0, k_begin + i, wanted); });
+        return;
+    }
     const int w = W_CT > 0 ? W_CT : a.W;
     float *gx_wave = a.gx + n_wave;   // transposed scratch [n_in][ld], plain layout
     for (int k = k_begin; k < k_end; ++k) {
@@ -901,6 +925,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         gate.slab_landed();
     }
 
+    if (n_wave >= a.B) {
+        gate.feed_only<WAVES>(k_end - k_begin, [&](int i, bool wanted) { feed.issue(i & 1 ? base1 : base0, k_begin + i, wanted); });
+        return;
+    }
     for (int k = k_begin; k < k_end; ++k) {
         const unsigned cur = ((k - k_begin) & 1) ? base1 : base0;
         const unsigned nxt = ((k - k_begin) & 1) ? base0 : base1;
@@ -1046,6 +1074,10 @@ __device__ __forceinline__ void backward_input_lane32(const GradInArgs &a, char 
         gate.slab_landed();
     }
 
+    if (n_wave >= a.B) {
+        gate.feed_only<WAVES>(k_end - k_begin, [&](int i, bool wanted) { feed.issue(i & 1 ? base1 : base0, k_begin + i, wanted); });
+        return;
+    }
     for (int k = k_begin; k < k_end; ++k) {
         const unsigned cur = ((k - k_begin) & 1) ? base1 : base0;
         const unsigned nxt = ((k - k_begin) & 1) ? base0 : base1;
@@ -1226,6 +1258,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         gate.slab_landed();
     }
 
+    if (n_wave >= a.B) {
+        gate.feed_only<WAVES>(k_end - k_begin, [&](int i, bool wanted) { feed.issue(i & 1 ? base1 : base0, k_begin + i, wanted); });
+        return;
+    }
     for (int k = k_begin; k < k_end; ++k) {
         const unsigned cur = ((k - k_begin) & 1) ? base1 : base0;
         const unsigned nxt = ((k - k_begin) & 1) ? base0 : base1;
@@ -1367,6 +1403,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         gate.slab_landed();
     }
 
+    if (n_wave >= a.B) {
+        gate.feed_only<WAVES>(k_end - k_begin, [&](int i, bool wanted) { feed.issue(i & 1 ? base1 : base0, k_begin + i, wanted); });
+        return;
+    }
     for (int k = k_begin; k < k_end; ++k) {
         const unsigned cur = ((k - k_begin) & 1) ? base1 : base0;
         const unsigned nxt = ((k - k_begin) & 1) ? base0 : base1;
@@ -1588,6 +1628,14 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             gate.slab_landed();
         }
     }
+    if constexpr (kGated) {
+        if (n_wave >= a.B) {
+            gate.feed_only<WAVES>(k_end - k_begin, [&](int i, bool wanted) {
+                feed.issue(i & 1 ? lds0 + 4 * (unsigned)slab_floats : lds0, k_begin + i, wanted);
+            });
+            return;
+        }
+    }
     int lane_bytes = sub * 16;
     for (int k = k_begin; k < k_end; ++k) {
         const float *slab = ((k - k_begin) & 1) ? slab1 : slab0;
@@ -1800,6 +1848,14 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             fill.template commit<0>(sa, slab0, wave, lane);
             fill.template issue<1>(sa, slab0, k0, jt, wave, lane);
             fill.template commit<1>(sa, slab0, wave, lane);
+        }
+    }
+    if constexpr (kDirect) {
+        if (n_wave >= a.B) {
+            gate.feed_only<WAVES>(n_k, [&](int i, bool wanted) {
+                feed.issue(i & 1 ? lds0 + 4 * (unsigned)slab_floats : lds0, pair_at(i), wanted);
+            });
+            return;
         }
     }
     const int lane_bytes = sub * 16;

@@ -262,6 +262,21 @@ struct SlabGate {
     {
         wait(read, WAVES * step);
     }
+    // The walk of a wave without samples: it fetches its part of every slab, as soon as there is room, and leaves the
+    // SIMD to the others.  request(i, wanted): the slab of pair i.
+    template <int WAVES, typename F>
+    __device__ __forceinline__ void feed_only(int n_pairs, F &&request) const
+    {
+        // (the first slab is in place before anyone reports the second: one count per wave and slab.  Later on
+        // wait_read sees to that.)
+        wait_landed<WAVES>(0);
+        for (int i = 0; i < n_pairs; ++i) {
+            wait_read<WAVES>(i);
+            request(i + 1, i + 1 < n_pairs);
+            slab_landed();
+            slab_read();
+        }
+    }
 };
 
 // Records of 64 consecutive samples of a pair, from sample n on: scalar base, 32-bit lane offset.  Samples past

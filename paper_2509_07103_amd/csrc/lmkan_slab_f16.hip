@@ -118,6 +118,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
         __syncthreads();  // the counters are in place
         gate.slab_landed();
     }
+    if (n_wave >= a.B) {
+        gate.feed_only<kWaves>(k_end - k_begin, [&](int i, bool wanted) { feed.issue(i & 1 ? base1 : base0, k_begin + i, wanted); });
+        return;
+    }
     const int lane_bytes = l16 * 8;
     for (int k = k_begin; k < k_end; ++k) {
         const unsigned cur = ((k - k_begin) & 1) ? base1 : base0;

@@ -290,6 +290,14 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
     fetch_record(k_begin);
     gate.slab_landed();
 
+    if (n_wave >= a.B) {
+        gate.feed_only<WAVES>(k_end - k_begin, [&](int i, bool wanted) {
+#pragma unroll
+            for (int c = 0; c < kChunks; ++c) issue_piece(c, i & 1 ? base0 + slab_bytes : base0, k_begin + i, wanted);
+            if constexpr (PREFETCH) prefetch(k_begin + i + 1, k_begin + i + 1 < k_end);
+        });
+        return;
+    }
     const bool valid = n_wave + lane < a.B;
     const float inv_w = 1.0f / (float)W;
     const float part_factor = !Part::kScaled || part == 0 ? 1.0f : part == 1 ? 0x1p-11f : 0x1p-22f;

@@ -29,7 +29,6 @@ constexpr int kTile = LMKAN_PACK_TILE;
 constexpr int kSortThreads = 1024;
 
 constexpr int kDepth = 8;    // chunks of gy values in flight
-constexpr int kPerW = 4;     // chunks whose entries one load instruction brings in
 static_assert(kUnroll % kDepth == 0, "the gy ring must divide the unrolled trip");
 
 // Counting sort of the samples of every pair by cell, one launch: a workgroup takes the samples of one
@@ -266,10 +265,9 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
     if (split && nch == 0) return;
     ScalarIntPtr cc = (ScalarIntPtr)(a.chunk_cell + (int64_t)k * (a.S / kChunk) + c_begin);
 
-    // entries: lane (g, 4 j + q) fetches the entry of group g's sample of chunk c + j and will
-    // form its product q, so one load brings in four chunks (256 contiguous bytes); sample
-    // indices: lane (g, j) fetches the index of group g's sample of chunk c + j, sixteen chunks
-    // per load
+    // entries: lane (g, j) fetches the entry of group g's sample of chunk c + j, sixteen chunks per load (a trip).
+    // The texture addresser takes four lanes per clock, so a load costs 16 clocks whatever it brings; with four
+    // loads of entries and one of indices per trip it was busy 85 % of the kernel (1024 -> 1024, G = 16).
     const f4v *rec_k = a.rec + (int64_t)k * a.S + (int64_t)c_begin * kChunk;  // wave-uniform
     // The loads of the main loop are written as inline assembly, and so are the waits for them:
     // vector loads return in the order they were issued, and with the cell changes branching
@@ -278,18 +276,12 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
     // may stay in flight).  Every load below is issued at a fixed place of a trip, so the number
     // of younger loads at the point of use is known; loads the compiler adds on the rare paths
     // (row stores, atomics) only add to that number, which keeps the waits safe.
-    const unsigned e_off = (unsigned)(((l16 >> 2) * kChunk + g) * sizeof(f4v));
-    const unsigned n_off = (unsigned)((l16 * kChunk + g) * sizeof(f4v) + 12);
+    const unsigned e_off = (unsigned)((l16 * kChunk + g) * sizeof(f4v));
     // (operands are copied into locals first: a name used only as an asm operand is not captured)
     auto load_e = [&](f4v &dst, int chunk) {
         const f4v *base = rec_k + (int64_t)chunk * kChunk;
         const unsigned off = e_off;
         asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(dst) : "v"(off), "s"(base) : "memory");
-    };
-    auto load_n = [&](int &dst, int chunk) {
-        const f4v *base = rec_k + (int64_t)chunk * kChunk;
-        const unsigned off = n_off;
-        asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(off), "s"(base) : "memory");
     };
     // blocks until at most N loads younger than the one that fills v are outstanding, i.e. until v has landed.
     // The compiler does not know that v is in flight between the load and this wait: were it to copy
@@ -332,29 +324,19 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
 
     if (nch > 0) {
         // Software pipeline, all through in-order vector loads: at step P of a trip the chunk
-        // c + P is consumed and the gy values of chunk c + P + kDepth are requested (their sample
-        // indices were loaded a trip earlier); a register of products is refilled for the next
-        // trip as soon as its fourth chunk has been consumed.  Order of issue in a trip: the
-        // indices of the next trip, then per step one gy load, after every fourth step one load
-        // of entries: 21 loads.
-        f4v eq[kUnroll / kPerW];   // entries as loaded
-        float wq[kUnroll / kPerW];  // their products, formed when the first of the four chunks is consumed
+        // c + P is consumed and the gy values of chunk c + P + kDepth are requested; the entries of the
+        // next trip are requested at its top, their sample indices are needed from the step on that
+        // requests its first chunk.  Order of issue in a trip: the entries, then per step one gy load.
+        f4v entry;          // of this lane's chunk: on its way from the top of a trip to its middle
+        float prod[4];      // products of the trip's entries, chunk 4 j + i in register i and quad j
         f4v gq[kDepth];
         int n_now, n_nxt;
-        // The fill is issued in the order the steady state leaves the loads in at the top of a
-        // trip, so that the wait counts of the first steps are those of every other trip.
-        load_n(n_now, 0);
-        static_for(std::make_integer_sequence<int, kUnroll / kPerW>{}, [&](auto rc) {
-            constexpr int r = decltype(rc)::value;
-            if constexpr (r * kPerW < kUnroll - kDepth) load_e(eq[r], r * kPerW);
-        });
-        landed(n_now, std::integral_constant<int, (kUnroll - kDepth) / kPerW>{});
-        n_now = row_offset(n_now);
+        load_e(entry, 0);
+        landed(entry, std::integral_constant<int, 0>{});
+        n_now = row_offset(__float_as_int(entry.w));
         static_for(std::make_integer_sequence<int, kDepth>{}, [&](auto dc) {
             constexpr int d = decltype(dc)::value;
-            constexpr int P = kUnroll - kDepth + d;  // the step that requests this chunk in later trips
             load_gy(gq[d], std::integral_constant<int, d>{}, n_now);
-            if constexpr (P % kPerW == kPerW - 1) load_e(eq[P / kPerW], (P / kPerW) * kPerW);
         });
         // cells of a whole trip are fetched one trip ahead (scalar loads return out of order, so
         // every use waits for all of them: keep them few and early)
@@ -365,32 +347,26 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         for (int c = 0; c < nch; c += kUnroll) {
 #pragma unroll
             for (int p = 0; p < kUnroll; ++p) cells_nxt[p] = cc[c + kUnroll + p];
-            load_n(n_nxt, c + kUnroll);
+            entry_products(entry, l16, prod);
+            load_e(entry, c + kUnroll);
             static_for(std::make_integer_sequence<int, kUnroll>{}, [&](auto pc) {
                 constexpr int P = decltype(pc)::value;
                 const int cell_cur = cells_now[P];
-                // Younger loads at this point.  A gy value: the 7 gy loads after it and two loads
-                // of entries (three in the first trip, four when the top of a trip lies between).
-                // Entries: 16 (12 for the first register in the first trip).  Indices: 8 gy loads
-                // and 2 loads of entries.
+                // Younger loads at this point.  A gy value: the 7 gy loads after it, and the load of entries
+                // where the top of a trip lies between.  Entries: the gy loads of the steps since.
                 if constexpr (P == kUnroll - kDepth) {
-                    landed(n_nxt, std::integral_constant<int, kDepth + kDepth / kPerW>{});
-                    n_nxt = row_offset(n_nxt);  // first needed below
+                    landed(entry, std::integral_constant<int, kUnroll - kDepth>{});
+                    n_nxt = row_offset(__float_as_int(entry.w));  // first needed below
                 }
-                if constexpr (P % kPerW == 0) {
-                    landed(eq[P / kPerW], std::integral_constant<int, P == 0 ? 12 : 15>{});
-                    wq[P / kPerW] = entry_product(eq[P / kPerW], l16 & 3);
-                }
-                landed(gq[P % kDepth], std::integral_constant<int, kDepth - 1 + kDepth / kPerW>{});
+                landed(gq[P % kDepth], std::integral_constant<int, P < kDepth ? kDepth : kDepth - 1>{});
                 if (cell_cur != cur_cell) {
                     if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, cell_cur, lane);
                     retire_before(ring, out, done, cell_cur, lane);
                     cur_cell = cell_cur;
                 }
-                chunk_fma<P % kPerW>(acc, wq[P / kPerW], gq[P % kDepth]);
+                chunk_fma<P / 4>(acc, prod[P % 4], gq[P % kDepth]);
                 load_gy(gq[P % kDepth], std::integral_constant<int, (P + kDepth) % kUnroll>{},
                         P + kDepth < kUnroll ? n_now : n_nxt);
-                if constexpr (P % kPerW == kPerW - 1) load_e(eq[P / kPerW], c + kUnroll + (P / kPerW) * kPerW);
             });
             n_now = n_nxt;
 #pragma unroll

@@ -217,7 +217,10 @@ __device__ __forceinline__ void retire_nodes(const NodeRing &ring, const GradOut
                     const f4v v = *p;
                     if ((o.n_out & 3) == 0) {
                         f4v *d4 = reinterpret_cast<f4v *>(dst);
-                        *d4 = o.accumulate ? *d4 + v : v;
+                        // (past the caches: the gradient of a wave is read by nobody soon, and would push out the
+                        // rows of gy that all waves of an XCD gather from: 2048 -> 2048, G = 32: 4290 -> 4130 us,
+                        // 1024 -> 1024 at G = 28 1280 -> 1170, with 32 samples per cell no difference)
+                        __builtin_nontemporal_store(o.accumulate ? *d4 + v : v, d4);
                     } else {
                         // rows of the gradient do not start on 16 bytes and the last one is short
 #pragma unroll
@@ -236,6 +239,35 @@ __device__ __forceinline__ void retire_before(const NodeRing &ring, const GradOu
 {
     const int c = (cell >> 8) * ring.W + (cell & 255);
     retire_nodes(ring, o, done, done + ((c - done) & ~3), lane);
+}
+
+// All four products of this lane's entry, in that order, spread over its quad: r[i] of lane q is product q of the
+// entry of the quad's lane i (a 4 x 4 transposition).  One load per lane then serves sixteen chunks.
+__device__ __forceinline__ void entry_products(const f4v &e, int lane, float (&r)[4])
+{
+    const float a0 = 1.0f - e.x, b_lo = 1.0f - e.y, there = __builtin_fabsf(e.z);
+    const bool odd = e.z < 0.f;
+    const float b0 = (odd ? e.y : b_lo) * there, b1 = (odd ? b_lo : e.y) * there;
+    const float p[4] = {a0 * b0, e.x * b0, a0 * b1, e.x * b1};
+    auto from = [](float v, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    constexpr std::integral_constant<int, 0xB1> across1{};   // quad_perm [1,0,3,2]
+    constexpr std::integral_constant<int, 0x4E> across2{};   // quad_perm [2,3,0,1]
+    const bool q0 = (lane & 1) != 0, q1 = (lane & 2) != 0;
+    float t[4];
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+        const float x = from(p[i + 1], across1), y = from(p[i], across1);   // (by all lanes, before anyone chooses)
+        t[i] = q0 ? x : p[i];
+        t[i + 1] = q0 ? p[i + 1] : y;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float x = from(t[i + 2], across2), y = from(t[i], across2);
+        r[i] = q1 ? x : t[i];
+        r[i + 2] = q1 ? t[i + 2] : y;
+    }
 }
 
 // product q = (lane & 3) of an entry, in the order of the accumulators: ((1-u)(1-v), u(1-v), (1-u)v, uv)[q]

@@ -251,18 +251,17 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
     // With one block and one wave per (pair, tile) the wave owns its columns of the gradient and
     // writes every row once.  Otherwise (long batches; too few pairs x tiles to fill the chip)
     // a wave takes a run of whole trips of one block; a run may begin and end anywhere, even
-    // inside a cell: every wave then adds what it has into a gradient that starts at zero.
-    const bool split = a.n_blocks > 1 || a.n_sub > 1;
+    // inside a cell, and some or all of its nodes are other waves' too (run_nodes).
+    bool last_run = true;
     int c_begin = blk * a.block_stride;
     int nch = ((ScalarIntPtr)(a.block_chunks + (int64_t)k * a.n_blocks))[blk];
     if (a.n_sub > 1) {
-        const int trips = nch / kUnroll;
-        const int per = (trips + a.n_sub - 1) / a.n_sub * kUnroll;
-        const int skip = min(sub * per, nch);
+        const int per = run_chunks(nch, a.n_sub), skip = min(sub * per, nch);
+        last_run = skip + per >= nch;
         c_begin += skip;
         nch = min(per, nch - skip);
+        if (nch == 0) return;
     }
-    if (split && nch == 0) return;
     ScalarIntPtr cc = (ScalarIntPtr)(a.chunk_cell + (int64_t)k * (a.S / kChunk) + c_begin);
 
     // entries: lane (g, j) fetches the entry of group g's sample of chunk c + j, sixteen chunks per load (a trip).
@@ -314,13 +313,15 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
 
     const NodeRing ring(win, W);
     for (int i = lane; i < ring.R * kTile; i += 64) win[i] = 0.0f;
-    const GradOut out{a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0, split};
+    const RunNodes nodes = run_nodes(cc, nch, sub == 0, last_run, a.n_blocks > 1, W);
+    const GradOut out{a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0,
+                      nodes.own()};
 
     f4v acc[4];  // [output i of the lane][2 (column parity) + row], see lmkan_sorted.h
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] = f4v{0.f, 0.f, 0.f, 0.f};
     int cur_cell = -1;  // (i1 << 8 | i2) of the cell the accumulators belong to
-    int done = 0;       // nodes below have been written
+    int done = nodes.begin;  // nodes below have been written, or are not this wave's
 
     if (nch > 0) {
         // Software pipeline, all through in-order vector loads: at step P of a trip the chunk
@@ -343,7 +344,6 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         int cells_now[kUnroll], cells_nxt[kUnroll];
 #pragma unroll
         for (int p = 0; p < kUnroll; ++p) cells_now[p] = cc[p];
-        if (split) done = (cells_now[0] >> 8) * W + (cells_now[0] & 255);  // nodes before the run's first cell are not this wave's
         // One step; LAST: of the last trip, which requests nothing beyond itself.
         auto step = [&](auto pc, auto last) {
             constexpr int P = decltype(pc)::value;
@@ -384,7 +384,23 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, -1, lane);
-    retire_nodes(ring, out, done, split ? ((cur_cell >> 8) + 1) * W + (cur_cell & 255) + 2 : W * W, lane);
+    retire_nodes(ring, out, done, run_end(out.own, cur_cell, W), lane);
+}
+
+// The nodes that run blockIdx.x + 1 of pair blockIdx.y shares with the runs before it start at zero
+__global__ __launch_bounds__(256) void fill_zero_kernel(const int32_t *__restrict__ chunk_cell,
+                                                                const int32_t *__restrict__ block_chunks, int64_t S, int n_sub,
+                                                                int W, float *gP, CoefMap gmap, int n_out)
+{
+    const int k = blockIdx.y, chunks = block_chunks[k], first = ((int)blockIdx.x + 1) * run_chunks(chunks, n_sub);
+    if (first >= chunks) return;
+    const int32_t *cell = chunk_cell + (int64_t)k * (S / kChunk) + first;
+    // (a group of four nodes of a run is shared as a whole)
+    const int beyond = ((cell[-1] >> 8) + 1) * W + (cell[-1] & 255) + 2;
+    const int from = max(min((cell[0] >> 8) * W + (cell[0] & 255), beyond) - 3, 0), to = min(beyond + 3, W * W);
+    float *out = gP + (int64_t)k * gmap.s_pair;
+    for (int id = from + (int)(threadIdx.x >> 6); id < to; id += 4)
+        for (int col = threadIdx.x & 63; col < n_out; col += 64) out[id * gmap.s_node + col] = 0.0f;
 }
 
 }  // namespace
@@ -439,6 +455,21 @@ SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted,
     return st;
 }
 
+void launch_clear_shared_nodes(const LayerShape &s, const SortedStream &st, int n_sub, float *gcoef, hipStream_t stream)
+{
+    if (st.n_blocks == 1 && n_sub == 1) return;
+    LayerShape g = s;
+    g.layout = LMKAN_LAYOUT_PAPER;
+    // (where the runs meet is in the stream: two loads before the first store.  Clearing the whole of a gradient of
+    // 7 MB takes 4.2 us, the shared nodes of it 5.0; of 17 MB 6.1 and 5.3, of 147 MB 19.6 and 7.7)
+    const size_t elems = (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out;
+    if (st.n_blocks > 1 || elems < 3000000)
+        launch_fill_zero(gcoef, elems, stream);
+    else
+        fill_zero_kernel<<<dim3((unsigned)(n_sub - 1), (unsigned)s.pairs()), 256, 0, stream>>>(
+            st.chunk_cell, st.block_chunks, st.S, n_sub, s.G + 1, gcoef, coef_map(g), s.n_out);
+}
+
 void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, const GyView &gy, float *gcoef,
                                  bool accumulate, hipStream_t stream)
 {
@@ -462,8 +493,7 @@ void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, co
     const int n_sub = stream_run_split(s);
     a.n_blocks = st.n_blocks;
     a.n_sub = n_sub;
-    if ((st.n_blocks > 1 || n_sub > 1) && !accumulate)
-        launch_fill_zero(gcoef, (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out, stream);
+    if (!accumulate) launch_clear_shared_nodes(s, st, n_sub, gcoef, stream);
     const unsigned grid = (unsigned)((int64_t)s.pairs() * s.out_tiles() * st.n_blocks * n_sub);
     KernelTiming timing(stream, kTimeGradCoef);
     if (gy_offsets_fit_32_bits(s, gy))
@@ -476,19 +506,19 @@ void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, co
 // 256 CUs x 16 waves.  Several blocks: as many runs as it takes for the pairs of one (tile,
 // block) to occupy an XCD (512 waves), so that the XCD works on one block at a time.  A run
 // keeps at least four trips.
-// Uncut streams own their nodes and save the zero fill and the atomics.  A few waves per CU do nearly
-// the work of sixteen (the walk is bound by vector instructions), so that wins well below a full chip,
-// and the sooner the fewer samples there are per node.  Training steps, uncut against cut: 3072 streams
-// (768 -> 512) at G = 28 with 3 samples per cell 967 / 1336 us, at G = 16 with 32 1099 / 1223; 2048 at
-// G = 9 with 100 677 / 680; 1536 at G = 20 with 12 595 / 611; 1280 at G = 16 with 32
-// 555 / 544; 1024 at G = 28 with 4 499 / 507, at G = 20 with 12 467 / 460; 768 450 / 415.
+// A run of one block shares with its neighbours the nodes of about a row of cells at either end and writes the
+// others like an uncut stream (run_nodes), so cutting costs little.  Kernel, uncut / cut in two or four: 3900 streams
+// (1300 -> 380) at G = 32 with 10 samples per cell 1567 / 850 us with the clearing, 3072 (768 -> 512) at G = 16 with
+// 32 390 / 353, 2450 (700 -> 400) at G = 30 with 3 382 / 333, 2500 (1000 -> 300) at G = 24 with 9 355 / 295, 2048 at
+// G = 9 with 100 222 / 205, at G = 28 with 5 309 / 240.  With few samples per cell the shared rows weigh more: 3600 streams
+// (900 -> 512) at G = 20 with 4 210 / 217, 3072 at G = 28 with 3 382 / 380; those stay whole.
+// (While every node of a cut stream was cleared and added atomically, from 1024 to 2048 streams on were better uncut.)
 int stream_run_split(const LayerShape &s)
 {
     const int64_t streams = (int64_t)s.pairs() * s.out_tiles();
     int n_sub = 1;
     if (stream_blocks(s.batch) == 1) {
-        const int64_t cells = (int64_t)s.G * s.G;
-        if (streams >= (s.batch <= 4 * cells ? 1024 : s.batch <= 16 * cells ? 1536 : 2048)) return 1;
+        if (streams >= 3072 && s.batch <= (int64_t)4 * s.G * s.G) return 1;
         const int64_t trips = stream_stride(s.batch, s.G) / (kChunk * kUnroll);
         while (streams * n_sub < 4096 && trips / (n_sub * 2) >= 4 && n_sub < 64) n_sub *= 2;
     } else {

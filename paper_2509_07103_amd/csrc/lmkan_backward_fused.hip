@@ -125,13 +125,12 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     const int col = jt * kTile + l16 * 4;
     const bool col_ok = col < a.n_out;
     typedef __attribute__((address_space(4))) const int32_t *ScalarIntPtr;
-    const bool split = a.n_blocks > 1 || a.n_sub > 1;
+    bool last_run = true;
     int c_begin = blk * a.block_stride;
     int nch = ((ScalarIntPtr)(a.block_chunks + (int64_t)k * a.n_blocks))[blk];
     if (a.n_sub > 1) {
-        const int trips = nch / kUnroll;
-        const int per = (trips + a.n_sub - 1) / a.n_sub * kUnroll;
-        const int skip = min(sub * per, nch);
+        const int per = run_chunks(nch, a.n_sub), skip = min(sub * per, nch);
+        last_run = skip + per >= nch;
         c_begin += skip;
         nch = min(per, nch - skip);
     }
@@ -192,7 +191,9 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     }
 
     const NodeRing ring(win, W);
-    const GradOut out{DO_GP ? a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile : nullptr, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0, split};
+    const RunNodes nodes = run_nodes(cc, nch, sub == 0, last_run, a.n_blocks > 1, W);
+    const GradOut out{DO_GP ? a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile : nullptr, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0,
+                      nodes.own()};
     if constexpr (DO_GP)
         for (int i = lane; i < ring.R * kTile; i += 64) win[i] = 0.0f;
 
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] = f4v{0.f, 0.f, 0.f, 0.f};
     int cur_cell = -1;  // (i1 << 8 | i2) of the cell being accumulated
-    int done = 0;       // nodes of gP below have been written
+    int done = nodes.begin;  // nodes of gP below have been written, or are not this wave's
     int cur_slot = 0;    // LDS slot of the current cell's coefficient rows
     unsigned slots = 0;  // slot of each chunk of the current group, one byte each
 
@@ -252,7 +253,6 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     int cells_now[kUnroll], cells_nxt[kUnroll];
 #pragma unroll
     for (int p = 0; p < kUnroll; ++p) cells_now[p] = cc[p];
-    if (DO_GP && split) done = (cells_now[0] >> 8) * W + (cells_now[0] & 255);  // nodes before the run's first cell are not this wave's
 
     // prologue: entries of trip 0, gy of the first kDepth chunks, coefficient rows of the first kCellDepth
 #pragma unroll
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     asm volatile("" ::"v"(touched));
     if constexpr (DO_GP) {
         if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, -1, lane);
-        retire_nodes(ring, out, done, split ? ((cur_cell >> 8) + 1) * W + (cur_cell & 255) + 2 : W * W, lane);
+        retire_nodes(ring, out, done, run_end(out.own, cur_cell, W), lane);
     }
 }
 
@@ -465,11 +465,14 @@ size_t fused_partial_bytes(const LayerShape &s)
 // Runs per (pair, tile, block).  Few waves fit a CU (registers: two per SIMD, three for 16-bit tables
 // without the coefficient gradient; LDS: seven per CU at G = 40) and each waits for its own loads, so the walk takes as
 // long as its rounds of resident waves: the count of runs with the fewest trips over all rounds, two
-// trips of start and end per run.  Runs that share nodes pay for the zero fill and the atomics, about three
-// times the gradient's bytes, 1 trip per 6 MB.  A run keeps at least four trips.
+// trips of start and end per run.  Nodes that runs share (run_nodes: about a row of cells where a run meets the
+// next; all of them in streams of several blocks) pay for the zero fill and the atomics, about three times
+// their bytes of the gradient, 1 trip per 6 MB.  A run keeps at least four trips.
 // Powers of two up to 4096 waves before: 128 -> 128 at G = 40 on 8192 rows 222 us for the step (32 runs,
 // 2.3 rounds of waves), 207 with 14 (one round); 256 -> 256 654 -> 586 us; 200 -> 320 at G = 48 724 -> 664;
-// 512 -> 384 at G = 40 on 12000 rows 2048 -> 1905 (uncut).
+// 512 -> 384 at G = 40 on 12000 rows 2048 -> 1905 (uncut).  With every node of a cut stream cleared and added atomically
+// 256 -> 256 at G = 40 took 612 us (now 558), 512 -> 512 with a float16 table 2068 (1875); 512 -> 384 was better uncut,
+// 2075 (2025 in runs), and 400 -> 320 at G = 48 on 6000 rows 1514 (1132).
 static int fused_run_split(const LayerShape &s, unsigned lds, bool want_gp)
 {
     constexpr unsigned kLdsBytes = 160 * 1024, kLdsGranule = 1280;
@@ -484,7 +487,8 @@ static int fused_run_split(const LayerShape &s, unsigned lds, bool want_gp)
     int64_t best_cost = 0;
     for (int n = 1; n <= 64 && (n == 1 || trips / n >= 4); ++n) {
         const int64_t rounds = (units * n + resident - 1) / resident;
-        const int64_t cost = rounds * ((trips + n - 1) / n + 2) + (n > 1 || blocks > 1 ? shared : 0);
+        const int64_t part = blocks > 1 ? s.nodes() : std::min((n - 1) * (s.G + 9), s.nodes());
+        const int64_t cost = rounds * ((trips + n - 1) / n + 2) + shared * part / s.nodes();
         if (n == 1 || cost < best_cost) best = n, best_cost = cost;
     }
     return best;
@@ -518,8 +522,7 @@ void launch_backward_fused(const LayerShape &s, const GridTab &tab, const Sorted
     const int n_sub = fused_run_split(s, lds, gcoef != nullptr);
     a.n_blocks = st.n_blocks;
     a.n_sub = n_sub;
-    if (gcoef && (st.n_blocks > 1 || n_sub > 1) && !accumulate)
-        launch_fill_zero(gcoef, (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out, stream);
+    if (gcoef && !accumulate) launch_clear_shared_nodes(s, st, n_sub, gcoef, stream);
     const unsigned grid = (unsigned)((int64_t)s.pairs() * s.out_tiles() * st.n_blocks * n_sub);
     typedef void (*Kernel)(FusedArgs);
 #define LMKAN_FUSED_ROW(CT, GP)                                                                       \

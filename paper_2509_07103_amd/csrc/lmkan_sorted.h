@@ -85,6 +85,8 @@ struct GyView {
 size_t gy_tiles_bytes(const LayerShape &s);
 GyView launch_gy_tiles(const LayerShape &s, const float *gy, void *tiles, hipStream_t stream);
 bool gy_offsets_fit_32_bits(const LayerShape &s, const GyView &gy);
+// clears what several runs of a stream add to: nothing, nodes that runs share, or all (see run_nodes)
+void launch_clear_shared_nodes(const LayerShape &s, const SortedStream &st, int n_sub, float *gcoef, hipStream_t stream);
 // coefficient gradient alone (lmkan_backward.hip)
 void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, const GyView &gy, float *gcoef,
                                  bool accumulate, hipStream_t stream);
@@ -183,15 +185,59 @@ __device__ __forceinline__ void leave_cell(f4v (&acc)[4], const NodeRing &ring, 
     if (all || odd != 0) flush_column<1>(acc, ring, c + 1 - odd, lane);
 }
 
-// Where the nodes of a wave's 64 columns go.  Owned columns: four nodes per store instruction, group g
-// takes node 4 i + g.  Shared gradient (`split`): one atomic instruction per node, lanes on consecutive
-// floats (256 contiguous bytes), sums that are zero left out.
+// The nodes of a run of a pair's stream, i1 W + b: `begin` ... `end` (run_end) are written when the walk has passed them.  A
+// cell c (its node i1 W + i2) adds to nodes c, c + 1, c + W, c + W + 1 and cells do not decrease along the stream,
+// so nodes from the last cell of the runs before + W + 2 on, and below the first cell of the run behind, are this
+// run's alone: own_from ... own_to.  The rest of what it touches it shares with a neighbour and adds atomically
+// (launch_clear_shared_nodes has set that to zero).  Every node is in one run's own range or a shared one, also where
+// nothing is added.  In a stream of several blocks all nodes are shared.
+// (Clearing the whole gradient and adding all of it atomically moves its bytes three more times: backward of 500 -> 333,
+// G = 20, 10000 rows 211 -> 172 us with the clearing, of 256 -> 256, G = 40, 8192 rows 383 -> 337, of 256 -> 512, G = 24,
+// 10000 rows 254 -> 170, of 1000 -> 96, G = 30, 9000 rows 281 -> 214.)
+struct RunNodes {
+    int begin, own_from, own_to;
+    __device__ __forceinline__ unsigned own() const { return (unsigned)own_from | (unsigned)own_to << 16; }
+};
+template <typename Cells>
+__device__ __forceinline__ RunNodes run_nodes(Cells cell, int n_chunks, bool first_run, bool last_run, bool several_blocks, int W)
+{
+    auto node = [&](int i) { return (cell[i] >> 8) * W + (cell[i] & 255); };
+    if (several_blocks) return {node(0), 0, 0};
+    RunNodes r = {0, 0, W * W};
+    if (!first_run) {
+        r.own_from = node(-1) + W + 2;
+        r.begin = min(node(0), r.own_from);
+    }
+    // (four nodes are written at a time, from `begin` on: whole groups are owned or shared)
+    r.own_from = r.begin + ((r.own_from - r.begin + 3) & ~3);
+    if (!last_run) r.own_to = r.begin + (max(min(node(n_chunks), node(n_chunks - 1) + W + 2) - r.begin, 0) & ~3);
+    return r;
+}
+// `end` of a run whose last cell is `last`
+__device__ __forceinline__ int run_end(unsigned own, int last, int W)
+{
+    return (int)(own >> 16) == W * W ? W * W : ((last >> 8) + 1) * W + (last & 255) + 2;
+}
+static_assert((LMKAN_MAX_GRID + 1) * (LMKAN_MAX_GRID + 1) < 1 << 16, "GradOut::own");
+
+// Chunks of a run, when a block's chunks are dealt to n_sub runs in whole trips
+__host__ __device__ inline int run_chunks(int chunks, int n_sub)
+{
+    return (chunks / kUnroll + n_sub - 1) / n_sub * kUnroll;
+}
+
+// Where the nodes of a wave's 64 columns go.  Owned nodes: four per store instruction, group g takes node 4 i + g.
+// Shared ones: one atomic instruction per node, lanes on consecutive floats (256 contiguous bytes), sums that are
+// zero left out.
 struct GradOut {
     float *base;  // first column of the tile, node 0
     int64_t s_node;
     int tile_col;  // first column of the tile
     int n_out;
-    bool accumulate, split;
+    bool accumulate;
+    unsigned own;  // RunNodes: own_from | own_to << 16 (scalar registers are scarce in the walks)
+    __device__ __forceinline__ int own_from() const { return (int)(own & 0xffffu); }
+    __device__ __forceinline__ int own_to() const { return (int)(own >> 16); }
 };
 
 // Nodes [done, upto) can receive nothing more: they are written and their slots cleared.
@@ -199,7 +245,7 @@ __device__ __forceinline__ void retire_nodes(const NodeRing &ring, const GradOut
 {
     const int g = lane >> 4, l16 = lane & 15;
     for (; done < upto; done += 4) {
-        if (o.split) {
+        if (done < o.own_from() || done >= o.own_to()) {
             for (int id = done; id < min(done + 4, upto); ++id) {
                 float *p = ring.win + ring.slot(id) * LMKAN_PACK_TILE + lane;
                 const float v = *p;

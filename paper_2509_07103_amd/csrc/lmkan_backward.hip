@@ -235,9 +235,7 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
 
     // Waves that run together on one XCD (ids congruent mod 8) take the same output tile and the
     // same block of the batch, so the piece of gy they all gather from stays in that XCD's L2.
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    int id = xcd_wave();
     const int sub = id % a.n_sub;
     id /= a.n_sub;
     const int k = id % a.K;
@@ -508,8 +506,8 @@ void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, co
 // keeps at least four trips.
 // A run of one block shares with its neighbours the nodes of about a row of cells at either end and writes the
 // others like an uncut stream (run_nodes), so cutting costs little.  Kernel, uncut / cut in two or four: 3900 streams
-// (1300 -> 380) at G = 32 with 10 samples per cell 1567 / 850 us with the clearing, 3072 (768 -> 512) at G = 16 with
-// 32 390 / 353, 2450 (700 -> 400) at G = 30 with 3 382 / 333, 2500 (1000 -> 300) at G = 24 with 9 355 / 295, 2048 at
+// (1300 -> 380) at G = 32 with 10 samples per cell 1008 / 972 us with the clearing, 3072 (768 -> 512) at G = 16 with
+// 32 390 / 353, 2450 (700 -> 400) at G = 30 with 3 388 / 337, 2500 (1000 -> 300) at G = 24 with 9 341 / 300, 2048 at
 // G = 9 with 100 222 / 205, at G = 28 with 5 309 / 240.  With few samples per cell the shared rows weigh more: 3600 streams
 // (900 -> 512) at G = 20 with 4 210 / 217, 3072 at G = 28 with 3 382 / 380; those stay whole.
 // (While every node of a cut stream was cleared and added atomically, from 1024 to 2048 streams on were better uncut.)

@@ -112,9 +112,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
 
     // Waves that run together on one XCD (ids congruent mod 8) take the same output tile and the
     // same block of the batch, so the piece of gy they all gather from stays in that XCD's L2.
-    int id = blockIdx.x;
-    const int total = gridDim.x;
-    if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    int id = xcd_wave();
     const int sub = id % a.n_sub;
     id /= a.n_sub;
     const int k = id % a.K;

@@ -65,6 +65,14 @@ struct SortedStream {
 // records = output of launch_preamble_records; fills the stream in `sorted`
 // (sorted_records_bytes()) and returns its description
 SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted, hipStream_t stream);
+// Number of this workgroup (one wave) such that each XCD has a contiguous run of them: workgroups go to the 8 XCDs
+// in turn.  (Any count of workgroups.  With the runs for multiples of eight alone, 1042 -> 800 at G = 12 on 12000
+// rows, 6773 waves, took 2218 us and takes 1073, 1026 -> 514 at G = 16 on 8192 rows, 4617 waves, 978 and 628.)
+__device__ __forceinline__ int xcd_wave()
+{
+    const int total = gridDim.x, xcd = blockIdx.x & 7, each = total >> 3, over = total & 7;
+    return xcd * each + min(xcd, over) + ((int)blockIdx.x >> 3);
+}
 // whether the batch is short enough for the 32-bit stream positions and 16-bit grid coordinates
 bool sorted_batch_ok(const LayerShape &s);
 // waves per (pair, output tile, block) of the coefficient gradient's walk

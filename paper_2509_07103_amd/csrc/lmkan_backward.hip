@@ -223,6 +223,7 @@ struct CoefGradArgs {
     int accumulate;
     int n_blocks;  // locality blocks of the batch
     int n_sub;     // waves per (pair, output tile, block)
+    int all_shared;  // every node is added to atomically
 };
 
 template <bool kOffset32>
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
 
     const NodeRing ring(win, W);
     for (int i = lane; i < ring.R * kTile; i += 64) win[i] = 0.0f;
-    const RunNodes nodes = run_nodes(cc, nch, sub == 0, last_run, a.n_blocks > 1, W);
+    const RunNodes nodes = run_nodes(cc, nch, sub == 0, last_run, a.all_shared != 0, W);
     const GradOut out{a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0,
                       nodes.own()};
 
@@ -453,17 +454,22 @@ SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted,
     return st;
 }
 
+// A gradient of fewer than three million entries is cleared as a whole: where the runs meet is in the stream, two loads
+// before the first store (7 MB in 4.2 us, its shared nodes alone in 5.0; 17 MB in 6.1 and 5.3, 147 MB in 19.6 and 7.7).
+// Adding all of it atomically then costs the walk 1 us at most, and leaves it in the L2 for who reads it next: training steps of
+// 358 -> 61, G = 9, 1827 rows 103.8 us, 104.4 with owned nodes, of 198 -> 65, G = 15, 3016 rows 164.9 and 165.4.
+bool all_nodes_shared(const LayerShape &s, int n_blocks, int n_sub)
+{
+    return n_blocks > 1 || (n_sub > 1 && (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out < 3000000);
+}
+
 void launch_clear_shared_nodes(const LayerShape &s, const SortedStream &st, int n_sub, float *gcoef, hipStream_t stream)
 {
-    if (st.n_blocks == 1 && n_sub == 1) return;
     LayerShape g = s;
     g.layout = LMKAN_LAYOUT_PAPER;
-    // (where the runs meet is in the stream: two loads before the first store.  Clearing the whole of a gradient of
-    // 7 MB takes 4.2 us, the shared nodes of it 5.0; of 17 MB 6.1 and 5.3, of 147 MB 19.6 and 7.7)
-    const size_t elems = (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out;
-    if (st.n_blocks > 1 || elems < 3000000)
-        launch_fill_zero(gcoef, elems, stream);
-    else
+    if (all_nodes_shared(s, st.n_blocks, n_sub))
+        launch_fill_zero(gcoef, (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out, stream);
+    else if (n_sub > 1)
         fill_zero_kernel<<<dim3((unsigned)(n_sub - 1), (unsigned)s.pairs()), 256, 0, stream>>>(
             st.chunk_cell, st.block_chunks, st.S, n_sub, s.G + 1, gcoef, coef_map(g), s.n_out);
 }
@@ -491,6 +497,7 @@ void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, co
     const int n_sub = stream_run_split(s);
     a.n_blocks = st.n_blocks;
     a.n_sub = n_sub;
+    a.all_shared = all_nodes_shared(s, st.n_blocks, n_sub);
     if (!accumulate) launch_clear_shared_nodes(s, st, n_sub, gcoef, stream);
     const unsigned grid = (unsigned)((int64_t)s.pairs() * s.out_tiles() * st.n_blocks * n_sub);
     KernelTiming timing(stream, kTimeGradCoef);

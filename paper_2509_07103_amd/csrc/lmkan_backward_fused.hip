@@ -66,6 +66,7 @@ struct FusedArgs {
     int accumulate;
     int n_blocks;
     int n_sub;
+    int all_shared;   // every node of gP is added to atomically
     int col_limit;    // columns >= col_limit do not exist in P
 };
 
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     }
 
     const NodeRing ring(win, W);
-    const RunNodes nodes = run_nodes(cc, nch, sub == 0, last_run, a.n_blocks > 1, W);
+    const RunNodes nodes = run_nodes(cc, nch, sub == 0, last_run, a.all_shared != 0, W);
     const GradOut out{DO_GP ? a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile : nullptr, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0,
                       nodes.own()};
     if constexpr (DO_GP)
@@ -520,6 +521,7 @@ void launch_backward_fused(const LayerShape &s, const GridTab &tab, const Sorted
     const int n_sub = fused_run_split(s, lds, gcoef != nullptr);
     a.n_blocks = st.n_blocks;
     a.n_sub = n_sub;
+    a.all_shared = all_nodes_shared(s, st.n_blocks, n_sub);
     if (gcoef && !accumulate) launch_clear_shared_nodes(s, st, n_sub, gcoef, stream);
     const unsigned grid = (unsigned)((int64_t)s.pairs() * s.out_tiles() * st.n_blocks * n_sub);
     typedef void (*Kernel)(FusedArgs);

@@ -93,7 +93,9 @@ struct GyView {
 size_t gy_tiles_bytes(const LayerShape &s);
 GyView launch_gy_tiles(const LayerShape &s, const float *gy, void *tiles, hipStream_t stream);
 bool gy_offsets_fit_32_bits(const LayerShape &s, const GyView &gy);
-// clears what several runs of a stream add to: nothing, nodes that runs share, or all (see run_nodes)
+// whether every node of a gradient counts as shared by the runs (see run_nodes)
+bool all_nodes_shared(const LayerShape &s, int n_blocks, int n_sub);
+// clears what several runs of a stream add to: nothing, the nodes that runs share, or all
 void launch_clear_shared_nodes(const LayerShape &s, const SortedStream &st, int n_sub, float *gcoef, hipStream_t stream);
 // coefficient gradient alone (lmkan_backward.hip)
 void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, const GyView &gy, float *gcoef,
@@ -198,7 +200,7 @@ __device__ __forceinline__ void leave_cell(f4v (&acc)[4], const NodeRing &ring, 
 // so nodes from the last cell of the runs before + W + 2 on, and below the first cell of the run behind, are this
 // run's alone: own_from ... own_to.  The rest of what it touches it shares with a neighbour and adds atomically
 // (launch_clear_shared_nodes has set that to zero).  Every node is in one run's own range or a shared one, also where
-// nothing is added.  In a stream of several blocks all nodes are shared.
+// nothing is added.  In a stream of several blocks all nodes are shared, and they count as shared in a small gradient.
 // (Clearing the whole gradient and adding all of it atomically moves its bytes three more times: backward of 500 -> 333,
 // G = 20, 10000 rows 211 -> 172 us with the clearing, of 256 -> 256, G = 40, 8192 rows 383 -> 337, of 256 -> 512, G = 24,
 // 10000 rows 254 -> 170, of 1000 -> 96, G = 30, 9000 rows 281 -> 214.)
@@ -207,10 +209,10 @@ struct RunNodes {
     __device__ __forceinline__ unsigned own() const { return (unsigned)own_from | (unsigned)own_to << 16; }
 };
 template <typename Cells>
-__device__ __forceinline__ RunNodes run_nodes(Cells cell, int n_chunks, bool first_run, bool last_run, bool several_blocks, int W)
+__device__ __forceinline__ RunNodes run_nodes(Cells cell, int n_chunks, bool first_run, bool last_run, bool all_shared, int W)
 {
     auto node = [&](int i) { return (cell[i] >> 8) * W + (cell[i] & 255); };
-    if (several_blocks) return {node(0), 0, 0};
+    if (all_shared) return {node(0), 0, 0};
     RunNodes r = {0, 0, W * W};
     if (!first_run) {
         r.own_from = node(-1) + W + 2;

@@ -91,7 +91,6 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
 // float16 tables kept as float16 in LDS (lmkan_slab_f16.hip); reached through the two slab
 // launchers above when slab_f16_native_ok().  gx_scratch is the zero-filled transposed scratch.
 bool slab_f16_native_ok(const LayerShape &s);
-bool slab_f16_split_ok(const LayerShape &s);
 void launch_forward_slab_f16(const LayerShape &s, const void *coef, float *y, const void *records, float *partials,
                              int split, hipStream_t stream);
 void launch_backward_input_slab_f16(const LayerShape &s, const GridTab &tab, const void *coef, const float *gy,

@@ -1165,7 +1165,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 {
     extern __shared__ __align__(16) char smem32[];
     if constexpr (is_bf16<CT>::value)
-        backward_input_split<CT, kHalfTile, 16, 80, false, true, 0>(a, smem32);
+        backward_input_split<kHalfTile, 16, 80>(a, smem32);
     else
         backward_input_lane32<CT>(a, smem32);
 }
@@ -2323,7 +2323,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
                                 int64_t gy_tile_stride, int64_t gy_row_stride, float *gx, const void *records,
                                 void *scratch, hipStream_t stream, const ConvGeom *conv)
 {
-    if (slab_wide_fits(s) && slab_f16_split_ok(s)) {
+    if (slab_wide_fits(s) && slab_f16_native_ok(s)) {
         launch_fill_zero(static_cast<float *>(scratch), (size_t)scratch_row_stride(s.batch, kScratchPlain) * s.n_in,
                          stream);
         launch_backward_input_slab_f16(s, tab, coef, gy, gy_tile_stride, gy_row_stride, static_cast<float *>(scratch),

@@ -1,13 +1,12 @@
-// Input gradient of 16-bit tables on the matrix cores, for the kernels that stream slabs.
+// Input gradient of bfloat16 tables on the matrix cores, for the kernels that stream slabs.
 //
 //   s_c(n, k) = sum_j gy[n][j] P[corner c of the cell of (n, k)][j],   c = 00, 01, 10, 11
 //
 // is four dot products of a sample: a 4 x TILE matrix times a vector.  A 4x4x4 MFMA multiplies sixteen
 // such matrices at once, four outputs deep, but by four columns each, and a sample has one vector.  It is
 // given three: gy split into three 16-bit parts whose sum is gy to the last bit, so that every product is
-// exact in float32 and the table needs no conversion (the vector pipe spends a conversion per multiply-add
-// on a bfloat16 table and a mixed multiply-add at half rate on a float16 one).  Per instruction 256
-// multiply-adds are of use, in about 9 clocks.
+// exact in float32 and the table needs no conversion (the vector pipe spends one beside every multiply-add).
+// Per instruction 256 multiply-adds are of use, in about 9 clocks.
 //
 // Lane 4 b + i of a wave reads corner i of sample b as it lies in LDS (16 bytes = 8 outputs = the A operands of two
 // MFMAs) and holds part i of that sample's gy (B operand, resident); it receives the sums of part i with all
@@ -24,11 +23,11 @@
 
 namespace lmkan {
 
-// bytes between two grid lines of a slab in LDS: rows of 64 bytes need 128 modulo 256, rows of 128 bytes 64 or 192
-__host__ __device__ inline int split_pitch(int W, int row_bytes)
+// bytes between two grid lines of a slab in LDS: 128 modulo 256
+inline int split_pitch(int W, int row_bytes)
 {
     const int line = W * row_bytes;
-    return row_bytes == 64 ? line + ((128 - line) & 255) : line + 64;
+    return line + ((128 - line) & 255);
 }
 
 typedef unsigned u4v __attribute__((ext_vector_type(4)));
@@ -46,18 +45,13 @@ __device__ __forceinline__ V high_half(u4v v)
     return __builtin_bit_cast(V, u2v{v[2], v[3]});
 }
 
-template <typename CT>
-struct SplitPart;
-
 // of(): part of one value, whatever it is (0: an infinity or NaN in part 0, zero in the others, so that its
-// products are those of the value).  Splitter: the same for two finite values at a time in few instructions, its
+// products are those of the value).  SplitPart: the same for two finite values at a time in few instructions, its
 // constants chosen by the lane's part.
-template <>
-struct SplitPart<bf16_t> {
+struct SplitPart {
     typedef short Vec __attribute__((ext_vector_type(4)));
-    static constexpr bool kScaled = false;
     // 8 + 8 + 8 significant bits, cut off and not rounded; the exponent range is float32's
-    static __device__ __forceinline__ unsigned of(float g, int part, int)
+    static __device__ __forceinline__ unsigned of(float g, int part)
     {
         const float hi = __uint_as_float(__float_as_uint(g) & 0xffff0000u);
         const float rest = g - hi;
@@ -67,7 +61,7 @@ struct SplitPart<bf16_t> {
         return __float_as_uint(v) >> 16;
     }
     unsigned cut1, cut2, keep;
-    __device__ __forceinline__ SplitPart(int part, int)
+    explicit __device__ __forceinline__ SplitPart(int part)
         : cut1(part >= 1 ? 0xffff0000u : 0u), cut2(part >= 2 ? 0xffff0000u : 0u), keep(part < 3 ? ~0u : 0u)
     {
     }
@@ -82,43 +76,6 @@ struct SplitPart<bf16_t> {
     static __device__ __forceinline__ void mac(f4v &d, Vec a, Vec b, bool first)
     {
         d = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a, b, first ? f4v{0.f, 0.f, 0.f, 0.f} : d, 0, 0, 0);
-    }
-};
-
-template <>
-struct SplitPart<_Float16> {
-    typedef _Float16 Vec __attribute__((ext_vector_type(4)));
-    typedef __fp16 Half2 __attribute__((ext_vector_type(2)));
-    static constexpr bool kScaled = true;
-    // 11 + 11 + 2 significant bits, cut off and not rounded, of g 2^-exponent (exponent: the sum of the sample's |g|
-    // over the tile becomes 2^13 ... 2^14); the second and third part are kept 2^11 and 2^22 times too large, in the range of
-    // normal numbers
-    static __device__ __forceinline__ unsigned of(float g, int part, int exponent)
-    {
-        if (!(fabsf(g) < __builtin_inff())) return part != 0 ? 0u : g != g ? 0x7e00u : g > 0.0f ? 0x7c00u : 0xfc00u;
-        const SplitPart split(part, exponent);
-        return split.pair(g, 0.0f) & 0xffffu;
-    }
-    int exponent;
-    float scale1, cut1, scale2, cut2;
-    unsigned keep;
-    __device__ __forceinline__ SplitPart(int part, int e)
-        : exponent(e), scale1(part >= 1 ? 2048.0f : 1.0f), cut1(part >= 1 ? -2048.0f : 0.0f), scale2(part >= 2 ? 2048.0f : 1.0f),
-          cut2(part >= 2 ? -2048.0f : 0.0f), keep(part < 3 ? ~0u : 0u)
-    {
-    }
-    __device__ __forceinline__ unsigned pair(float g0, float g1) const
-    {
-        float s0 = ldexpf(g0, -exponent), s1 = ldexpf(g1, -exponent);
-        Half2 h = __builtin_amdgcn_cvt_pkrtz(s0, s1);
-        s0 = fmaf((float)h[0], cut1, s0 * scale1), s1 = fmaf((float)h[1], cut1, s1 * scale1);
-        h = __builtin_amdgcn_cvt_pkrtz(s0, s1);
-        s0 = fmaf((float)h[0], cut2, s0 * scale2), s1 = fmaf((float)h[1], cut2, s1 * scale2);
-        return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(s0, s1)) & keep;
-    }
-    static __device__ __forceinline__ void mac(f4v &d, Vec a, Vec b, bool first)
-    {
-        d = __builtin_amdgcn_mfma_f32_4x4x4f16(a, b, first ? f4v{0.f, 0.f, 0.f, 0.f} : d, 0, 0, 0);
     }
 };
 
@@ -146,14 +103,12 @@ __device__ __forceinline__ float split_exchange(float a, float b, bool bit)
     return keep + dpp_move<XOR>(send);
 }
 
-// WAVES x 64 samples, TILE outputs (32 or 64) per workgroup, slabs of at most SLAB_KIB.  LATE: a pair's derivatives are
-// added behind the wait for the slab after the next, so that the next wait does not find them in flight (3 %
-// where the fill is short, a loss of 2 % where it is what bounds the kernel).  PREFETCH: see kFillStep.
-template <typename CT, int TILE, int WAVES, int SLAB_KIB, bool LATE, bool PREFETCH, int W_CT>
+// WAVES x 64 samples, TILE outputs (a tile of the packed layout or half of one) per workgroup, slabs of at most SLAB_KIB
+template <int TILE, int WAVES, int SLAB_KIB>
 __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *smem)
 {
-    typedef SplitPart<CT> Part;
-    typedef typename Part::Vec Vec;
+    typedef SplitPart Part;
+    typedef Part::Vec Vec;
     typedef PaceLate PACE;   // (its priorities; the fill is spread, see below)
     constexpr int kTileBytes = kSlabTile * 2, kRowB = TILE * 2, kPieces = TILE / 8, kSets = 4, kSteps = kSets * kPieces;
     constexpr int kAhead = 3;                              // LDS reads in flight
@@ -168,8 +123,7 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int part = lane & 3, block = lane >> 2, q = block & 3;
-    const int W = W_CT > 0 ? W_CT : a.W;
-    const int pitch = W_CT > 0 ? split_pitch(W_CT, kRowB) : a.slab_pitch;
+    const int W = a.W, pitch = a.slab_pitch;
     const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
@@ -186,9 +140,6 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
     for (int i = threadIdx.x; i < a.tab.G; i += WAVES * 64) s_invh[i] = a.tab.inv_h[i];
     SlabGate gate;
     gate.init(base0 + 2 * slab_bytes + LMKAN_MAX_GRID * 4);
-    // (columns that do not exist are never loaded: they read as zero; a packed table has them all)
-    if (!a.packed) for (unsigned i = threadIdx.x * 16u; i < 2 * slab_bytes; i += WAVES * 64 * 16u)
-        *reinterpret_cast<float4 *>(smem + i) = make_float4(0.f, 0.f, 0.f, 0.f);
 
     // what this lane fetches of a slab: 16 bytes of every chunk, from the node and piece they belong to
     const int first_col = jt * TILE;
@@ -206,7 +157,7 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
     auto issue_piece = [&](int i, unsigned lds_base, int k, bool wanted) {
         lds_dma16_lanes(tile + (int64_t)k * a.map.s_pair * 2, from[i], lds_base + (wave + i * WAVES) * 1024, wanted ? lanes[i] : 0);
     };
-    // one word of every row of pair k's slab (packed: a row is a line of the L2), dealt to the workgroups that stream it
+    // one word of every row of pair k's slab (a row of the packed layout is a line of the L2), dealt to the workgroups that stream it
     const int share = a.n_btiles >= 4 ? 3 : a.n_btiles >= 2 ? 1 : 0;
     const unsigned nowhere = base0 + 2 * slab_bytes + LMKAN_MAX_GRID * 4 + kGateBytes;
     auto prefetch = [&](int k, bool wanted) {
@@ -215,19 +166,18 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
         for (int i = 0; i < (SLAB_KIB * 1024 / kRowB + WAVES * 64 - 1) / (WAVES * 64); ++i) {
             const int row = (wave + i * WAVES) * 64;
             lds_dma4_lanes(src + row * kTileBytes, (unsigned)lane * kTileBytes, nowhere,
-                           wanted && a.packed && (wave & share) == (btile & share) ? first_lanes(W * W - row) : 0);
+                           wanted && (wave & share) == (btile & share) ? first_lanes(W * W - row) : 0);
         }
     };
 
-    __syncthreads();  // zeros, s_invh and the counters in place before any slab load lands
+    __syncthreads();  // s_invh and the counters in place before any slab load lands
 #pragma unroll
     for (int i = 0; i < kChunks; ++i) issue_piece(i, base0, k_begin, true);
-    if constexpr (PREFETCH) prefetch(k_begin + 1, k_begin + 1 < k_end);
+    prefetch(k_begin + 1, k_begin + 1 < k_end);
 
     const int64_t n_wave = (int64_t)btile * (WAVES * 64) + wave * 64;
     // part `part` of gy of sample n_wave + 4 block + t, outputs first_col + 8 (j ^ q) ... + 7
     u4v gyr[kSets][kPieces];
-    int exponent = 0;   // of sample n_wave + lane
     static_for(std::make_integer_sequence<int, kSets>{}, [&](auto tc) {
         constexpr int t = decltype(tc)::value;
         const float *row = a.gy + min(n_wave + block * 4 + t, a.B - 1) * a.gy_row_stride + (int64_t)(first_col >> 6) * a.gy_tile_stride;
@@ -242,18 +192,13 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
             g[j][0] = lo.x, g[j][1] = lo.y, g[j][2] = lo.z, g[j][3] = lo.w;
             g[j][4] = hi.x, g[j][5] = hi.y, g[j][6] = hi.z, g[j][7] = hi.w;
         }
-        float total = 0.0f;   // of |gy|: says whether all of it is finite, and how large it is
+        float total = 0.0f;   // of |gy|: not finite where one of them is not
 #pragma unroll
         for (int j = 0; j < kPieces; ++j)
 #pragma unroll
             for (int i = 0; i < 8; ++i) total += fabsf(g[j][i]);
         const bool finite = total < __builtin_inff();
-        int e = 0;
-        if constexpr (Part::kScaled) {
-            if (total > 0.0f && finite) e = __builtin_amdgcn_frexp_expf(total) - 14;
-            if (part == t) exponent = e;
-        }
-        const Part split(part, e);
+        const Part split(part);
         if (__all(finite)) {
 #pragma unroll
             for (int j = 0; j < kPieces; ++j)
@@ -264,7 +209,7 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
             for (int j = 0; j < kPieces; ++j)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    gyr[t][j][i] = Part::of(g[j][2 * i], part, e) | Part::of(g[j][2 * i + 1], part, e) << 16;
+                    gyr[t][j][i] = Part::of(g[j][2 * i], part) | Part::of(g[j][2 * i + 1], part) << 16;
         }
 #pragma unroll
         for (int j = 0; j < kPieces; ++j) {
@@ -294,13 +239,12 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
         gate.feed_only<WAVES>(k_end - k_begin, [&](int i, bool wanted) {
 #pragma unroll
             for (int c = 0; c < kChunks; ++c) issue_piece(c, i & 1 ? base0 + slab_bytes : base0, k_begin + i, wanted);
-            if constexpr (PREFETCH) prefetch(k_begin + i + 1, k_begin + i + 1 < k_end);
+            prefetch(k_begin + i + 1, k_begin + i + 1 < k_end);
         });
         return;
     }
     const bool valid = n_wave + lane < a.B;
     const float inv_w = 1.0f / (float)W;
-    const float part_factor = !Part::kScaled || part == 0 ? 1.0f : part == 1 ? 0x1p-11f : 0x1p-22f;
     float *gx_wave = a.gx + n_wave;   // transposed scratch [n_in][ld], plain layout
     unsigned piece_off[kPieces];      // of corner `part` and the piece read at step j
 #pragma unroll
@@ -313,7 +257,6 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
             unsafeAtomicAdd(dst + a.ld + (unsigned)lane, d2);
         }
     };
-    float p1 = 0.f, p2 = 0.f;   // LATE: the pair's before
     for (int k = k_begin; k < k_end; ++k) {
         const int step = k - k_begin;
         const bool more = k + 1 < k_end;
@@ -362,7 +305,6 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
                 float t1 = split_mul_bcast<t>(b_lo, dif_a), t2 = split_mul_bcast<t>(a_lo, dif_c);
                 split_fmac_bcast<t>(t1, b_hi, dif_b);
                 split_fmac_bcast<t>(t2, a_hi, dif_d);
-                if constexpr (Part::kScaled) t1 *= part_factor, t2 *= part_factor;
                 if constexpr ((t & 1) == 0) {
                     x1 = t1, x2 = t2;
                 } else {
@@ -382,18 +324,12 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
                 issue_piece((s - kFillStep) / kFillEvery, nxt, k + 1, more);
             if constexpr (s == kLandedStep) {
                 gate.slab_landed();
-                if (LATE && step > 0) add_derivatives(k - 1, p1, p2);
-                if constexpr (PREFETCH) prefetch(k + 2, k + 2 < k_end);
+                prefetch(k + 2, k + 2 < k_end);
             }
         });
         gate.slab_read();
-        if constexpr (Part::kScaled) d1 = ldexpf(d1, exponent), d2 = ldexpf(d2, exponent);
-        if constexpr (LATE)
-            p1 = d1, p2 = d2;
-        else
-            add_derivatives(k, d1, d2);
+        add_derivatives(k, d1, d2);
     }
-    if constexpr (LATE) add_derivatives(k_end - 1, p1, p2);
 }
 
 }  // namespace lmkan

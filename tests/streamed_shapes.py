@@ -63,6 +63,24 @@ SHAPES = [
     (1500, 40, 2116, 9, "f32", PACKED, SLAB, (LANE, STREAM)),
 ]
 
+# grad_x of 16-bit packed or 8-aligned tables where it streams them: B, n_in, n_out, G, storage, layout, kernel.  Edges of
+# the tiles of rows and outputs, every pitch of a grid line, the smallest batch
+INPUT_16BIT = [
+    (1023, 2000, 65, 16, "f16", PACKED, IN_SLAB16), (1025, 1000, 260, 11, "f16", PACKED, IN_SLAB16),
+    (2049, 600, 191, 16, "f16", PACKED, IN_SLAB16), (1023, 2000, 129, 3, "f16", PACKED, IN_SLAB16),
+    (1025, 600, 200, 16, "f16", PAPER, IN_SLAB16), (3000, 600, 200, 6, "f16", PAPER, IN_SLAB16),
+    (256, 2000, 129, 16, "bf16", PACKED, IN_LANE32), (1023, 2000, 97, 12, "bf16", PACKED, IN_LANE32),
+    (1025, 2000, 67, 15, "bf16", PACKED, IN_LANE32), (1023, 2000, 260, 3, "bf16", PACKED, IN_LANE32),
+    (1024, 1000, 100, 17, "bf16", PACKED, IN_LANE32), (2049, 1000, 65, 20, "bf16", PACKED, IN_LANE32),
+    (1100, 1000, 100, 30, "bf16", PACKED, IN_LANE32), (1030, 1000, 130, 33, "bf16", PACKED, IN_LANE32),
+    (1030, 1000, 130, 34, "bf16", PACKED, IN_LANE32), (3000, 1000, 33, 32, "bf16", PACKED, IN_LANE32),
+]
+# the same with unusual values in gy and tables, and with smooth tables
+UNUSUAL_16BIT = [(600, 1000, 260, G, storage, PACKED, IN_SLAB16 if storage == "f16" and G <= 16 else IN_LANE32)
+                 for storage in ("f16", "bf16") for G in (8, 16, 20, 24)]
+SMOOTH_16BIT = [(2048, 400, 256, 16, "f16", PACKED, IN_SLAB16), (2048, 400, 256, 11, "f16", PACKED, IN_SLAB16),
+                (2048, 400, 256, 16, "f16", PAPER, IN_SLAB16)]
+
 # walks that are not cut into runs: a gradient that one wave writes repeats bit for bit
 WHOLE_STREAMS = (2000, 512, 1024, 8)
 # grad_x of the walk over the sorted samples repeats bit for bit, with the coefficient gradient and without

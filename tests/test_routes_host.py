@@ -209,3 +209,20 @@ def test_rows_too_far_apart_for_a_lane_offset_are_not_streamed(rec, grid, n_in, 
         (status, launches), = routes([dict(call, **fn)], rec)
         assert status == 0
         assert streams == any("slab" in n or "lane" in n for n in names(launches)), names(launches)
+
+
+def test_tables_of_4_gib_and_more_keep_their_kernel(rec):
+    """Layout of Alg. 1, float16: a slab's nodes lie up to the whole table apart, rows that one load brings do not."""
+    for grid, n in ((16, 4096), (8, 8192), (16, 2048)):
+        call = dict(n_in=n, n_out=n, grid=grid, batch=512, dtype=1, layout=0, fn="backward", grad_coef=0)
+        (status, launches), = routes([call], rec)
+        assert status == 0 and "backward_input_slab_f16_kernel" in names(launches), names(launches)
+
+
+def test_grad_x_of_16_bit_tables_reaches_the_kernels_it_is_listed_for(rec):
+    from streamed_shapes import INPUT_16BIT, SMOOTH_16BIT, UNUSUAL_16BIT
+    listed = INPUT_16BIT + SMOOTH_16BIT + UNUSUAL_16BIT
+    got = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, dtype=DTYPE[storage], layout=layout, fn="backward", grad_coef=0)
+                  for B, n_in, n_out, G, storage, layout, _ in listed], rec)
+    for layer, (_, launches) in zip(listed, got):
+        assert layer[-1] in names(launches), (layer, names(launches))

@@ -1154,8 +1154,8 @@ __device__ __forceinline__ void backward_input_lane32(const GradInArgs &a, char 
 }
 
 // bfloat16: on the matrix cores (lmkan_slab_split.h), 1024 samples per workgroup.  A conversion beside every
-// multiply-add is gone: 2048 -> 2048 at G = 32, 4096 rows 3740 -> 2500 us, 300 -> 200 at G = 18, 3000 rows
-// 64 -> 35.  A float16 table needs no conversion (mixed multiply-adds); the matrix cores win 8192 rows of 1024 ->
+// multiply-add is gone: 2048 -> 2048 at G = 32, 4096 rows 3740 -> 2610 us, 300 -> 200 at G = 18, 3000 rows
+// 64 -> 39.  A float16 table needs no conversion (mixed multiply-adds); the matrix cores win 8192 rows of 1024 ->
 // 1024 at G = 24 (1260 us lane per sample and barrier, 1025 matrix cores) but lose where a slab serves few rows,
 // which costs them twice the fill (512 -> 512 at G = 32, 1500 rows: 108 against 131), and are not taken.
 constexpr int kLane32Rows = 2048, kLane32RowsBf16 = 1024;   // per workgroup
@@ -2337,8 +2337,8 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
     const bool narrow = !slab_wide_fits(s);
     // packed tables on the grids of the 16-output tiles: 32-output tiles kept as stored where two fit.  bfloat16 also
     // where 64-output tiles would fit (they widen the table on its way to LDS), but for a few rows: 8192 rows of 1024 ->
-    // 1024 at G = 16 1290 us with 64-output tiles, 940 here, 1500 rows of 512 -> 512 at G = 12 88 and 67, 500 rows
-    // of 1024 -> 1024 175 and 153; below 256 rows tiles are mostly empty and the difference comes down to the fill.
+    // 1024 at G = 16 1300 us with 64-output tiles, 1030 here, 1500 rows of 512 -> 512 at G = 12 89 and 78, 1000 rows
+    // of 1024 -> 1024 189 and 171; below 256 rows tiles are mostly empty and the difference comes down to the fill.
     const bool lane32 = slab_backward_input_takes_half_tiles(s) ||
                         (slab_wide_fits(s) && s.dtype == LMKAN_BF16 && s.layout == LMKAN_LAYOUT_PACKED && s.batch >= 256);
     if (lane32) {

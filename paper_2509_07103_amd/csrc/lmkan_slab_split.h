@@ -4,9 +4,16 @@
 //
 // is four dot products of a sample: a 4 x TILE matrix times a vector.  A 4x4x4 MFMA multiplies sixteen
 // such matrices at once, four outputs deep, but by four columns each, and a sample has one vector.  It is
-// given three: gy split into three 16-bit parts whose sum is gy to the last bit, so that every product is
-// exact in float32 and the table needs no conversion (the vector pipe spends one beside every multiply-add).
-// Per instruction 256 multiply-adds are of use, in about 9 clocks.
+// given as four: gy split into parts of six significant bits whose sum is gy to the last bit, so that the table needs no
+// conversion (the vector pipe spends one beside every multiply-add).  Per instruction 256 multiply-adds
+// are of use, in about 9 clocks.
+//
+// Products of such a part have 14 bits, and sums of eight of them mostly fit float32 without rounding, which is
+// what the derivatives ask for: they are differences of neighbouring corners, which agree in most of their digits where a
+// table is smooth.  Relative error, 256 -> 256 at G = 24, of tables that are independent from node to node, affine, 2 % apart
+// with either sign, 2 % apart with one sign (and a gy of one sign): 9.3e-8, 1.0e-7, 3.4e-7, 3.5e-7; with three parts of
+// eight bits and differences every 32 outputs 9.8e-8, 3.1e-7, 1.6e-6, 5.1e-6; on the vector pipe with differences
+// every eight outputs 1.1e-7, 5.1e-7, 2.6e-6, 5.2e-6 (every four, G = 16: 1.0e-7, 2.7e-7, 2.0e-6, 2.9e-6).
 //
 // Lane 4 b + i of a wave reads corner i of sample b as it lies in LDS (16 bytes = 8 outputs = the A operands of two
 // MFMAs) and holds part i of that sample's gy (B operand, resident); it receives the sums of part i with all
@@ -45,32 +52,30 @@ __device__ __forceinline__ V high_half(u4v v)
     return __builtin_bit_cast(V, u2v{v[2], v[3]});
 }
 
-// of(): part of one value, whatever it is (0: an infinity or NaN in part 0, zero in the others, so that its
-// products are those of the value).  SplitPart: the same for two finite values at a time in few instructions, its
-// constants chosen by the lane's part.
+// gy in four parts of six significant bits, cut off and not rounded; the exponent range is float32's.  of(): a part
+// of one value, whatever it is (an infinity or NaN in part 0, zero in the others, so that its products are those of
+// the value).  SplitPart: the same for two finite values at a time in few instructions, its constants chosen by the
+// lane's part.
 struct SplitPart {
     typedef short Vec __attribute__((ext_vector_type(4)));
-    // 8 + 8 + 8 significant bits, cut off and not rounded; the exponent range is float32's
+    static constexpr unsigned kSixBits = 0xfffc0000u;   // of a float32
     static __device__ __forceinline__ unsigned of(float g, int part)
     {
-        const float hi = __uint_as_float(__float_as_uint(g) & 0xffff0000u);
-        const float rest = g - hi;
-        const float mid = __uint_as_float(__float_as_uint(rest) & 0xffff0000u);
-        float v = part == 0 ? hi : part == 1 ? mid : part == 2 ? rest - mid : 0.0f;
-        if (!(fabsf(g) < __builtin_inff())) v = part != 0 ? 0.0f : g != g ? __builtin_nanf("") : g;
-        return __float_as_uint(v) >> 16;
+        if (!(fabsf(g) < __builtin_inff())) return part != 0 ? 0u : g != g ? 0x7fc0u : g > 0.0f ? 0x7f80u : 0xff80u;
+        return SplitPart(part).pair(g, 0.0f) & 0xffffu;
     }
-    unsigned cut1, cut2, keep;
+    unsigned cut1, cut2, cut3, keep;
     explicit __device__ __forceinline__ SplitPart(int part)
-        : cut1(part >= 1 ? 0xffff0000u : 0u), cut2(part >= 2 ? 0xffff0000u : 0u), keep(part < 3 ? ~0u : 0u)
+        : cut1(part >= 1 ? kSixBits : 0u), cut2(part >= 2 ? kSixBits : 0u), cut3(part >= 3 ? kSixBits : 0u), keep(part < 3 ? 0xfffcfffcu : ~0u)
     {
     }
     __device__ __forceinline__ unsigned pair(float g0, float g1) const
     {
-        g0 -= __uint_as_float(__float_as_uint(g0) & cut1);
-        g1 -= __uint_as_float(__float_as_uint(g1) & cut1);
-        g0 -= __uint_as_float(__float_as_uint(g0) & cut2);
-        g1 -= __uint_as_float(__float_as_uint(g1) & cut2);
+        auto next = [&](unsigned cut) {
+            g0 -= __uint_as_float(__float_as_uint(g0) & cut);
+            g1 -= __uint_as_float(__float_as_uint(g1) & cut);
+        };
+        next(cut1), next(cut2), next(cut3);
         return __builtin_amdgcn_perm(__float_as_uint(g1), __float_as_uint(g0), 0x07060302u) & keep;
     }
     static __device__ __forceinline__ void mac(f4v &d, Vec a, Vec b, bool first)
@@ -114,10 +119,11 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
     constexpr int kAhead = 3;                              // LDS reads in flight
     constexpr int kChunks = (SLAB_KIB + WAVES - 1) / WAVES;  // 1 KiB pieces of a slab per wave
     // What bounds this kernel is the fill: a slab serves half the samples that it serves in the forward kernel
-    // (three parts of gy and an idle fourth lane take twice the registers of float32).  So the pieces of the next
+    // (four parts of gy take twice the registers of float32).  So the pieces of the next
     // slab are requested one by one over half of a pair, and the lines of the slab after that are brought into the
-    // L2 by loads of one word per row.  2048 -> 2048, bfloat16, G = 32, 4096 rows: 3005 us with the fill in one
-    // place, 2840 spread, 2600 prefetched, 2535 both (1390 without any fill).
+    // L2 by loads of one word per row.  2048 -> 2048, G = 32, 4096 rows: 3005 us with the fill in one
+    // place, 2840 spread, 2600 prefetched, 2500 both (1390 without any fill);
+    // with differences every eight outputs 2610.
     constexpr int kFillStep = kSteps / 4 - 1, kFillEvery = kSteps / 8, kLandedStep = kSteps * 7 / 8 - 1;
     static_assert(kFillStep + (kChunks - 1) * kFillEvery < kLandedStep, "the last piece is requested before it is awaited");
     const int lane = threadIdx.x & 63;
@@ -289,18 +295,14 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
             // requests all of a pair's pieces, halves of a piece apart, and spills them)
             asm volatile("" : "+v"(off), "+v"(p));
             if constexpr (s + kAhead < kSteps) request(std::integral_constant<int, s + kAhead>{});
-            constexpr int kSum = 4;   // pieces (of 8 outputs) summed before corners are subtracted
-            Part::mac(d, low_half<Vec>(p), low_half<Vec>(gyr[t][j]), j % kSum == 0);
+            Part::mac(d, low_half<Vec>(p), low_half<Vec>(gyr[t][j]), true);
             Part::mac(d, high_half<Vec>(p), high_half<Vec>(gyr[t][j]), false);
             asm volatile("" : "+v"(off), "+v"(d));
-            // d[0 ... 3]: this part's sums with corners 00, 01, 10, 11.  Neighbouring corners of a smooth table agree in
-            // most of their digits, and so do sums over many outputs: they are subtracted every 32.
-            if constexpr (j % kSum == kSum - 1) {
-                if constexpr (j < kSum)
-                    dif_a = d[2] - d[0], dif_b = d[3] - d[1], dif_c = d[1] - d[0], dif_d = d[3] - d[2];
-                else
-                    dif_a += d[2] - d[0], dif_b += d[3] - d[1], dif_c += d[1] - d[0], dif_d += d[3] - d[2];
-            }
+            // d[0 ... 3]: this part's sums of eight outputs with corners 00, 01, 10, 11
+            if constexpr (j == 0)
+                dif_a = d[2] - d[0], dif_b = d[3] - d[1], dif_c = d[1] - d[0], dif_d = d[3] - d[2];
+            else
+                dif_a += d[2] - d[0], dif_b += d[3] - d[1], dif_c += d[1] - d[0], dif_d += d[3] - d[2];
             if constexpr (j == kPieces - 1) {
                 float t1 = split_mul_bcast<t>(b_lo, dif_a), t2 = split_mul_bcast<t>(a_lo, dif_c);
                 split_fmac_bcast<t>(t1, b_hi, dif_b);

@@ -79,7 +79,8 @@ INPUT_16BIT = [
 UNUSUAL_16BIT = [(600, 1000, 260, G, storage, PACKED, IN_SLAB16 if storage == "f16" and G <= 16 else IN_LANE32)
                  for storage in ("f16", "bf16") for G in (8, 16, 20, 24)]
 SMOOTH_16BIT = [(2048, 400, 256, 16, "f16", PACKED, IN_SLAB16), (2048, 400, 256, 11, "f16", PACKED, IN_SLAB16),
-                (2048, 400, 256, 16, "f16", PAPER, IN_SLAB16)]
+                (2048, 400, 256, 16, "f16", PAPER, IN_SLAB16), (2048, 400, 256, 16, "bf16", PACKED, IN_LANE32),
+                (2048, 400, 256, 11, "bf16", PACKED, IN_LANE32), (2048, 400, 256, 24, "bf16", PACKED, IN_LANE32)]
 
 # walks that are not cut into runs: a gradient that one wave writes repeats bit for bit
 WHOLE_STREAMS = (2000, 512, 1024, 8)

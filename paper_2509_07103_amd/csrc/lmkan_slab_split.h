@@ -61,8 +61,9 @@ struct SplitPart {
     static constexpr unsigned kSixBits = 0xfffc0000u;   // of a float32
     static __device__ __forceinline__ unsigned of(float g, int part)
     {
-        if (!(fabsf(g) < __builtin_inff())) return part != 0 ? 0u : g != g ? 0x7fc0u : g > 0.0f ? 0x7f80u : 0xff80u;
-        return SplitPart(part).pair(g, 0.0f) & 0xffffu;
+        const bool finite = fabsf(g) < __builtin_inff();
+        const unsigned split = SplitPart(part).pair(finite ? g : 0.0f, 0.0f), whole = g != g ? 0x7fc0u : __float_as_uint(g) >> 16;
+        return finite ? split & 0xffffu : part == 0 ? whole : 0u;
     }
     unsigned cut1, cut2, cut3, keep;
     explicit __device__ __forceinline__ SplitPart(int part)
@@ -106,6 +107,36 @@ __device__ __forceinline__ float split_exchange(float a, float b, bool bit)
     const float keep = bit ? b : a;
     const float send = bit ? a : b;
     return keep + dpp_move<XOR>(send);
+}
+
+// The derivatives of the samples in `rows` (bits: lanes) by float32 products, lane j its output of the tile.  An infinite
+// entry of the table meets the zeros among the parts of gy and makes the sums above NaN; here it gives the infinity,
+// or NaN, that the products themselves give.  gy: first sample of the wave; off, b_lo ... a_hi: as in the walk, of a
+// lane's own sample.
+__device__ __forceinline__ void split_again(uint64_t rows, const float *gy, int64_t gy_row_stride, int columns, int lane, int off, int pitch,
+                                            int row_bytes, float b_lo, float b_hi, float a_lo, float a_hi, float &d1, float &d2)
+{
+    typedef __attribute__((address_space(3))) const unsigned short *LdsHalf;
+    auto of_row = [](float v, int s) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), s)); };
+#pragma unroll 1
+    for (; rows; rows &= rows - 1) {
+        const int s = __builtin_ctzll(rows);
+        float p[4] = {0.f, 0.f, 0.f, 0.f};
+        if (lane < columns) {
+            const float g = gy[s * gy_row_stride + lane];
+            const unsigned at = (unsigned)__builtin_amdgcn_readlane(off, s) + (unsigned)lane * 2u;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                p[c] = g * __uint_as_float((unsigned)*reinterpret_cast<LdsHalf>(at + (c >> 1) * pitch + (c & 1) * row_bytes) << 16);
+        }
+        float dif[4] = {p[2] - p[0], p[3] - p[1], p[1] - p[0], p[3] - p[2]};
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            for (int apart = 32; apart > 0; apart >>= 1) dif[c] += __shfl_xor(dif[c], apart);
+        const float e1 = fmaf(of_row(b_hi, s), dif[1], of_row(b_lo, s) * dif[0]);
+        const float e2 = fmaf(of_row(a_hi, s), dif[3], of_row(a_lo, s) * dif[2]);
+        if (lane == s) d1 = e1, d2 = e2;
+    }
 }
 
 // WAVES x 64 samples, TILE outputs (a tile of the packed layout or half of one) per workgroup, slabs of at most SLAB_KIB
@@ -184,6 +215,7 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
     const int64_t n_wave = (int64_t)btile * (WAVES * 64) + wave * 64;
     // part `part` of gy of sample n_wave + 4 block + t, outputs first_col + 8 (j ^ q) ... + 7
     u4v gyr[kSets][kPieces];
+    bool nan_in_gy = false;   // of sample n_wave + lane
     static_for(std::make_integer_sequence<int, kSets>{}, [&](auto tc) {
         constexpr int t = decltype(tc)::value;
         const float *row = a.gy + min(n_wave + block * 4 + t, a.B - 1) * a.gy_row_stride + (int64_t)(first_col >> 6) * a.gy_tile_stride;
@@ -204,6 +236,7 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
 #pragma unroll
             for (int i = 0; i < 8; ++i) total += fabsf(g[j][i]);
         const bool finite = total < __builtin_inff();
+        if (part == t) nan_in_gy = total != total;
         const Part split(part);
         if (__all(finite)) {
 #pragma unroll
@@ -329,6 +362,10 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
                 prefetch(k + 2, k + 2 < k_end);
             }
         });
+        const uint64_t again = __ballot(valid && !nan_in_gy && (d1 != d1 || d2 != d2));
+        if (again)
+            split_again(again, a.gy + n_wave * a.gy_row_stride + (int64_t)(first_col >> 6) * a.gy_tile_stride + (first_col & 63), a.gy_row_stride,
+                        min(TILE, a.n_out - first_col), lane, off, pitch, kRowB, b_lo, b_hi, a_lo, a_hi, d1, d2);
         gate.slab_read();
         add_derivatives(k, d1, d2);
     }

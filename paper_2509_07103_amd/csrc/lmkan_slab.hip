@@ -337,7 +337,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     // 1024, G = 16: the same time with it, and with priorities), and keeps a barrier per pair.
     typedef std::conditional_t<kDirect, PaceEarly, PaceLate> PACE;
     SlabGate gate;
-    SlabFeed<kRowBytes, WAVES> feed;
+    SlabFeed<kRowBytes, WAVES, 80, is_far<CT>::value> feed;
     SlabFill<CT, WAVES> fill;
     if constexpr (kDirect) {
         gate.init(__builtin_amdgcn_readfirstlane(lds_address(smem)) + 8 * (unsigned)slab_floats);
@@ -714,7 +714,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     SlabGate gate;
     gate.init(__builtin_amdgcn_readfirstlane(lds_address(smem)) + 8 * (unsigned)slab_floats + LMKAN_MAX_GRID * 4);
     __syncthreads();  // zeros, s_invh and the counters in place before any slab load lands
-    SlabFeed<kRowBytes, WAVES> feed;
+    SlabFeed<kRowBytes, WAVES, 80, is_far<CT>::value> feed;
     feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kTile, wave, lane);
     if (k_begin < k_end) feed.issue(__builtin_amdgcn_readfirstlane(lds_address(slab0)), k_begin);
 
@@ -1606,7 +1606,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     typedef PaceLate PACE;
     SlabGate gate;
     if constexpr (kGated) gate.init(lds0 + 8 * (unsigned)slab_floats);
-    SlabFeed<kNarrowRowBytes, WAVES, SINGLE ? 160 : 80> feed;
+    SlabFeed<kNarrowRowBytes, WAVES, SINGLE ? 160 : 80, is_far<CT>::value> feed;
     if constexpr (kDirect) feed.template init<4>(a.P, a.map, a.nodes, a.col_limit, jt * kNarrowTile, wave, lane);
     SlabFill<CT, WAVES, LPS, SINGLE ? 4 : 2> fill;
     auto fill_whole = [&](int k) {  // every phase, one after the other
@@ -1819,7 +1819,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
     typedef PaceLate PACE;
     SlabGate gate;
-    SlabFeed<kNarrowRowBytes, WAVES> feed;
+    SlabFeed<kNarrowRowBytes, WAVES, 80, is_far<CT>::value> feed;
     if constexpr (kDirect) {
         for (int i = threadIdx.x; i < 2 * slab_floats; i += blockDim.x) smem[i] = 0.0f;
         gate.init(lds0 + 8 * (unsigned)slab_floats + LMKAN_MAX_GRID * 4);
@@ -1973,21 +1973,20 @@ static bool slab_batch_ok(const LayerShape &s, bool forward)
 // which tile a shape takes when it takes a slab kernel at all
 static bool slab_wide_fits(const LayerShape &s)
 {
-    return outputs_by_four_ok(s) && slab_forward_lds_bytes(s) <= 160 * 1024 && slab_feed_reaches(s, 4, 4);
+    return outputs_by_four_ok(s) && slab_forward_lds_bytes(s) <= 160 * 1024;
 }
 
 // 16-output tiles for larger grids (G <= 34)
 static bool slab_narrow_fits(const LayerShape &s)
 {
-    return outputs_by_four_ok(s) && !slab_wide_fits(s) && (size_t)2 * s.nodes() * kNarrowRowBytes <= 160 * 1024 &&
-           slab_feed_reaches(s, 16, 4);
+    return outputs_by_four_ok(s) && !slab_wide_fits(s) && (size_t)2 * s.nodes() * kNarrowRowBytes <= 160 * 1024;
 }
 
 // forward only: one 16-output slab at a time (35 <= G <= 48)
 static bool slab_narrow_single_fits(const LayerShape &s)
 {
     return outputs_by_four_ok(s) && !slab_wide_fits(s) && !slab_narrow_fits(s) &&
-           (size_t)s.nodes() * kNarrowRowBytes <= 160 * 1024 - 512 && slab_feed_reaches(s, 16, 4);
+           (size_t)s.nodes() * kNarrowRowBytes <= 160 * 1024 - 512;
 }
 
 bool slab_forward_shape_ok(const LayerShape &s)
@@ -2120,7 +2119,9 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
                                forward_slab_narrow_kernel<float, 2 * WAVES, SETS / 2, true>,
                                forward_slab_narrow_kernel<_Float16, WAVES, SETS, true>,
                                forward_slab_narrow_kernel<bf16_t, WAVES, SETS, true>};
-    const Kernel kernel = kernels[s.dtype + (single ? 3 : 0)];
+    const Kernel far[2] = {forward_slab_narrow_kernel<FarF32, 2 * WAVES, SETS / 2>,
+                           forward_slab_narrow_kernel<FarF32, 2 * WAVES, SETS / 2, true>};
+    const Kernel kernel = s.dtype == LMKAN_F32 && rows_far_apart(s, 16, 4) ? far[single] : kernels[s.dtype + (single ? 3 : 0)];
     const int waves = s.dtype == LMKAN_F32 ? 2 * WAVES : WAVES;
     allow_large_lds(reinterpret_cast<const void *>(kernel), 160 * 1024);
     const size_t n = (size_t)s.pairs() * (size_t)s.batch;
@@ -2171,7 +2172,9 @@ void launch_forward_slab(const LayerShape &s, const void *coef, float *y, const 
                                forward_slab_kernel<_Float16, 8, 2, 2, 0>, forward_slab_kernel<bf16_t, 8, 2, 2, 0>};
     const Kernel kernels17[3] = {forward_slab_kernel<float, 16, 1, 1, 17>,
                                  forward_slab_kernel<_Float16, 8, 2, 2, 17>, forward_slab_kernel<bf16_t, 8, 2, 2, 17>};
-    const Kernel kernel = s.G == 16 ? kernels17[s.dtype] : kernels[s.dtype];
+    const Kernel kernel = s.dtype == LMKAN_F32 && rows_far_apart(s, 4, 4) ? forward_slab_kernel<FarF32, 16, 1, 1, 0>
+                          : s.G == 16                                    ? kernels17[s.dtype]
+                                                                         : kernels[s.dtype];
     const int waves = s.dtype == LMKAN_F32 ? 16 : 8;
     allow_large_lds(reinterpret_cast<const void *>(kernel), 160 * 1024);
     const size_t n = (size_t)s.pairs() * (size_t)s.batch;
@@ -2402,7 +2405,9 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
                                backward_input_slab_kernel<_Float16, WAVES, SETS, 2, 17>,
                                backward_input_slab_kernel<bf16_t, WAVES, SETS, 2, 17>};
     const int which = s.dtype + (narrow ? 3 : (s.G == 16 ? 6 : 0));
-    const Kernel kernel = kernels[which];
+    const Kernel kernel = s.dtype != LMKAN_F32 || !rows_far_apart(s, narrow ? 16 : 4, 4) ? kernels[which]
+                          : narrow ? backward_input_slab_narrow_kernel<FarF32, 2 * WAVES, kNarrowSets / 2>
+                                   : backward_input_lane_kernel<FarF32, 0>;
     allow_large_lds(reinterpret_cast<const void *>(kernel), 160 * 1024);
     const size_t n = (size_t)s.pairs() * (size_t)s.batch;
     GradInArgs a;

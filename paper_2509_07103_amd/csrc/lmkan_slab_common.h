@@ -2,6 +2,8 @@
 // argument blocks, the LDS-direct load, small DPP helpers.
 #pragma once
 
+#include <type_traits>
+
 #include "lmkan_kernels.h"
 #include "lmkan_split.h"
 
@@ -106,6 +108,23 @@ __device__ __forceinline__ void lds_dma16_lanes(const void *gbase, unsigned lane
                  : "memory", "scc");
 }
 
+// The same for a chunk of rows of LANES lanes each, however far apart: a load per row, its base row_bytes behind the one
+// before.  (The base is counted in fixed registers: 64 bits are added in halves, which an operand cannot name.)
+template <int LANES>
+__device__ __forceinline__ void lds_dma16_rows(const void *gbase, unsigned lane_off, unsigned lds_base, uint64_t lanes, int64_t row_bytes)
+{
+    uint64_t left, row;
+    asm volatile("s_cmp_eq_u64 %5, 0\n\ts_cbranch_scc1 .Labsent%=\n\ts_mov_b32 m0, %4\n\ts_mov_b64 %0, %5\n\ts_mov_b64 %1, %6\n\t"
+                 "s_mov_b64 s[96:97], %3\n.Lrow%=:\n\ts_and_b64 exec, %0, %1\n\tglobal_load_lds_dwordx4 %2, s[96:97]\n\t"
+                 "s_andn2_b64 %0, %0, %1\n\ts_cbranch_scc0 .Llast%=\n\ts_lshl_b64 %1, %1, %9\n\t"
+                 "s_add_u32 s96, s96, %7\n\ts_addc_u32 s97, s97, %8\n\ts_branch .Lrow%=\n"
+                 ".Llast%=:\n\ts_mov_b64 exec, -1\n.Labsent%=:"
+                 : "=&s"(left), "=&s"(row)
+                 : "v"(lane_off), "s"(gbase), "s"(lds_base), "s"(lanes), "n"((1 << LANES) - 1), "s"((unsigned)row_bytes),
+                   "s"((unsigned)((uint64_t)row_bytes >> 32)), "n"(LANES)
+                 : "memory", "scc", "s96", "s97");
+}
+
 // Four bytes per lane of `lanes` to lds_base + 4 lane: to bring a line into the L2 without a register to receive it
 __device__ __forceinline__ void lds_dma4_lanes(const void *gbase, unsigned lane_off, unsigned lds_base, uint64_t lanes)
 {
@@ -124,14 +143,14 @@ __device__ __forceinline__ uint64_t first_lanes(int n)
 
 // Slabs of one output tile in the form they are stored in: ROW_BYTES per node, filled by LDS-direct loads of
 // 1 KiB (64 lanes x 16 bytes, whole rows), dealt round-robin to the waves.  One code for both layouts: the
-// rows of a chunk lie node_bytes apart, columns that do not exist are lanes that never load.
-template <int ROW_BYTES, int WAVES, int MOST_KIB = 80>
+// rows of a chunk lie row_bytes apart, columns that do not exist are lanes that never load.  FAR: rows_far_apart.
+template <int ROW_BYTES, int WAVES, int MOST_KIB = 80, bool FAR = false>
 struct SlabFeed {
     static constexpr int kLanes = ROW_BYTES / 16;   // lanes per row
     static constexpr int kRows = 64 / kLanes;       // rows per chunk
     static constexpr int kMostChunks = (MOST_KIB + WAVES - 1) / WAVES;   // per wave; two slabs share 160 KiB
     const char *tile;
-    int64_t pair_bytes, chunk_bytes;
+    int64_t pair_bytes, chunk_bytes, row_bytes;
     uint64_t columns;
     unsigned lane_off;
     int nodes, wave;
@@ -143,8 +162,9 @@ struct SlabFeed {
         const int col = first_col + (lane % kLanes) * (16 / ELEMENT);
         tile = static_cast<const char *>(P) + ((int64_t)(first_col >> 6) * map.s_tile + (first_col & 63)) * ELEMENT;
         pair_bytes = map.s_pair * ELEMENT;
-        chunk_bytes = map.s_node * (kRows * ELEMENT);
-        lane_off = (unsigned)(lane / kLanes) * (unsigned)(map.s_node * ELEMENT) + (unsigned)(lane % kLanes) * 16u;
+        row_bytes = map.s_node * ELEMENT;
+        chunk_bytes = row_bytes * kRows;
+        lane_off = (FAR ? 0 : (unsigned)(lane / kLanes) * (unsigned)row_bytes) + (unsigned)(lane % kLanes) * 16u;
         columns = __ballot(col < col_limit);
         nodes = n_nodes;
         wave = wave_id;
@@ -155,18 +175,30 @@ struct SlabFeed {
 #pragma unroll
         for (int i = 0; i < kMostChunks; ++i) {
             const int c = wave + i * WAVES;
-            lds_dma16_lanes(src + c * chunk_bytes, lane_off, lds_base + c * 1024,
-                            wanted ? first_lanes((nodes - c * kRows) * kLanes) & columns : 0);
+            const uint64_t lanes = wanted ? first_lanes((nodes - c * kRows) * kLanes) & columns : 0;
+            if constexpr (FAR)
+                lds_dma16_rows<kLanes>(src + c * chunk_bytes, lane_off, lds_base + c * 1024, lanes, row_bytes);
+            else
+                lds_dma16_lanes(src + c * chunk_bytes, lane_off, lds_base + c * 1024, lanes);
         }
     }
 };
 
-// (layout of Alg. 1: the rows of a chunk lie pairs x outputs elements apart, and a lane's offset has 32 bits)
-inline bool slab_feed_reaches(const LayerShape &s, int rows_per_chunk, int element)
+// Layout of Alg. 1: rows lie pairs x outputs elements apart, and the 32 bits of a lane's offset do not reach over a chunk of
+// them where that is 3.6e8 or more (float32, four rows a chunk; 7.2e7 with sixteen).  Kernels of their own then load
+// row by row: in the others the few scalar instructions more per chunk cost 2 % (a chain of 64-256-256-256-1 on 65536 rows
+// 897 -> 917 us).
+inline bool rows_far_apart(const LayerShape &s, int rows_per_chunk, int element)
 {
-    return s.layout == LMKAN_LAYOUT_PACKED ||
-           (int64_t)s.pairs() * s.n_out * element * (rows_per_chunk - 1) < ((int64_t)1 << 32) - 1024;
+    return s.layout != LMKAN_LAYOUT_PACKED &&
+           (int64_t)s.pairs() * s.n_out * element * (rows_per_chunk - 1) >= ((int64_t)1 << 32) - 1024;
 }
+struct FarF32 {   // table type of such a kernel
+    float value;
+};
+template <typename CT>
+struct is_far : std::is_same<CT, FarF32> {
+};
 
 // How the waves of a workgroup that walks over pairs hand its two slab buffers over.  A barrier per pair
 // lets the waves of a SIMD start every pair together, with nothing in their pipelines, and makes all wait

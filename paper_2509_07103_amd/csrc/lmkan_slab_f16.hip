@@ -68,9 +68,9 @@ __device__ __forceinline__ void fma_corners_h(float *acc, const CornersH &c, flo
     for (int i = 0; i < 4; ++i) acc[i] = fmaf(e, (float)c.c11[i], acc[i]);
 }
 
-__global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void forward_slab_f16_kernel(SlabArgs a)
+template <bool FAR>
+__device__ __forceinline__ void forward_slab_f16(const SlabArgs &a, char *smem_h)
 {
-    extern __shared__ __align__(16) char smem_h[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, g = lane >> 4;
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
         nx_v = (a.rec_v + o)[l];
     };
 
-    SlabFeed<kRowBytesH, kWaves> feed;
+    SlabFeed<kRowBytesH, kWaves, 80, FAR> feed;
     feed.template init<2>(a.P, a.map, a.nodes, a.col_limit, jt * kTile, wave, lane);
     typedef PaceLate PACE;
     SlabGate gate;
@@ -167,6 +167,18 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
     }
 }
 
+__global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void forward_slab_f16_kernel(SlabArgs a)
+{
+    extern __shared__ __align__(16) char smem_h[];
+    forward_slab_f16<false>(a, smem_h);
+}
+
+__global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void forward_slab_f16_far_kernel(SlabArgs a)
+{
+    extern __shared__ __align__(16) char smem_h[];
+    forward_slab_f16<true>(a, smem_h);
+}
+
 // acc += gy . c over the four outputs of a piece (v_fma_mix_f32 widens the float16 operand)
 __device__ __forceinline__ float fma4_h(const float4 g, const h4v c, float acc)
 {
@@ -183,7 +195,7 @@ __device__ __forceinline__ float fma4_h(const float4 g, const h4v c, float acc)
 // 8192 rows 1130 -> 1020 us, 1000 rows 156 -> 130, 500 rows 147 -> 91; 131072 rows of 128 -> 128 at G = 12 308 -> 302, 1500 rows
 // of 512 -> 512 at G = 12 76 -> 76.  On the matrix cores as in lmkan_slab_split.h, which loses no accuracy against this
 // kernel only with gy in parts of six bits and differences every eight outputs, these take 1210, 170, 107, 305 and 67.
-// W_CT: G + 1 when known at compile time (the corner offsets are then immediates), else 0
+// W_CT: G + 1 when known at compile time (the corner offsets are then immediates), 0 if not, negative for rows_far_apart too
 template <int W_CT>
 __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void backward_input_slab_f16_kernel(
     GradInArgs a)
@@ -218,7 +230,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 
         for (unsigned i = threadIdx.x * 16u; i < 2 * slab_bytes; i += blockDim.x * 16u)
             *reinterpret_cast<float4 *>(smem_h + i) = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();  // zeros, s_invh and the counters in place before any slab load lands
-    SlabFeed<kRowBytesH, kWaves> feed;
+    SlabFeed<kRowBytesH, kWaves, 80, (W_CT < 0)> feed;
     feed.template init<2>(a.P, a.map, a.nodes, a.col_limit, jt * kTile, wave, lane);
     if (k_begin < k_end) feed.issue(base0, k_begin);
 
@@ -318,14 +330,15 @@ bool slab_f16_native_ok(const LayerShape &s)
 {
     if (s.dtype != LMKAN_F16) return false;
     if (s.layout != LMKAN_LAYOUT_PACKED && s.n_out % 8 != 0) return false;
-    return slab_feed_reaches(s, 8, 2);
+    return true;
 }
 
 void launch_forward_slab_f16(const LayerShape &s, const void *coef, float *y, const void *records, float *partials,
                              int split, hipStream_t stream)
 {
     constexpr int kTileB = kWaves * 64;
-    allow_large_lds(reinterpret_cast<const void *>(forward_slab_f16_kernel), 160 * 1024);
+    void (*const kernel)(SlabArgs) = rows_far_apart(s, 8, 2) ? forward_slab_f16_far_kernel : forward_slab_f16_kernel;
+    allow_large_lds(reinterpret_cast<const void *>(kernel), 160 * 1024);
     const size_t n = (size_t)s.pairs() * (size_t)s.batch;
     SlabArgs a;
     a.P = coef;
@@ -349,7 +362,7 @@ void launch_forward_slab_f16(const LayerShape &s, const void *coef, float *y, co
     finish_split_setup(a, s, y, partials, stream);
     {
         KernelTiming timing(stream, kTimeForward);
-        forward_slab_f16_kernel<<<tiles * split, kWaves * 64, (((size_t)2 * s.nodes() * kRowBytesH + 15) & ~(size_t)15) + kGateBytes, stream>>>(a);
+        kernel<<<tiles * split, kWaves * 64, (((size_t)2 * s.nodes() * kRowBytesH + 15) & ~(size_t)15) + kGateBytes, stream>>>(a);
     }
     if (a.y_part) launch_sum_partials(y, a.y_part, split - 1, (int64_t)s.batch * s.n_out, stream);
 }
@@ -359,7 +372,9 @@ void launch_backward_input_slab_f16(const LayerShape &s, const GridTab &tab, con
                                     const void *records, hipStream_t stream)
 {
     constexpr int kTileB = kWaves * 64;
-    void (*const kernel)(GradInArgs) = s.G == 16 ? backward_input_slab_f16_kernel<17> : backward_input_slab_f16_kernel<0>;
+    void (*const kernel)(GradInArgs) = rows_far_apart(s, 8, 2) ? backward_input_slab_f16_kernel<-1>
+                                       : s.G == 16             ? backward_input_slab_f16_kernel<17>
+                                                               : backward_input_slab_f16_kernel<0>;
     allow_large_lds(reinterpret_cast<const void *>(kernel), 160 * 1024);
     const size_t n = (size_t)s.pairs() * (size_t)s.batch;
     GradInArgs a;

@@ -82,6 +82,10 @@ SMOOTH_16BIT = [(2048, 400, 256, 16, "f16", PACKED, IN_SLAB16), (2048, 400, 256,
                 (2048, 400, 256, 16, "f16", PAPER, IN_SLAB16), (2048, 400, 256, 16, "bf16", PACKED, IN_LANE32),
                 (2048, 400, 256, 11, "bf16", PACKED, IN_LANE32), (2048, 400, 256, 24, "bf16", PACKED, IN_LANE32)]
 
+# tables in the layout of Alg. 1 whose rows lie so far apart that the rows of one load to LDS are 4 GiB apart: n_in, n_out,
+# G, storage (batch 512; 23, 12 and 93 GB)
+FAR_ROWS = [(32768, 22016, 3, "f32"), (32768, 22016, 3, "f16"), (16384, 8768, 17, "f32")]
+
 # walks that are not cut into runs: a gradient that one wave writes repeats bit for bit
 WHOLE_STREAMS = (2000, 512, 1024, 8)
 # grad_x of the walk over the sorted samples repeats bit for bit, with the coefficient gradient and without

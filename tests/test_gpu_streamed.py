@@ -7,7 +7,7 @@ import torch
 import paper_2509_07103_amd as pkg
 from paper_2509_07103_amd import workloads as wl
 from parity_util import ORACLE_DTYPE, TOL_F32, bits, output_rel_err, pair_slice_rel_err, rowwise_rel_err
-from streamed_shapes import CONV, DRAWN, REPLAYED, SHAPES, WALKS, WHOLE_STREAMS, every_grid
+from streamed_shapes import CONV, DRAWN, FAR_ROWS, REPLAYED, SHAPES, WALKS, WHOLE_STREAMS, every_grid
 
 pytestmark = pytest.mark.gpu
 
@@ -163,3 +163,27 @@ def test_replays_of_a_captured_step_match_eager_calls(B, n_in, n_out, G, storage
         assert torch.equal(y, y_e), rep             # the forward sums in a fixed order
         assert float((gx - gx_e).abs().max()) <= TOL_F32 * float(gx_e.abs().max())
         assert float((gP - gP_e).abs().max()) <= TOL_F32 * float(gP_e.abs().max())
+
+
+@pytest.mark.parametrize("n_in,n_out,G,storage", FAR_ROWS)
+def test_rows_of_a_table_4_gib_apart(n_in, n_out, G, storage):
+    """Layout of Alg. 1: outputs and derivatives are those of the layer that has 192 of the outputs alone."""
+    torch.cuda.empty_cache()
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    P = torch.empty((G + 1, G + 1, n_in // 2, n_out), dtype=torch.float16 if storage == "f16" else torch.float32, device="cuda")
+    P.uniform_(-0.1, 0.1, generator=gen)
+    x, gy = (torch.randn((512, n), device="cuda", generator=gen) for n in (n_in, n_out))
+    first = (0, n_out // 128 * 64, n_out - 64)
+    few = torch.cat([P.narrow(3, at, 64) for at in first], 3)
+    gy_few = torch.cat([gy.narrow(1, at, 64) for at in first], 1)
+    gy.zero_()
+    for i, at in enumerate(first):
+        gy[:, at:at + 64] = gy_few[:, i * 64:i * 64 + 64]
+    of = dict(coef_dtype=DT_CODE[storage])
+    y = pkg.lmkan_forward(pkg.LayerDesc(n_in, n_out, G, **of), x, P)
+    gx, _ = pkg.lmkan_backward(pkg.LayerDesc(n_in, n_out, G, **of), x, P, gy, need_grad_coef=False)
+    y_few = pkg.lmkan_forward(pkg.LayerDesc(n_in, 192, G, **of), x, few)
+    gx_few, _ = pkg.lmkan_backward(pkg.LayerDesc(n_in, 192, G, **of), x, few, gy_few, need_grad_coef=False)
+    y = torch.cat([y.narrow(1, at, 64) for at in first], 1)
+    assert rowwise_rel_err(y.cpu().numpy(), y_few.double().cpu().numpy()) <= TOL_F32
+    assert rowwise_rel_err(gx.cpu().numpy(), gx_few.double().cpu().numpy()) <= TOL_F32

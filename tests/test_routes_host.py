@@ -6,6 +6,7 @@ import pytest
 
 import paper_2509_07103_amd as pkg
 from routes import names, recorder, routes
+from streamed_shapes import FAR_ROWS
 
 REUSE = pkg.LMKAN_FLAG_WORKSPACE_HAS_RECORDS
 
@@ -196,19 +197,21 @@ def test_streamed_shapes_reach_the_kernels_they_are_listed_for(rec):
     assert len(gathered) <= 2, gathered
 
 
-@pytest.mark.parametrize("grid,n_in,n_out,layout,streams", [
-    (3, 16384, 16384, 0, True),     # rows of a table node 0.5 GB apart: three of them within a lane's 32 bits
-    (3, 32768, 32768, 0, False),    # 2.1 GB apart
-    (3, 32768, 32768, 1, True),     # packed: 256 bytes apart
-    (17, 8192, 8192, 0, True),      # sixteen rows per load
-    (17, 16384, 16384, 0, False),
-    (40, 16384, 16384, 0, False)])
-def test_rows_too_far_apart_for_a_lane_offset_are_not_streamed(rec, grid, n_in, n_out, layout, streams):
-    call = dict(n_in=n_in, n_out=n_out, grid=grid, batch=512, dtype=0, layout=layout)
-    for fn in (dict(fn="forward"), dict(fn="backward", grad_coef=0)):
+@pytest.mark.parametrize("grid,n_in,n_out,dtype,layout", [
+    (3, 16384, 16384, 0, 0),     # rows of a table node 0.5 GB apart: three of them within a lane's 32 bits
+    (3, 32768, 32768, 0, 0),     # 2.1 GB apart
+    (3, 32768, 32768, 0, 1),     # packed: 256 bytes apart
+    (17, 8192, 8192, 0, 0),      # sixteen rows per load
+    (17, 16384, 16384, 0, 0),
+    (40, 16384, 16384, 0, 0),
+    (16, 32768, 32768, 1, 0), (30, 16384, 16384, 1, 0), (3, 65536, 32768, 2, 0)]
+    + [(G, n_in, n_out, DTYPE[storage], 0) for n_in, n_out, G, storage in FAR_ROWS])
+def test_rows_of_any_distance_are_streamed(rec, grid, n_in, n_out, dtype, layout):
+    call = dict(n_in=n_in, n_out=n_out, grid=grid, batch=512, dtype=dtype, layout=layout)
+    for fn in (dict(fn="forward"), dict(fn="backward", grad_coef=0))[:1 if grid > 34 else 2]:
         (status, launches), = routes([dict(call, **fn)], rec)
         assert status == 0
-        assert streams == any("slab" in n or "lane" in n for n in names(launches)), names(launches)
+        assert any("slab" in n or "lane" in n for n in names(launches)), names(launches)
 
 
 def test_tables_of_4_gib_and_more_keep_their_kernel(rec):

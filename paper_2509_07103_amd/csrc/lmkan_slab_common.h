@@ -4,6 +4,7 @@
 
 #include <type_traits>
 
+#include "lmkan_gate.h"
 #include "lmkan_kernels.h"
 #include "lmkan_split.h"
 
@@ -200,17 +201,8 @@ template <typename CT>
 struct is_far : std::is_same<CT, FarF32> {
 };
 
-// How the waves of a workgroup that walks over pairs hand its two slab buffers over.  A barrier per pair
-// lets the waves of a SIMD start every pair together, with nothing in their pipelines, and makes all wait
-// for the last one; what has to hold is less: a pair is walked when every wave's part of its slab has
-// landed, and a buffer is filled when every wave has read it.  Two counters in LDS say so, and a wave may
-// then run ahead of another by part of a pair (Pace):
-//   wait_landed(i); first steps of pair i; wait_read(i), request the slab of pair i + 1; more steps;
-//   slab_landed(); last steps; slab_read().
-// Every wave of the workgroup goes through the same number of pairs, and none waits for something that it
-// has not itself done before: wait_landed(i) asks for what every wave does within pair i - 1 (the first
-// slab: before the walk), wait_read(i) for the end of pair i - 1.  So the last wave never waits for long.
-// LDS instructions of a wave execute in order, so a counter moves after the reads before it.
+// The counters of lmkan_gate.h are in LDS.  LDS instructions of a wave execute in order, so a counter moves after the
+// reads before it.
 // Kernel times with a barrier per pair -> with gate and priorities, 1024 -> 1024, 8192 rows unless stated:
 // forward float32 G = 16 945 -> 830 us, G = 20 915 -> 785, G = 28 1293 -> 1130, float16 G = 16 837 -> 750,
 // G = 24 910 -> 766, bfloat16 4096 -> 4096 at G = 32, 4096 rows 9100 -> 8130; input gradient float32 G = 16
@@ -246,7 +238,7 @@ struct Pace {
 typedef Pace<4, 12, true> PaceEarly;
 typedef Pace<8, 14, false> PaceLate;
 
-struct SlabGate {
+struct LdsCounters {
     unsigned landed, read;  // LDS addresses of the counters
 
     // (a barrier has to follow before the first use)
@@ -276,40 +268,13 @@ struct SlabGate {
                      : "s"(counter), "s"(target)
                      : "memory", "scc");
     }
-    // waits until this wave's part of the slab requested last is in LDS, and says so
-    __device__ __forceinline__ void slab_landed() const
-    {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        arrive(landed);
-    }
-    __device__ __forceinline__ void slab_read() const { arrive(read); }
-    // step = pairs this workgroup has walked before this one
-    template <int WAVES>
-    __device__ __forceinline__ void wait_landed(int step) const
-    {
-        wait(landed, WAVES * (step + 1));
-    }
-    template <int WAVES>
-    __device__ __forceinline__ void wait_read(int step) const
-    {
-        wait(read, WAVES * step);
-    }
-    // The walk of a wave without samples: it fetches its part of every slab, as soon as there is room, and leaves the
-    // SIMD to the others.  request(i, wanted): the slab of pair i.
-    template <int WAVES, typename F>
-    __device__ __forceinline__ void feed_only(int n_pairs, F &&request) const
-    {
-        // (the first slab is in place before anyone reports the second: one count per wave and slab.  Later on
-        // wait_read sees to that.)
-        wait_landed<WAVES>(0);
-        for (int i = 0; i < n_pairs; ++i) {
-            wait_read<WAVES>(i);
-            request(i + 1, i + 1 < n_pairs);
-            slab_landed();
-            slab_read();
-        }
-    }
+    __device__ __forceinline__ void arrive_landed() const { arrive(landed); }
+    __device__ __forceinline__ void arrive_read() const { arrive(read); }
+    __device__ __forceinline__ void until_landed(int n) const { wait(landed, n); }
+    __device__ __forceinline__ void until_read(int n) const { wait(read, n); }
+    __device__ __forceinline__ void own_landed() const { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 };
+typedef GateOrder<LdsCounters> SlabGate;
 
 // Records of 64 consecutive samples of a pair, from sample n on: scalar base, 32-bit lane offset.  Samples past
 // the end of the batch read the record of the last one.  (The limit is kept from the compiler: the offset is

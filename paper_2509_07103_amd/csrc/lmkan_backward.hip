@@ -343,42 +343,34 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         int cells_now[kUnroll], cells_nxt[kUnroll];
 #pragma unroll
         for (int p = 0; p < kUnroll; ++p) cells_now[p] = cc[p];
-        // One step; LAST: of the last trip, which requests nothing beyond itself.
-        auto step = [&](auto pc, auto last) {
-            constexpr int P = decltype(pc)::value;
-            constexpr bool LAST = decltype(last)::value;
-            const int cell_cur = cells_now[P];
-            // Younger loads at this point.  A gy value: the 7 gy loads after it, and the load of entries
-            // where the top of a trip lies between.  Entries: the gy loads of the steps since.
-            if constexpr (!LAST && P == kUnroll - kDepth) {
-                landed(entry, std::integral_constant<int, kUnroll - kDepth>{});
-                n_nxt = row_offset(__float_as_int(entry.w));  // first needed below
-            }
-            constexpr int kYounger = LAST ? (P < kUnroll - kDepth ? kDepth - 1 : kUnroll - 1 - P) : P < kDepth ? kDepth : kDepth - 1;
-            landed(gq[P % kDepth], std::integral_constant<int, kYounger>{});
-            if (cell_cur != cur_cell) {
-                if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, cell_cur, lane);
-                retire_before(ring, out, done, cell_cur, lane);
-                cur_cell = cell_cur;
-            }
-            chunk_fma<P / 4>(acc, prod[P % 4], gq[P % kDepth]);
-            if constexpr (!LAST || P + kDepth < kUnroll)
-                load_gy(gq[P % kDepth], std::integral_constant<int, (P + kDepth) % kUnroll>{},
-                        P + kDepth < kUnroll ? n_now : n_nxt);
-        };
-        const int last_trip = nch - kUnroll;
-        for (int c = 0; c < last_trip; c += kUnroll) {
+        for (int c = 0; c < nch; c += kUnroll) {
 #pragma unroll
             for (int p = 0; p < kUnroll; ++p) cells_nxt[p] = cc[c + kUnroll + p];
             entry_products(entry, l16, prod);
             load_e(entry, c + kUnroll);
-            static_for(std::make_integer_sequence<int, kUnroll>{}, [&](auto pc) { step(pc, std::false_type{}); });
+            static_for(std::make_integer_sequence<int, kUnroll>{}, [&](auto pc) {
+                constexpr int P = decltype(pc)::value;
+                const int cell_cur = cells_now[P];
+                // Younger loads at this point.  A gy value: the 7 gy loads after it, and the load of entries
+                // where the top of a trip lies between.  Entries: the gy loads of the steps since.
+                if constexpr (P == kUnroll - kDepth) {
+                    landed(entry, std::integral_constant<int, kUnroll - kDepth>{});
+                    n_nxt = row_offset(__float_as_int(entry.w));  // first needed below
+                }
+                landed(gq[P % kDepth], std::integral_constant<int, P < kDepth ? kDepth : kDepth - 1>{});
+                if (cell_cur != cur_cell) {
+                    if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, cell_cur, lane);
+                    retire_before(ring, out, done, cell_cur, lane);
+                    cur_cell = cell_cur;
+                }
+                chunk_fma<P / 4>(acc, prod[P % 4], gq[P % kDepth]);
+                load_gy(gq[P % kDepth], std::integral_constant<int, (P + kDepth) % kUnroll>{},
+                        P + kDepth < kUnroll ? n_now : n_nxt);
+            });
             n_now = n_nxt;
 #pragma unroll
             for (int p = 0; p < kUnroll; ++p) cells_now[p] = cells_nxt[p];
         }
-        entry_products(entry, l16, prod);
-        static_for(std::make_integer_sequence<int, kUnroll>{}, [&](auto pc) { step(pc, std::true_type{}); });
         // nothing may still be on its way to a register once the compiler is free to reuse it
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }

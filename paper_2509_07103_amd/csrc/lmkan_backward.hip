@@ -379,9 +379,9 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
 }
 
 // The nodes that run blockIdx.x + 1 of pair blockIdx.y shares with the runs before it start at zero
-__global__ __launch_bounds__(256) void fill_zero_kernel(const int32_t *__restrict__ chunk_cell,
-                                                                const int32_t *__restrict__ block_chunks, int64_t S, int n_sub,
-                                                                int W, float *gP, CoefMap gmap, int n_out)
+__global__ __launch_bounds__(256) void clear_shared_nodes_kernel(const int32_t *__restrict__ chunk_cell,
+                                                                 const int32_t *__restrict__ block_chunks, int64_t S, int n_sub,
+                                                                 int W, float *gP, CoefMap gmap, int n_out)
 {
     const int k = blockIdx.y, chunks = block_chunks[k], first = ((int)blockIdx.x + 1) * run_chunks(chunks, n_sub);
     if (first >= chunks) return;
@@ -448,8 +448,10 @@ SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted,
 
 // A gradient of fewer than three million entries is cleared as a whole: where the runs meet is in the stream, two loads
 // before the first store (7 MB in 4.2 us, its shared nodes alone in 5.0; 17 MB in 6.1 and 5.3, 147 MB in 19.6 and 7.7).
-// Adding all of it atomically then costs the walk 1 us at most, and leaves it in the L2 for who reads it next: training steps of
-// 358 -> 61, G = 9, 1827 rows 103.8 us, 104.4 with owned nodes, of 198 -> 65, G = 15, 3016 rows 164.9 and 165.4.
+// Adding all of it atomically then costs the walk 1 us at most, and leaves it in the L2 for who reads it next.  The call for this
+// gradient alone, all shared -> nodes owned: 128 -> 96, G = 12, 9000 rows 57.5 -> 60.8 us, 358 -> 61, G = 9, 1827 rows 41.6 -> 42.4;
+// training steps of 64 -> 64, G = 8, 4096 rows 53.0 -> 54.0, of 358 -> 61 with the regulariser 112.5 -> 113.2.  Added to a gradient
+// that is there, when nothing is cleared: 39.2 -> 39.7, 198 -> 65, G = 15, 3016 rows 52.7 -> 53.9, 128 -> 96 56.4 -> 56.3.
 bool all_nodes_shared(const LayerShape &s, int n_blocks, int n_sub)
 {
     return n_blocks > 1 || (n_sub > 1 && (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out < 3000000);
@@ -462,7 +464,7 @@ void launch_clear_shared_nodes(const LayerShape &s, const SortedStream &st, int 
     if (all_nodes_shared(s, st.n_blocks, n_sub))
         launch_fill_zero(gcoef, (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out, stream);
     else if (n_sub > 1)
-        fill_zero_kernel<<<dim3((unsigned)(n_sub - 1), (unsigned)s.pairs()), 256, 0, stream>>>(
+        clear_shared_nodes_kernel<<<dim3((unsigned)(n_sub - 1), (unsigned)s.pairs()), 256, 0, stream>>>(
             st.chunk_cell, st.block_chunks, st.S, n_sub, s.G + 1, gcoef, coef_map(g), s.n_out);
 }
 

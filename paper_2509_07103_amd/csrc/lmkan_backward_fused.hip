@@ -465,13 +465,14 @@ size_t fused_partial_bytes(const LayerShape &s)
 // without the coefficient gradient; LDS: seven per CU at G = 40) and each waits for its own loads, so the walk takes as
 // long as its rounds of resident waves: the count of runs with the fewest trips over all rounds, two
 // trips of start and end per run.  Nodes that runs share (run_nodes: about a row of cells where a run meets the
-// next; all of them in streams of several blocks) pay for the zero fill and the atomics, about three times
+// next; all of them in streams of several blocks and in small gradients: all_nodes_shared) pay for the zero fill and the atomics, about three times
 // their bytes of the gradient, 1 trip per 6 MB.  A run keeps at least four trips.
 // Powers of two up to 4096 waves before: 128 -> 128 at G = 40 on 8192 rows 222 us for the step (32 runs,
 // 2.3 rounds of waves), 207 with 14 (one round); 256 -> 256 654 -> 586 us; 200 -> 320 at G = 48 724 -> 664;
 // 512 -> 384 at G = 40 on 12000 rows 2048 -> 1905 (uncut).  With every node of a cut stream cleared and added atomically
 // 256 -> 256 at G = 40 took 612 us (now 558), 512 -> 512 with a float16 table 2068 (1875); 512 -> 384 was better uncut,
-// 2075 (2025 in runs), and 400 -> 320 at G = 48 on 6000 rows 1514 (1132).
+// 2075 (2025 in runs), and 400 -> 320 at G = 48 on 6000 rows 1514 (1132).  Small gradients charged for their shared rows alone
+// were cut too little: backward of 30 -> 60 at G = 47, float16, 6810 rows 101.1 -> 93.6 us, 24 -> 60 at G = 58, 3733 rows 101.8 -> 92.3.
 static int fused_run_split(const LayerShape &s, unsigned lds, bool want_gp)
 {
     constexpr unsigned kLdsBytes = 160 * 1024, kLdsGranule = 1280;
@@ -486,7 +487,7 @@ static int fused_run_split(const LayerShape &s, unsigned lds, bool want_gp)
     int64_t best_cost = 0;
     for (int n = 1; n <= 64 && (n == 1 || trips / n >= 4); ++n) {
         const int64_t rounds = (units * n + resident - 1) / resident;
-        const int64_t part = blocks > 1 ? s.nodes() : std::min((n - 1) * (s.G + 9), s.nodes());
+        const int64_t part = all_nodes_shared(s, blocks, n) ? s.nodes() : std::min((n - 1) * (s.G + 9), s.nodes());
         const int64_t cost = rounds * ((trips + n - 1) / n + 2) + shared * part / s.nodes();
         if (n == 1 || cost < best_cost) best = n, best_cost = cost;
     }

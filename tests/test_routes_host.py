@@ -20,7 +20,7 @@ WITHOUT = {"forward_generic_kernel", "forward_gather_kernel", "forward_head_kern
            "backward_gather_kernel", "backward_input_gather_kernel", "backward_coef_gather_kernel",
            "backward_input_head_kernel", "backward_coef_head_kernel", "backward_coef_stream_kernel",
            "backward_fused_kernel", "preamble_records_kernel"}
-AROUND = {"fill_zero_kernel", "gy_tiles_kernel", "transpose_kernel", "sum_partials_kernel", "head_combine_kernel",
+AROUND = {"fill_zero_kernel", "clear_shared_nodes_kernel", "gy_tiles_kernel", "transpose_kernel", "sum_partials_kernel", "head_combine_kernel",
           "gx_combine_kernel", "conv_input_gradient_kernel", "conv_input_gradient_scatter_kernel"}
 
 
@@ -229,3 +229,23 @@ def test_grad_x_of_16_bit_tables_reaches_the_kernels_it_is_listed_for(rec):
                   for B, n_in, n_out, G, storage, layout, _ in listed], rec)
     for layer, (_, launches) in zip(listed, got):
         assert layer[-1] in names(launches), (layer, names(launches))
+
+
+@pytest.mark.parametrize("layer,clears", [
+    # two runs and more per stream: what they share; all of it below three million entries and in streams of several blocks
+    (dict(n_in=256, n_out=128, grid=16, batch=8192), "clear_shared_nodes_kernel"),
+    (dict(n_in=160, n_out=128, grid=16, batch=8192), "fill_zero_kernel"),
+    (dict(n_in=256, n_out=128, grid=16, batch=12289), "fill_zero_kernel"),
+    (dict(n_in=128, n_out=128, grid=40, batch=8192, layout=1), "clear_shared_nodes_kernel"),        # (the walk, with grad_x)
+    (dict(n_in=30, n_out=60, grid=47, batch=6810, dtype=1), "fill_zero_kernel"),
+    # a run per stream
+    (dict(n_in=1024, n_out=512, grid=16, batch=8192), None)])
+@pytest.mark.parametrize("adds", [0, 1])
+def test_nodes_that_runs_share_are_cleared_unless_added_to(rec, layer, clears, adds):
+    walk = layer["grid"] >= 40
+    call = dict(layer, fn="backward", grad_x=int(walk), flags=pkg.LMKAN_FLAG_ACCUMULATE_GRAD_COEF if adds else 0)
+    (status, launches), = routes([call], rec)
+    walks = names(launches)
+    assert status == 0 and ("backward_fused_kernel" if walk else "backward_coef_stream_kernel") in walks, walks
+    cleared = {"fill_zero_kernel", "clear_shared_nodes_kernel"} & set(walks)
+    assert cleared == ({clears} if clears and not adds else set()), walks

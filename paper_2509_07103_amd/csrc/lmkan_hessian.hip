@@ -40,7 +40,6 @@ struct HessArgs {
     float scale;
     int K;
     int n_out;
-    int tiles;
 };
 
 // a value that is the same in every lane, moved to a scalar register
@@ -110,12 +109,16 @@ __global__ __launch_bounds__(64 * kMaxBands) void hessian_reg_kernel(HessArgs a)
     // contiguous run of them, so that the line is put together in one L2: 500 -> 333, G = 20, adding 128 -> 121 us,
     // writing 107 -> 109; 512 -> 500, G = 30, bfloat16 297 -> 278 and 255 -> 219.  With whole lines it is no gain
     // (512 -> 512, G = 27: 266 and 196 us without, 266 and 199 with).
-    int id = blockIdx.x;
+    // (workgroups go to the XCDs in the order y gridDim.x + x; a table of the largest layers has 2^32 tiles nearly,
+    // more than one dimension of a launch holds)
+    int tile = blockIdx.x, k = blockIdx.y;
     if ((a.n_out & 31) != 0) {
-        const int total = gridDim.x, xcd = id & 7, each = total >> 3, over = total & 7;
-        id = xcd * each + min(xcd, over) + (id >> 3);
+        const unsigned tiles = gridDim.x, total = tiles * gridDim.y, id = k * tiles + tile;
+        const unsigned xcd = id & 7, each = total >> 3, over = total & 7;
+        const unsigned moved = xcd * each + min(xcd, over) + (id >> 3);
+        k = moved / tiles;
+        tile = moved - k * tiles;
     }
-    const int tile = id % a.tiles, k = id / a.tiles;
     const int j = tile * 64 + lane;
     const bool live = j < a.n_out;
     // A lane past the last output works on the last output once more: it reads the same values,
@@ -295,8 +298,7 @@ void launch_hessian_reg(const LayerShape &s, const GridTab &tab, const void *coe
     a.K = s.pairs();
     a.n_out = s.n_out;
     if (value) launch_fill_zero(reinterpret_cast<float *>(value), 2, stream);
-    a.tiles = s.out_tiles();
-    const unsigned grid = (unsigned)((int64_t)s.out_tiles() * s.pairs());
+    const dim3 grid((unsigned)s.out_tiles(), (unsigned)s.pairs());
     const int bands = (s.G + 1 + kBand - 1) / kBand;
     typedef void (*Kernel)(HessArgs);
     static const Kernel table[3][3] = {

@@ -5,7 +5,7 @@ and reports the launches.
     routes([dict(fn="backward", n_in=16, n_out=16, grid=8, batch=256, grad_x=1, grad_coef=1), ...])
 
 gives for every call (status, [(kernel, grid, threads, LDS bytes), ...]).  A call is a dict of
-  fn         "forward", "forward_static", "backward" or "workspace" (whose status is the size)
+  fn         "forward", "forward_static", "backward", "hessian" or "workspace" (whose status is the size)
   n_in, n_out, grid, batch; dtype (0, 1, 2), layout (0, 1), flags (default 0)
   conv       (n, h, w, c_in, kh, kw, stride) instead of batch
   grad_x, grad_coef   which gradients a backward call is asked for (1 or 0)
@@ -81,6 +81,8 @@ def _main():
             status = call(dp, geometry, p["x"], p["coef"], p["y"], ws, C.c_size_t(size), None)
         elif fn == "forward_static":
             status = lib.lmkan_forward_static(dp, C.c_int64(rows), p["x"], p["coef"], p["y"], None)
+        elif fn == "hessian":
+            status = lib.lmkan_hessian_reg(dp, p["coef"], C.c_float(1.0), p["ws"], p["gp"] if grad_coef else None, None)
         else:
             call = lib.lmkan_conv2d_backward if conv else lib.lmkan_backward
             status = call(dp, geometry, p["x"], p["coef"], p["gy"], p["gx"] if grad_x else None,

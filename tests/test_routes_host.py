@@ -214,6 +214,16 @@ def test_rows_of_any_distance_are_streamed(rec, grid, n_in, n_out, dtype, layout
         assert any("slab" in n or "lane" in n for n in names(launches)), names(launches)
 
 
+@pytest.mark.parametrize("n_out", [65600, 65601, 1048576])
+def test_the_regulariser_of_the_largest_layers_can_be_launched(rec, n_out):
+    """A 16-bit table of 138 GB and more has more tiles than one dimension of a launch holds threads for."""
+    call = dict(n_in=131070, n_out=n_out, grid=3, batch=1, dtype=1, layout=1, fn="hessian", grad_coef=0)
+    (status, launches), = routes([call], rec)
+    kernel, grid, threads, _ = launches[-1]
+    assert status == 0 and kernel.startswith("hessian_reg_kernel")
+    assert grid[0] * threads < 1 << 32 and grid[1] < 1 << 16 and grid[0] * grid[1] == (n_out + 63) // 64 * 65535, grid
+
+
 def test_tables_of_4_gib_and_more_keep_their_kernel(rec):
     """Layout of Alg. 1, float16: a slab's nodes lie up to the whole table apart, rows that one load brings do not."""
     for grid, n in ((16, 4096), (8, 8192), (16, 2048)):

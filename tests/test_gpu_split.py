@@ -56,20 +56,21 @@ _STREAMED = [layer[:5] for layer in UNUSUAL_16BIT]
 @pytest.mark.parametrize("B,n_in,n_out,G,storage", _GATHERED + _STREAMED)
 @pytest.mark.parametrize("scale", [1e-30, 1e-8, 1.0, 1e30])
 def test_parts_of_gy_hold_every_magnitude(oracle, B, n_in, n_out, G, storage, scale):
-    """A row is scaled as a whole; within a row 2^-40 ... 1, whose small values the large ones must not swallow:
-    half of the rows have small values only in the outputs of one tile."""
+    """A row is scaled as a whole; within a row 2^-40 ... 1, and small values that large ones beside them must not swallow."""
     x, P, table, gy, desc = _layer(B, n_in, n_out, G, storage, "packed")
     spread = torch.exp2(-40.0 * torch.rand(gy.shape, generator=torch.Generator().manual_seed(6)))
     gy = gy * scale * torch.where(torch.arange(B)[:, None] % 2 == 0, spread, torch.where(torch.arange(n_out)[None, :] < 64, 2.0 ** -40, 1.0))
     want = oracle.backward_input(x.numpy(), bits(P), gy.numpy(), G, dtype=ORACLE_DTYPE[storage], threads=8)
     assert rowwise_rel_err(_grad_x(desc, x, table, gy) / scale, want / scale) <= TOL_F32
-    # outputs of the first tile alone: their values are all there is
-    gy[:, 64:] = 0.0
-    want = oracle.backward_input(x.numpy(), bits(P), gy.numpy(), G, dtype=ORACLE_DTYPE[storage], threads=8)
-    factor = 2.0 ** 20 / scale       # (float32's smallest numbers are not reached by the sums themselves)
-    got = _grad_x(desc, x, table, gy)
-    if scale > 1e-20:
-        assert rowwise_rel_err(got.astype(np.float64) * factor, want * factor) <= TOL_F32
+    # small values beside large ones in every tile, whose outputs have a table of zeros: the small ones are all there is
+    small = 2.0 ** (-40 if scale > 1e-20 else -6)        # (products stay normal numbers)
+    x, P, _, gy, desc = _layer(B, n_in, n_out, G, storage, "packed")
+    P[..., 1::2] = 0.0
+    gy[:, 0::2] *= small
+    gy *= scale
+    table = pkg.lmkan_pack(pkg.LayerDesc(n_in, n_out, G, coef_dtype=DTYPE[storage][0]), P)
+    want = oracle.backward_input(x.numpy(), bits(P), gy.numpy(), G, dtype=ORACLE_DTYPE[storage], threads=8) / (scale * small)
+    assert rowwise_rel_err(_grad_x(desc, x, table, gy).astype(np.float64) / (scale * small), want) <= TOL_F32
 
 
 @pytest.mark.parametrize("B,n_in,n_out,G,storage", _GATHERED + _STREAMED)

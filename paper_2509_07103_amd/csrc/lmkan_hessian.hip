@@ -106,8 +106,8 @@ __global__ __launch_bounds__(64 * kMaxBands) void hessian_reg_kernel(HessArgs a)
 
     // Neighbouring workgroups are the output tiles of one pair, next to each other in the gradient.  Where rows do not
     // start on lines of 128 bytes neighbours share a line at the end of every row of theirs, and each XCD gets a
-    // contiguous run of them, so that the line is put together in one L2: 500 -> 333, G = 20, adding 128 -> 121 us,
-    // writing 107 -> 109; 512 -> 500, G = 30, bfloat16 297 -> 278 and 255 -> 219.  With whole lines it is no gain
+    // contiguous run of them, so that the line is put together in one L2: 500 -> 333, G = 20, adding 135 -> 123 us,
+    // writing 116 -> 98; 512 -> 500, G = 30, bfloat16 330 -> 305 and 262 -> 230.  With whole lines it is no gain
     // (512 -> 512, G = 27: 266 and 196 us without, 266 and 199 with).
     // (workgroups go to the XCDs in the order y gridDim.x + x; a table of the largest layers has 2^32 tiles nearly,
     // more than one dimension of a launch holds)

@@ -265,8 +265,6 @@ __device__ __forceinline__ void slab_pipeline(float *acc, Corners (&ring)[AHEAD 
 }
 
 // WAVES waves per workgroup, SETS x 64 samples per wave.
-// Two waves per SIMD by construction (one workgroup per CU); telling the compiler lets
-// it spend registers on keeping several LDS reads in flight.
 // WAVES / 4 waves per SIMD by construction (one workgroup per CU); telling the compiler lets
 // it spend exactly that share of the registers.  The multiply-add rate of a SIMD grows with
 // the number of waves it can pick from (measured: DPP multiply-adds 49 per clock and CU with
@@ -547,7 +545,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     float *slab1 = smem + slab_floats;
     float *s_invh = smem + 2 * slab_floats;
     for (int i = threadIdx.x; i < a.tab.G; i += blockDim.x) s_invh[i] = a.tab.inv_h[i];
-    SlabArgs sa;  // only the fields issue_slab_load reads
+    SlabArgs sa;  // only the fields SlabFill reads
     sa.P = a.P;
     sa.map = a.map;
     sa.nodes = a.nodes;
@@ -1180,9 +1178,6 @@ struct HalfRowF32 {
     static constexpr int kBytes = kHalfTile * 4;         // a row of the slab
     static constexpr int kPieces = kBytes / 16;          // 16-byte pieces per row
     static constexpr int kPer = 4;                       // outputs per piece
-    static constexpr int kRowsPerFill = 64 / kPieces;    // rows one wave instruction moves
-    static constexpr int kPieceShift = 3;                // log2 of the two above
-    static constexpr int kFillShift = 3;
 };
 
 __device__ __forceinline__ void piece_as_floats(const uint4 raw, float (&f)[4])

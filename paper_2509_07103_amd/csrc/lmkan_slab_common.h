@@ -216,6 +216,13 @@ constexpr int kNowhereBytes = 256;   // what loads for the L2's sake write into
 // for.  A wave that lags behind gets the SIMD first: its priority falls from quarter to quarter of a pair, and
 // steps back up at the start of a pair or (FROM_FILL) at its second quarter, where wait_read has made sure
 // that no wave is still in the pair before.
+// Which of the two below a kernel takes was measured, all kernels with each (us, early / late; 1024 -> 1024 on 8192 rows unless
+// stated).  Early: forward_slab_kernel 815 / 827, forward_lane32_kernel 736 / 750 (float16, G = 24), 114 / 120 (3000 rows of 512 ->
+// 512, G = 30), 2022 / 2023 (2048 -> 2048, bfloat16, G = 32).  Late: forward_slab_f16_kernel 861 / 808,
+// backward_input_slab_f16_kernel 953 / 905, backward_input_lane32_kernel 1074 / 918 (float16, G = 24) and 1113 / 1077 (bfloat16),
+// backward_input_lane32_f32_kernel 1141 / 1110 (G = 20).  Late, though early is no slower: forward_lane32_f32_kernel
+// 791 / 810 (G = 20), the 16-output kernels 1090 / 1072 and 1699 / 1725 (forward, input gradient, float32, G = 28).
+// backward_input_lane_kernel is late untried: the compiler does not translate its form for rows far apart with early.
 template <int FILL, int LANDED, bool FROM_FILL>
 struct Pace {
     static constexpr int kFill = FILL, kLanded = LANDED;

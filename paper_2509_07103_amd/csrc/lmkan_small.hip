@@ -355,8 +355,9 @@ __global__ __launch_bounds__(kHeadThreads) void backward_input_head_kernel(HeadA
 // head_combine_kernel adds the partials up in a fixed order (adding them to the gradient with atomics, as
 // a call without room for them does, took 38 us for 256 partials of 148 KB, three times as long).
 // (LDS float atomics before this took about 3.5 clocks per lane and CU whatever their addresses: 0.22 ms
-// for 256 -> 1 on 65536 rows.  Bound now by the chain of reads and writes, about 120 clocks per sample,
-// and by the locates.)
+// for 256 -> 1 on 65536 rows.  Of the 51 us there 15 go into clearing, staging and writing the
+// tables; the rest is bound by the vector port, 100 instructions per four samples and pair: locates further ahead of the chain
+// of reads and writes, or several reads in flight, gained 3 % at most.)
 // ---------------------------------------------------------------------------
 template <int S>
 __device__ __forceinline__ float quad_bcast(float v)

@@ -90,3 +90,4 @@ if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     from paper_2509_07103_amd import check_codegen
     check_codegen.check(verbose=True)
+    check_codegen.check(verbose=True, sources=check_codegen.SPARSE_SOURCES)

@@ -26,6 +26,7 @@ import tempfile
 from . import build as hip_build
 
 CHECKED_SOURCES = ("lmkan_backward.hip",)
+SPARSE_SOURCES = ("lmkan_backward_sparse.hip",)   # the walk of sparse cells: trips of another length
 
 
 def _regs(text: str) -> frozenset[int]:
@@ -108,12 +109,12 @@ def check_assembly(text: str) -> dict[str, int]:
     return counts
 
 
-def check(verbose: bool = False) -> dict[str, int]:
-    """Compiles the checked sources to assembly with the flags of the library and checks them."""
+def check(verbose: bool = False, sources=CHECKED_SOURCES) -> dict[str, int]:
+    """Compiles the sources to assembly with the flags of the library and checks them."""
     flags = [f for f in hip_build.FLAGS if f not in ("-shared", "-fPIC")]
     counts: dict[str, int] = {}
     with tempfile.TemporaryDirectory() as tmp:
-        for name in CHECKED_SOURCES:
+        for name in sources:
             out = os.path.join(tmp, name + ".s")
             cmd = [hip_build.HIPCC, *flags, "-S", "--cuda-device-only", "-o", out, os.path.join(hip_build.CSRC, name)]
             res = subprocess.run(cmd, capture_output=True, text=True)
@@ -132,6 +133,7 @@ def check(verbose: bool = False) -> dict[str, int]:
 
 if __name__ == "__main__":
     check(verbose=True)
+    check(verbose=True, sources=SPARSE_SOURCES)
 
 
 # Kernels that must not touch scratch memory at all (substrings of the mangled names), and the

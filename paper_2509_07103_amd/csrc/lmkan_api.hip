@@ -443,7 +443,7 @@ lmkan_status backward_impl(const lmkan_desc *desc, int64_t batch, const float *x
     if (!have_records && (need_records || (kept && room))) launch_preamble_records(s, tab, x_dev, ws, hs, conv);
     SortedStream stream_k{};
     GyView gy_k{};
-    if (gp_sorted || gx_fused) stream_k = launch_sort(s, ws, ws_sorted, hs);
+    if (gp_sorted || gx_fused) stream_k = launch_sort(s, ws, ws_sorted, !gx_fused && coef_stream_is_sparse(s), hs);
     // (the slab kernels read gy as it is, except with a ragged output count)
     if (gp_sorted || gx_fused || (gx_slab && ragged_outputs(s))) gy_k = launch_gy_tiles(s, grad_y_dev, ws + w.gy_tiles, hs);
     else gy_k = GyView{grad_y_dev, (int64_t)(LMKAN_PACK_TILE * sizeof(float)), (unsigned)(s.n_out * sizeof(float))};

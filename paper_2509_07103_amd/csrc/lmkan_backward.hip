@@ -65,15 +65,16 @@ __host__ __device__ inline size_t sort_lds_bytes(int G)
     return (cells + 1) * sizeof(int) + (counts > stage ? counts : stage);
 }
 
-__global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__restrict__ rec_node,
-                                                           const float *__restrict__ rec_u,
-                                                           const float *__restrict__ rec_v, f4v *__restrict__ rec,
-                                                           int32_t *__restrict__ chunk_cell,
-                                                           int32_t *__restrict__ block_chunks, int64_t B, int G)
+template <bool SPARSE>
+__device__ __forceinline__ void sort_block(const int32_t *__restrict__ rec_node, const float *__restrict__ rec_u,
+                                           const float *__restrict__ rec_v, f4v *__restrict__ rec,
+                                           int32_t *__restrict__ chunk_cell, int32_t *__restrict__ block_chunks, int64_t B,
+                                           int G)
 {
     extern __shared__ __align__(16) int s_dyn[];
     __shared__ int s_wave_total[kSortWaves];
     __shared__ int s_last_cell;
+    constexpr int kPad = SPARSE ? kHalf : kChunk;
     const int cells = G * G, even = (cells + 1) & ~1;
     int *s_start = s_dyn;                                                             // [cells + 1]
     unsigned short *s_off = reinterpret_cast<unsigned short *>(s_start + cells + 1);  // [waves][even]
@@ -110,7 +111,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
         if (cell[j] >= 0) {
             const int i1 = (int)(((unsigned)cell[j] * inv_w) >> 20);
             const int c = cell[j] - i1;  // i1 (G + 1) + i2 -> i1 G + i2
-            odd |= ((cell[j] ^ (i1 & (int)W)) & 1u) << j;  // i2 = node - i1 W
+            odd |= ((SPARSE ? cell[j] : cell[j] ^ (i1 & (int)W)) & 1u) << j;  // i2 = node - i1 W
             cell[j] = c;
             rank[j] = count_in_order(s_count, wave * even + c, c, cells > 256);
         }
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
                 run += n;
             }
             s_total[c] = (unsigned short)run;
-            mine += (run + kChunk - 1) / kChunk * kChunk;
+            mine += (run + kPad - 1) / kPad * kPad;
             if (run > 0) atomicMax(&s_last_cell, c);
         }
         int incl = mine;
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
         for (int w = 0; w < wave; ++w) run += s_wave_total[w];
         for (int c = c0; c < c1; ++c) {
             s_start[c] = run;
-            run += (s_total[c] + kChunk - 1) / kChunk * kChunk;
+            run += (s_total[c] + kPad - 1) / kPad * kPad;
         }
         if (tid == kSortThreads - 1) s_start[cells] = run;
     }
@@ -179,52 +180,51 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
             }
         }
         __syncthreads();
-        if (real_end > base) last_sample = s_n[min(real_end - base, kSortStage) - kChunk];
+        if (real_end > base) last_sample = s_n[min(real_end - base, kSortStage) - kPad];
         for (int p = tid; p < kSortStage && base + p < fill_end; p += kSortThreads) {
-            // (a chunk's first entry is always a sample, unless the chunk lies past the real ones)
-            const int n = s_n[p], first = s_n[p & ~(kChunk - 1)];
+            // (the first entry of a chunk, or half chunk, is always a sample, unless it lies past the real ones)
+            const int n = s_n[p], first = s_n[p & ~(kPad - 1)];
             f4v e = {0.f, 0.f, 0.f, __int_as_float((first >= 0 ? first : last_sample) & ~kOddCell)};
             if (n >= 0) e = f4v{s_u[p], s_v[p], (n & kOddCell) != 0 ? -1.0f : 1.0f, __int_as_float(n & ~kOddCell)};
             out[base + p] = e;
         }
         __syncthreads();
     }
-    // the cell of every chunk: the highest cell whose start is <= the chunk's first position (an empty
+    // the cell of every chunk, or half chunk: the highest cell whose start is <= its first position (an empty
     // cell shares its start with the next one, so the highest such cell is never empty); chunks past
     // the real ones belong to the block's last cell
-    for (int q = tid; q < fill_end / kChunk; q += kSortThreads) {
+    for (int q = tid; q < fill_end / kPad; q += kSortThreads) {
         int c = last;
-        if (q * kChunk < real_end) {
+        if (q * kPad < real_end) {
             int lo = 0, hi = cells - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
-                if (s_start[mid] <= q * kChunk) lo = mid; else hi = mid - 1;
+                if (s_start[mid] <= q * kPad) lo = mid; else hi = mid - 1;
             }
             c = lo;
         }
-        out_cell[q] = ((c / G) << 8) | (c % G);
+        if constexpr (SPARSE)
+            reinterpret_cast<unsigned short *>(out_cell)[q] = (unsigned short)(c + c / G);
+        else
+            out_cell[q] = ((c / G) << 8) | (c % G);
     }
     if (tid == 0) block_chunks[(int64_t)k * blocks + blk] = block_end / kChunk;
 }
 
-struct CoefGradArgs {
-    const f4v *rec;
-    const int32_t *chunk_cell;
-    const int32_t *block_chunks;  // [K][n_blocks]
-    GyView gy;
-    float *gP;
-    CoefMap gmap;  // layout of Alg. 1
-    int64_t B;
-    int64_t S;     // stream_stride
-    int block_stride;  // chunks from one block of the stream to the next
-    int n_out;
-    int K;
-    int G;
-    int accumulate;
-    int n_blocks;  // locality blocks of the batch
-    int n_sub;     // waves per (pair, output tile, block)
-    int all_shared;  // every node is added to atomically
-};
+__global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *rec_node, const float *rec_u, const float *rec_v,
+                                                           f4v *rec, int32_t *chunk_cell, int32_t *block_chunks, int64_t B, int G)
+{
+    sort_block<false>(rec_node, rec_u, rec_v, rec, chunk_cell, block_chunks, B, G);
+}
+
+// (the same for a sparse stream, cells padded to kPad = kHalf)
+template <int kPad>
+__global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *rec_node, const float *rec_u, const float *rec_v,
+                                                           f4v *rec, int32_t *chunk_cell, int32_t *block_chunks, int64_t B, int G)
+{
+    static_assert(kPad == kHalf, "");
+    sort_block<true>(rec_node, rec_u, rec_v, rec, chunk_cell, block_chunks, B, G);
+}
 
 template <bool kOffset32>
 __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a)
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
 
     const NodeRing ring(win, W);
     for (int i = lane; i < ring.R * kTile; i += 64) win[i] = 0.0f;
-    const RunNodes nodes = run_nodes(cc, nch, sub == 0, last_run, a.all_shared != 0, W);
+    const RunNodes nodes = run_nodes<false>(cc, nch, sub == 0, last_run, a.all_shared != 0, W);
     const GradOut out{a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0,
                       nodes.own()};
 
@@ -375,20 +375,21 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, -1, lane);
-    retire_nodes(ring, out, done, run_end(out.own, cur_cell, W), lane);
+    retire_nodes(ring, out, done, run_end(out.own, first_node<false>(cur_cell, W), W), lane);
 }
 
 // The nodes that run blockIdx.x + 1 of pair blockIdx.y shares with the runs before it start at zero
 __global__ __launch_bounds__(256) void clear_shared_nodes_kernel(const int32_t *__restrict__ chunk_cell,
                                                                  const int32_t *__restrict__ block_chunks, int64_t S, int n_sub,
-                                                                 int W, float *gP, CoefMap gmap, int n_out)
+                                                                 int W, float *gP, CoefMap gmap, int n_out, int sparse)
 {
     const int k = blockIdx.y, chunks = block_chunks[k], first = ((int)blockIdx.x + 1) * run_chunks(chunks, n_sub);
     if (first >= chunks) return;
     const int32_t *cell = chunk_cell + (int64_t)k * (S / kChunk) + first;
     // (a group of four nodes of a run is shared as a whole)
-    const int beyond = ((cell[-1] >> 8) + 1) * W + (cell[-1] & 255) + 2;
-    const int from = max(min((cell[0] >> 8) * W + (cell[0] & 255), beyond) - 3, 0), to = min(beyond + 3, W * W);
+    const int beyond = (sparse ? last_node<true>(cell[-1], W) : last_node<false>(cell[-1], W)) + W + 2;
+    const int here = sparse ? first_node<true>(cell[0], W) : first_node<false>(cell[0], W);
+    const int from = max(min(here, beyond) - 3, 0), to = min(beyond + 3, W * W);
     float *out = gP + (int64_t)k * gmap.s_pair;
     for (int id = from + (int)(threadIdx.x >> 6); id < to; id += 4)
         for (int col = threadIdx.x & 63; col < n_out; col += 64) out[id * gmap.s_node + col] = 0.0f;
@@ -422,7 +423,7 @@ bool coef_sorted_applicable(const LayerShape &s, const float *gy, const float *g
     return ((reinterpret_cast<uintptr_t>(gy) | reinterpret_cast<uintptr_t>(gcoef)) & 15) == 0;
 }
 
-SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted, hipStream_t stream)
+SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted, bool sparse, hipStream_t stream)
 {
     const size_t n = (size_t)s.pairs() * (size_t)s.batch;
     const size_t K = (size_t)s.pairs();
@@ -437,12 +438,15 @@ SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted,
     int32_t *chunk_cell = reinterpret_cast<int32_t *>(rec + K * (size_t)st.S);
     int32_t *block_chunks = chunk_cell + K * (size_t)(st.S / kChunk);
     const size_t lds = sort_lds_bytes(s.G);
-    if (lds > 60 * 1024) allow_large_lds(reinterpret_cast<const void *>(sort_kernel), 160 * 1024 - 256);
-    sort_kernel<<<dim3((unsigned)st.n_blocks, (unsigned)K), kSortThreads, lds, stream>>>(
+    typedef void (*Kernel)(const int32_t *, const float *, const float *, f4v *, int32_t *, int32_t *, int64_t, int);
+    const Kernel kernel = sparse ? static_cast<Kernel>(sort_kernel<kHalf>) : static_cast<Kernel>(sort_kernel);
+    if (lds > 60 * 1024) allow_large_lds(reinterpret_cast<const void *>(kernel), 160 * 1024 - 256);
+    kernel<<<dim3((unsigned)st.n_blocks, (unsigned)K), kSortThreads, lds, stream>>>(
         rec_node, rec_u, rec_v, rec, chunk_cell, block_chunks, s.batch, s.G);
     st.rec = rec;
     st.chunk_cell = chunk_cell;
     st.block_chunks = block_chunks;
+    st.sparse = sparse;
     return st;
 }
 
@@ -465,7 +469,7 @@ void launch_clear_shared_nodes(const LayerShape &s, const SortedStream &st, int 
         launch_fill_zero(gcoef, (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out, stream);
     else if (n_sub > 1)
         clear_shared_nodes_kernel<<<dim3((unsigned)(n_sub - 1), (unsigned)s.pairs()), 256, 0, stream>>>(
-            st.chunk_cell, st.block_chunks, st.S, n_sub, s.G + 1, gcoef, coef_map(g), s.n_out);
+            st.chunk_cell, st.block_chunks, st.S, n_sub, s.G + 1, gcoef, coef_map(g), s.n_out, st.sparse ? 1 : 0);
 }
 
 void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, const GyView &gy, float *gcoef,
@@ -495,7 +499,10 @@ void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, co
     if (!accumulate) launch_clear_shared_nodes(s, st, n_sub, gcoef, stream);
     const unsigned grid = (unsigned)((int64_t)s.pairs() * s.out_tiles() * st.n_blocks * n_sub);
     KernelTiming timing(stream, kTimeGradCoef);
-    if (gy_offsets_fit_32_bits(s, gy))
+    const bool offsets32 = gy_offsets_fit_32_bits(s, gy);
+    if (st.sparse)
+        launch_coef_sparse(a, offsets32, grid, lds, stream);
+    else if (offsets32)
         backward_coef_stream_kernel<true><<<grid, 64, lds, stream>>>(a);
     else
         backward_coef_stream_kernel<false><<<grid, 64, lds, stream>>>(a);

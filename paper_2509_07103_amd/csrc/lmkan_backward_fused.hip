@@ -190,7 +190,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     }
 
     const NodeRing ring(win, W);
-    const RunNodes nodes = run_nodes(cc, nch, sub == 0, last_run, a.all_shared != 0, W);
+    const RunNodes nodes = run_nodes<false>(cc, nch, sub == 0, last_run, a.all_shared != 0, W);
     const GradOut out{DO_GP ? a.gP + (int64_t)k * a.gmap.s_pair + jt * kTile : nullptr, a.gmap.s_node, jt * kTile, a.n_out, a.accumulate != 0,
                       nodes.own()};
     if constexpr (DO_GP)
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     asm volatile("" ::"v"(touched));
     if constexpr (DO_GP) {
         if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, -1, lane);
-        retire_nodes(ring, out, done, run_end(out.own, cur_cell, W), lane);
+        retire_nodes(ring, out, done, run_end(out.own, first_node<false>(cur_cell, W), W), lane);
     }
 }
 

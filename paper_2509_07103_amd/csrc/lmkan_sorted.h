@@ -14,7 +14,8 @@ namespace lmkan {
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef unsigned u2v __attribute__((ext_vector_type(2)));
 
-constexpr int kChunk = 4;    // samples per chunk; a chunk never straddles two cells
+constexpr int kChunk = 4;    // samples per chunk; a chunk never straddles two cells (sparse streams: half a chunk)
+constexpr int kHalf = kChunk / 2;
 constexpr int kUnroll = 16;  // chunks per trip of the walking kernels' main loops
 constexpr int64_t kMaxSortedBatch = (int64_t)65535 * 4096;
 // A wave reads gy rows in the order of the sorted stream, i.e. all over the batch; as long as
@@ -55,16 +56,20 @@ __host__ __device__ inline int64_t stream_stride(int64_t B, int G)
 struct SortedStream {
     const f4v *rec;              // [K][S]
     const int32_t *chunk_cell;   // [K][S/4]  i1 << 8 | i2 of the cell each chunk belongs to,
-                                 //           non-decreasing inside a block
+                                 //           non-decreasing inside a block.  Sparse: the lower nodes i1 W + i2 of
+                                 //           the cells of either half of each chunk, 16 bits each
     const int32_t *block_chunks; // [K][blocks]  chunks of the block to process (a multiple of kUnroll)
     int64_t S;                   // stream_stride
     int block_stride;            // chunks from the start of a block to that of the next
     int n_blocks;
+    bool sparse;                 // cells padded to half chunks, the factor's sign by the parity of the cell's lower node
 };
 
+// whether the coefficient gradient alone walks a sparse stream
+bool coef_stream_is_sparse(const LayerShape &s);
 // records = output of launch_preamble_records; fills the stream in `sorted`
 // (sorted_records_bytes()) and returns its description
-SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted, hipStream_t stream);
+SortedStream launch_sort(const LayerShape &s, const void *records, void *sorted, bool sparse, hipStream_t stream);
 // Number of this workgroup (one wave) such that each XCD has a contiguous run of them: workgroups go to the 8 XCDs
 // in turn.  (Any count of workgroups.  With the runs for multiples of eight alone, 1042 -> 800 at G = 12 on 12000
 // rows, 6773 waves, took 2218 us and takes 1073, 1026 -> 514 at G = 16 on 8192 rows, 4617 waves, 978 and 628.)
@@ -100,6 +105,28 @@ void launch_clear_shared_nodes(const LayerShape &s, const SortedStream &st, int 
 // coefficient gradient alone (lmkan_backward.hip)
 void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, const GyView &gy, float *gcoef,
                                  bool accumulate, hipStream_t stream);
+
+struct CoefGradArgs {
+    const f4v *rec;
+    const int32_t *chunk_cell;
+    const int32_t *block_chunks;  // [K][n_blocks]
+    GyView gy;
+    float *gP;
+    CoefMap gmap;  // layout of Alg. 1
+    int64_t B;
+    int64_t S;     // stream_stride
+    int block_stride;  // chunks from one block of the stream to the next
+    int n_out;
+    int K;
+    int G;
+    int accumulate;
+    int n_blocks;  // locality blocks of the batch
+    int n_sub;     // waves per (pair, output tile, block)
+    int all_shared;  // every node is added to atomically
+};
+
+// its walk of a sparse stream (lmkan_backward_sparse.hip)
+void launch_coef_sparse(const CoefGradArgs &a, bool offsets32, unsigned waves, unsigned lds, hipStream_t stream);
 
 // input gradient, with the coefficient gradient when gcoef is not NULL (lmkan_backward_fused.hip).
 // `partial` is scratch of fused_partial_bytes(); the result goes to gx [batch][n_in], or, when
@@ -204,29 +231,41 @@ __device__ __forceinline__ void leave_cell(f4v (&acc)[4], const NodeRing &ring, 
 // (Clearing the whole gradient and adding all of it atomically moves its bytes three more times: backward of 500 -> 333,
 // G = 20, 10000 rows 211 -> 172 us with the clearing, of 256 -> 256, G = 40, 8192 rows 383 -> 337, of 256 -> 512, G = 24,
 // 10000 rows 254 -> 170, of 1000 -> 96, G = 30, 9000 rows 281 -> 214.)
+// (lower nodes of the first and the last cell of a chunk)
+template <bool SPARSE>
+__device__ __forceinline__ int first_node(int chunk_cell, int W)
+{
+    return SPARSE ? chunk_cell & 0xffff : (chunk_cell >> 8) * W + (chunk_cell & 255);
+}
+template <bool SPARSE>
+__device__ __forceinline__ int last_node(int chunk_cell, int W)
+{
+    return SPARSE ? (int)((unsigned)chunk_cell >> 16) : first_node<false>(chunk_cell, W);
+}
 struct RunNodes {
     int begin, own_from, own_to;
     __device__ __forceinline__ unsigned own() const { return (unsigned)own_from | (unsigned)own_to << 16; }
 };
-template <typename Cells>
+template <bool SPARSE, typename Cells>
 __device__ __forceinline__ RunNodes run_nodes(Cells cell, int n_chunks, bool first_run, bool last_run, bool all_shared, int W)
 {
-    auto node = [&](int i) { return (cell[i] >> 8) * W + (cell[i] & 255); };
-    if (all_shared) return {node(0), 0, 0};
+    auto first = [&](int i) { return first_node<SPARSE>(cell[i], W); };
+    auto last = [&](int i) { return last_node<SPARSE>(cell[i], W); };
+    if (all_shared) return {first(0), 0, 0};
     RunNodes r = {0, 0, W * W};
     if (!first_run) {
-        r.own_from = node(-1) + W + 2;
-        r.begin = min(node(0), r.own_from);
+        r.own_from = last(-1) + W + 2;
+        r.begin = min(first(0), r.own_from);
     }
     // (four nodes are written at a time, from `begin` on: whole groups are owned or shared)
     r.own_from = r.begin + ((r.own_from - r.begin + 3) & ~3);
-    if (!last_run) r.own_to = r.begin + (max(min(node(n_chunks), node(n_chunks - 1) + W + 2) - r.begin, 0) & ~3);
+    if (!last_run) r.own_to = r.begin + (max(min(first(n_chunks), last(n_chunks - 1) + W + 2) - r.begin, 0) & ~3);
     return r;
 }
-// `end` of a run whose last cell is `last`
+// `end` of a run whose last cell's lower node is `last`
 __device__ __forceinline__ int run_end(unsigned own, int last, int W)
 {
-    return (int)(own >> 16) == W * W ? W * W : ((last >> 8) + 1) * W + (last & 255) + 2;
+    return (int)(own >> 16) == W * W ? W * W : last + W + 2;
 }
 static_assert((LMKAN_MAX_GRID + 1) * (LMKAN_MAX_GRID + 1) < 1 << 16, "GradOut::own");
 
@@ -251,11 +290,15 @@ struct GradOut {
 };
 
 // Nodes [done, upto) can receive nothing more: they are written and their slots cleared.
+// BY_FOUR: a multiple of four of them; ROWS4: n_out is a multiple of four.
+template <bool BY_FOUR = false, bool ROWS4 = false>
 __device__ __forceinline__ void retire_nodes(const NodeRing &ring, const GradOut &o, int &done, int upto, int lane)
 {
     const int g = lane >> 4, l16 = lane & 15;
+#pragma unroll 1
     for (; done < upto; done += 4) {
         if (done < o.own_from() || done >= o.own_to()) {
+#pragma unroll 1
             for (int id = done; id < min(done + 4, upto); ++id) {
                 float *p = ring.win + ring.slot(id) * LMKAN_PACK_TILE + lane;
                 const float v = *p;
@@ -266,12 +309,12 @@ __device__ __forceinline__ void retire_nodes(const NodeRing &ring, const GradOut
             int slot = ring.slot(done) + g;
             if (slot >= ring.R) slot -= ring.R;
             f4v *p = reinterpret_cast<f4v *>(ring.win + slot * LMKAN_PACK_TILE) + l16;
-            if (done + g < upto) {
+            if (BY_FOUR || done + g < upto) {
                 const int col = o.tile_col + l16 * 4;
                 if (col < o.n_out) {
                     float *dst = o.base + (done + g) * o.s_node + l16 * 4;
                     const f4v v = *p;
-                    if ((o.n_out & 3) == 0) {
+                    if (ROWS4 || (o.n_out & 3) == 0) {
                         f4v *d4 = reinterpret_cast<f4v *>(dst);
                         // (past the caches: the gradient of a wave is read by nobody soon, and would push out the
                         // rows of gy that all waves of an XCD gather from: 2048 -> 2048, G = 32: 4290 -> 4130 us,

@@ -211,16 +211,16 @@ __device__ __forceinline__ void sort_block(const int32_t *__restrict__ rec_node,
     if (tid == 0) block_chunks[(int64_t)k * blocks + blk] = block_end / kChunk;
 }
 
-__global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *rec_node, const float *rec_u, const float *rec_v,
-                                                           f4v *rec, int32_t *chunk_cell, int32_t *block_chunks, int64_t B, int G)
+__global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__restrict__ rec_node, const float *__restrict__ rec_u, const float *__restrict__ rec_v,
+                                                           f4v *__restrict__ rec, int32_t *__restrict__ chunk_cell, int32_t *__restrict__ block_chunks, int64_t B, int G)
 {
     sort_block<false>(rec_node, rec_u, rec_v, rec, chunk_cell, block_chunks, B, G);
 }
 
 // (the same for a sparse stream, cells padded to kPad = kHalf)
 template <int kPad>
-__global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *rec_node, const float *rec_u, const float *rec_v,
-                                                           f4v *rec, int32_t *chunk_cell, int32_t *block_chunks, int64_t B, int G)
+__global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__restrict__ rec_node, const float *__restrict__ rec_u, const float *__restrict__ rec_v,
+                                                           f4v *__restrict__ rec, int32_t *__restrict__ chunk_cell, int32_t *__restrict__ block_chunks, int64_t B, int G)
 {
     static_assert(kPad == kHalf, "");
     sort_block<true>(rec_node, rec_u, rec_v, rec, chunk_cell, block_chunks, B, G);

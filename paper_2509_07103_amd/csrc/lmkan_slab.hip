@@ -1544,6 +1544,11 @@ __device__ __forceinline__ void fma_corners_quad(float *acc, const Corners &c, f
     fmac_quad_bcast<T>(acc[3], w11, c.c11.w);
 }
 
+// Table type of the kernel below that brings the next pair's slab near: packed float32, SINGLE.
+struct NearF32 {
+    float value;
+};
+
 // SINGLE: the slab fits LDS only once (35 <= G <= 48): no slab is fetched while another is
 // walked; the wave waits for its part of the fill and for the others' at the top of every pair.
 template <typename CT, int WAVES, int SETS, bool SINGLE = false>
@@ -1561,8 +1566,13 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
-    const int ks = rest % a.n_split;
-    const int jt = rest / a.n_split;
+    int ks = rest % a.n_split, jt = rest / a.n_split;
+    constexpr bool kBringsNear = std::is_same<CT, NearF32>::value;
+    if constexpr (kBringsNear) {
+        // the (up to four) tiles of outputs whose rows are pieces of one line or two next to each other as well
+        const int block = rest / (4 * a.n_split), width = min(4, a.n_jt - 4 * block), in_block = rest - block * 4 * a.n_split;
+        jt = 4 * block + in_block % width, ks = in_block / width;
+    }
 
     const int k_begin = ks * a.pairs_per_split;
     const int k_end = min(a.K, k_begin + a.pairs_per_split);
@@ -1614,6 +1624,23 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             fill.template commit<decltype(pc)::value>(a, slab0, wave, lane);
         });
     };
+    // (near_pays) One word of every row of pair k's slab, dealt to the workgroups that share the lines: tiles of samples, and the two
+    // tiles of outputs whose 64-byte pieces make a line.  `ways` of them, this one is number `mine`.
+    const int ways_b = a.n_btiles >= 4 ? 4 : a.n_btiles >= 2 ? 2 : 1;
+    const int ways = (jt ^ 1) < a.n_jt ? 2 * ways_b : ways_b;
+    const int mine = (btile & (ways_b - 1)) + (ways > ways_b ? (jt & 1) * ways_b : 0);
+    auto bring_near = [&](int k, bool wanted) {
+        constexpr int kRow = kTile * (int)sizeof(CT);   // of the packed layout
+        const char *src = static_cast<const char *>(a.P) + (int64_t)k * a.map.s_pair * (int)sizeof(CT) +
+                          ((int64_t)((jt * kNarrowTile) >> 6) * a.map.s_tile + ((jt * kNarrowTile) & 63)) * (int)sizeof(CT);
+        const unsigned nowhere = lds0 + 4 * (unsigned)slab_floats + kGateBytes;
+        wanted = wanted && (wave & (ways - 1)) == mine;
+#pragma unroll
+        for (int i = 0; i < (160 * 1024 / kNarrowRowBytes + WAVES * 64 - 1) / (WAVES * 64); ++i) {
+            const int row = (wave + i * WAVES) * 64;
+            lds_dma4_lanes(src + row * kRow, (unsigned)(lane * kRow), nowhere, wanted ? first_lanes(a.nodes - row) : 0);
+        }
+    };
     if (k_begin < k_end) {
 #pragma unroll
         for (int s = 0; s < SETS; ++s) fetch_record(s, k_begin);
@@ -1651,6 +1678,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             __syncthreads();  // the slab of pair k is complete, nobody reads the other buffer any more
             if constexpr (!SINGLE) fill.template issue<0>(a, slab_next, k_next, jt, wave, lane);
         }
+
+        if constexpr (kBringsNear) bring_near(k + 1, more);
 
         constexpr int kNear = 1;  // LDS reads run one step ahead (registers are short here)
         Corners ring[kNear + 1];
@@ -2067,6 +2096,21 @@ bool slab_forward_applicable(const LayerShape &s, const void *coef, const float 
     return ((reinterpret_cast<uintptr_t>(coef) | reinterpret_cast<uintptr_t>(y)) & 15) == 0;
 }
 
+// Where a slab fits LDS only once, nobody computes while it is filled, and its 1300 to 2500 lines come from memory, as many at a
+// time as the first-level cache of a CU waits for.  forward_slab_narrow_kernel<NearF32> brings the lines of the next pair's slab into
+// the L2 while a pair is walked, by loads of one word that the workgroups which share the lines deal out among
+// themselves (every workgroup for itself it is no gain: these loads queue where the fill does).  Forward call, packed float32:
+// 256 -> 256, G = 40, 8192 rows 162 -> 122 us, 1024 -> 512 1085 -> 730, 1000 rows of 1024 -> 512 at G = 35 438 -> 364, 14000 rows of
+// 800 -> 40 at G = 39 201 -> 149.  Not where the walk is too short to hide them (600 rows of 512 -> 300 at G = 42 187 -> 195, 1000
+// rows 193 -> 200), in runs of a few pairs unless it is long (eight pairs of 128 -> 256: 5000 rows at G = 44 70 -> 73, 8192 at
+// G = 40 80 -> 77), nor for 16-bit tables, which are staged in four parts (2 to 10 % slower).
+static bool near_pays(const LayerShape &s, int n_btiles, int pairs_per_split)
+{
+    const int64_t rows = s.batch / n_btiles;
+    return s.dtype == LMKAN_F32 && s.layout == LMKAN_LAYOUT_PACKED && 4 * rows >= 3 * s.nodes() &&
+           (pairs_per_split >= 10 || rows >= 2 * s.nodes());
+}
+
 static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, float *y, const void *records,
                                        float *partials, int split, hipStream_t stream)
 {
@@ -2116,7 +2160,10 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
                                forward_slab_narrow_kernel<bf16_t, WAVES, SETS, true>};
     const Kernel far[2] = {forward_slab_narrow_kernel<FarF32, 2 * WAVES, SETS / 2>,
                            forward_slab_narrow_kernel<FarF32, 2 * WAVES, SETS / 2, true>};
-    const Kernel kernel = s.dtype == LMKAN_F32 && rows_far_apart(s, 16, 4) ? far[single] : kernels[s.dtype + (single ? 3 : 0)];
+    const int n_btiles = (int)((s.batch + kTileB - 1) / kTileB), pairs_per_split = (s.pairs() + split - 1) / split;
+    const bool near = single && near_pays(s, n_btiles, pairs_per_split);
+    const Kernel kernel = near ? forward_slab_narrow_kernel<NearF32, 2 * WAVES, SETS / 2, true>
+                          : s.dtype == LMKAN_F32 && rows_far_apart(s, 16, 4) ? far[single] : kernels[s.dtype + (single ? 3 : 0)];
     const int waves = s.dtype == LMKAN_F32 ? 2 * WAVES : WAVES;
     allow_large_lds(reinterpret_cast<const void *>(kernel), 160 * 1024);
     const size_t n = (size_t)s.pairs() * (size_t)s.batch;
@@ -2134,15 +2181,15 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
     a.nodes = s.nodes();
     a.col_limit = s.layout == LMKAN_LAYOUT_PACKED ? s.out_tiles() * kTile : s.n_out;
     a.packed = s.layout == LMKAN_LAYOUT_PACKED;
-    a.n_btiles = (int)((s.batch + kTileB - 1) / kTileB);
+    a.n_btiles = n_btiles;
     a.n_jt = (s.n_out + kNarrowTile - 1) / kNarrowTile;
     const int tiles = a.n_btiles * a.n_jt;
     a.n_split = split;
-    a.pairs_per_split = (a.K + split - 1) / split;
+    a.pairs_per_split = pairs_per_split;
     finish_split_setup(a, s, y, partials, stream);
     {
         KernelTiming timing(stream, kTimeForward);
-        kernel<<<tiles * split, waves * 64, (size_t)(single ? 1 : 2) * s.nodes() * kNarrowRowBytes + kGateBytes, stream>>>(a);
+        kernel<<<tiles * split, waves * 64, (size_t)(single ? 1 : 2) * s.nodes() * kNarrowRowBytes + kGateBytes + (near ? kNowhereBytes : 0), stream>>>(a);
     }
     if (a.y_part) launch_sum_partials(y, a.y_part, split - 1, (int64_t)s.batch * s.n_out, stream);
 }

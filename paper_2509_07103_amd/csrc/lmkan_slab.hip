@@ -1568,11 +1568,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const int rest = id / a.n_btiles;
     int ks = rest % a.n_split, jt = rest / a.n_split;
     constexpr bool kBringsNear = std::is_same<CT, NearF32>::value;
-    if constexpr (kBringsNear) {
-        // the (up to four) tiles of outputs whose rows are pieces of one line or two next to each other as well
-        const int block = rest / (4 * a.n_split), width = min(4, a.n_jt - 4 * block), in_block = rest - block * 4 * a.n_split;
-        jt = 4 * block + in_block % width, ks = in_block / width;
-    }
+    if constexpr (sizeof(CT) == 4 && (!SINGLE || kBringsNear)) place_tile<4>(rest, a.n_split, a.n_jt, jt, ks);
 
     const int k_begin = ks * a.pairs_per_split;
     const int k_end = min(a.K, k_begin + a.pairs_per_split);
@@ -1791,8 +1787,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const int id = xcd_tile();
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
-    const int ks = rest % a.n_split;
-    const int jt = rest / a.n_split;
+    int ks = rest % a.n_split, jt = rest / a.n_split;
+    if constexpr (sizeof(CT) == 4) place_tile<4>(rest, a.n_split, a.n_jt, jt, ks);
 
     const int k_begin = ks * a.pairs_per_split;
     const int k_end = min(a.K, k_begin + a.pairs_per_split);

@@ -375,21 +375,21 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, -1, lane);
-    retire_nodes(ring, out, done, run_end(out.own, first_node<false>(cur_cell, W), W), lane);
+    retire_nodes(ring, out, done, run_end<false>(out.own, cur_cell, W), lane);
 }
 
 // The nodes that run blockIdx.x + 1 of pair blockIdx.y shares with the runs before it start at zero
+template <bool SPARSE>
 __global__ __launch_bounds__(256) void clear_shared_nodes_kernel(const int32_t *__restrict__ chunk_cell,
                                                                  const int32_t *__restrict__ block_chunks, int64_t S, int n_sub,
-                                                                 int W, float *gP, CoefMap gmap, int n_out, int sparse)
+                                                                 int W, float *gP, CoefMap gmap, int n_out)
 {
     const int k = blockIdx.y, chunks = block_chunks[k], first = ((int)blockIdx.x + 1) * run_chunks(chunks, n_sub);
     if (first >= chunks) return;
     const int32_t *cell = chunk_cell + (int64_t)k * (S / kChunk) + first;
     // (a group of four nodes of a run is shared as a whole)
-    const int beyond = (sparse ? last_node<true>(cell[-1], W) : last_node<false>(cell[-1], W)) + W + 2;
-    const int here = sparse ? first_node<true>(cell[0], W) : first_node<false>(cell[0], W);
-    const int from = max(min(here, beyond) - 3, 0), to = min(beyond + 3, W * W);
+    const int beyond = node_beyond<SPARSE>(SPARSE ? last_node<true>(cell[-1], W) : cell[-1], W);
+    const int from = max(min(first_node<SPARSE>(cell[0], W), beyond) - 3, 0), to = min(beyond + 3, W * W);
     float *out = gP + (int64_t)k * gmap.s_pair;
     for (int id = from + (int)(threadIdx.x >> 6); id < to; id += 4)
         for (int col = threadIdx.x & 63; col < n_out; col += 64) out[id * gmap.s_node + col] = 0.0f;
@@ -468,8 +468,8 @@ void launch_clear_shared_nodes(const LayerShape &s, const SortedStream &st, int 
     if (all_nodes_shared(s, st.n_blocks, n_sub))
         launch_fill_zero(gcoef, (size_t)s.nodes() * (size_t)s.pairs() * (size_t)s.n_out, stream);
     else if (n_sub > 1)
-        clear_shared_nodes_kernel<<<dim3((unsigned)(n_sub - 1), (unsigned)s.pairs()), 256, 0, stream>>>(
-            st.chunk_cell, st.block_chunks, st.S, n_sub, s.G + 1, gcoef, coef_map(g), s.n_out, st.sparse ? 1 : 0);
+        (st.sparse ? clear_shared_nodes_kernel<true> : clear_shared_nodes_kernel<false>)<<<dim3((unsigned)(n_sub - 1), (unsigned)s.pairs()), 256, 0, stream>>>(
+            st.chunk_cell, st.block_chunks, st.S, n_sub, s.G + 1, gcoef, coef_map(g), s.n_out);
 }
 
 void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, const GyView &gy, float *gcoef,

@@ -368,7 +368,7 @@ __global__ __launch_bounds__(64) void backward_fused_kernel(FusedArgs a)
     asm volatile("" ::"v"(touched));
     if constexpr (DO_GP) {
         if (cur_cell >= 0) leave_cell(acc, ring, cur_cell, -1, lane);
-        retire_nodes(ring, out, done, run_end(out.own, first_node<false>(cur_cell, W), W), lane);
+        retire_nodes(ring, out, done, run_end<false>(out.own, cur_cell, W), lane);
     }
 }
 

@@ -239,7 +239,7 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         leave_cell(acc, ring, cur, -1, lane);
     }
-    retire_nodes(ring, out, done, run_end(out.own, cur, W), lane);
+    retire_nodes(ring, out, done, run_end<true>(out.own, cur, W), lane);
 }
 
 }  // namespace

@@ -44,6 +44,11 @@ def names(launches):
     return [launch[0].split("<")[0] for launch in launches]
 
 
+def variants(launches, kernel):
+    """The template arguments with which `kernel` is launched, "" where it is no template."""
+    return [launch[0][len(kernel):].strip("<>") for launch in launches if launch[0].split("<")[0] == kernel]
+
+
 class _Desc(C.Structure):
     _fields_ = [(f, C.c_int32) for f in ("n_in", "n_out", "grid", "order", "dtype", "layout", "flags")]
 

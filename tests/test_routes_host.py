@@ -5,7 +5,7 @@ import random
 import pytest
 
 import paper_2509_07103_amd as pkg
-from routes import names, recorder, routes
+from routes import names, recorder, routes, variants
 from streamed_shapes import FAR_ROWS
 
 REUSE = pkg.LMKAN_FLAG_WORKSPACE_HAS_RECORDS
@@ -259,3 +259,12 @@ def test_nodes_that_runs_share_are_cleared_unless_added_to(rec, layer, clears, a
     assert status == 0 and ("backward_fused_kernel" if walk else "backward_coef_stream_kernel") in walks, walks
     cleared = {"fill_zero_kernel", "clear_shared_nodes_kernel"} & set(walks)
     assert cleared == ({clears} if clears and not adds else set()), walks
+
+
+@pytest.mark.parametrize("layer,form", [(dict(n_in=256, n_out=128, grid=16, batch=8192), "false"),
+                                        (dict(n_in=500, n_out=333, grid=20, batch=1000), "true")])
+def test_shared_nodes_are_cleared_in_the_form_of_the_stream(rec, layer, form):
+    """Dense and sparse streams name their cells differently: a kernel for each, no choice at run time."""
+    (status, launches), = routes([dict(layer, fn="backward", grad_x=0)], rec)
+    assert status == 0 and variants(launches, "clear_shared_nodes_kernel") == [form], launches
+    assert variants(launches, "sort_kernel") == ["2" if form == "true" else ""], launches

@@ -1509,6 +1509,7 @@ __device__ __forceinline__ void fmac_quad_bcast(float &acc, float w, float c)
 }
 
 constexpr int kNarrowTile = 16;               // outputs per workgroup tile
+constexpr int kNarrowSamples = 4096;          // samples of one
 constexpr int kNarrowRowBytes = kNarrowTile * 4;
 
 template <int T>
@@ -1621,7 +1622,9 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         });
     };
     // (near_pays) One word of every row of pair k's slab, dealt to the workgroups that share the lines: tiles of samples, and the two
-    // tiles of outputs whose 64-byte pieces make a line.  `ways` of them, this one is number `mine`.
+    // tiles of outputs whose 64-byte pieces make a line.  `ways` of them, this one is number `mine`.  Alone (one tile of samples, the
+    // last of an odd count of tiles of outputs) it brings nothing: all loads for itself took longer than the plain fill, and the
+    // launch as long as that workgroup: 4000 rows and fewer, 30 layers of 3 to 39 tiles 1.02 of the time without, 0.96 so.
     const int ways_b = a.n_btiles >= 4 ? 4 : a.n_btiles >= 2 ? 2 : 1;
     const int ways = (jt ^ 1) < a.n_jt ? 2 * ways_b : ways_b;
     const int mine = (btile & (ways_b - 1)) + (ways > ways_b ? (jt & 1) * ways_b : 0);
@@ -1630,7 +1633,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         const char *src = static_cast<const char *>(a.P) + (int64_t)k * a.map.s_pair * (int)sizeof(CT) +
                           ((int64_t)((jt * kNarrowTile) >> 6) * a.map.s_tile + ((jt * kNarrowTile) & 63)) * (int)sizeof(CT);
         const unsigned nowhere = lds0 + 4 * (unsigned)slab_floats + kGateBytes;
-        wanted = wanted && (wave & (ways - 1)) == mine;
+        wanted = wanted && ways > 1 && (wave & (ways - 1)) == mine;
 #pragma unroll
         for (int i = 0; i < (160 * 1024 / kNarrowRowBytes + WAVES * 64 - 1) / (WAVES * 64); ++i) {
             const int row = (wave + i * WAVES) * 64;
@@ -2100,11 +2103,19 @@ bool slab_forward_applicable(const LayerShape &s, const void *coef, const float 
 // 800 -> 40 at G = 39 201 -> 149.  Not where the walk is too short to hide them (600 rows of 512 -> 300 at G = 42 187 -> 195, 1000
 // rows 193 -> 200), in runs of a few pairs unless it is long (eight pairs of 128 -> 256: 5000 rows at G = 44 70 -> 73, 8192 at
 // G = 40 80 -> 77), nor for 16-bit tables, which are staged in four parts (2 to 10 % slower).
-static bool near_pays(const LayerShape &s, int n_btiles, int pairs_per_split)
+// A single tile of outputs needs four tiles of samples to share its lines, and runs of seven pairs: 1024 -> 16, G = 40 at 4096 rows 83.5 ->
+// 85.4 us, at 8192 92.2 -> 93.4, 210 -> 12, G = 41, 29687 rows (runs of five) 65.3 -> 66.1, but 672 -> 12, G = 43, 19834 rows (seven) 121 ->
+// 106.  Of two tiles of samples the second must not be nearly empty: it is through its pairs long before the first, whose share of
+// the lines it brings too early (564 -> 80, G = 41, 4133 rows 98 -> 113, 108 -> 512, G = 35, 4125 rows 93 -> 99), unless the runs are long
+// (754 -> 217, G = 37, 4166 rows, 42 pairs, 13 % less so).
+// Of 500 layers drawn from what the rule takes the mean needs 0.91 of the time without; one in nine is 1 % slower and more, 10 % the
+// worst (94 -> 637, G = 39, 4756 rows 108 -> 117).
+static bool near_pays(const LayerShape &s, int n_btiles, int n_jt, int pairs_per_split)
 {
-    const int64_t rows = s.batch / n_btiles;
-    return s.dtype == LMKAN_F32 && s.layout == LMKAN_LAYOUT_PACKED && 4 * rows >= 3 * s.nodes() &&
-           (pairs_per_split >= 10 || rows >= 2 * s.nodes());
+    const int64_t rows = s.batch / n_btiles, last_rows = s.batch - (int64_t)(n_btiles - 1) * kNarrowSamples;
+    const bool shared = n_jt > 1 ? n_btiles != 2 || 4 * last_rows >= s.nodes() || pairs_per_split >= 24 : n_btiles >= 4;
+    return s.dtype == LMKAN_F32 && s.layout == LMKAN_LAYOUT_PACKED && shared && 4 * rows >= 3 * s.nodes() &&
+           (pairs_per_split >= 10 || (rows >= 2 * s.nodes() && (n_jt > 1 || pairs_per_split >= 7)));
 }
 
 static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, float *y, const void *records,
@@ -2112,6 +2123,7 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
 {
     constexpr int WAVES = 8, SETS = 8;
     constexpr int kTileB = WAVES * SETS * 64;
+    static_assert(kTileB == kNarrowSamples, "");
     typedef void (*Kernel)(SlabArgs);
     if (slab_forward_takes_half_tiles(s)) {
         const Kernel k32 = s.dtype == LMKAN_F32   ? forward_lane32_f32_kernel
@@ -2156,8 +2168,9 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
                                forward_slab_narrow_kernel<bf16_t, WAVES, SETS, true>};
     const Kernel far[2] = {forward_slab_narrow_kernel<FarF32, 2 * WAVES, SETS / 2>,
                            forward_slab_narrow_kernel<FarF32, 2 * WAVES, SETS / 2, true>};
-    const int n_btiles = (int)((s.batch + kTileB - 1) / kTileB), pairs_per_split = (s.pairs() + split - 1) / split;
-    const bool near = single && near_pays(s, n_btiles, pairs_per_split);
+    const int n_btiles = (int)((s.batch + kTileB - 1) / kTileB), n_jt = (s.n_out + kNarrowTile - 1) / kNarrowTile;
+    const int pairs_per_split = (s.pairs() + split - 1) / split;
+    const bool near = single && near_pays(s, n_btiles, n_jt, pairs_per_split);
     const Kernel kernel = near ? forward_slab_narrow_kernel<NearF32, 2 * WAVES, SETS / 2, true>
                           : s.dtype == LMKAN_F32 && rows_far_apart(s, 16, 4) ? far[single] : kernels[s.dtype + (single ? 3 : 0)];
     const int waves = s.dtype == LMKAN_F32 ? 2 * WAVES : WAVES;
@@ -2178,7 +2191,7 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
     a.col_limit = s.layout == LMKAN_LAYOUT_PACKED ? s.out_tiles() * kTile : s.n_out;
     a.packed = s.layout == LMKAN_LAYOUT_PACKED;
     a.n_btiles = n_btiles;
-    a.n_jt = (s.n_out + kNarrowTile - 1) / kNarrowTile;
+    a.n_jt = n_jt;
     const int tiles = a.n_btiles * a.n_jt;
     a.n_split = split;
     a.pairs_per_split = pairs_per_split;

@@ -268,3 +268,12 @@ def test_shared_nodes_are_cleared_in_the_form_of_the_stream(rec, layer, form):
     (status, launches), = routes([dict(layer, fn="backward", grad_x=0)], rec)
     assert status == 0 and variants(launches, "clear_shared_nodes_kernel") == [form], launches
     assert variants(launches, "sort_kernel") == ["2" if form == "true" else ""], launches
+
+
+@pytest.mark.parametrize("form", ["NearF32, 16, 4, true", "float, 16, 4, true"])
+def test_the_next_slab_is_brought_near_where_its_lines_are_shared(rec, form):
+    from streamed_shapes import NEAR, NOT_NEAR
+    shapes = NEAR if form.startswith("Near") else NOT_NEAR
+    got = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, layout=1, fn="forward") for B, n_in, n_out, G in shapes], rec)
+    for shape, (status, launches) in zip(shapes, got):
+        assert status == 0 and variants(launches, "forward_slab_narrow_kernel") == [form], (shape, launches)

@@ -1569,7 +1569,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const int rest = id / a.n_btiles;
     int ks = rest % a.n_split, jt = rest / a.n_split;
     constexpr bool kBringsNear = std::is_same<CT, NearF32>::value;
-    if constexpr (sizeof(CT) == 4 && (!SINGLE || kBringsNear)) place_tile<4>(rest, a.n_split, a.n_jt, jt, ks);
+    if constexpr (sizeof(CT) == 4 && (!SINGLE || kBringsNear)) place_tile(4, rest, a.n_split, a.n_jt, jt, ks);
 
     const int k_begin = ks * a.pairs_per_split;
     const int k_end = min(a.K, k_begin + a.pairs_per_split);
@@ -1791,7 +1791,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     int ks = rest % a.n_split, jt = rest / a.n_split;
-    if constexpr (sizeof(CT) == 4) place_tile<4>(rest, a.n_split, a.n_jt, jt, ks);
+    if constexpr (sizeof(CT) == 4) place_tile(a.tile_share, rest, a.n_split, a.n_jt, jt, ks);
 
     const int k_begin = ks * a.pairs_per_split;
     const int k_end = min(a.K, k_begin + a.pairs_per_split);
@@ -2395,6 +2395,14 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
     // of 1024 -> 1024 189 and 171; below 256 rows tiles are mostly empty and the difference comes down to the fill.
     const bool lane32 = slab_backward_input_takes_half_tiles(s) ||
                         (slab_wide_fits(s) && s.dtype == LMKAN_BF16 && s.layout == LMKAN_LAYOUT_PACKED && s.batch >= 256);
+    // Tiles that share lines side by side (place_tile) also add to the same rows of the scratch gradient side by side.  It pays up to
+    // 16384 rows (float32, 16-output tiles, 206 layers drawn: one tile of samples 0.970 of the time, two 0.982, three and four 0.999, but
+    // five 1.003, eight to eleven 1.016: 68 -> 39, G = 33, 35241 rows 71.5 -> 75.5 us), beyond that for packed tables of many pairs on more
+    // workgroups than the chip holds (836 -> 88, G = 32, 52397 rows 1338 -> 1275; nine such layers 0.98), and for bfloat16 where
+    // a slab is large (G > 20 0.985, 17 to 20 1.001, up to 16 1.004: 534 -> 535, G = 10, 1177 rows 110 -> 112).
+    auto tiles_side_by_side = [&](int workgroups) {
+        return s.G > 16 && (s.batch <= 16384 || (s.dtype == LMKAN_F32 && s.layout == LMKAN_LAYOUT_PACKED && s.pairs() >= 180 && workgroups > 256));
+    };
     if (lane32) {
         const Kernel k32 = s.dtype == LMKAN_F32   ? backward_input_lane32_f32_kernel
                            : s.dtype == LMKAN_F16 ? backward_input_lane32_kernel<_Float16>
@@ -2427,6 +2435,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
         const int tiles32 = a.n_btiles * a.n_jt;
         const int split32 = pair_split_count(tiles32, a.K, 0, a.K);
         a.n_split = split32;
+        a.tile_share = tiles_side_by_side(tiles32 * split32) ? kTile / kHalfTile : 1;
         a.pairs_per_split = (a.K + split32 - 1) / split32;
         a.ld = scratch_row_stride(s.batch, kScratchPlain);
         launch_fill_zero(a.gx, (size_t)a.ld * s.n_in, stream);
@@ -2486,6 +2495,7 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
     const int tiles = a.n_btiles * a.n_jt;
     const int split = pair_split_count(tiles, a.K, 0, a.K);
     a.n_split = split;
+    a.tile_share = narrow && tiles_side_by_side(tiles * split) ? kTile / kNarrowTile : 1;
     a.pairs_per_split = (a.K + split - 1) / split;
     const bool lane_kernel = !narrow && s.dtype == LMKAN_F32;   // its lanes are consecutive samples
     const int layout = lane_kernel ? kScratchPlain : narrow ? kScratchQuad : kScratchOct;

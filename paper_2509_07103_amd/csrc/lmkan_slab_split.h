@@ -165,7 +165,7 @@ __device__ __forceinline__ void backward_input_split(const GradInArgs &a, char *
     const int btile = id % a.n_btiles;
     const int rest = id / a.n_btiles;
     int ks, jt;
-    place_tile<kSlabTile / TILE>(rest, a.n_split, a.n_jt, jt, ks);
+    place_tile(a.tile_share, rest, a.n_split, a.n_jt, jt, ks);
     const int k_begin = ks * a.pairs_per_split;
     const int k_end = min(a.K, k_begin + a.pairs_per_split);
     if (k_begin >= k_end) return;

@@ -95,6 +95,15 @@ NEAR = [(9000, 512, 72, 41), (17000, 400, 100, 45), (20500, 150, 96, 48), (20000
 # pairs, a second tile of rows that is nearly empty
 NOT_NEAR = [(970, 260, 336, 35), (4096, 512, 16, 40), (8192, 512, 16, 40), (29687, 210, 12, 41), (4096, 500, 100, 48), (4133, 564, 80, 41)]
 
+# Tiles of 16 outputs (float32) that share lines of the table in groups of four and a rest, forward and grad_x: B, n_in, n_out, G, layout.
+# One to seven tiles of 4096 rows, pairs split or not; grad_x has them side by side up to 16384 rows and in the last layer
+SIDE_BY_SIDE = [(9000, 128, 100, 33, PACKED), (1500, 300, 130, 28, PACKED), (20000, 300, 72, 30, PACKED), (16384, 160, 48, 34, PACKED),
+                (16385, 160, 48, 34, PACKED), (5000, 300, 100, 25, PACKED), (2000, 600, 72, 20, PAPER), (26000, 100, 200, 27, PACKED),
+                (21000, 360, 130, 25, PACKED)]
+# ... and of 32 outputs, grad_x of bfloat16 tables, in pairs and a rest (side by side from G = 17 on): B, n_in, n_out, G
+SIDE_BY_SIDE_BF16 = [(2600, 900, 161, 30), (1100, 1000, 160, 17), (3000, 600, 416, 28), (1030, 1000, 130, 16), (3000, 300, 260, 12),
+                     (16400, 300, 100, 20)]
+
 # walks that are not cut into runs: a gradient that one wave writes repeats bit for bit
 WHOLE_STREAMS = (2000, 512, 1024, 8)
 # grad_x of the walk over the sorted samples repeats bit for bit, with the coefficient gradient and without

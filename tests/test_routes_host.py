@@ -277,3 +277,17 @@ def test_the_next_slab_is_brought_near_where_its_lines_are_shared(rec, form):
     got = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, layout=1, fn="forward") for B, n_in, n_out, G in shapes], rec)
     for shape, (status, launches) in zip(shapes, got):
         assert status == 0 and variants(launches, "forward_slab_narrow_kernel") == [form], (shape, launches)
+
+
+def test_tiles_that_share_lines_reach_the_kernels_that_place_them(rec):
+    from streamed_shapes import SIDE_BY_SIDE, SIDE_BY_SIDE_BF16
+    got = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, layout=layout, fn=fn, grad_coef=0)
+                  for B, n_in, n_out, G, layout in SIDE_BY_SIDE for fn in ("forward", "backward")], rec)
+    for i, shape in enumerate(SIDE_BY_SIDE):
+        (fwd, forward), (bwd, backward) = got[2 * i:2 * i + 2]
+        assert fwd == 0 and variants(forward, "forward_slab_narrow_kernel") == ["float, 16, 4, false"], (shape, forward)
+        assert bwd == 0 and variants(backward, "backward_input_slab_narrow_kernel") == ["float, 16, 4"], (shape, backward)
+    got = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, dtype=2, layout=1, fn="backward", grad_coef=0)
+                  for B, n_in, n_out, G in SIDE_BY_SIDE_BF16], rec)
+    for shape, (status, launches) in zip(SIDE_BY_SIDE_BF16, got):
+        assert status == 0 and variants(launches, "backward_input_lane32_kernel") == ["bf16_t"], (shape, launches)

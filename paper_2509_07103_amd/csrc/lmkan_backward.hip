@@ -499,10 +499,9 @@ void launch_backward_coef_sorted(const LayerShape &s, const SortedStream &st, co
     if (!accumulate) launch_clear_shared_nodes(s, st, n_sub, gcoef, stream);
     const unsigned grid = (unsigned)((int64_t)s.pairs() * s.out_tiles() * st.n_blocks * n_sub);
     KernelTiming timing(stream, kTimeGradCoef);
-    const bool offsets32 = gy_offsets_fit_32_bits(s, gy);
     if (st.sparse)
-        launch_coef_sparse(a, offsets32, grid, lds, stream);
-    else if (offsets32)
+        launch_coef_sparse(a, grid, lds, stream);
+    else if (gy_offsets_fit_32_bits(s, gy))
         backward_coef_stream_kernel<true><<<grid, 64, lds, stream>>>(a);
     else
         backward_coef_stream_kernel<false><<<grid, 64, lds, stream>>>(a);

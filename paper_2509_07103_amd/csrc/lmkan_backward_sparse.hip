@@ -97,12 +97,13 @@ __device__ __forceinline__ void leave_cell(f4v (&acc)[2], const NodeRing &ring, 
 // vector and as many scalar ones.  Trips of eight chunks, since a chunk holds two cell changes and more than 45 KB of code run
 // slower than they gain (sixteen chunks, 67 KB: 4150 us at 2048 -> 2048, G = 32, where these take 3680 and the kernel for chunks of one cell 4100).
 constexpr int kSparseTrip = 8;
-static_assert(kSparseTrip == kDepth && kUnroll % kSparseTrip == 0, "the ring of gy values is one trip; runs are whole trips");
 
-template <bool kOffset32, bool ROWS4>
+// TRIP: chunks per trip; ROWS4: n_out is a multiple of four
+template <int TRIP, bool ROWS4>
 __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a)
 {
     extern __shared__ __align__(16) float win[];  // the NodeRing of this wave's columns
+    static_assert(TRIP == kDepth && kUnroll % TRIP == 0, "the ring of gy values is one trip; runs are whole trips");
     const int lane = threadIdx.x;
     const int g = lane >> 4, l16 = lane & 15;
     const int G = a.G, W = G + 1;
@@ -144,17 +145,12 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
     const unsigned col_bytes = col_ok ? (unsigned)l16 * 16u : 0u;
     const unsigned row_bytes = a.gy.row_stride;
     const char *gy_tile = reinterpret_cast<const char *>(a.gy.base) + (int64_t)jt * a.gy.tile_stride;
-    auto row_offset = [&](int n) { return kOffset32 ? (int)__umul24((unsigned)n, row_bytes) : n; };
+    // (the batch is short enough for 32-bit offsets: kSparseRows)
+    auto row_offset = [&](int n) { return (int)__umul24((unsigned)n, row_bytes); };
     auto load_gy = [&](f4v &dst, auto subc, int off16) {
-        constexpr int SUB = decltype(subc)::value;
-        if constexpr (kOffset32) {
-            const unsigned off = (unsigned)row_bcast<SUB>(off16) + col_bytes;
-            const char *base = gy_tile;
-            asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(dst) : "v"(off), "s"(base) : "memory");
-        } else {
-            const char *ptr = gy_tile + ((int64_t)row_bcast<SUB>(off16) * row_bytes + col_bytes);
-            asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(dst) : "v"(ptr) : "memory");
-        }
+        const unsigned off = (unsigned)row_bcast<decltype(subc)::value>(off16) + col_bytes;
+        const char *base = gy_tile;
+        asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(dst) : "v"(off), "s"(base) : "memory");
     };
 
     const NodeRing ring(win, W);
@@ -208,21 +204,21 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
         f4v gq[kDepth];
         load_e(coming, 0);
         take(std::integral_constant<int, 0>{});
-        load_e(coming, kSparseTrip);
+        load_e(coming, TRIP);
         static_for(std::make_integer_sequence<int, kDepth>{}, [&](auto dc) {
             constexpr int d = decltype(dc)::value;
             load_gy(gq[d], std::integral_constant<int, d>{}, n_next);
         });
-        int cells_now[kSparseTrip], cells_nxt[kSparseTrip];
+        int cells_now[TRIP], cells_nxt[TRIP];
 #pragma unroll
-        for (int p = 0; p < kSparseTrip; ++p) cells_now[p] = cc[p];
-        for (int c = 0; c < nch; c += kSparseTrip) {
+        for (int p = 0; p < TRIP; ++p) cells_now[p] = cc[p];
+        for (int c = 0; c < nch; c += TRIP) {
 #pragma unroll
-            for (int p = 0; p < kSparseTrip; ++p) cells_nxt[p] = cc[c + kSparseTrip + p];
+            for (int p = 0; p < TRIP; ++p) cells_nxt[p] = cc[c + TRIP + p];
             entry_products(entry, l16, prod);
             take(std::integral_constant<int, kDepth>{});
-            load_e(coming, c + 2 * kSparseTrip);
-            static_for(std::make_integer_sequence<int, kSparseTrip>{}, [&](auto pc) {
+            load_e(coming, c + 2 * TRIP);
+            static_for(std::make_integer_sequence<int, TRIP>{}, [&](auto pc) {
                 constexpr int P = decltype(pc)::value;
                 landed(gq[P], std::integral_constant<int, kDepth>{});
                 const HalfRows rows = deal_out(gq[P]);
@@ -233,7 +229,7 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
                 load_gy(gq[P], pc, n_next);
             });
 #pragma unroll
-            for (int p = 0; p < kSparseTrip; ++p) cells_now[p] = cells_nxt[p];
+            for (int p = 0; p < TRIP; ++p) cells_now[p] = cells_nxt[p];
         }
         // nothing may still be on its way to a register once the compiler is free to reuse it
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -244,18 +240,33 @@ __global__ __launch_bounds__(64) void backward_coef_stream_kernel(CoefGradArgs a
 
 }  // namespace
 
-// Fewer than seven samples per cell: the end of a cell outweighs what its chunks pay for it .
-// Kernels, stream / sparse: 2048 -> 2048 at G = 32 with 4 samples per cell 4100 / 3680 us, 512 -> 512 at G = 24 with 3
-// 150 / 122 and with 7 183 / 174, at G = 16 with 6 85 / 77 and with 7 103 / 95; from there on even (at G = 16 with 9 105 / 103)
-// or the other way (300 -> 333, G = 30, with 9 183 / 188; 256 -> 512, G = 32, with 9 197 / 223; 512 -> 512, G = 24, with 10 211 / 254).
-bool coef_stream_is_sparse(const LayerShape &s) { return s.batch < (int64_t)7 * s.G * s.G; }
-
-void launch_coef_sparse(const CoefGradArgs &a, bool offsets32, unsigned waves, unsigned lds, hipStream_t stream)
+// Few samples per cell, of a block: the end of a cell outweighs what its chunks pay for it.  Calls for this gradient alone, layers
+// drawn, the walk of whole chunks / this one, us:
+// - Streams uncut or cut in two or four: 930 -> 966, G = 8, 285 rows (4.5 per cell) 101 / 90 us, 512 -> 512, G = 24, 3455 rows (6) 204 / 192,
+//   502 -> 297, G = 17, 1854 rows (6.4) 115 / 98 (up to G = 26 five waves of this walk find room on a SIMD, four of the other);
+//   from seven samples on even or the other way (1000 -> 356, G = 13, 1345 rows (8) 127 / 132).
+// - The more runs, the fewer samples each has beside the row of cells it shares with its neighbours: in eight 136 -> 570, G = 21, 2449
+//   rows (5.6) 106 / 97, but 244 -> 82, G = 17, 2005 rows (6.9) 56 / 58; in sixteen 112 -> 446, G = 45, 5192 rows (2.6) 240 / 236, but
+//   272 -> 69, G = 36, 9059 rows (7) 148 / 156; in 32 40 -> 643, G = 43, 5472 rows (3) 212 / 182, but 62 -> 238, G = 35, 5443 rows (4.4) 112 / 123.
+// - Where every node is added to, of a small gradient or of several blocks, even to 8 % more (84 -> 33, G = 25, 2925 rows 52 / 56), but for
+//   streams of several blocks of four samples per cell at most in few runs (258 -> 26, G = 61, 23701 rows 454 / 420).
+// Over 520 layers: 0.988 of the time in the mean, 20 of them 1 % slower and more, 8 % at most (fewer than seven samples of the whole
+// batch per cell, whatever the runs: 0.997, 145, 20 %).
+constexpr int64_t kSparseRows = 1 << 18;   // rows of gy lie less than 8 KB apart (gy_tiles_pay): offsets of 31 bits
+bool coef_stream_is_sparse(const LayerShape &s)
 {
-    typedef void (*Kernel)(CoefGradArgs);
-    static const Kernel kernels[2][2] = {{backward_coef_stream_kernel<false, false>, backward_coef_stream_kernel<false, true>},
-                                         {backward_coef_stream_kernel<true, false>, backward_coef_stream_kernel<true, true>}};
-    kernels[offsets32][a.n_out % 4 == 0]<<<waves, 64, lds, stream>>>(a);
+    const int64_t cells = (int64_t)s.G * s.G;
+    const int n_sub = stream_run_split(s);
+    if (s.batch > kSparseRows) return false;
+    if (stream_blocks(s.batch) > 1) return n_sub <= 8 && kBlockSamples < 4 * cells;
+    if (all_nodes_shared(s, 1, n_sub)) return false;
+    const int quarters = 32 - 3 * __builtin_ctz((unsigned)n_sub);   // of a sample per cell; runs are powers of two
+    return 4 * s.batch < (quarters < 28 ? quarters : 28) * cells;
+}
+
+void launch_coef_sparse(const CoefGradArgs &a, unsigned waves, unsigned lds, hipStream_t stream)
+{
+    (a.n_out % 4 == 0 ? backward_coef_stream_kernel<kSparseTrip, true> : backward_coef_stream_kernel<kSparseTrip, false>)<<<waves, 64, lds, stream>>>(a);
 }
 
 }  // namespace lmkan

@@ -126,7 +126,7 @@ struct CoefGradArgs {
 };
 
 // its walk of a sparse stream (lmkan_backward_sparse.hip)
-void launch_coef_sparse(const CoefGradArgs &a, bool offsets32, unsigned waves, unsigned lds, hipStream_t stream);
+void launch_coef_sparse(const CoefGradArgs &a, unsigned waves, unsigned lds, hipStream_t stream);
 
 // input gradient, with the coefficient gradient when gcoef is not NULL (lmkan_backward_fused.hip).
 // `partial` is scratch of fused_partial_bytes(); the result goes to gx [batch][n_in], or, when

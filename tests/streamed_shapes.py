@@ -104,6 +104,14 @@ SIDE_BY_SIDE = [(9000, 128, 100, 33, PACKED), (1500, 300, 130, 28, PACKED), (200
 SIDE_BY_SIDE_BF16 = [(2600, 900, 161, 30), (1100, 1000, 160, 17), (3000, 600, 416, 28), (1030, 1000, 130, 16), (3000, 300, 260, 12),
                      (16400, 300, 100, 20)]
 
+# Coefficient gradient alone by the walk of sparse cells: B, n_in, n_out, G.  Streams uncut and in 2, 4, ... 64 runs, the largest batch of
+# several of them, two and three blocks, ragged and even outputs, wide rows of gy copied tile by tile, the finest grid
+SPARSE = [(2001, 256, 2050, 20), (1371, 1000, 448, 14), (447, 800, 1000, 8), (1878, 700, 333, 17), (2600, 700, 260, 28), (3311, 300, 256, 24),
+          (4499, 200, 128, 30), (3001, 130, 261, 64), (5779, 100, 131, 37), (8379, 36, 85, 62), (12289, 130, 66, 46), (20000, 260, 40, 48)]
+# ... and by the one of whole chunks: one more row, a small gradient, blocks of more samples or in more runs
+NOT_SPARSE = [(1372, 1000, 448, 14), (448, 800, 1000, 8), (3312, 300, 256, 24), (4500, 200, 128, 30), (3000, 64, 64, 30), (12290, 128, 130, 45),
+              (12289, 40, 66, 50), (1791, 400, 192, 16), (1792, 400, 192, 16), (1100, 600, 333, 13), (4031, 300, 65, 24), (12290, 64, 130, 44)]
+
 # walks that are not cut into runs: a gradient that one wave writes repeats bit for bit
 WHOLE_STREAMS = (2000, 512, 1024, 8)
 # grad_x of the walk over the sorted samples repeats bit for bit, with the coefficient gradient and without

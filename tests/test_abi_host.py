@@ -282,4 +282,4 @@ def test_codegen_check_passes_on_the_walk_of_sparse_cells():
     from paper_2509_07103_amd import check_codegen
     counts = check_codegen.check(sources=check_codegen.SPARSE_SOURCES)
     # the entries of two trips and eight chunks of gy, then one load of entries and eight of gy per trip
-    assert len(counts) == 4 and all(n == 2 + 8 + 1 + 8 for n in counts.values()), counts
+    assert len(counts) == 2 and all(n == 2 + 8 + 1 + 8 for n in counts.values()), counts

@@ -1,17 +1,16 @@
-"""Coefficient gradient of sparse cells (fewer than seven samples per cell): two samples per matrix instruction."""
+"""Coefficient gradient of sparse cells: two samples per matrix instruction."""
 import pytest
 import torch
 
 import paper_2509_07103_amd as pkg
 from parity_util import TOL_F32
+from streamed_shapes import NOT_SPARSE, SPARSE
 
 pytestmark = pytest.mark.gpu
 
 
-# either side of seven samples per cell, whole and ragged tiles, cut and uncut streams, two blocks, the finest grid,
-# wide rows of gy copied tile by tile
-@pytest.mark.parametrize("B,n_in,n_out,G", [(1791, 400, 192, 16), (1792, 400, 192, 16), (1100, 600, 333, 13), (4031, 300, 65, 24),
-                                            (2001, 256, 2050, 20), (12290, 64, 130, 44), (3001, 130, 261, 64), (2600, 700, 260, 28)])
+# (test_routes_host.py: which of these are sparse)
+@pytest.mark.parametrize("B,n_in,n_out,G", SPARSE + NOT_SPARSE)
 def test_coefficient_gradient_of_sparse_cells(oracle, B, n_in, n_out, G):
     g = torch.Generator(device="cpu").manual_seed(91)
     x, gy = torch.randn((B, n_in), generator=g), torch.randn((B, n_out), generator=g)

@@ -291,3 +291,27 @@ def test_tiles_that_share_lines_reach_the_kernels_that_place_them(rec):
                   for B, n_in, n_out, G in SIDE_BY_SIDE_BF16], rec)
     for shape, (status, launches) in zip(SIDE_BY_SIDE_BF16, got):
         assert status == 0 and variants(launches, "backward_input_lane32_kernel") == ["bf16_t"], (shape, launches)
+
+
+def test_sparse_streams_are_walked_where_cells_of_a_run_hold_few_samples(rec):
+    from streamed_shapes import NOT_SPARSE, SPARSE
+    got = routes([dict(n_in=n_in, n_out=n_out, grid=G, batch=B, fn="backward", grad_x=0) for B, n_in, n_out, G in SPARSE + NOT_SPARSE], rec)
+    runs = set()
+    for shape, (status, launches) in zip(SPARSE + NOT_SPARSE, got):
+        n_in, n_out, sparse = shape[1], shape[2], shape in SPARSE
+        assert status == 0 and variants(launches, "sort_kernel") == ["2" if sparse else ""], (shape, launches)
+        form = f"8, {'false' if n_out % 4 else 'true'}" if sparse else "true"
+        assert variants(launches, "backward_coef_stream_kernel") == [form], (shape, launches)
+        waves, = [grid[0] for name, grid, _, _ in launches if name.startswith("backward_coef_stream_kernel")]
+        runs.add((sparse, waves // (n_in // 2 * ((n_out + 63) // 64))))
+    assert {1, 2, 4, 8, 16, 32, 64} <= {n for sparse, n in runs if sparse}, runs
+
+
+def test_rows_of_gy_in_a_sparse_stream_are_within_32_bit_offsets(rec):
+    """The walk of sparse cells adds 32-bit offsets to the tile of gy: no batch whose rows reach further is given to it."""
+    rng = random.Random(8)
+    layers = [dict(n_in=2 * rng.randint(64, 400), n_out=rng.choice([16, 512, 2040, 2044]), grid=rng.randint(46, 64),
+                   batch=round(20000 * 100 ** rng.random())) for _ in range(200)]
+    sparse = [layer["batch"] * 4 * layer["n_out"] for layer, (_, launches) in
+              zip(layers, routes([dict(layer, fn="backward", grad_x=0) for layer in layers], rec)) if variants(launches, "sort_kernel") == ["2"]]
+    assert len(sparse) > 50 and 1 << 30 < max(sparse) < 1 << 32

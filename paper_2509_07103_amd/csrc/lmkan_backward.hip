@@ -5,7 +5,8 @@
 //
 // Pass 1 (sort_kernel): for every pair k the samples are grouped by cell with a counting sort, each
 // cell padded to whole chunks of four samples, the local coordinates stored next to the sample
-// index.
+// index.  (Sparse streams, coef_stream_is_sparse: cells padded to half a chunk, and pass 2 is the walk of
+// lmkan_backward_sparse.hip.)
 // Pass 2 (backward_coef_stream_kernel): one wave owns (pair k, 64 outputs) and walks the
 // sorted chunks, cell after cell.  The four samples of a chunk go to the four 16-lane
 // groups of the wave and a lane covers four adjacent outputs, so gy is read with 16-byte
@@ -34,10 +35,10 @@ static_assert(kUnroll % kDepth == 0, "the gy ring must divide the unrolled trip"
 // Counting sort of the samples of every pair by cell, one launch: a workgroup takes the samples of one
 // (pair, block).  records_in: [3][K][B] (node, u, v) from the preamble pass.  Per pair k, with
 // S = stream_stride and C = stream_block_entries, block b owns the entries [b C, (b + 1) C):
-//   rec [K][S]           (u, v, 1 or -1 for an even or odd i2, index) of a sample, 16 bytes;
+//   rec [K][S]           (u, v, 1 or -1 for an even or odd i2 - sparse: i1 W + i2 -, index) of a sample, 16 bytes;
 //                        padding entries are (0, 0, 0, index of a sample of the same cell)
 //   chunk_cell [K][S/4]  i1 << 8 | i2 of the cell each chunk belongs to, non-decreasing
-//                        inside a block
+//                        inside a block; sparse: i1 W + i2 of the cells of its halves, 16 bits each
 //   block_chunks [K][blocks]  chunks of the block to process, a multiple of kUnroll; one trip of
 //                        padding entries follows (the walking kernels prefetch into it)
 // A thread keeps its samples in registers; LDS holds a population per (wave, cell) (16 bits each).
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__res
     sort_block<false>(rec_node, rec_u, rec_v, rec, chunk_cell, block_chunks, B, G);
 }
 
-// (the same for a sparse stream, cells padded to kPad = kHalf)
+// (the same for a sparse stream: cells padded to kPad = kHalf entries, the one value there is)
 template <int kPad>
 __global__ __launch_bounds__(kSortThreads) void sort_kernel(const int32_t *__restrict__ rec_node, const float *__restrict__ rec_u, const float *__restrict__ rec_v,
                                                            f4v *__restrict__ rec, int32_t *__restrict__ chunk_cell, int32_t *__restrict__ block_chunks, int64_t B, int G)

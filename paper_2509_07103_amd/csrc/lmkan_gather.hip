@@ -853,8 +853,8 @@ static double slab_us(const LayerShape &s, double least, double wide, double hal
 
 bool forward_gather_shape_ok(const LayerShape &s)
 {
-    // (no slab fits from G = 49 on; the kernel for few outputs, which takes them beyond G = 34, is three
-    // times slower however many rows there are)
+    // (no slab fits from G = 50 on, and one just does at G = 49, where the two are not weighed; the kernel for few outputs, which
+    // takes them beyond G = 34, is three times slower however many rows there are)
     if (!rows_by_16_bytes(s)) return false;
     if (s.G > 48 || (s.n_out > 1 && small_out_shape_ok(s))) return true;
     const int per_lane = forward_per_lane(s), tile = lanes_for(s.n_out, per_lane) * per_lane;

@@ -1509,7 +1509,6 @@ __device__ __forceinline__ void fmac_quad_bcast(float &acc, float w, float c)
 }
 
 constexpr int kNarrowTile = 16;               // outputs per workgroup tile
-constexpr int kNarrowSamples = 4096;          // samples of one
 constexpr int kNarrowRowBytes = kNarrowTile * 4;
 
 template <int T>
@@ -1550,7 +1549,7 @@ struct NearF32 {
     float value;
 };
 
-// SINGLE: the slab fits LDS only once (35 <= G <= 48): no slab is fetched while another is
+// SINGLE: the slab fits LDS only once (35 <= G <= 49): no slab is fetched while another is
 // walked; the wave waits for its part of the fill and for the others' at the top of every pair.
 template <typename CT, int WAVES, int SETS, bool SINGLE = false>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVES / 4, WAVES / 4))) void forward_slab_narrow_kernel(
@@ -2005,7 +2004,7 @@ static bool slab_narrow_fits(const LayerShape &s)
     return outputs_by_four_ok(s) && !slab_wide_fits(s) && (size_t)2 * s.nodes() * kNarrowRowBytes <= 160 * 1024;
 }
 
-// forward only: one 16-output slab at a time (35 <= G <= 48)
+// forward only: one 16-output slab at a time (35 <= G <= 49)
 static bool slab_narrow_single_fits(const LayerShape &s)
 {
     return outputs_by_four_ok(s) && !slab_wide_fits(s) && !slab_narrow_fits(s) &&
@@ -2103,19 +2102,17 @@ bool slab_forward_applicable(const LayerShape &s, const void *coef, const float 
 // 800 -> 40 at G = 39 201 -> 149.  Not where the walk is too short to hide them (600 rows of 512 -> 300 at G = 42 187 -> 195, 1000
 // rows 193 -> 200), in runs of a few pairs unless it is long (eight pairs of 128 -> 256: 5000 rows at G = 44 70 -> 73, 8192 at
 // G = 40 80 -> 77), nor for 16-bit tables, which are staged in four parts (2 to 10 % slower).
-// A single tile of outputs needs four tiles of samples to share its lines, and runs of seven pairs: 1024 -> 16, G = 40 at 4096 rows 83.5 ->
-// 85.4 us, at 8192 92.2 -> 93.4, 210 -> 12, G = 41, 29687 rows (runs of five) 65.3 -> 66.1, but 672 -> 12, G = 43, 19834 rows (seven) 121 ->
-// 106.  Of two tiles of samples the second must not be nearly empty: it is through its pairs long before the first, whose share of
-// the lines it brings too early (564 -> 80, G = 41, 4133 rows 98 -> 113, 108 -> 512, G = 35, 4125 rows 93 -> 99), unless the runs are long
-// (754 -> 217, G = 37, 4166 rows, 42 pairs, 13 % less so).
-// Of 500 layers drawn from what the rule takes the mean needs 0.91 of the time without; one in nine is 1 % slower and more, 10 % the
-// worst (94 -> 637, G = 39, 4756 rows 108 -> 117).
+// What it gives depends on where the table is.  With tables, rows and outputs in rotation, so that the table comes from memory, 185 drawn
+// layers of two tiles of outputs and more take 0.854 of the time without in the mean, four of them 1 % longer and more, 6 % at most; 102 of a
+// single tile (and several tiles of samples) 0.947, none longer.  The same table in every call, where one below 210 MB stays in the
+// cache behind the L2: 200 layers 0.914, 28 longer, 10 % at most; the worst have two tiles of samples, the second nearly empty (200
+// such layers 0.947, 78 longer, 13 % at most; from memory 0.880, none longer).
 static bool near_pays(const LayerShape &s, int n_btiles, int n_jt, int pairs_per_split)
 {
-    const int64_t rows = s.batch / n_btiles, last_rows = s.batch - (int64_t)(n_btiles - 1) * kNarrowSamples;
-    const bool shared = n_jt > 1 ? n_btiles != 2 || 4 * last_rows >= s.nodes() || pairs_per_split >= 24 : n_btiles >= 4;
+    const int64_t rows = s.batch / n_btiles;
+    const bool shared = n_btiles > 1 || n_jt > 1;
     return s.dtype == LMKAN_F32 && s.layout == LMKAN_LAYOUT_PACKED && shared && 4 * rows >= 3 * s.nodes() &&
-           (pairs_per_split >= 10 || (rows >= 2 * s.nodes() && (n_jt > 1 || pairs_per_split >= 7)));
+           (pairs_per_split >= 10 || rows >= 2 * s.nodes());
 }
 
 static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, float *y, const void *records,
@@ -2123,7 +2120,6 @@ static void launch_forward_slab_narrow(const LayerShape &s, const void *coef, fl
 {
     constexpr int WAVES = 8, SETS = 8;
     constexpr int kTileB = WAVES * SETS * 64;
-    static_assert(kTileB == kNarrowSamples, "");
     typedef void (*Kernel)(SlabArgs);
     if (slab_forward_takes_half_tiles(s)) {
         const Kernel k32 = s.dtype == LMKAN_F32   ? forward_lane32_f32_kernel
@@ -2398,10 +2394,11 @@ void launch_backward_input_slab(const LayerShape &s, const GridTab &tab, const v
     // Tiles that share lines side by side (place_tile) also add to the same rows of the scratch gradient side by side.  It pays up to
     // 16384 rows (float32, 16-output tiles, 206 layers drawn: one tile of samples 0.970 of the time, two 0.982, three and four 0.999, but
     // five 1.003, eight to eleven 1.016: 68 -> 39, G = 33, 35241 rows 71.5 -> 75.5 us), beyond that for packed tables of many pairs on more
-    // workgroups than the chip holds (836 -> 88, G = 32, 52397 rows 1338 -> 1275; nine such layers 0.98), and for bfloat16 where
-    // a slab is large (G > 20 0.985, 17 to 20 1.001, up to 16 1.004: 534 -> 535, G = 10, 1177 rows 110 -> 112).
+    // workgroups than the chip holds (836 -> 88, G = 32, 52397 rows 1338 -> 1275; nine such layers 0.98, of bfloat16 37 0.99), and for
+    // bfloat16 where a slab is large (G > 20 0.985, 17 to 20 1.001, up to 16 1.004: 534 -> 535, G = 10, 1177 rows 110 -> 112; 0.997 there
+    // when the table comes from memory instead of the cache behind the L2, as it does not after a forward pass).
     auto tiles_side_by_side = [&](int workgroups) {
-        return s.G > 16 && (s.batch <= 16384 || (s.dtype == LMKAN_F32 && s.layout == LMKAN_LAYOUT_PACKED && s.pairs() >= 180 && workgroups > 256));
+        return s.G > 16 && (s.batch <= 16384 || (s.layout == LMKAN_LAYOUT_PACKED && s.pairs() >= 180 && workgroups > 256));
     };
     if (lane32) {
         const Kernel k32 = s.dtype == LMKAN_F32   ? backward_input_lane32_f32_kernel

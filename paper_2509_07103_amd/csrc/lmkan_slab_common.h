@@ -331,10 +331,10 @@ struct GradInArgs {
     int n_btiles;
     int n_jt;
     int n_split;
-    int tile_share;    // place_tile
     int col_limit;
     int packed;
     int slab_pitch;    // kernels on the matrix cores: bytes between two grid lines of a slab in LDS
+    int tile_share;    // place_tile: the 16-output kernel of float32 tables, the one on the matrix cores
 };
 
 // Layouts of a row of the transposed scratch gradient.  The slab kernels leave a set of 64

@@ -1,8 +1,8 @@
 // The cell-sorted sample stream shared by the backward kernels (lmkan_backward.hip builds it,
-// lmkan_backward.hip and lmkan_backward_fused.hip walk it), and the matrix-core pieces both use.
+// lmkan_backward.hip, lmkan_backward_sparse.hip and lmkan_backward_fused.hip walk it), and the matrix-core pieces they use.
 //
 // For every pair k the samples are grouped by the cell their two inputs fall in (counting
-// sort), every non-empty cell padded to whole chunks of four samples.  Inside a cell the
+// sort), every non-empty cell padded to whole chunks of four samples, or to halves of them in a sparse stream.  Inside a cell the
 // gradients are small dense contractions over the samples of the cell (Alg. 1's four-term sum,
 // differentiated), which is what lets them run on the matrix cores.
 #pragma once

@@ -90,10 +90,9 @@ FAR_ROWS = [(32768, 22016, 3, "f32"), (32768, 22016, 3, "f16"), (16384, 8768, 17
 # of 4096 rows, the last one ragged, the fifth and sixth with the share of the first and second; one to sixteen tiles of 16 outputs and
 # a count of 21 (the last one alone with its lines where there is one tile of rows); both ends of the range of grids
 NEAR = [(9000, 512, 72, 41), (17000, 400, 100, 45), (20500, 150, 96, 48), (20000, 672, 12, 43), (4800, 564, 80, 41), (5000, 200, 256, 44),
-        (2500, 300, 330, 48), (980, 260, 336, 35), (12400, 180, 100, 36), (7000, 300, 144, 38)]
-# ... and as it was, on the other side of the rule: rows too few for the grid, nobody or too few to share the lines with, runs of few
-# pairs, a second tile of rows that is nearly empty
-NOT_NEAR = [(970, 260, 336, 35), (4096, 512, 16, 40), (8192, 512, 16, 40), (29687, 210, 12, 41), (4096, 500, 100, 48), (4133, 564, 80, 41)]
+        (2500, 300, 330, 48), (980, 260, 336, 35), (12400, 180, 100, 36), (7000, 300, 144, 38), (8192, 512, 16, 40), (4133, 564, 80, 41)]
+# ... and as it was, on the other side of the rule: rows too few for the grid, nobody to share the lines with, runs of few pairs
+NOT_NEAR = [(970, 260, 336, 35), (4096, 512, 16, 40), (4096, 1024, 13, 36), (4096, 500, 100, 48)]
 
 # Tiles of 16 outputs (float32) that share lines of the table in groups of four and a rest, forward and grad_x: B, n_in, n_out, G, layout.
 # One to seven tiles of 4096 rows, pairs split or not; grad_x has them side by side up to 16384 rows and in the last layer

@@ -95,7 +95,8 @@ __device__ __forceinline__ void leave_cell(f4v (&acc)[2], const NodeRing &ring, 
 // for (dropping the gradient's stores, or gathering one row of gy for all, changes nothing).  At four samples per cell a chunk
 // came to 34 vector and 39 scalar instructions and 8 branches, most of them at the end of a cell; here a cell's end is 15
 // vector and as many scalar ones.  Trips of eight chunks, since a chunk holds two cell changes and more than 45 KB of code run
-// slower than they gain (sixteen chunks, 67 KB: 4150 us at 2048 -> 2048, G = 32, where these take 3680 and the kernel for chunks of one cell 4100).
+// slower than they gain (2048 -> 2048, G = 32, 4096 rows: 3470 us where the walk of whole chunks takes 3880; sixteen chunks, 67 KB, 1 % longer
+// than that one).
 constexpr int kSparseTrip = 8;
 
 // TRIP: chunks per trip; ROWS4: n_out is a multiple of four
